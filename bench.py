@@ -71,12 +71,15 @@ def box_kind(frame) -> int:
 
 
 def kernel_source_hash() -> str:
-    """Hash of the device code (the kernel file and its shared header) with
+    """Hash of the device code (the kernel files and their shared header) with
     comments and whitespace removed: counters taken on other code are stale."""
     import re
     h = hashlib.sha256()
-    for f in ("dh_kernels.hip", "dh_internal.h"):
-        with open(os.path.join(ROOT, "paper_1808_01478_amd", "csrc", f)) as fh:
+    for f in ("dh_kernels.hip", "dh_pairs.h", "dh_internal.h"):
+        path = os.path.join(ROOT, "paper_1808_01478_amd", "csrc", f)
+        if not os.path.exists(path):
+            continue
+        with open(path) as fh:
             code = fh.read()
         code = re.sub(r"/\*.*?\*/", "", code, flags=re.S)
         code = re.sub(r"//[^\n]*", "", code)

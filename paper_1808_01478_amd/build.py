@@ -14,6 +14,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -21,10 +22,13 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libdisthist.so")
 SOURCES = ["dh_api.hip", "dh_kernels.hip", "dh_server.hip", "dh_traj.hip", "dh_noalloc.hip"]
+# the pair kernel's instances, one object per precision and accumulation mode
+PAIR_SOURCE = "dh_pairs.hip"
+PAIR_INSTANCES = [(t, m) for t in ("double", "float") for m in (0, 1, 2)]
 ARCH = os.environ.get("DH_OFFLOAD_ARCH", "gfx950")
 
 HIPCC_FLAGS = [
-    f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-shared",
+    f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",
     "-ffp-contract=off", "-fno-fast-math",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-command-line-argument",
@@ -56,20 +60,30 @@ def _run(cmd, verbose):
 
 
 def build(verbose: bool = False) -> str:
-    """Compile libdisthist.so in place (always recompiles)."""
-    tmp = LIB + f".tmp{os.getpid()}"
-    objs = []
+    """Compile libdisthist.so in place (always recompiles, the sources side by
+    side)."""
+    pid = os.getpid()
+    tmp = LIB + f".tmp{pid}"
+    rocm_inc = os.path.join(os.path.dirname(os.path.dirname(os.path.realpath(hipcc()))), "include")
+    jobs = []
+
+    def job(src, flags, tag=""):
+        obj = os.path.join(PKG, f".{os.path.splitext(src)[0]}{tag}.{pid}.o")
+        jobs.append((obj, [hipcc(), *flags, f"-I{INCLUDE}", f"-I{CSRC}", "-c",
+                           os.path.join(CSRC, src), "-o", obj]))
+
+    for real, mode in PAIR_INSTANCES:
+        job(PAIR_SOURCE, HIPCC_FLAGS + [f"-DDH_REAL={real}", f"-DDH_MODE={mode}"],
+            f"_{real}{mode}")
+    for src in SOURCES:
+        job(src, HIPCC_FLAGS)
     for src in CPU_SOURCES:
-        obj = os.path.join(PKG, f".{os.path.splitext(src)[0]}.{os.getpid()}.o")
-        rocm_inc = os.path.join(os.path.dirname(os.path.dirname(os.path.realpath(hipcc()))),
-                                "include")
-        _run([hipcc(), *CPU_FLAGS, "-D__HIP_PLATFORM_AMD__", f"-I{rocm_inc}",
-              f"-I{INCLUDE}", f"-I{CSRC}", "-c",
-              os.path.join(CSRC, src), "-o", obj], verbose)
-        objs.append(obj)
+        job(src, CPU_FLAGS + ["-D__HIP_PLATFORM_AMD__", f"-I{rocm_inc}"])
+    objs = [obj for obj, _ in jobs]
     try:
-        _run([hipcc(), *HIPCC_FLAGS, f"-I{INCLUDE}", f"-I{CSRC}",
-              *[os.path.join(CSRC, s) for s in SOURCES], "-x", "none", *objs, "-o", tmp], verbose)
+        with ThreadPoolExecutor(max_workers=8) as pool:
+            list(pool.map(lambda j: _run(j[1], verbose), jobs))
+        _run([hipcc(), f"--offload-arch={ARCH}", "-shared", *objs, "-o", tmp], verbose)
     finally:
         for obj in objs:
             if os.path.exists(obj):

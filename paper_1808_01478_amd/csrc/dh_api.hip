@@ -367,7 +367,7 @@ size_t search_queue_bytes(int precision, int threads, int r) {
 }
 
 // Smallest work item (pairs) when a frame is split into bounded launches.
-constexpr int64_t kMinItemPairs = int64_t{1} << 21;
+constexpr int64_t kMinBoundedPairs = int64_t{1} << 21;
 
 // Launch shape for one frame (heuristic defaults).
 // Launch knobs. Every choice yields identical counts; they only change speed.
@@ -388,7 +388,7 @@ struct Knobs {
   int32_t tj = 256;          // j-tile length: 128 or 256
   int32_t noclamp = 1;       // allow unclamped interior blocks
   int32_t occ_cap = 0;       // workgroups per CU at most (0: as many as fit)
-  int32_t items_per_wg = 8;  // work items per workgroup (sets the j-chunk)
+  int32_t items_per_wg = 4;  // work items per workgroup (sets the item size)
   // workgroup size: 256, 512 or 1024; 0 = the smallest that gives every
   // SIMD at least four waves within the LDS limit on workgroups per CU
   int32_t threads = 0;
@@ -443,16 +443,21 @@ BaseConfig base_config(size_t lds_per_block, int precision, const Knobs &k, int 
   c.copies = k.copies;
   c.tj = k.tj;
   c.wg_per_cu = k.occ_cap;
-  c.jchunk = c.tj;
-  // two j-tiles, plus one entry of pad: the look-ahead read of j may touch
-  // the entry just past the second tile
-  b.tile_bytes = (2 * static_cast<size_t>(c.tj) + 1) * staged_point_bytes(precision, kind);
-  if (kind == kBoxTricSorted) b.tile_bytes += kSortedBoxBytes;
+  c.iblock = c.threads * c.r;
+  c.jchunk = c.dchunk = c.tj;
+  // the guard below the histogram; sorted frames keep two j-tiles, plus one
+  // entry of pad: the look-ahead read of j may touch the entry just past the
+  // second tile
+  b.tile_bytes = 32;
+  if (kind == kBoxTricSorted)
+    b.tile_bytes = (2 * static_cast<size_t>(c.tj) + 1) * staged_point_bytes(precision, kind) +
+                   kSortedBoxBytes;
   // the search kernels keep their queues after the histogram; counting them
   // with the tiles leaves the histogram budget below them
   if (kind == kBoxTricSearch) b.tile_bytes += search_queue_bytes(precision, c.threads, c.r);
   const size_t budget = std::min<size_t>(lds_per_block, 160 * 1024) - b.tile_bytes - 256;
-  b.win_max = static_cast<int64_t>(budget / 4 / c.copies) - kDump;
+  // at most 38 passes of a 1,024-thread flush
+  b.win_max = std::min<int64_t>(static_cast<int64_t>(budget / 4 / c.copies) - kDump, 38 * 1024);
   b.occ_cap = k.occ_cap;
   b.items_per_wg = k.items_per_wg;
   const char *env = std::getenv("DH_NOCLAMP");
@@ -460,23 +465,19 @@ BaseConfig base_config(size_t lds_per_block, int precision, const Knobs &k, int 
   return b;
 }
 
-int32_t jchunk_for(const KernelConfig &c, int grid, uint64_t work, int items_per_wg) {
-  const uint64_t bi = static_cast<uint64_t>(c.threads) * c.r;
-  uint64_t jc = work / (static_cast<uint64_t>(grid) * items_per_wg * bi + 1);
-  jc = (jc + c.tj - 1) / c.tj * c.tj;
-  jc = std::max<uint64_t>(jc, c.tj);
-  jc = std::min<uint64_t>(jc, 64ull * c.tj);
-  return static_cast<int32_t>(jc);
-}
-
 // Workgroup size "auto": the LDS histogram caps the workgroups per CU, so
 // take the smallest workgroup that still gives each of the 4 SIMDs at least
-// four waves (measured on MI355X: 256 threads when several workgroups fit,
-// 512 with two per CU, 1024 with one).
+// four waves. Frames of kSmallWork pairs and more start at 512 threads: every
+// workgroup adds its own histogram into the output, and half as many of them
+// save more than the finer grain gives (60,000 points in a cube, 1,000 bins,
+// binary32: 482 us against 497 us with 256 threads; 20,000 points: 86 and
+// 94 us); 1,024 threads gain nothing where 512 fill the SIMDs.
+constexpr uint64_t kSmallWork = uint64_t{1} << 22;
 void resolve_threads(int precision, int kind, int mode, const Knobs &k, size_t lds,
-                     KernelConfig &cfg) {
+                     uint64_t work, KernelConfig &cfg) {
   if (k.threads != 0 || kind == kBoxTricSearch) return;
   for (int th : {256, 512}) {
+    if (th == 256 && work >= kSmallWork) continue;
     KernelConfig c = cfg;
     c.threads = th;
     if (pairs_occupancy(precision, kind, mode, c, lds) * (th / 64) >= 16) {
@@ -516,9 +517,9 @@ Launch choose_launch(int n_cu, size_t lds_per_block, int precision, const FrameP
     L.win = n_bins;
     L.stride = 0;
     L.lds = b.tile_bytes;
-    resolve_threads(precision, fp.box, L.mode, k, L.lds, L.cfg);
+    resolve_threads(precision, fp.box, L.mode, k, L.lds, total_pairs, L.cfg);
     L.grid = grid_for_config(n_cu, precision, fp.box, L.mode, b, L.lds, L.cfg);
-    L.cfg.jchunk = jchunk_for(L.cfg, L.grid, total_pairs, b.items_per_wg);
+    set_items(L.cfg, precision, fp.box, L.grid, total_pairs, b.items_per_wg);
     return L;
   }
   L.mode = L.n_sweeps > 1 ? kModeSweep : kModeLds;
@@ -536,10 +537,10 @@ Launch choose_launch(int n_cu, size_t lds_per_block, int precision, const FrameP
     }
   }
   L.lds = b.tile_bytes + static_cast<size_t>(L.cfg.copies) * L.stride * 4;
-  resolve_threads(precision, fp.box, L.mode, k, L.lds, L.cfg);
+  resolve_threads(precision, fp.box, L.mode, k, L.lds, total_pairs, L.cfg);
   L.grid = grid_for_config(n_cu, precision, fp.box, L.mode, b, L.lds, L.cfg);
-  L.cfg.jchunk = jchunk_for(L.cfg, L.grid, total_pairs * static_cast<uint64_t>(L.n_sweeps),
-                            b.items_per_wg);
+  set_items(L.cfg, precision, fp.box, L.grid, total_pairs * static_cast<uint64_t>(L.n_sweeps),
+            b.items_per_wg);
   return L;
 }
 
@@ -553,8 +554,7 @@ Launch choose_launch(const dh_ctx *ctx, int precision, const FrameParams &fp,
 // device-side planner).
 void plan_frame(int32_t frame, const int64_t *off, int32_t k, const Launch &L,
                 std::vector<WorkItem> &items, std::vector<uint64_t> &pairs) {
-  const int64_t bi = static_cast<int64_t>(L.cfg.threads) * L.cfg.r;
-  const int64_t jc = L.cfg.jchunk;
+  const int64_t bi = L.cfg.iblock, jc = L.cfg.jchunk, dc = L.cfg.dchunk;
   const int32_t n_hist = k * (k + 1) / 2;
   for (int32_t h = 0; h < n_hist; ++h) {
     const HistRows r = hist_rows(off, k, h);
@@ -563,8 +563,8 @@ void plan_frame(int32_t frame, const int64_t *off, int32_t k, const Launch &L,
     const int64_t nr = hist_row_count(r, bi);
     for (int64_t b = 0; b < nr; ++b) {
       const size_t at = items.size();
-      items.resize(at + static_cast<size_t>(row_item_count(r, b, bi, jc)));
-      emit_row(r, h, 0, b, bi, jc, items.data() + at);
+      items.resize(at + static_cast<size_t>(row_item_count(r, b, bi, jc, dc)));
+      emit_row(r, h, 0, b, bi, jc, dc, items.data() + at);
     }
     const size_t last = items.size();
     for (size_t q = first; q < last; ++q) items[q].frame = frame;
@@ -579,21 +579,22 @@ void plan_frame(int32_t frame, const int64_t *off, int32_t k, const Launch &L,
 }
 
 // Splits the last `grid` items of a work list (the ones workgroups take
-// when the rest is done) into pieces of about a quarter of their j-range,
-// in whole j-tiles, so that the workgroups finish close together instead of
-// idling for up to one full item. Diagonal items stay whole; the grouping
-// by (histogram, window) is kept.
-void refine_tail(std::vector<WorkItem> &items, int grid, int tj) {
+// when the rest is done) into pieces of about a quarter of their j-range, in
+// multiples of `step`, so that the workgroups finish close together instead of
+// idling for up to one full item; lists of fewer than four items per
+// workgroup are already cut fine. The grouping by (histogram, window) is
+// kept.
+void refine_tail(std::vector<WorkItem> &items, int grid, int step, bool split_diag) {
   const size_t n = items.size();
-  const size_t tail = std::min<size_t>(n, static_cast<size_t>(std::max(grid, 0)));
-  if (tail == 0) return;
+  const size_t tail = static_cast<size_t>(std::max(grid, 0));
+  if (tail == 0 || n < 4 * tail) return;
   std::vector<WorkItem> out(items.begin(), items.end() - static_cast<std::ptrdiff_t>(tail));
   out.reserve(n + 3 * tail);
   for (size_t q = n - tail; q < n; ++q) {
     const WorkItem &w = items[q];
     const int32_t len = w.j1 - w.j0;
-    const int32_t piece = std::max<int32_t>(tj, (len / 4 + tj - 1) / tj * tj);
-    if ((w.flags & kItemDiag) || len <= piece) {
+    const int32_t piece = std::max<int32_t>(step, (len / 4 + step - 1) / step * step);
+    if ((!split_diag && (w.flags & kItemDiag)) || len <= piece) {
       out.push_back(w);
       continue;
     }
@@ -773,11 +774,13 @@ int run_frame(dh_ctx *ctx, hipStream_t st, const FrameJob &job, const Knobs &k, 
   const uint64_t work = job.total * static_cast<uint64_t>(L.n_sweeps);
   const uint64_t limit = ctx->launch_pairs;
   if (limit > 0 && work > limit) {
-    // items of at least kMinItemPairs keep the work list of a huge frame small
-    const int64_t bi = static_cast<int64_t>(L.cfg.threads) * L.cfg.r;
-    const int64_t min_jc = (kMinItemPairs / bi + L.cfg.tj - 1) / L.cfg.tj * L.cfg.tj;
-    L.cfg.jchunk = std::max<int32_t>(jchunk_for(L.cfg, L.grid, limit, k.items_per_wg),
-                                     static_cast<int32_t>(std::min<int64_t>(min_jc, 64 * L.cfg.tj)));
+    // items of at least kMinBoundedPairs keep the work list of a huge frame small
+    set_items(L.cfg, job.precision, fp.box, L.grid, limit, k.items_per_wg);
+    const int64_t min_jc =
+        (kMinBoundedPairs / L.cfg.iblock + L.cfg.tj - 1) / L.cfg.tj * L.cfg.tj;
+    L.cfg.jchunk = std::max<int32_t>(
+        L.cfg.jchunk, static_cast<int32_t>(std::min<int64_t>(min_jc, 64 * L.cfg.tj)));
+    if (fp.box != kBoxTricSorted) L.cfg.dchunk = L.cfg.jchunk;
   }
   std::vector<WorkItem> items;
   std::vector<uint64_t> pairs;
@@ -802,7 +805,7 @@ int run_frame(dh_ctx *ctx, hipStream_t st, const FrameJob &job, const Knobs &k, 
     for (size_t c = 0; c + 1 < cuts.size(); ++c) {
       seg.assign(items.begin() + static_cast<std::ptrdiff_t>(cuts[c]),
                  items.begin() + static_cast<std::ptrdiff_t>(cuts[c + 1]));
-      refine_tail(seg, L.grid, L.cfg.tj);
+      refine_tail(seg, L.grid, tail_step(fp.box, L.cfg.tj), fp.box != kBoxTricSorted);
       all.insert(all.end(), seg.begin(), seg.end());
       at.push_back(all.size());
     }
@@ -1164,7 +1167,7 @@ void ctx_release_scratch(dh_ctx *ctx) {
 size_t job_scratch_bytes(int64_t n_points, int32_t n_hist, int32_t n_bins, int32_t precision,
                          int64_t launch_pairs) {
   // staged coordinates plus the work blob (frame constants, pair counts and
-  // work items: a few MB, plus one item per kMinItemPairs pairs of every bin
+  // work items: a few MB, plus one item per kMinBoundedPairs pairs of every bin
   // window when the frame runs as bounded launches, and the tail pieces of
   // every launch, at most three more items per workgroup of a grid of at
   // most 2,048; at least 9,000 bins fit one window, and beyond 64 windows
@@ -1176,7 +1179,7 @@ size_t job_scratch_bytes(int64_t n_points, int32_t n_hist, int32_t n_bins, int32
       launch_pairs > 0 ? work / static_cast<uint64_t>(launch_pairs) + 1 : 1;
   return static_cast<size_t>(n) * coord_bytes(precision) + (4u << 20) +
          static_cast<size_t>(n_hist) * 8 +
-         static_cast<size_t>(work / kMinItemPairs + launches * 3 * 2048) * sizeof(WorkItem);
+         static_cast<size_t>(work / kMinBoundedPairs + launches * 3 * 2048) * sizeof(WorkItem);
 }
 
 }  // namespace dh
@@ -1587,9 +1590,13 @@ int dh_batch_create(dh_ctx *ctx, const dh_frame_desc *frames, int32_t n_frames, 
     for (int32_t f : fs) info[f].fp.noclamp = (info[f].noclamp_ok && info[f].slots <= stride) ? 1 : 0;
     g.stride = static_cast<int>(stride);
     g.lds = gbase.tile_bytes + static_cast<size_t>(g.cfg.copies) * g.stride * 4;
-    resolve_threads(precision, g.kind, g.mode, bk, g.lds, g.cfg);
+    resolve_threads(precision, g.kind, g.mode, bk, g.lds, work, g.cfg);
     g.grid = grid_for_config(ctx->n_cu, precision, g.kind, g.mode, gbase, g.lds, g.cfg);
-    g.cfg.jchunk = jchunk_for(g.cfg, g.grid, work, gbase.items_per_wg);
+    // four times as many items as a single frame gets: the list ends with the
+    // small frames, whose items cannot be cut by the size of the large ones
+    // (24 frames of 11k to 188k points, binary32: 24.1 ms with as many as a
+    // single frame, 21.9 ms with these and the cut tail)
+    set_items(g.cfg, precision, g.kind, g.grid, work, 4 * gbase.items_per_wg);
     // large frames first: the tail of the work list is made of small items
     std::stable_sort(fs.begin(), fs.end(),
                      [&](int32_t x, int32_t y) { return info[x].pairs > info[y].pairs; });
@@ -1601,6 +1608,11 @@ int dh_batch_create(dh_ctx *ctx, const dh_frame_desc *frames, int32_t n_frames, 
       pairs_base[f] = pairs.size();
       plan_frame(f, info[f].offsets.data(), frames[f].n_species, L, items, pairs);
     }
+    std::vector<WorkItem> own(items.begin() + static_cast<std::ptrdiff_t>(g.item_begin),
+                              items.end());
+    refine_tail(own, g.grid, tail_step(g.kind, g.cfg.tj), g.kind != kBoxTricSorted);
+    items.resize(g.item_begin);
+    items.insert(items.end(), own.begin(), own.end());
     g.item_count = items.size() - g.item_begin;
     b->groups.push_back(g);
     b->total_pairs += static_cast<double>(work);

@@ -59,7 +59,7 @@ enum HistMode : int32_t {
 };
 
 // WorkItem::flags
-constexpr int32_t kItemDiag = 1;  // i- and j-range are the same block: count j > i only
+constexpr int32_t kItemDiag = 1;  // the j-range lies in the i-block: count j > i only
 constexpr int32_t kItemFull = 2;  // every lane holds a valid i-particle
 
 constexpr int kShifts = 27;
@@ -173,10 +173,62 @@ struct KernelConfig {
   int32_t threads;   // workgroup size: 256, 512 or 1024
   int32_t r;         // i-particles per lane (4 or 8)
   int32_t copies;    // interleaved sub-histogram copies (1, 2, 4)
-  int32_t tj;        // j-tile length (<= threads)
-  int32_t jchunk;    // j-range of one work item (multiple of tj)
+  int32_t tj;        // j-tile length (sorted frames), longest j-piece of a unit
+  int32_t iblock;    // i-range of one work item (multiple of 64 r)
+  int32_t jchunk;    // j-range of one work item
+  int32_t dchunk;    // j-range of one item on the diagonal of its i-block
   int32_t wg_per_cu; // 0 = as many as fit
 };
+
+// How a work list cuts pairs into items: `work` pairs over `grid` workgroups,
+// about items_per_wg items each, as i-blocks of whole 64 r-particle slices by
+// j-ranges.
+//
+// Unsorted frames: an item's waves share it in units (see run_units), so its
+// i-block may be any number of slices. It starts as one slice per wave and is
+// halved while the item would be wider in i than in j: a frame of a few
+// thousand points then still gives every CU an item, where whole
+// threads x r blocks left most of the chip idle. An item costs a few
+// microseconds to draw, start and, where the histogram changes, flush, in
+// which a CU counts some 5e4 binary32 pairs: items are not cut below
+// kMinItemPairs, nor, once every workgroup has one, below the size given
+// here (20,000 points in a cube, 1,000 bins: binary32 123 us with 8 items of
+// 32k pairs a workgroup, 86 us with two of 122k; binary64 234 and 202 us).
+//
+// Sorted frames: one slice per wave, whole j-tiles, the block on the
+// diagonal in one item.
+constexpr int64_t kMinItemPairs = int64_t{1} << 15;
+constexpr int32_t kMinChunk = 32;
+// granularity of the j-pieces the tail of a work list is cut into
+inline int32_t tail_step(int32_t kind, int32_t tj) {
+  return kind == kBoxTricSorted ? tj : kMinChunk;
+}
+inline void set_items(KernelConfig &c, int32_t precision, int32_t kind, int grid, uint64_t work,
+                      int items_per_wg) {
+  const uint64_t g = static_cast<uint64_t>(grid > 0 ? grid : 1);
+  const int64_t full = static_cast<int64_t>(c.threads) * c.r;
+  int64_t bi = full, jc;
+  if (kind == kBoxTricSorted) {
+    jc = static_cast<int64_t>(work / (g * items_per_wg * full + 1));
+    jc = (jc + c.tj - 1) / c.tj * c.tj;
+    jc = jc < c.tj ? c.tj : jc;
+    jc = jc > 64 * c.tj ? 64 * c.tj : jc;
+    c.dchunk = static_cast<int32_t>(bi);
+  } else {
+    const int64_t per_wg = static_cast<int64_t>(work / g), small = int64_t{1}
+                                                                   << (precision ? 16 : 17);
+    int64_t target = per_wg < small ? per_wg : small;
+    target = target < kMinItemPairs ? kMinItemPairs : target;
+    target = per_wg / items_per_wg > target ? per_wg / items_per_wg : target;
+    while (bi > 64 * c.r && target / bi < bi) bi /= 2;
+    jc = (target / bi + kMinChunk - 1) / kMinChunk * kMinChunk;
+    jc = jc < kMinChunk ? kMinChunk : jc;
+    jc = jc > 64 * c.tj ? 64 * c.tj : jc;
+    c.dchunk = static_cast<int32_t>(jc);
+  }
+  c.iblock = static_cast<int32_t>(bi);
+  c.jchunk = static_cast<int32_t>(jc);
+}
 
 // Species pair (s, t) of histogram h among k species, in the library order:
 // (0,0), (1,1), ..., (k-1,k-1), then (s,t) for s < t lexicographically.
@@ -196,11 +248,11 @@ __host__ __device__ inline void hist_pair(int32_t k, int32_t h, int32_t &s, int3
 
 // How the work list of one histogram is cut (the host planner and the
 // device planner of the allocation-free entry point emit the same items):
-// rows are blocks of bi particles in the lanes; an intra-species row has a
-// diagonal item (when its block holds at least two particles) followed by
-// j-chunks of at most jc particles from the end of its block to the end of
-// the species; a cross-species row puts the larger species in the lanes and
-// streams the smaller one in j-chunks.
+// rows are blocks of bi particles in the lanes; an intra-species row has
+// diagonal items (when its block holds at least two particles) of at most dc
+// j each, followed by j-chunks of at most jc particles from the end of its
+// block to the end of the species; a cross-species row puts the larger
+// species in the lanes and streams the smaller one in j-chunks.
 struct HistRows {
   int64_t lane0, lane1;  // particles in the lanes
   int64_t str0, str1;    // particles streamed as j (cross-species)
@@ -232,17 +284,18 @@ __host__ __device__ inline int64_t hist_row_count(const HistRows &r, int64_t bi)
 }
 
 __host__ __device__ inline int64_t row_item_count(const HistRows &r, int64_t row, int64_t bi,
-                                                  int64_t jc) {
+                                                  int64_t jc, int64_t dc) {
   const int64_t b0 = r.lane0 + row * bi;
   const int64_t b1 = b0 + bi < r.lane1 ? b0 + bi : r.lane1;
-  if (r.intra) return (b1 - b0 >= 2 ? 1 : 0) + (r.lane1 - b1 + jc - 1) / jc;
+  if (r.intra)
+    return (b1 - b0 >= 2 ? (b1 - b0 + dc - 1) / dc : 0) + (r.lane1 - b1 + jc - 1) / jc;
   return (r.str1 - r.str0 + jc - 1) / jc;
 }
 
 // Writes the items of one row (for bin window `sweep`) from dst on; returns
 // how many. Flags as in WorkItem.
 __host__ __device__ inline int64_t emit_row(const HistRows &r, int32_t h, int32_t sweep,
-                                            int64_t row, int64_t bi, int64_t jc,
+                                            int64_t row, int64_t bi, int64_t jc, int64_t dc,
                                             WorkItem *dst) {
   const int64_t b0 = r.lane0 + row * bi;
   const int64_t b1 = b0 + bi < r.lane1 ? b0 + bi : r.lane1;
@@ -256,13 +309,26 @@ __host__ __device__ inline int64_t emit_row(const HistRows &r, int32_t h, int32_
     dst[n++] = w;
   };
   if (r.intra) {
-    if (b1 - b0 >= 2) put(b0, b1, kItemDiag);
+    if (b1 - b0 >= 2)
+      for (int64_t j = b0; j < b1; j += dc) put(j, j + dc < b1 ? j + dc : b1, kItemDiag);
     for (int64_t j = b1; j < r.lane1; j += jc) put(j, j + jc < r.lane1 ? j + jc : r.lane1, 0);
   } else {
     for (int64_t j = r.str0; j < r.str1; j += jc) put(j, j + jc < r.str1 ? j + jc : r.str1, 0);
   }
   return n;
 }
+
+// The pair kernel of a precision (T = float or double) and accumulation mode
+// for r i-particles per lane and a box kind (dh_pairs.hip).
+using PairFn = void (*)(PairKernelArgs);
+template <typename T, int MODE>
+PairFn pick_pairs(int r, int box);
+template <> PairFn pick_pairs<float, kModeLds>(int r, int box);
+template <> PairFn pick_pairs<float, kModeSweep>(int r, int box);
+template <> PairFn pick_pairs<float, kModeGlobal>(int r, int box);
+template <> PairFn pick_pairs<double, kModeLds>(int r, int box);
+template <> PairFn pick_pairs<double, kModeSweep>(int r, int box);
+template <> PairFn pick_pairs<double, kModeGlobal>(int r, int box);
 
 // host-side launchers (dh_kernels.hip)
 // Staging of a kBoxTricSorted frame: the points of every species in Morton

@@ -88,7 +88,7 @@ struct PlanArgs {
   int32_t k;
   int32_t n_sweeps;
   int32_t n_counters;
-  int64_t bi, jc;
+  int64_t bi, jc, dc;
   int64_t n_items;  // items the host counted: the list is never written past it
   FrameParams *fp_dst;
   uint64_t *pairs;
@@ -115,7 +115,7 @@ __global__ __launch_bounds__(kPlanThreads) void noalloc_plan_kernel(FrameParams 
     for (int32_t sw = 0; sw < a.n_sweeps; ++sw) {
       for (int64_t r0 = 0; r0 < nr; r0 += blockDim.x) {
         const int64_t row = r0 + tid;
-        const int64_t cnt = row < nr ? row_item_count(r, row, a.bi, a.jc) : 0;
+        const int64_t cnt = row < nr ? row_item_count(r, row, a.bi, a.jc, a.dc) : 0;
         scan[tid] = cnt;
         __syncthreads();
         for (int o = 1; o < static_cast<int>(blockDim.x); o <<= 1) {
@@ -125,7 +125,8 @@ __global__ __launch_bounds__(kPlanThreads) void noalloc_plan_kernel(FrameParams 
           __syncthreads();
         }
         const int64_t at = base + scan[tid] - cnt;
-        if (cnt > 0 && at + cnt <= a.n_items) emit_row(r, h, sw, row, a.bi, a.jc, a.items + at);
+        if (cnt > 0 && at + cnt <= a.n_items) 
+          emit_row(r, h, sw, row, a.bi, a.jc, a.dc, a.items + at);
         base += scan[blockDim.x - 1];
         __syncthreads();
       }
@@ -172,13 +173,12 @@ extern "C" int dh_histo_noalloc(dh_stream stream, const double *d_coords,
   uint64_t total = 0;
   for (int32_t h = 0; h < n_hist; ++h) total += hist_rows(offsets, n_species, h).pairs;
   const LaunchPlan L = default_launch(dev.n_cu, dev.lds, precision, fp, total);
-  const int64_t bi = static_cast<int64_t>(L.cfg.threads) * L.cfg.r;
-  const int64_t jc = L.cfg.jchunk;
+  const int64_t bi = L.cfg.iblock, jc = L.cfg.jchunk, dc = L.cfg.dchunk;
   int64_t n_items = 0;
   for (int32_t h = 0; h < n_hist; ++h) {
     const HistRows r = hist_rows(offsets, n_species, h);
     const int64_t nr = hist_row_count(r, bi);
-    for (int64_t row = 0; row < nr; ++row) n_items += row_item_count(r, row, bi, jc);
+    for (int64_t row = 0; row < nr; ++row) n_items += row_item_count(r, row, bi, jc, dc);
   }
   n_items *= L.n_sweeps;
 
@@ -220,6 +220,7 @@ extern "C" int dh_histo_noalloc(dh_stream stream, const double *d_coords,
   pa.n_counters = n_counters;
   pa.bi = bi;
   pa.jc = jc;
+  pa.dc = dc;
   pa.n_items = n_items;
   pa.fp_dst = reinterpret_cast<FrameParams *>(base + off_fp);
   pa.pairs = reinterpret_cast<uint64_t *>(base + off_pairs);

@@ -241,36 +241,22 @@ int64_t job_footprint(int64_t n, int32_t n_hist, int32_t n_bins, int32_t precisi
          2 * static_cast<int64_t>(n_hist) * static_cast<int64_t>(sizeof(uint64_t));
 }
 
-// j-range of one item: about kItemsPerWg items per workgroup of a launch's
-// share of the job, in whole j-tiles (the host planner's rule, applied to
-// at most one launch of work).
-int64_t serve_jchunk(const LaunchPlan &p, uint64_t work) {
-  const uint64_t bi = static_cast<uint64_t>(p.cfg.threads) * p.cfg.r;
-  const uint64_t w = std::min<uint64_t>(work, kLaunchPairs);
-  uint64_t jc = w / (static_cast<uint64_t>(std::max(1, p.grid)) * kItemsPerWg * bi + 1);
-  jc = (jc + p.cfg.tj - 1) / p.cfg.tj * p.cfg.tj;
-  jc = std::max<uint64_t>(jc, p.cfg.tj);
-  jc = std::min<uint64_t>(jc, 64ull * p.cfg.tj);
-  return static_cast<int64_t>(jc);
-}
-
 uint64_t item_pairs(const WorkItem &w) {
   return static_cast<uint64_t>(w.i1 - w.i0) * static_cast<uint64_t>(w.j1 - w.j0);
 }
 
 // Splits the last `grid` items of a launch into pieces of about a quarter of
-// their j-range (whole j-tiles; diagonal items stay whole), so workgroups
-// finish close together.
-void refine_tail(std::vector<WorkItem> &items, int grid, int tj) {
+// their j-range (in multiples of `step`), so workgroups finish close together.
+void refine_tail(std::vector<WorkItem> &items, int grid, int step, bool split_diag) {
   const size_t n = items.size();
-  const size_t tail = std::min<size_t>(n, static_cast<size_t>(std::max(grid, 0)));
-  if (tail == 0) return;
+  const size_t tail = static_cast<size_t>(std::max(grid, 0));
+  if (tail == 0 || n < 4 * tail) return;
   std::vector<WorkItem> last(items.end() - static_cast<std::ptrdiff_t>(tail), items.end());
   items.resize(n - tail);
   for (const WorkItem &w : last) {
     const int32_t len = w.j1 - w.j0;
-    const int32_t piece = std::max<int32_t>(tj, (len / 4 + tj - 1) / tj * tj);
-    if ((w.flags & dh::kItemDiag) || len <= piece) {
+    const int32_t piece = std::max<int32_t>(step, (len / 4 + step - 1) / step * step);
+    if ((!split_diag && (w.flags & dh::kItemDiag)) || len <= piece) {
       items.push_back(w);
       continue;
     }
@@ -336,8 +322,11 @@ int start_job(dh_server *s, int slot_idx) {
   s->h_frames[slot_idx] = fp;
 
   // items of every histogram and bin window; the frame is the slot index
-  const int64_t bi = static_cast<int64_t>(j.plan.cfg.threads) * j.plan.cfg.r;
-  const int64_t jc = serve_jchunk(j.plan, total * static_cast<uint64_t>(j.plan.n_sweeps));
+  // (about kItemsPerWg items per workgroup of at most one launch of work)
+  dh::set_items(j.plan.cfg, j.precision, j.kind, j.plan.grid,
+                std::min<uint64_t>(total * static_cast<uint64_t>(j.plan.n_sweeps), kLaunchPairs),
+                kItemsPerWg);
+  const int64_t bi = j.plan.cfg.iblock, jc = j.plan.cfg.jchunk, dc = j.plan.cfg.dchunk;
   j.items.clear();
   for (int32_t h = 0; h < j.n_hist; ++h) {
     const dh::HistRows r = dh::hist_rows(j.offsets.data(), k, h);
@@ -345,8 +334,8 @@ int start_job(dh_server *s, int slot_idx) {
     for (int32_t sw = 0; sw < j.plan.n_sweeps; ++sw)
       for (int64_t row = 0; row < nr; ++row) {
         const size_t at = j.items.size();
-        j.items.resize(at + static_cast<size_t>(dh::row_item_count(r, row, bi, jc)));
-        dh::emit_row(r, h, sw, row, bi, jc, j.items.data() + at);
+        j.items.resize(at + static_cast<size_t>(dh::row_item_count(r, row, bi, jc, dc)));
+        dh::emit_row(r, h, sw, row, bi, jc, dc, j.items.data() + at);
       }
   }
   j.left = 0;
@@ -487,7 +476,8 @@ bool issue_launch(dh_server *s) {
     if (j.next_item == j.items.size()) finished.push_back(q);
   }
   grid = std::max(1, std::min<int>(grid, static_cast<int>(list.size())));
-  refine_tail(list, grid, top.plan.cfg.tj);
+  refine_tail(list, grid, dh::tail_step(top.kind, top.plan.cfg.tj),
+              top.kind != dh::kBoxTricSorted);
   Region &R = s->regions[reg];
   std::memcpy(R.h_items, list.data(), list.size() * sizeof(WorkItem));
   int32_t *h_counter = reinterpret_cast<int32_t *>(R.h_items + kMaxItemsPerLaunch);
