@@ -449,7 +449,7 @@ BaseConfig base_config(size_t lds_per_block, int precision, const Knobs &k, int 
   // entry of pad: the look-ahead read of j may touch the entry just past the
   // second tile
   b.tile_bytes = 32;
-  if (kind == kBoxTricSorted)
+  if (kind == kBoxTricSorted && !padded_frame(precision, kind))
     b.tile_bytes = (2 * static_cast<size_t>(c.tj) + 1) * staged_point_bytes(precision, kind) +
                    kSortedBoxBytes;
   // the search kernels keep their queues after the histogram; counting them
@@ -552,12 +552,12 @@ Launch choose_launch(const dh_ctx *ctx, int precision, const FrameParams &fp,
 // Work items of one frame, grouped by (histogram, sweep); the rows and items
 // of each histogram as hist_rows / emit_row cut them (shared with the
 // device-side planner).
-void plan_frame(int32_t frame, const int64_t *off, int32_t k, const Launch &L,
+void plan_frame(int32_t frame, const int64_t *off, int32_t k, bool padded, const Launch &L,
                 std::vector<WorkItem> &items, std::vector<uint64_t> &pairs) {
   const int64_t bi = L.cfg.iblock, jc = L.cfg.jchunk, dc = L.cfg.dchunk;
   const int32_t n_hist = k * (k + 1) / 2;
   for (int32_t h = 0; h < n_hist; ++h) {
-    const HistRows r = hist_rows(off, k, h);
+    const HistRows r = hist_rows(off, k, h, padded);
     pairs.push_back(r.pairs);
     const size_t first = items.size();
     const int64_t nr = hist_row_count(r, bi);
@@ -780,11 +780,13 @@ int run_frame(dh_ctx *ctx, hipStream_t st, const FrameJob &job, const Knobs &k, 
         (kMinBoundedPairs / L.cfg.iblock + L.cfg.tj - 1) / L.cfg.tj * L.cfg.tj;
     L.cfg.jchunk = std::max<int32_t>(
         L.cfg.jchunk, static_cast<int32_t>(std::min<int64_t>(min_jc, 64 * L.cfg.tj)));
-    if (fp.box != kBoxTricSorted) L.cfg.dchunk = L.cfg.jchunk;
+    if (fp.box != kBoxTricSorted || padded_frame(job.precision, fp.box))
+      L.cfg.dchunk = L.cfg.jchunk;
   }
   std::vector<WorkItem> items;
   std::vector<uint64_t> pairs;
-  plan_frame(0, job.offsets, job.n_species, L, items, pairs);
+  plan_frame(0, job.offsets, job.n_species, padded_frame(job.precision, job.kind), L, items,
+             pairs);
   std::vector<size_t> cuts(1, 0);
   if (limit > 0 && work > limit) {
     uint64_t acc = 0;
@@ -805,7 +807,8 @@ int run_frame(dh_ctx *ctx, hipStream_t st, const FrameJob &job, const Knobs &k, 
     for (size_t c = 0; c + 1 < cuts.size(); ++c) {
       seg.assign(items.begin() + static_cast<std::ptrdiff_t>(cuts[c]),
                  items.begin() + static_cast<std::ptrdiff_t>(cuts[c + 1]));
-      refine_tail(seg, L.grid, tail_step(fp.box, L.cfg.tj), fp.box != kBoxTricSorted);
+      refine_tail(seg, L.grid, tail_step(job.precision, fp.box, L.cfg.tj),
+                  fp.box != kBoxTricSorted || padded_frame(job.precision, fp.box));
       all.insert(all.end(), seg.begin(), seg.end());
       at.push_back(all.size());
     }
@@ -1332,6 +1335,7 @@ int histo_job(dh_ctx *ctx, hipStream_t stream, const double *d_coords, const int
   job.kind = staged_kind(frame_consts(box_type, box, r_max, n_bins, job.fp), precision,
                          job.fp.L, n);
   job.fp.box = job.kind;
+  job.fp.n_pad = static_cast<int32_t>(padded_start(offsets, n_species));
   for (int s = 0; s < n_species; ++s) {
     const uint64_t a = static_cast<uint64_t>(offsets[s + 1] - offsets[s]);
     job.total += a * (a > 0 ? a - 1 : 0) / 2;
@@ -1516,6 +1520,7 @@ int dh_batch_create(dh_ctx *ctx, const dh_frame_desc *frames, int32_t n_frames, 
         staged_kind(frame_consts(d.box_type, d.box, d.r_max, d.n_bins, fi.fp), precision,
                     fi.fp.L, n);
     fi.fp.box = kind;
+    fi.fp.n_pad = static_cast<int32_t>(padded_start(d.offsets, d.n_species));
     fi.offsets.assign(d.offsets, d.offsets + d.n_species + 1);
     // the bin window that fits beside this kind's j-tiles
     const BaseConfig fbase = base_config(ctx->lds_per_block, precision, bk, kind);
@@ -1606,11 +1611,13 @@ int dh_batch_create(dh_ctx *ctx, const dh_frame_desc *frames, int32_t n_frames, 
     for (int32_t f : fs) {
       L.n_sweeps = info[f].fp.n_sweeps;
       pairs_base[f] = pairs.size();
-      plan_frame(f, info[f].offsets.data(), frames[f].n_species, L, items, pairs);
+      plan_frame(f, info[f].offsets.data(), frames[f].n_species,
+                 padded_frame(precision, info[f].fp.box), L, items, pairs);
     }
     std::vector<WorkItem> own(items.begin() + static_cast<std::ptrdiff_t>(g.item_begin),
                               items.end());
-    refine_tail(own, g.grid, tail_step(g.kind, g.cfg.tj), g.kind != kBoxTricSorted);
+    refine_tail(own, g.grid, tail_step(precision, g.kind, g.cfg.tj),
+                g.kind != kBoxTricSorted || padded_frame(precision, g.kind));
     items.resize(g.item_begin);
     items.insert(items.end(), own.begin(), own.end());
     g.item_count = items.size() - g.item_begin;

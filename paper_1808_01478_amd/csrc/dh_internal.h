@@ -32,13 +32,40 @@ constexpr int64_t kSortMinPoints = int64_t{1} << 16;
 // counts bit for bit) and the binary32 special case of equal orthorhombic
 // edges.
 inline int staged_kind(int kind, int precision, const double L[3], int64_t n_points) {
-  if (n_points >= kSortMinPoints &&
+  // (padded indices fit in 32 bits)
+  if (n_points >= kSortMinPoints && n_points <= 0x7FFFFFFF - 64 * kMaxSpeciesStage &&
       (kind == kBoxTric || (kind == kBoxOrtho && precision != 0)))
     return kBoxTricSorted;
   if (precision != 0) return kind;
   if (kind == kBoxOrtho && L[0] == L[1] && L[1] == L[2]) return kBoxCube;
   return kind;
 }
+
+// i-span of a work unit of a sorted frame (see dh_sorted.h)
+constexpr int32_t kUnitPoints = 512;
+
+// Binary32 sorted frames are staged with every species at a multiple of 64
+// points ("padded" indices, used by their work items too), so that index / 64
+// is a point's group: the Cartesian positions (float4), the fixed-point words
+// (three each) and the groups' boxes, which together fit in the 32 bytes per
+// point of staged_point_bytes (29 per padded point plus one box; frames have
+// at least kSortMinPoints points and at most kMaxSpeciesStage species).
+inline bool padded_frame(int precision, int kind) {
+  return kind == kBoxTricSorted && precision == 0;
+}
+__host__ __device__ inline int64_t padded_start(const int64_t *off, int32_t s) {
+  int64_t p = 0;
+  for (int32_t u = 0; u < s; ++u) p += (off[u + 1] - off[u] + 63) / 64 * 64;
+  return p;
+}
+// Bounding boxes of a group of 64 points of one species: fixed-point
+// fractional coordinates and Cartesian positions relative to the cell centre.
+struct GroupBox {
+  uint32_t ulo[3], uhi[3];
+  float clo[3], chi[3];
+  uint32_t unused[4];
+};
+static_assert(sizeof(GroupBox) == 64, "one box per 64 points at one byte a point");
 
 // Bytes per staged point (binary64 double4; binary32 float4, two of them
 // for spatially sorted frames) and the sort workspace of a frame.
@@ -101,6 +128,7 @@ struct FrameParams {
   uint64_t *oor;       // caller's out-of-range counts [H] or null (device)
   const uint64_t *pairs;  // pairs per histogram [H] (device)
   int64_t n_points;
+  int32_t n_pad;   // sorted binary32 frames: points with every species padded
   int32_t n_hist;
   int32_t oor_by_flush;  // 1: oor starts at pairs and every flush subtracts its counts
   int32_t n_bins;
@@ -195,20 +223,31 @@ struct KernelConfig {
 // here (20,000 points in a cube, 1,000 bins: binary32 123 us with 8 items of
 // 32k pairs a workgroup, 86 us with two of 122k; binary64 234 and 202 us).
 //
-// Sorted frames: one slice per wave, whole j-tiles, the block on the
+// Sorted binary32 frames are cut alike, in units of kUnitPoints: their items
+// are larger, since most of an item may be beyond the cut-off.
+//
+// Sorted binary64 frames: one slice per wave, whole j-tiles, the block on the
 // diagonal in one item.
 constexpr int64_t kMinItemPairs = int64_t{1} << 15;
 constexpr int32_t kMinChunk = 32;
 // granularity of the j-pieces the tail of a work list is cut into
-inline int32_t tail_step(int32_t kind, int32_t tj) {
-  return kind == kBoxTricSorted ? tj : kMinChunk;
+inline int32_t tail_step(int32_t precision, int32_t kind, int32_t tj) {
+  return kind != kBoxTricSorted ? kMinChunk : precision ? tj : kUnitPoints;
 }
 inline void set_items(KernelConfig &c, int32_t precision, int32_t kind, int grid, uint64_t work,
                       int items_per_wg) {
   const uint64_t g = static_cast<uint64_t>(grid > 0 ? grid : 1);
   const int64_t full = static_cast<int64_t>(c.threads) * c.r;
   int64_t bi = full, jc;
-  if (kind == kBoxTricSorted) {
+  if (padded_frame(precision, kind)) {
+    const int64_t target = static_cast<int64_t>(work / (g * items_per_wg));
+    bi = 16 * kUnitPoints;
+    while (bi > kUnitPoints && target / bi < bi) bi /= 2;
+    jc = (target / bi + kUnitPoints - 1) / kUnitPoints * kUnitPoints;
+    jc = jc < kUnitPoints ? kUnitPoints : jc;
+    jc = jc > 32 * kUnitPoints ? 32 * kUnitPoints : jc;
+    c.dchunk = static_cast<int32_t>(jc);
+  } else if (kind == kBoxTricSorted) {
     jc = static_cast<int64_t>(work / (g * items_per_wg * full + 1));
     jc = (jc + c.tj - 1) / c.tj * c.tj;
     jc = jc < c.tj ? c.tj : jc;
@@ -260,20 +299,25 @@ struct HistRows {
   uint64_t pairs;        // pairs of the histogram
 };
 
-__host__ __device__ inline HistRows hist_rows(const int64_t *off, int32_t k, int32_t h) {
+__host__ __device__ inline HistRows hist_rows(const int64_t *off, int32_t k, int32_t h,
+                                              bool padded = false) {
   int32_t s, t;
   hist_pair(k, h, s, t);
   HistRows r;
   const int64_t ns = off[s + 1] - off[s], nt = off[t + 1] - off[t];
+  const int64_t ps = padded ? padded_start(off, s) : off[s];
+  const int64_t pt = padded ? padded_start(off, t) : off[t];
   r.intra = s == t;
   if (r.intra) {
-    r.lane0 = r.str0 = off[s];
-    r.lane1 = r.str1 = off[s + 1];
+    r.lane0 = r.str0 = ps;
+    r.lane1 = r.str1 = ps + ns;
     r.pairs = static_cast<uint64_t>(ns) * static_cast<uint64_t>(ns > 0 ? ns - 1 : 0) / 2;
   } else {
-    const int32_t si = ns >= nt ? s : t, sj = ns >= nt ? t : s;
-    r.lane0 = off[si]; r.lane1 = off[si + 1];
-    r.str0 = off[sj]; r.str1 = off[sj + 1];
+    // the larger species in the lanes
+    r.lane0 = ns >= nt ? ps : pt;
+    r.lane1 = r.lane0 + (ns >= nt ? ns : nt);
+    r.str0 = ns >= nt ? pt : ps;
+    r.str1 = r.str0 + (ns >= nt ? nt : ns);
     r.pairs = static_cast<uint64_t>(ns) * static_cast<uint64_t>(nt);
   }
   return r;
@@ -333,8 +377,9 @@ template <> PairFn pick_pairs<double, kModeGlobal>(int r, int box);
 // host-side launchers (dh_kernels.hip)
 // Staging of a kBoxTricSorted frame: the points of every species in Morton
 // order of their wrapped fractional coordinates (keys: a workspace of
-// sort_keys_count(n) words); binary32: two float4 per point in `out`,
-// binary64: the input coordinates as one double4 per point.
+// sort_keys_count(n) words); binary32: positions, words and group boxes at
+// padded indices (see padded_frame), binary64: the input coordinates as one
+// double4 per point.
 hipError_t launch_stage_sorted(int precision, const double *in, void *out, int64_t n,
                                const int64_t *offsets, int32_t n_species, const FrameParams &fp,
                                uint64_t *keys, hipStream_t st);

@@ -158,30 +158,68 @@ __global__ void bitonic_global_kernel(uint64_t *__restrict__ keys, int64_t npad,
   }
 }
 
-// Staged entry of the sorted position p: the fixed-point fractional words
-// (a, b, c, c) as for the unsorted binary32 triclinic staging, then the
-// Cartesian position of the same wrapped point relative to the cell centre,
-// B (u - 1/2) with u the fixed-point fraction read back exactly, so the two
-// formats describe one point.
+// Minimum and maximum over the 64 lanes of a wave.
+template <typename V>
+__device__ __forceinline__ V wave_min(V v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o));
+  return v;
+}
+template <typename V>
+__device__ __forceinline__ V wave_max(V v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o));
+  return v;
+}
+
+// binary32 staging of a sorted frame at padded indices (see padded_frame),
+// one group of 64 points per wave: the fixed-point fractional words as for
+// unsorted triclinic frames, the Cartesian position of the same wrapped point
+// relative to the cell centre, B (u - 1/2) with u the fixed-point fraction
+// read back exactly, so the two formats describe one point, and the group's
+// boxes.
 __global__ void stage_sorted_kernel(const double *__restrict__ in,
-                                    const uint64_t *__restrict__ keys, int64_t n, FrameParams p,
-                                    float4 *__restrict__ out) {
-  const int64_t step = static_cast<int64_t>(gridDim.x) * blockDim.x;
-  for (int64_t q = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; q < n;
-       q += step) {
+                                    const uint64_t *__restrict__ keys, SpeciesOffsets off,
+                                    int32_t k, FrameParams p, char *__restrict__ out) {
+  const int lane = threadIdx.x & 63;
+  const int64_t group = blockIdx.x * static_cast<int64_t>(blockDim.x / 64) + threadIdx.x / 64;
+  if (64 * group >= p.n_pad) return;
+  int64_t g0 = 0;
+  int s = 0;
+  for (; s + 1 < k; ++s) {
+    const int64_t ng = (off.v[s + 1] - off.v[s] + 63) / 64;
+    if (group < g0 + ng) break;
+    g0 += ng;
+  }
+  const int64_t q = off.v[s] + 64 * (group - g0) + lane;
+  const bool ok = q < off.v[s + 1];
+  uint32_t u[3] = {0u, 0u, 0u};
+  float c[3] = {0.f, 0.f, 0.f};
+  if (ok) {
     const int64_t i = static_cast<int64_t>(keys[q] & 0x7FFFFFFFull);
     const double x = in[3 * i], y = in[3 * i + 1], z = in[3 * i + 2];
-    const uint32_t ua = fix32(fma(z, p.h13, fma(y, p.h12, x * p.h11)));
-    const uint32_t ub = fix32(fma(z, p.h23, y * p.h22));
-    const uint32_t uc = fix32(z * p.h33);
-    const double va = ua * 0x1p-32 - 0.5, vb = ub * 0x1p-32 - 0.5, vc = uc * 0x1p-32 - 0.5;
-    const float cx = static_cast<float>(fma(p.cx, vc, fma(p.bx, vb, p.ax * va)));
-    const float cy = static_cast<float>(fma(p.cy, vc, p.by * vb));
-    const float cz = static_cast<float>(p.cz * vc);
-    out[2 * q] = make_float4(__uint_as_float(ua), __uint_as_float(ub), __uint_as_float(uc),
-                             __uint_as_float(uc));
-    out[2 * q + 1] = make_float4(cx, cy, cz, 0.f);
+    u[0] = fix32(fma(z, p.h13, fma(y, p.h12, x * p.h11)));
+    u[1] = fix32(fma(z, p.h23, y * p.h22));
+    u[2] = fix32(z * p.h33);
+    const double va = u[0] * 0x1p-32 - 0.5, vb = u[1] * 0x1p-32 - 0.5, vc = u[2] * 0x1p-32 - 0.5;
+    c[0] = static_cast<float>(fma(p.cx, vc, fma(p.bx, vb, p.ax * va)));
+    c[1] = static_cast<float>(fma(p.cy, vc, p.by * vb));
+    c[2] = static_cast<float>(p.cz * vc);
   }
+  const int64_t at = 64 * group + lane;
+  reinterpret_cast<float4 *>(out)[at] = make_float4(c[0], c[1], c[2], 0.f);
+  uint32_t *const words = reinterpret_cast<uint32_t *>(out + 16 * static_cast<int64_t>(p.n_pad)) + 3 * at;
+  GroupBox b;
+#pragma unroll
+  for (int ax = 0; ax < 3; ++ax) {
+    words[ax] = u[ax];
+    b.ulo[ax] = wave_min(ok ? u[ax] : 0xFFFFFFFFu);
+    b.uhi[ax] = wave_max(ok ? u[ax] : 0u);
+    b.clo[ax] = wave_min(ok ? c[ax] : __builtin_inff());
+    b.chi[ax] = wave_max(ok ? c[ax] : -__builtin_inff());
+  }
+  for (uint32_t &v : b.unused) v = 0u;
+  if (lane == 0) reinterpret_cast<GroupBox *>(out + 28 * static_cast<int64_t>(p.n_pad))[group] = b;
 }
 
 // binary64: the input point of the sorted position q, unchanged.
@@ -345,8 +383,8 @@ hipError_t launch_stage_sorted(int precision, const double *in, void *out, int64
     stage_sorted64_kernel<<<grid_for(n, threads), threads, 0, st>>>(in, keys, n,
                                                                     static_cast<double4 *>(out));
   else
-    stage_sorted_kernel<<<grid_for(n, threads), threads, 0, st>>>(in, keys, n, fp,
-                                                                  static_cast<float4 *>(out));
+    stage_sorted_kernel<<<static_cast<int>((fp.n_pad / 64 + 3) / 4), threads, 0, st>>>(
+        in, keys, off, n_species, fp, static_cast<char *>(out));
   return hipGetLastError();
 }
 

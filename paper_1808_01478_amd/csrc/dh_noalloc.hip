@@ -88,6 +88,7 @@ struct PlanArgs {
   int32_t k;
   int32_t n_sweeps;
   int32_t n_counters;
+  bool padded;
   int64_t bi, jc, dc;
   int64_t n_items;  // items the host counted: the list is never written past it
   FrameParams *fp_dst;
@@ -110,7 +111,7 @@ __global__ __launch_bounds__(kPlanThreads) void noalloc_plan_kernel(FrameParams 
   for (int h = tid; h < n_hist; h += blockDim.x) a.pairs[h] = hist_rows(off, a.k, h).pairs;
   int64_t base = 0;
   for (int32_t h = 0; h < n_hist; ++h) {
-    const HistRows r = hist_rows(off, a.k, h);
+    const HistRows r = hist_rows(off, a.k, h, a.padded);
     const int64_t nr = hist_row_count(r, a.bi);
     for (int32_t sw = 0; sw < a.n_sweeps; ++sw) {
       for (int64_t r0 = 0; r0 < nr; r0 += blockDim.x) {
@@ -166,6 +167,7 @@ extern "C" int dh_histo_noalloc(dh_stream stream, const double *d_coords,
   const int kind =
       staged_kind(frame_constants(box_type, box, r_max, n_bins, fp), precision, fp.L, n);
   fp.box = kind;
+  fp.n_pad = static_cast<int32_t>(padded_start(offsets, n_species));
   const size_t point_bytes = staged_point_bytes(precision, kind);
   const size_t keys_bytes =
       kind == kBoxTricSorted ? static_cast<size_t>(sort_keys_count(n)) * sizeof(uint64_t) : 0;
@@ -218,6 +220,7 @@ extern "C" int dh_histo_noalloc(dh_stream stream, const double *d_coords,
   pa.k = n_species;
   pa.n_sweeps = L.n_sweeps;
   pa.n_counters = n_counters;
+  pa.padded = padded_frame(precision, kind);
   pa.bi = bi;
   pa.jc = jc;
   pa.dc = dc;

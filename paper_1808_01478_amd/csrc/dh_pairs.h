@@ -617,263 +617,6 @@ __device__ __forceinline__ void flush_hist(uint32_t *hist, const PairKernelArgs 
   }
 }
 
-// One j-tile of a spatially sorted frame for one wave. For every group of 64
-// j-points of the tile and every slice r of the wave's i-points, the two
-// groups' bounding boxes (fixed-point fractions) decide, axis by axis,
-// whether one lattice shift n is the Eq. 5 wrap of all their pairs: the wrap
-// of u_j - u_i is the n with u_j - u_i - n 2^32 in [-2^31, 2^31), i.e.
-// floor((u_j - u_i + 2^31) / 2^32), in {-1, 0, 1}, and it is shared iff both
-// ends of [jlo - ihi, jhi - ilo] give the same n. Lane 3r + k of the wave
-// tests axis k of slice r, so one pass of a few instructions and four ballots
-// classify all R slices. If every axis is shared, the pairs take the short
-// path: the Cartesian difference to the i-point shifted by B n (a table
-// entry), with no conversion and no cell matrix per pair (3 subtractions, q,
-// root, bin). If exactly one axis K is ambiguous and its two ends differ by
-// one, the pairs take the short path with the shift of K's lower end, or
-// with one more cell vector B_K when the pair's fractional coordinate along
-// K (row K of B^-1 applied to the difference) exceeds 1/2: a compare of the
-// j-point's projection with a threshold of the slice and a select of the
-// shifted i-point. Otherwise they take the fixed-point path of unsorted
-// triclinic frames. The path and the arithmetic of a pair depend only on its
-// two groups (species-aligned blocks of 64 points), not on the launch shape
-// or on the other slices of the wave, so every launch shape, batch and server
-// path gives the same counts.
-template <int R, int MODE, bool DIAG, bool CLAMP, typename CountT>
-__device__ __forceinline__ void sorted_tile(
-    const float4 *__restrict__ tb, const uint32_t *__restrict__ boxes, int jt, int js,
-    int jcount, int wbase, int lane, const FrameParams *F, const Geo32 &g,
-    const float4 *__restrict__ X, int i0, int i1, const float (&cxi)[R], const float (&cyi)[R],
-    const float (&czi)[R], uint32_t ib_lo, uint32_t ib_hi, uint32_t ib_empty, uint32_t hi,
-    uint32_t hib, CountT &count_t) {
-  const float ax = uni(F->cell32[0]), bx = uni(F->cell32[1]), by = uni(F->cell32[2]);
-  const float cx = uni(F->cell32[3]), cy = uni(F->cell32[4]), cz = uni(F->cell32[5]);
-  const float s32 = uni(F->s32);
-  const float h11 = uni(F->hinv32[0]), h12 = uni(F->hinv32[1]), h13 = uni(F->hinv32[2]);
-  const float h22 = uni(F->hinv32[3]), h23 = uni(F->hinv32[4]), h33 = uni(F->hinv32[5]);
-  // the lattice shifts B n, read through the scalar cache with a uniform index
-  using ConstF = const __attribute__((address_space(4))) float;
-  const ConstF *gshift = (const ConstF *)(&F->gshift32[0][0]);
-  constexpr uint32_t kAll = (1u << R) - 1u;
-  // this lane's axis of the group boxes (lanes 3R and up repeat axis 0)
-  const int bk = lane < 3 * R ? lane % 3 : 0;
-  const uint32_t keep = ~ib_empty;
-  for (int g0 = js & ~63; g0 < jcount; g0 += 64) {
-    const int j_begin = max(js, g0), j_end = min(jcount, g0 + 64);
-    const uint32_t *gb = boxes + (g0 >> 6) * 8;
-    const uint32_t jl = gb[bk], jh = gb[3 + bk];
-    // wrap of the lower and upper end of this lane's interval
-    const int nl = static_cast<int>(jl - ib_hi >= 0x80000000u) - static_cast<int>(jl < ib_hi);
-    const int nh = static_cast<int>(jh - ib_lo >= 0x80000000u) - static_cast<int>(jh < ib_lo);
-    // bit 3r + k: axis k of slice r is ambiguous, spans more than two wraps,
-    // has lower-end wrap +1, -1 (an empty slice counts nothing: shift 0)
-    const uint32_t m_amb = static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(nl != nh)) & keep;
-    const uint32_t m_wide = static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(nh - nl > 1)) & keep;
-    const uint32_t m_pos = static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(nl > 0)) & keep;
-    const uint32_t m_neg = static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(nl < 0)) & keep;
-    // per slice: bit r of `fast` when all three shifts are shared, of `fix`
-    // when exactly one axis is ambiguous by one wrap (`amb`: those axes, over
-    // the slices); both get the i-point shifted by the wraps of the lower ends
-    uint32_t fast = 0, fix = 0, amb = 0, ambr[R];
-    float sx[R], sy[R], sz[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const uint32_t a_r = (m_amb >> (3 * r)) & 7u;
-      ambr[r] = a_r;
-      if ((a_r & (a_r - 1u)) == 0u && ((m_wide >> (3 * r)) & 7u) == 0u) {
-        if (a_r == 0u)
-          fast |= 1u << r;
-        else
-          fix |= 1u << r;
-        amb |= a_r;
-        const uint32_t q = ((m_pos >> (3 * r)) & 7u) | (((m_neg >> (3 * r)) & 7u) << 3);
-        const ConstF *S = gshift + 4 * q;
-        sx[r] = cxi[r] + S[0];
-        sy[r] = cyi[r] + S[1];
-        sz[r] = czi[r] + S[2];
-      } else {
-        sx[r] = sy[r] = sz[r] = 0.f;
-      }
-    }
-    // Clamp bounds of a pair (see count_t): l = 0 and lb = the guard word
-    // below bin 0 for a pair that counts, the lane's discard slot for the
-    // lower triangle of a diagonal item. The short paths need nothing else:
-    // a lane past the end of the item holds an i-point at infinity, whose q
-    // is +inf, which the upper clamp discards. The fixed-point path passes
-    // the lane's own bounds (l0, lb0).
-    auto mask = [&](int r, int j, uint32_t &l, uint32_t &lb, uint32_t l0 = 0u,
-                    uint32_t lb0 = kMagicBits - 1u) {
-      l = l0;
-      lb = lb0;
-      if constexpr (DIAG) {
-        const bool up = jt + j > wbase + r * 64 + lane;
-        l = up ? l : hi;
-        lb = up ? lb : hib;
-      }
-    };
-    auto bin = [&](int r, int j, float dx, float dy, float dz) {
-      uint32_t l, lb;
-      mask(r, j, l, lb);
-      const float q = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-      count_t(__float_as_uint(fmaf(__builtin_amdgcn_sqrtf(q), s32, kMagic32)), l, lb);
-    };
-    auto fast_pair = [&](int r, const float4 &C, int j) {
-      bin(r, j, C.x - sx[r], C.y - sy[r], C.z - sz[r]);
-    };
-    // row K of B^-1 applied to a point: its fractional coordinate along K
-    // (up to the constant of the cell centre)
-    auto proj = [&](auto axis_c, float x, float y, float z) {
-      constexpr int K = decltype(axis_c)::value;
-      if constexpr (K == 0)
-        return fmaf(z, h13, fmaf(y, h12, x * h11));
-      else if constexpr (K == 1)
-        return fmaf(z, h23, y * h22);
-      else
-        return z * h33;
-    };
-    // One-axis wrap of slice r along K: the threshold the j-point's
-    // projection must exceed (1/2 above the shifted i-point's; +inf for a
-    // slice whose shift K is shared, which then takes exactly the short
-    // path) and the i-point shifted by one more cell vector B_K.
-    struct Wrap {
-      float th, x, y, z;
-    };
-    auto wrap_of = [&](auto axis_c, int r) {
-      constexpr int K = decltype(axis_c)::value;
-      Wrap w;
-      w.th = (fix >> r) & 1u ? proj(axis_c, sx[r], sy[r], sz[r]) + 0.5f : __builtin_inff();
-      w.x = sx[r] + (K == 0 ? ax : K == 1 ? bx : cx);
-      w.y = K == 0 ? sy[r] : sy[r] + (K == 1 ? by : cy);
-      w.z = K == 2 ? sz[r] + cz : sz[r];
-      return w;
-    };
-    auto fix_pair = [&](auto axis_c, int r, const Wrap &w, const float4 &C, float p, int j) {
-      constexpr int K = decltype(axis_c)::value;
-      const bool up = p > w.th;
-      const float ux = up ? w.x : sx[r];
-      const float uy = K >= 1 && up ? w.y : sy[r];
-      const float uz = K == 2 && up ? w.z : sz[r];
-      bin(r, j, C.x - ux, C.y - uy, C.z - uz);
-    };
-    // The fixed-point path (rare) reloads its i-words: -(b:a) of the
-    // i-point of slice r, -(c':c) of slices 2k and 2k+1 (one 64-bit addition
-    // to j's (c:c) gives both c differences, the second lowered by one unit
-    // when the first borrows), and the lane's clamp bounds.
-    struct SlowI {
-      uint64_t nab, nzz;
-      uint32_t l0, lb0;
-    };
-    auto slow_i = [&](int r) {
-      const int i = wbase + r * 64 + lane, ip = wbase + (r ^ 1) * 64 + lane;
-      const float4 P = X[2 * (i < i1 ? i : i0)];
-      const float4 Q = X[2 * (ip < i1 ? ip : i0)];
-      const float z0 = r % 2 == 0 ? P.z : Q.z, z1 = r % 2 == 0 ? Q.z : P.z;
-      SlowI v;
-      v.nab = 0ull - ((static_cast<uint64_t>(__float_as_uint(P.y)) << 32) | __float_as_uint(P.x));
-      v.nzz = 0ull - ((static_cast<uint64_t>(__float_as_uint(z1)) << 32) | __float_as_uint(z0));
-      v.l0 = i < i1 ? 0u : hi;
-      v.lb0 = i < i1 ? kMagicBits - 1u : hib;
-      return v;
-    };
-    auto slow_pair = [&](int r, const SlowI &v, uint64_t ab, uint64_t cc, int j) {
-      uint32_t l, lb;
-      mask(r, j, l, lb, v.l0, v.lb0);
-      const uint64_t dcc = cc + v.nzz;
-      const float fcd = static_cast<float>(
-          static_cast<int32_t>(static_cast<uint32_t>(r % 2 == 0 ? dcc : dcc >> 32)));
-      count_t(bits32_packed_c<kBoxTric>(ab, v.nab, fcd, g), l, lb);
-    };
-    // Every loop reads the next j before the current j's atomics: LDS
-    // operations complete in order, so a read issued after the atomics would
-    // wait for all of them. At the end of the tile the look-ahead read
-    // touches the entry just past it (the next tile or the box area), never
-    // used. The entry pointer lives in a VGPR so both reads use immediate
-    // offsets (the zero is opaque to the compiler on purpose).
-    int vzero;
-    asm volatile("v_mov_b32 %0, 0" : "=v"(vzero));
-    auto run_j = [&](auto &&body, int part) {
-      // part 1: the Cartesian float4 of each j; part 0: its fixed-point words
-      const float4 *cp = tb + 2 * j_begin + part + vzero;
-      float4 pa = cp[0];
-      int j = j_begin;
-      for (; j + 1 < j_end; j += 2, cp += 4) {
-        const float4 pb = cp[2];
-        __builtin_amdgcn_sched_barrier(0);
-        body(pa, j);
-        pa = cp[4];
-        __builtin_amdgcn_sched_barrier(0);
-        body(pb, j + 1);
-      }
-      if (j < j_end) body(pa, j);
-    };
-    auto words = [](const float4 &e, uint64_t &ab, uint64_t &cc) {
-      ab = (static_cast<uint64_t>(__float_as_uint(e.y)) << 32) | __float_as_uint(e.x);
-      cc = (static_cast<uint64_t>(__float_as_uint(e.w)) << 32) | __float_as_uint(e.z);
-    };
-    auto fix_all = [&](auto axis_c) {
-      Wrap w[R];
-#pragma unroll
-      for (int r = 0; r < R; ++r) w[r] = wrap_of(axis_c, r);
-      run_j([&](const float4 &C, int j) {
-        const float p = proj(axis_c, C.x, C.y, C.z);
-#pragma unroll
-        for (int r = 0; r < R; ++r) fix_pair(axis_c, r, w[r], C, p, j);
-      }, 1);
-    };
-    auto fix_one = [&](auto axis_c, int r) {
-      const Wrap w = wrap_of(axis_c, r);
-      run_j([&](const float4 &C, int j) {
-        fix_pair(axis_c, r, w, C, proj(axis_c, C.x, C.y, C.z), j);
-      }, 1);
-    };
-    if (fast == kAll) {
-      run_j([&](const float4 &C, int j) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) fast_pair(r, C, j);
-      }, 1);
-    } else if ((fast | fix) == kAll && amb == 1u) {
-      fix_all(std::integral_constant<int, 0>{});
-    } else if ((fast | fix) == kAll && amb == 2u) {
-      fix_all(std::integral_constant<int, 1>{});
-    } else if ((fast | fix) == kAll && amb == 4u) {
-      fix_all(std::integral_constant<int, 2>{});
-    } else if ((fast | fix) == 0) {
-      SlowI v[R];
-#pragma unroll
-      for (int r = 0; r < R; ++r) v[r] = slow_i(r);
-      run_j([&](const float4 &A, int j) {
-        uint64_t ab, cc;
-        words(A, ab, cc);
-#pragma unroll
-        for (int r = 0; r < R; ++r) slow_pair(r, v[r], ab, cc, j);
-      }, 0);
-    } else {
-      // slices of different kinds: one pass per slice, each slice the path
-      // its own ambiguity gives it (so the counts do not depend on which
-      // slices share a wave)
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        if (fast & (1u << r)) {
-          run_j([&](const float4 &C, int j) { fast_pair(r, C, j); }, 1);
-        } else if (fix & (1u << r)) {
-          if (ambr[r] == 1u)
-            fix_one(std::integral_constant<int, 0>{}, r);
-          else if (ambr[r] == 2u)
-            fix_one(std::integral_constant<int, 1>{}, r);
-          else
-            fix_one(std::integral_constant<int, 2>{}, r);
-        } else {
-          const SlowI v = slow_i(r);
-          run_j([&](const float4 &A, int j) {
-            uint64_t ab, cc;
-            words(A, ab, cc);
-            slow_pair(r, v, ab, cc, j);
-          }, 0);
-        }
-      }
-    }
-  }
-}
-
 // Lattice shift along one axis shared by every pair of two groups of a
 // binary64 sorted frame. The fractional difference s of a pair (the first
 // step of Eq. 5, with its rounding) lies in [jlo - ihi, jhi - ilo] (the
@@ -1418,13 +1161,6 @@ __device__ __forceinline__ void run_tiles(const PairKernelArgs &a, const WorkIte
     const int jcount = min(tj, w.j1 - jt);
     int js = 0;
     if constexpr (DIAG) js = max(0, min(jcount, wbase + 1 - jt));
-    if constexpr (SORTED && sizeof(T) == 4) {
-      if (wave_active && js < jcount)
-        sorted_tile<R, MODE, DIAG, CLAMP>(tile + buf * tj * EPJ, tboxes + buf * 32, jt, js,
-                                          jcount, wbase, lane, F, g, X, w.i0, w.i1, cxi, cyi,
-                                          czi, ib_lo, ib_hi, ib_empty, hi, hib, count_t);
-      continue;
-    }
     if constexpr (SORTED && sizeof(T) == 8) {
       if (wave_active && js < jcount)
         sorted_tile64<R, DIAG>(tile + buf * tj, reinterpret_cast<const double *>(tboxes) + buf * 32,
@@ -1592,6 +1328,14 @@ __device__ __forceinline__ void run_tiles(const PairKernelArgs &a, const WorkIte
     }
   }
 }
+
+}  // namespace
+}  // namespace dh
+
+#include "dh_sorted.h"
+
+namespace dh {
+namespace {
 
 // One work item of an unsorted frame: the workgroup's waves draw its units
 // from a counter in LDS, a unit being one slice of 64 R i-particles (held in
@@ -2030,7 +1774,7 @@ __global__ __launch_bounds__(max_threads<BOX>()) void pairs_kernel(PairKernelArg
   // binary32 bin -1 (t < 1/4), added to bin 0 on flush. (Sorted frames: the
   // two j-tiles of two entries per j and the tiles' group boxes come first.)
   constexpr int EPJ = BOX == kBoxTricSorted && sizeof(T) == 4 ? 2 : 1;
-  constexpr bool SORTED = BOX == kBoxTricSorted;
+  constexpr bool SORTED = BOX == kBoxTricSorted && sizeof(T) == 8;
   const size_t tiles_bytes =
       SORTED ? 2 * static_cast<size_t>(a.tj) * EPJ * sizeof(V) + kSortedBoxBytes : 0;
   uint32_t *hist = reinterpret_cast<uint32_t *>(smem + tiles_bytes + kGuardBytes);
@@ -2088,6 +1832,8 @@ __global__ __launch_bounds__(max_threads<BOX>()) void pairs_kernel(PairKernelArg
           run_tiles<T, R, BOX, kModeLds, false, false>(a, w, F, tile, my, queue, shifts);
       }
       if (tid == 0) s_item = static_cast<int>(gridDim.x) + atomicAdd(a.counter, 1);
+    } else if constexpr (BOX == kBoxTricSorted) {
+      run_sorted<MODE>(a, w, F, my, &s_unit, &s_item);
     } else {
       run_units<T, R, BOX, MODE>(a, w, F, my, queue, shifts, &s_unit, &s_item);
     }

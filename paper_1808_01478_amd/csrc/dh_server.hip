@@ -283,6 +283,7 @@ int start_job(dh_server *s, int slot_idx) {
       dh::frame_constants(j.box_type, j.has_box ? j.box : nullptr, j.r_max, j.n_bins, fp),
       j.precision, fp.L, j.n);
   fp.box = j.kind;
+  fp.n_pad = static_cast<int32_t>(dh::padded_start(j.offsets.data(), k));
   const size_t staged_b = pts * dh::staged_point_bytes(j.precision, j.kind);
   const size_t out_b = static_cast<size_t>(j.n_hist) * j.n_bins * sizeof(uint64_t);
   const size_t h_b = static_cast<size_t>(j.n_hist) * sizeof(uint64_t);
@@ -329,7 +330,8 @@ int start_job(dh_server *s, int slot_idx) {
   const int64_t bi = j.plan.cfg.iblock, jc = j.plan.cfg.jchunk, dc = j.plan.cfg.dchunk;
   j.items.clear();
   for (int32_t h = 0; h < j.n_hist; ++h) {
-    const dh::HistRows r = dh::hist_rows(j.offsets.data(), k, h);
+    const dh::HistRows r = dh::hist_rows(j.offsets.data(), k, h,
+                                         dh::padded_frame(j.precision, j.kind));
     const int64_t nr = dh::hist_row_count(r, bi);
     for (int32_t sw = 0; sw < j.plan.n_sweeps; ++sw)
       for (int64_t row = 0; row < nr; ++row) {
@@ -476,8 +478,8 @@ bool issue_launch(dh_server *s) {
     if (j.next_item == j.items.size()) finished.push_back(q);
   }
   grid = std::max(1, std::min<int>(grid, static_cast<int>(list.size())));
-  refine_tail(list, grid, dh::tail_step(top.kind, top.plan.cfg.tj),
-              top.kind != dh::kBoxTricSorted);
+  refine_tail(list, grid, dh::tail_step(top.precision, top.kind, top.plan.cfg.tj),
+              top.kind != dh::kBoxTricSorted || dh::padded_frame(top.precision, top.kind));
   Region &R = s->regions[reg];
   std::memcpy(R.h_items, list.data(), list.size() * sizeof(WorkItem));
   int32_t *h_counter = reinterpret_cast<int32_t *>(R.h_items + kMaxItemsPerLaunch);
