@@ -384,7 +384,7 @@ constexpr int32_t kWideDefault64 = 20;
 
 struct Knobs {
   int32_t r = 4;             // i-particles per lane: 4 or 8
-  int32_t copies = 1;        // interleaved LDS copies: 1, 2 or 4
+  int32_t copies = 1;        // LDS sized for 1, 2 or 4 histograms (one is counted into)
   int32_t tj = 256;          // j-tile length: 128 or 256
   int32_t noclamp = 1;       // allow unclamped interior blocks
   int32_t occ_cap = 0;       // workgroups per CU at most (0: as many as fit)
@@ -445,12 +445,13 @@ BaseConfig base_config(size_t lds_per_block, int precision, const Knobs &k, int 
   c.wg_per_cu = k.occ_cap;
   c.iblock = c.threads * c.r;
   c.jchunk = c.dchunk = c.tj;
-  // the guard below the histogram; sorted frames keep two j-tiles, plus one
+  // control words and the guard below the histogram; binary64 sorted frames
+  // keep two j-tiles, plus one
   // entry of pad: the look-ahead read of j may touch the entry just past the
   // second tile
-  b.tile_bytes = 32;
+  b.tile_bytes = kControlBytes + 32;
   if (kind == kBoxTricSorted && !padded_frame(precision, kind))
-    b.tile_bytes = (2 * static_cast<size_t>(c.tj) + 1) * staged_point_bytes(precision, kind) +
+    b.tile_bytes += (2 * static_cast<size_t>(c.tj) + 1) * staged_point_bytes(precision, kind) +
                    kSortedBoxBytes;
   // the search kernels keep their queues after the histogram; counting them
   // with the tiles leaves the histogram budget below them
@@ -466,26 +467,26 @@ BaseConfig base_config(size_t lds_per_block, int precision, const Knobs &k, int 
 }
 
 // Workgroup size "auto": the LDS histogram caps the workgroups per CU, so
-// take the smallest workgroup that still gives each of the 4 SIMDs at least
-// four waves. Frames of kSmallWork pairs and more start at 512 threads: every
-// workgroup adds its own histogram into the output, and half as many of them
-// save more than the finer grain gives (60,000 points in a cube, 1,000 bins,
-// binary32: 482 us against 497 us with 256 threads; 20,000 points: 86 and
-// 94 us); 1,024 threads gain nothing where 512 fill the SIMDs.
+// take the size that puts most waves on a CU, the smallest of equals. Frames
+// of kSmallWork pairs and more start at 512 threads: every workgroup adds its
+// own histogram into the output, and half as many of them save more than the
+// finer grain gives (60,000 points in a cube, 1,000 bins, binary32: 482 us
+// against 497 us with 256 threads; 20,000 points: 86 and 94 us).
 constexpr uint64_t kSmallWork = uint64_t{1} << 22;
 void resolve_threads(int precision, int kind, int mode, const Knobs &k, size_t lds,
                      uint64_t work, KernelConfig &cfg) {
   if (k.threads != 0 || kind == kBoxTricSearch) return;
-  for (int th : {256, 512}) {
+  int best = 0;
+  for (int th : {256, 512, 1024}) {
     if (th == 256 && work >= kSmallWork) continue;
     KernelConfig c = cfg;
     c.threads = th;
-    if (pairs_occupancy(precision, kind, mode, c, lds) * (th / 64) >= 16) {
+    const int waves = pairs_occupancy(precision, kind, mode, c, lds) * (th / 64);
+    if (waves > best) {
+      best = waves;
       cfg.threads = th;
-      return;
     }
   }
-  cfg.threads = 1024;
 }
 
 int grid_for_config(int n_cu, int precision, int kind, int mode, const BaseConfig &b,
@@ -872,7 +873,6 @@ int run_frame(dh_ctx *ctx, hipStream_t st, const FrameJob &job, const Knobs &k, 
     a.items = reinterpret_cast<const WorkItem *>(db + lay.items) + cuts[c];
     a.counter = reinterpret_cast<int32_t *>(db + lay.counter) + c;
     a.n_items = static_cast<int32_t>(cuts[c + 1] - cuts[c]);
-    a.copies = L.cfg.copies;
     a.stride = L.stride;
     a.tj = L.cfg.tj;
     const int g = std::max(1, std::min(grid, a.n_items));
@@ -1059,13 +1059,12 @@ int tune_frame(dh_ctx *ctx, hipStream_t st, const FrameJob &job, const std::stri
   }
   const std::vector<std::vector<int32_t>> choices = {
       {0, 1},            // noclamp
-      {1, 2, 4},         // copies
       {0, 1, 2, 3},      // occ_cap
       {4, 8, 16},        // items_per_wg
       {128, 256},        // tj
   };
-  const int order[5] = {3, 1, 4, 5, 2};  // knob index in pack() order
-  for (int d = 0; d < 5 && !rc; ++d) {
+  const int order[4] = {3, 4, 5, 2};  // knob index in pack() order
+  for (int d = 0; d < 4 && !rc; ++d) {
     const int q = order[d];
     for (int32_t v : choices[d]) {
       std::array<int32_t, kNumKnobs> kp = best.pack();
@@ -1211,7 +1210,6 @@ static int dh_batch_launch_direct(dh_batch *b, hipStream_t st) {
     a.items = reinterpret_cast<const WorkItem *>(db + b->off_items) + g.item_begin;
     a.counter = counters + k;
     a.n_items = static_cast<int32_t>(g.item_count);
-    a.copies = g.cfg.copies;
     a.stride = g.stride;
     a.tj = g.cfg.tj;
     const int grid = std::max(1, std::min<int>(g.grid, a.n_items));

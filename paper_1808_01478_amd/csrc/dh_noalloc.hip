@@ -246,7 +246,6 @@ extern "C" int dh_histo_noalloc(dh_stream stream, const double *d_coords,
     a.items = pa.items;
     a.counter = counters;
     a.n_items = static_cast<int32_t>(n_items);
-    a.copies = L.cfg.copies;
     a.stride = L.stride;
     a.tj = L.cfg.tj;
     const int grid = std::max(1, std::min<int>(L.grid, a.n_items));

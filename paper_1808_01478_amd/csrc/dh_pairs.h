@@ -308,21 +308,32 @@ template <int BOX>
 __device__ __forceinline__ float t32_packed_c(uint64_t ab_j, uint64_t neg_ab_i, float fc,
                                               const Geo32 &g);
 
-// Binary32 bins without a float-to-integer conversion: t + (2^23 - 1/2)
-// rounded to nearest lies in [2^23, 2^24) for 1/2 <= t < 2^22, where the
-// spacing is 1, so its bits minus those of 2^23 are floor(t), except at an
-// integer t: that is a tie, which goes to the even neighbour, so an odd
-// integer t counts one bin lower (a pair at a bin edge, inside the binary32
-// tolerance). For t < 1/4 the difference is -1 (bin 0; the counting code
-// maps it there); it grows monotonically with t and is at least 2^22 for
-// t >= 2^22, +inf and NaN (read as unsigned). Binary32 histograms have at
-// most 2^22 bins, so a pair counts iff the difference is below n_bins.
-constexpr float kMagic32 = 8388607.5f;        // 2^23 - 1/2
-constexpr int kGuardBytes = 16;               // >= 4 bytes per copy, 4 copies at most
-constexpr uint32_t kMagicBits = 0x4B000000u;  // bits of 2^23
+// Binary32 bins without a float-to-integer conversion: t 2^-22 + (2 - 2^-23)
+// rounded to nearest lies in [2, 4) for 1/2 <= t < 2^22, where the spacing is
+// 2^-22, so its bits minus those of 2 are floor(t), except at an integer t:
+// that is a tie, which goes to the even neighbour, so an odd integer t counts
+// one bin lower (a pair at a bin edge, inside the binary32 tolerance). For
+// t < 1/4 the difference is -1 (bin 0; the counting code maps it there); it
+// grows monotonically with t and is at least 2^22 for t >= 2^22, +inf and NaN
+// (read as unsigned). Binary32 histograms have at most 2^22 bins, so a pair
+// counts iff the difference is below n_bins. The bits of 2 leave a 32-bit word
+// when the bin is shifted to a byte offset, so the LDS address of a slot is
+// one shift and the instruction's own offset.
+constexpr float kBinScale = 0x1p-22f;
+constexpr float kBinOffset = 0x1.fffffep+0f;  // 2 - 2^-23
+// the offset of a lane that must not count: its bits are beyond every bin,
+// and the clamp sends them to the lane's discard slot
+constexpr float kNoBin = 3.5f;
+constexpr uint32_t kBinBits = 0x40000000u;  // bits of 2
+// LDS: the workgroup's control words, a guard whose last word is binary32 bin
+// -1, then slot 0. The kernels have no other LDS variable, so the dynamic
+// array starts at address 0 and slot 0 has a constant address, which the LDS
+// instructions take as their immediate offset.
+constexpr int kGuardBytes = 16;
+constexpr uint32_t kSlot0 = kControlBytes + kGuardBytes;
 
-__device__ __forceinline__ uint32_t bin_bits32(float t) {
-  return __float_as_uint(t + kMagic32);
+__device__ __forceinline__ uint32_t bin_bits32(float t, float offset = kBinOffset) {
+  return __float_as_uint(fmaf(t, kBinScale, offset));
 }
 
 // median of three unsigned values: x clamped to [lo, hi] when lo <= hi (the
@@ -457,7 +468,7 @@ __device__ __forceinline__ float t32_packed_c(uint64_t ab_j, uint64_t neg_ab_i, 
 // multiply-add on the root.
 template <int BOX>
 __device__ __forceinline__ uint32_t bits32_packed_c(uint64_t ab_j, uint64_t neg_ab_i, float fc,
-                                                    const Geo32 &g) {
+                                                    const Geo32 &g, float offset) {
   if constexpr (BOX == kBoxCube || BOX == kBoxOrtho || BOX == kBoxTric) {
     const uint64_t dab = ab_j + neg_ab_i;
     const float fa = static_cast<float>(static_cast<int32_t>(static_cast<uint32_t>(dab)));
@@ -465,22 +476,66 @@ __device__ __forceinline__ uint32_t bits32_packed_c(uint64_t ab_j, uint64_t neg_
     float q, k;
     if constexpr (BOX == kBoxCube) {
       q = fmaf(fc, fc, fmaf(fb, fb, fa * fa));
-      k = g.kx;
+      k = g.kx * kBinScale;
     } else if constexpr (BOX == kBoxOrtho) {
       q = fmaf(fc * g.rz, fc, fmaf(fb * g.ry, fb, fa * fa));
-      k = g.kx;
+      k = g.kx * kBinScale;
     } else {
       const float dx = fmaf(g.ncx, fc, fmaf(g.nbx, fb, fa));
       const float dy = fmaf(g.ncy, fc, g.nby * fb);
       const float dz = g.ncz * fc;
       q = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-      k = g.ax;
+      k = g.ax * kBinScale;
     }
-    return __float_as_uint(fmaf(__builtin_amdgcn_sqrtf(q), k, kMagic32));
+    return __float_as_uint(fmaf(__builtin_amdgcn_sqrtf(q), k, offset));
   } else {
-    return bin_bits32(t32_packed_c<BOX>(ab_j, neg_ab_i, fc, g));
+    return bin_bits32(t32_packed_c<BOX>(ab_j, neg_ab_i, fc, g), offset);
   }
 }
+
+// Counts binary32 pairs from their bin bits (see bin_bits32). The clamp is an
+// upper one only: bin -1 is the guard word below the histogram, added to bin 0
+// on flush, and a lane whose pair must not count passes bits beyond every bin
+// (kNoBin). Two-operand instructions throughout: v_min_u32, v_lshlrev_b32 and
+// v_sub_u32 take about 2.7 cycles of a SIMD, the three-operand v_med3_u32 and
+// v_lshl_add_u32 about 4.5.
+template <int MODE>
+struct Count32 {
+  using LdsU32 = __attribute__((address_space(3))) uint32_t;
+  using GlobalU64 = __attribute__((address_space(1))) unsigned long long;
+  uint32_t top;     // the lane's discard slot (LDS: in bin bits; windows: as a slot)
+  uint32_t base;    // bin bits of slot 0 of a window: the bin below its first
+  uint32_t n_bins;
+  GlobalU64 *out;
+
+  __device__ __forceinline__ Count32(const FrameParams *F, const WorkItem &w, int lane) {
+    const uint32_t win = static_cast<uint32_t>(uni(F->win));
+    const uint32_t b_lo = static_cast<uint32_t>(w.sweep) * win;
+    n_bins = static_cast<uint32_t>(uni(F->n_bins));
+    top = win + static_cast<uint32_t>(lane) + (MODE == kModeSweep ? 1u : kBinBits);
+    base = kBinBits + b_lo - 1u;
+    // global memory, said so that the atomics are global_atomic_* (a generic
+    // pointer would give flat atomics, which also count as LDS operations)
+    out = (GlobalU64 *)(F->out + static_cast<size_t>(w.hist) * n_bins);
+  }
+  // CLAMP = false: every t is known to lie below the LDS stride.
+  template <bool CLAMP>
+  __device__ __forceinline__ void add(uint32_t b) const {
+    if constexpr (MODE == kModeGlobal) {
+      const uint32_t k = max(b, kBinBits) - kBinBits;
+      if (k < n_bins)
+        __hip_atomic_fetch_add(out + k, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return;
+    }
+    // windows: slot 0 is the guard word (bin -1 of window 0; what other
+    // windows leave there is dropped on flush); bins below wrap to large
+    // values and are discarded with those above
+    const uint32_t m = MODE == kModeSweep ? min(b - base, top) : CLAMP ? min(b, top) : b;
+    const uint32_t at = (m << 2) + (MODE == kModeSweep ? kSlot0 - 4u : kSlot0);
+    __hip_atomic_fetch_add((LdsU32 *)(uintptr_t)at, 1u, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+};
 
 // min(a, b) of two arithmetic results (never signalling NaNs), without the
 // canonicalisation fmin adds; a NaN operand gives the other, as fmin does.
@@ -571,9 +626,8 @@ __device__ __forceinline__ T pair_t(T xi, T yi, T zi, T xj, T yj, T zj,
 // Pair kernel
 // --------------------------------------------------------------------------
 
-// Adds the LDS copies of bins [0, count) into out[] and clears every slot;
-// ends with a barrier. Copies are interleaved bin-major: slot b of copy c is
-// word b * copies + c. The out-of-range count of the histogram is its pair
+// Adds the LDS counts of bins [0, count) into out[] and clears every slot;
+// ends with a barrier. The out-of-range count of the histogram is its pair
 // count less every flushed count: the waves sum theirs in LDS (s_sum, zero
 // between calls) and one thread subtracts the total, since every subtraction
 // goes to the same address and takes its turn there (about 10 ns each: with
@@ -591,12 +645,12 @@ __device__ __forceinline__ void flush_hist(uint32_t *hist, const PairKernelArgs 
   const int clear = a.stride;
   uint64_t in_range = 0;
   for (int b = threadIdx.x; b < clear; b += blockDim.x) {
-    uint64_t v = 0;
-    // bin 0 also takes the guard words below the histogram (binary32 bin -1)
-    uint32_t *p = hist + (b == 0 ? -a.copies : b * a.copies);
-    for (int c = 0; c < (b == 0 ? 2 : 1) * a.copies; ++c) {
-      v += p[c];
-      p[c] = 0u;
+    uint64_t v = hist[b];
+    hist[b] = 0u;
+    if (b == 0) {
+      // the guard word: binary32 bin -1 (see Count32)
+      if (sweep == 0) v += hist[-1];
+      hist[-1] = 0u;
     }
     if (b < count && v != 0) {
       atomicAdd(reinterpret_cast<unsigned long long *>(out + b),
@@ -845,23 +899,6 @@ __device__ __forceinline__ void run_tiles(const PairKernelArgs &a, const WorkIte
   const int tj = a.tj;
   const int win = uni(F->win);
   const int b_lo = w.sweep * win;
-  const int log_copies = a.copies == 4 ? 2 : (a.copies == 2 ? 1 : 0);
-  const uint32_t shift_bytes = static_cast<uint32_t>(log_copies + 2);
-  char *const my_bytes = reinterpret_cast<char *>(my);
-  // binary32 counts address LDS as 32-bit integers: this lane's copy of bin 0,
-  // less the offset of the index that is shifted in (the wrap-around is
-  // intended): the bin bits for one LDS histogram; for bin windows the slot
-  // of the window, where window 0 starts at bin -1 (slot 0 is the guard word)
-  using LdsU32 = __attribute__((address_space(3))) uint32_t;
-  const uint32_t my_lds =
-      static_cast<uint32_t>(reinterpret_cast<uintptr_t>((LdsU32 *)my));
-  const uint32_t s0 = w.sweep == 0 ? 1u : 0u;
-  uint32_t my_lds_m = SWEEP ? my_lds - (s0 << shift_bytes) : my_lds - (kMagicBits << shift_bytes);
-  // opaque, so the compiler keeps (index << shift) + my_lds_m as one
-  // v_lshl_add_u32 instead of subtracting the offset from every bin
-  asm volatile("" : "+v"(my_lds_m));
-  // bin bits of slot 0 of this window
-  const uint32_t sweep_base = kMagicBits + static_cast<uint32_t>(b_lo) - s0;
   // largest slot index of binary64 unclamped items
   const double cap64 = static_cast<double>(a.stride - 1);
 
@@ -908,54 +945,6 @@ __device__ __forceinline__ void run_tiles(const PairKernelArgs &a, const WorkIte
       const double mag = wave_max_f64(ok ? fabs(p.x) + fabs(p.y) + fabs(p.z) : 0.0);
       if (lane >= 3 * r && lane < 3 * r + 3) ib64_mag = mag;
     }
-    if constexpr (SORTED && sizeof(T) == 4) {
-      // a lane past the end of the item: an i-point at infinity (every q of
-      // its short-path pairs is +inf and lands in its discard slot)
-      const V c = X[EPJ * (ok ? i : w.i0) + 1];
-      cxi[r] = ok ? c.x : __builtin_inff();
-      cyi[r] = ok ? c.y : __builtin_inff();
-      czi[r] = ok ? c.z : __builtin_inff();
-      const uint32_t u[3] = {__float_as_uint(p.x), __float_as_uint(p.y), __float_as_uint(p.z)};
-#pragma unroll
-      for (int ax = 0; ax < 3; ++ax) {
-        const uint32_t bl = wave_min_u32(ok ? u[ax] : 0xFFFFFFFFu);
-        const uint32_t bh = wave_max_u32(ok ? u[ax] : 0u);
-        if (lane == 3 * r + ax) {
-          ib_lo = bl;
-          ib_hi = bh;
-        }
-        if (ax == 0 && bl > bh) ib_empty |= 7u << (3 * r);
-      }
-    }
-  }
-  // binary32 clamp bounds in bin bits: the guard word below bin 0 for a
-  // lane that counts, its discard slot for one that must not
-  const uint32_t hib = kMagicBits + hi;
-  uint32_t lob[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) lob[r] = lo[r] == 0u ? kMagicBits - 1u : hib;
-  // -(b:a) of each i-particle for the packed periodic binary32 difference
-  uint64_t nab[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    if constexpr (sizeof(T) == 4)
-      nab[r] = 0ull - ((static_cast<uint64_t>(__float_as_uint(yi[r])) << 32) |
-                       __float_as_uint(xi[r]));
-    else
-      nab[r] = 0ull;
-  }
-  // -(c' : c) of i-particles 2k and 2k+1: one 64-bit addition to j's (c : c)
-  // gives both c differences, the second lowered by one unit when the first
-  // borrows (as for b above)
-  static_assert(R % 2 == 0, "i-particles are paired for the c difference");
-  uint64_t nzz[R / 2];
-#pragma unroll
-  for (int k = 0; k < R / 2; ++k) {
-    if constexpr (sizeof(T) == 4)
-      nzz[k] = 0ull - ((static_cast<uint64_t>(__float_as_uint(zi[2 * k + 1])) << 32) |
-                       __float_as_uint(zi[2 * k]));
-    else
-      nzz[k] = 0ull;
   }
   const int n_bins = uni(F->n_bins);
   // binary64: the correctly rounded root for every pair when t at or above
@@ -970,125 +959,23 @@ __device__ __forceinline__ void run_tiles(const PairKernelArgs &a, const WorkIte
   GlobalU64 *const gout =
       (GlobalU64 *)(F->out + static_cast<size_t>(w.hist) * static_cast<size_t>(n_bins));
 
-  // Counts one pair: binary64 at scaled distance v = t, binary32 from its bin
-  // bits v (bin_bits32). l: 0 for a pair that counts, the lane's discard slot
-  // for one that must not (the lower clamp); lb: the same bound in bin bits
-  // for the binary32 LDS clamp (guard word or discard slot), passed by the
-  // caller so that a diagonal item selects it directly.
-  auto count_t = [&](auto v, uint32_t l, uint32_t lb) {
-    if constexpr (sizeof(T) == 4) {
-      const uint32_t b = v;
-      if constexpr (GLOBAL) {
-        const uint32_t k = max(b, kMagicBits) - kMagicBits;
-        if (l == 0u && k < static_cast<uint32_t>(n_bins))
-          __hip_atomic_fetch_add(gout + k, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      } else {
-        uint32_t m;  // bin + kMagicBits
-        if constexpr (!CLAMP) {
-          // fixed-point staging bounds every t below the stride; bin -1 is
-          // the guard word below the histogram, added to bin 0 on flush
-          m = b;
-        } else if constexpr (!SWEEP) {
-          m = med3_u32(b, lb, kMagicBits + hi);
-        } else {
-          // slot in the window; bins below it wrap to large values and are
-          // discarded with those above (window 0 has no bins below it: bin -1
-          // is its slot 0, the guard word)
-          const uint32_t hs = hi + s0;
-          m = med3_u32(b - sweep_base, l == 0u ? 0u : hs, hs);
-        }
-        __hip_atomic_fetch_add((LdsU32 *)(uintptr_t)(my_lds_m + (m << shift_bytes)), 1u,
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      }
+  // Counts one pair at scaled distance t. l: 0 for a pair that counts, the
+  // lane's discard slot for one that must not (the lower clamp).
+  auto count_t = [&](double t, uint32_t l, uint32_t) {
+    if constexpr (GLOBAL) {
+      if (l == 0u && t < static_cast<double>(n_bins))
+        __hip_atomic_fetch_add(gout + static_cast<uint32_t>(t), 1ull, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
     } else {
-      const T t = v;
-      if constexpr (GLOBAL) {
-        // a pair counts iff t < n_bins (in the working precision)
-        if (l == 0u && t < static_cast<T>(n_bins))
-          __hip_atomic_fetch_add(gout + static_cast<uint32_t>(t), 1ull, __ATOMIC_RELAXED,
-                                 __HIP_MEMORY_SCOPE_AGENT);
+      uint32_t idx;
+      if constexpr (!CLAMP) {
+        idx = static_cast<uint32_t>(min_arith(t, cap64));
       } else {
-        uint32_t idx;
-        if constexpr (!CLAMP) {
-          // binary64 reads raw device coordinates: cap t so that even
-          // non-finite or absurd input stays inside the LDS histogram
-          idx = static_cast<uint32_t>(min_arith(t, cap64));
-        } else {
-          // floor(t), saturated; t >= 0 always
-          idx = static_cast<uint32_t>(min_arith(t, 4294967295.0));
-          if constexpr (SWEEP) idx -= static_cast<uint32_t>(b_lo);
-          // the slot clamped to [l, hi] (l is 0 or hi): one v_med3_u32
-          idx = med3_u32(idx, l, hi);
-        }
-        // byte offset with one shift (copies interleaved bin-major), so the
-        // address is a single v_lshl_add_u32
-        atomicAdd(reinterpret_cast<uint32_t *>(my_bytes + (idx << shift_bytes)), 1u);
+        idx = static_cast<uint32_t>(min_arith(t, 4294967295.0));
+        if constexpr (SWEEP) idx -= static_cast<uint32_t>(b_lo);
+        idx = med3_u32(idx, l, hi);
       }
-    }
-  };
-
-  // image-search ring of this wave: qn entries from head (wave-uniform)
-  constexpr int cap = queue_cap(R);
-  V *const wq = queue + wave * cap;
-  int head = 0, qn = 0;
-  [[maybe_unused]] uint64_t n_searched = 0;  // pairs this wave searched in this item
-  [[maybe_unused]] uint64_t n_images = 0;    // images it evaluated for them
-  [[maybe_unused]] T qskip;
-  if constexpr (sizeof(T) == 4)
-    qskip = uni(F->qskip32);
-  else
-    qskip = uni(F->qskip64);
-  if constexpr (SEARCH) {
-    // this frame's shift table; read after the first tile barrier below
-    // the search table: the 8 octant rows, then all 27 shift vectors
-    for (int k = tid; k < kSearchTable; k += blockDim.x) {
-      const int m = k < 8 * kOctCap ? F->oct_shift[k / kOctCap][k % kOctCap] : k - 8 * kOctCap;
-      V S;
-      if constexpr (sizeof(T) == 4) {
-        S.x = F->shift32[m][0]; S.y = F->shift32[m][1]; S.z = F->shift32[m][2];
-      } else {
-        S.x = F->shift64[m][0]; S.y = F->shift64[m][1]; S.z = F->shift64[m][2];
-      }
-      S.w = T(0);
-      sh[k] = S;
-    }
-  }
-  [[maybe_unused]] uint32_t oct_full = 0;
-  [[maybe_unused]] int oct_n = 0;
-  if constexpr (SEARCH) {
-    oct_full = static_cast<uint32_t>(uni(static_cast<int>(F->oct_full)));
-    oct_n = uni(static_cast<int>(F->oct_n));
-  }
-  // searches and counts the `cnt` (<= 64) oldest queued vectors
-  auto drain = [&](int cnt) {
-    if constexpr (SEARCH) {
-      __builtin_amdgcn_wave_barrier();
-      const bool v = lane < cnt;
-      int idx = head + (v ? lane : 0);
-      if (idx >= cap) idx -= cap;
-      const V e = wq[idx];
-      T q = fmaT(e.z, e.z, fmaT(e.y, e.y, e.x * e.x));
-      // the vector's octant (8: outside the octant boxes), 8 as well when its
-      // list is the full one; the wave runs the full list when any of its
-      // vectors needs it
-      int code;
-      if constexpr (sizeof(T) == 4)
-        code = __float_as_int(e.w);
-      else
-        code = octant64(e.x, e.y, e.z, g);
-      if ((oct_full >> code) & 1u) code = 8;
-      const int n = __builtin_amdgcn_ballot_w64(code == 8) != 0 ? kShifts : oct_n;
-      q = search_oct<T>(e.x, e.y, e.z, q, code == 8 ? 8 * kOctCap : code * kOctCap, n, sh);
-      n_images += static_cast<uint64_t>(cnt) * static_cast<uint64_t>(n);
-      if constexpr (sizeof(T) == 4)
-        count_t(bin_bits32(__builtin_amdgcn_sqrtf(q)), v ? 0u : hi, v ? kMagicBits - 1u : hib);
-      else
-        count_t(t_guarded64(q, g.s, big_bins), v ? 0u : hi, 0u);
-      n_searched += cnt;  // wave-uniform; added to the frame's count once per item
-      head += cnt;
-      if (head >= cap) head -= cap;
-      qn -= cnt;
-      __builtin_amdgcn_wave_barrier();
+      atomicAdd(my + idx, 1u);
     }
   };
 
@@ -1129,26 +1016,6 @@ __device__ __forceinline__ void run_tiles(const PairKernelArgs &a, const WorkIte
           reinterpret_cast<double *>(tboxes)[(buf * 4 + (tid >> 6)) * 8 + lane] = v;
         }
       }
-      if constexpr (SORTED && sizeof(T) == 4) {
-        tile[(buf * tj + tid) * EPJ + 1] = preC;
-        // the box of this wave's 64 j (tiles start on group boundaries of
-        // the species, so the group is the same whatever the launch shape)
-        const bool ok = jt + tid < w.j1;
-        const uint32_t u[3] = {__float_as_uint(pre.x), __float_as_uint(pre.y),
-                               __float_as_uint(pre.z)};
-        uint32_t b6[6];
-#pragma unroll
-        for (int ax = 0; ax < 3; ++ax) {
-          b6[ax] = wave_min_u32(ok ? u[ax] : 0xFFFFFFFFu);
-          b6[3 + ax] = wave_max_u32(ok ? u[ax] : 0u);
-        }
-        if (lane < 6) {
-          uint32_t v = b6[0];
-#pragma unroll
-          for (int q = 1; q < 6; ++q) v = lane == q ? b6[q] : v;
-          tboxes[(buf * 4 + (tid >> 6)) * 8 + lane] = v;
-        }
-      }
     }
     __syncthreads();
     {
@@ -1167,164 +1034,6 @@ __device__ __forceinline__ void run_tiles(const PairKernelArgs &a, const WorkIte
                                jt, js, jcount, wbase, lane, g, big_bins, xi, yi, zi, ib64_lo,
                                ib64_hi, ib64_mag, ib64_empty, lo,
                                hi, count_t);
-      continue;
-    }
-    if (wave_active && js < jcount) {
-      const V *__restrict__ tb = tile + buf * tj;
-      // periodic binary32: j as its packed (b:a) and (c:c) words, one
-      // 16-byte read (see t32_packed and the staging)
-      constexpr bool kPacked = sizeof(T) == 4 && BOX != kBoxNone;
-      struct JPacked {
-        uint64_t ab;
-        uint64_t cc;
-      };
-      using J = typename std::conditional<kPacked, JPacked, V>::type;
-      const uint64_t *__restrict__ tb64 = reinterpret_cast<const uint64_t *>(tb);
-      auto load_j = [&](int k) -> J {
-        if constexpr (kPacked)
-          return JPacked{tb64[2 * k], tb64[2 * k + 1]};
-        else
-          return tb[k];
-      };
-      // R pairs of one j: distance, bin, one atomic each
-      auto pairs_of = [&](const J &pj, int j) {
-        if constexpr (sizeof(T) == 8 && !SEARCH) {
-          // binary64: the short root for all R pairs, one ballot, and the
-          // correctly rounded root for all of them when any lane of the wave
-          // has a t near an integer (see t_fast64)
-          double q[R], t[R];
-          uint32_t gap = gap_init(big_bins);
-#pragma unroll
-          for (int r = 0; r < R; ++r) {
-            q[r] = q64<BOX>(xi[r], yi[r], zi[r], pj.x, pj.y, pj.z, g);
-            t[r] = t_fast64(q[r], g.s, gap);
-          }
-          if (__builtin_expect(any_near(gap), 0))
-#pragma unroll
-            for (int r = 0; r < R; ++r) t[r] = sqrt_cr(q[r]) * g.s;
-#pragma unroll
-          for (int r = 0; r < R; ++r) {
-            uint32_t l = lo[r];
-            if constexpr (DIAG) l = j > wbase + r * 64 + lane ? l : hi;
-            count_t(t[r], l, 0u);
-          }
-          return;
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          uint32_t l = lo[r], lb = lob[r];
-          if constexpr (DIAG) {
-            const bool up = j > wbase + r * 64 + lane;
-            l = up ? l : hi;
-            lb = up ? lb : hib;
-          }
-          if constexpr (SEARCH) {
-            T dx, dy, dz;
-            if constexpr (kPacked)
-              tric_vec32(pj.ab, nab[r], zi[r], __uint_as_float(static_cast<uint32_t>(pj.cc)),
-                         g, dx, dy, dz);
-            else
-              reduce64<BOX>(xi[r], yi[r], zi[r], pj.x, pj.y, pj.z, g, dx, dy, dz);
-            const T q0 = fmaT(dz, dz, fmaT(dy, dy, dx * dx));
-            // valid pairs at least half the shortest lattice vector long
-            // are searched later; they must not count now
-            const bool need = l == 0u && q0 >= qskip;
-            if constexpr (sizeof(T) == 4)
-              count_t(bin_bits32(__builtin_amdgcn_sqrtf(q0)), need ? hi : l, need ? hib : lb);
-            else
-              count_t(t_guarded64(q0, g.s, big_bins), need ? hi : l, 0u);
-            const uint64_t m = __builtin_amdgcn_ballot_w64(need);
-            if (m != 0) {
-              const int below = __builtin_amdgcn_mbcnt_hi(
-                  static_cast<uint32_t>(m >> 32),
-                  __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u));
-              if (need) {
-                int pos = head + qn + below;  // < 2 cap: head < cap, qn + below < cap
-                if (pos >= cap) pos -= cap;
-                // binary32: the octant from the exact signs of the
-                // fixed-point differences, as the bits of w; binary64 takes
-                // it in the drain from the vector itself
-                V e;
-                e.x = dx; e.y = dy; e.z = dz;
-                if constexpr (kPacked)
-                  e.w = __int_as_float(octant32(pj.ab, nab[r], zi[r],
-                                                __uint_as_float(static_cast<uint32_t>(pj.cc))));
-                else
-                  e.w = T(0);
-                wq[pos] = e;
-              }
-              qn += __builtin_popcountll(m);
-              if (qn >= 64) drain(64);
-            }
-          } else if constexpr (kPacked) {
-            // c differences of i-particles r and r+1 from one 64-bit add
-            const uint64_t dcc = pj.cc + nzz[r / 2];
-            const float fc = static_cast<float>(static_cast<int32_t>(
-                static_cast<uint32_t>(r % 2 == 0 ? dcc : dcc >> 32)));
-            count_t(bits32_packed_c<BOX>(pj.ab, nab[r], fc, g), l, lb);
-          } else if constexpr (sizeof(T) == 4) {
-            count_t(bin_bits32(pair_t<T, BOX>(xi[r], yi[r], zi[r], pj.x, pj.y, pj.z, g)), l, lb);
-          } else {
-            count_t(pair_t<T, BOX>(xi[r], yi[r], zi[r], pj.x, pj.y, pj.z, g), l, lb);
-          }
-        }
-      };
-      // Ping-pong over two j registers: the read of the next j is issued
-      // before the current j's atomics. LDS operations complete in order, so
-      // a read issued after the atomics would wait for all of them
-      // (bank-conflicted) before the arithmetic could start.
-      if constexpr (SEARCH) {
-        // one copy of the search code: a plain j loop whose next j is read
-        // before the current one's atomics (at the end of the tile the
-        // look-ahead reads the entry just past it, never used)
-        J pn = load_j(js);
-        for (int jj = js; jj < jcount; ++jj) {
-          const J pc = pn;
-          pn = load_j(jj + 1);
-          pairs_of(pc, jt + jj);
-        }
-      } else {
-        // j is read through a pointer kept in a VGPR, so the two reads of an
-        // iteration use immediate offsets and one add moves it on (a uniform
-        // SGPR address would cost a v_mov per read). The zero is opaque to
-        // the compiler on purpose.
-        int vzero;
-        asm volatile("v_mov_b32 %0, 0" : "=v"(vzero));
-        const V *cur = tb + js + vzero;
-        auto load_at = [&](const V *q) -> J {
-          if constexpr (kPacked)
-            return JPacked{reinterpret_cast<const uint64_t *>(q)[0],
-                           reinterpret_cast<const uint64_t *>(q)[1]};
-          else
-            return *q;
-        };
-        J pa = load_at(cur);
-        __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
-        int jj = js;
-        for (; jj + 1 < jcount; jj += 2, cur += 2) {
-          const J pb = load_at(cur + 1);
-          // binary32: pin the read ahead of the atomics (measured faster);
-          // binary64 has enough arithmetic per j to hide it unpinned
-          if constexpr (sizeof(T) == 4) __builtin_amdgcn_sched_barrier(0);
-          pairs_of(pa, jt + jj);
-          // at the end of a tile this reads the entry just past it (the
-          // next buffer, the histogram or the allocation's pad): never used
-          pa = load_at(cur + 2);
-          if constexpr (sizeof(T) == 4) __builtin_amdgcn_sched_barrier(0);
-          pairs_of(pb, jt + jj + 1);
-        }
-        if (jj < jcount) pairs_of(pa, jt + jj);
-      }
-    }
-  }
-  if constexpr (SEARCH) {
-    if (qn > 0) drain(qn);
-    // one atomic per wave and item for each count (one address each for
-    // the whole frame): searched pairs, then the images evaluated for them
-    unsigned long long *const searched = F->searched;
-    if (searched != nullptr && n_searched != 0 && lane == 0) {
-      atomicAdd(searched, static_cast<unsigned long long>(n_searched));
-      atomicAdd(searched + 1, static_cast<unsigned long long>(n_images));
     }
   }
 }
@@ -1377,27 +1086,10 @@ __device__ __forceinline__ void run_units(const PairKernelArgs &a, const WorkIte
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
   const int win = uni(F->win);
   const int b_lo = w.sweep * win;
-  const int log_copies = a.copies == 4 ? 2 : (a.copies == 2 ? 1 : 0);
-  const uint32_t shift_bytes = static_cast<uint32_t>(log_copies + 2);
-  char *const my_bytes = reinterpret_cast<char *>(my);
-  // binary32 counts address LDS as 32-bit integers: this lane's copy of bin 0,
-  // less the offset of the index that is shifted in (the wrap-around is
-  // intended): the bin bits for one LDS histogram; for bin windows the slot
-  // of the window, where window 0 starts at bin -1 (slot 0 is the guard word)
-  using LdsU32 = __attribute__((address_space(3))) uint32_t;
-  const uint32_t my_lds =
-      static_cast<uint32_t>(reinterpret_cast<uintptr_t>((LdsU32 *)my));
-  const uint32_t s0 = w.sweep == 0 ? 1u : 0u;
-  uint32_t my_lds_m = SWEEP ? my_lds - (s0 << shift_bytes) : my_lds - (kMagicBits << shift_bytes);
-  // opaque, so the compiler keeps (index << shift) + my_lds_m as one
-  // v_lshl_add_u32 instead of subtracting the offset from every bin
-  asm volatile("" : "+v"(my_lds_m));
-  // bin bits of slot 0 of this window
-  const uint32_t sweep_base = kMagicBits + static_cast<uint32_t>(b_lo) - s0;
+  [[maybe_unused]] const Count32<MODE> count32(F, w, lane);
   // largest slot index of binary64 unclamped units
   const double cap64 = static_cast<double>(a.stride - 1);
   const uint32_t hi = static_cast<uint32_t>(win + lane);  // discard slot of this lane
-  const uint32_t hib = kMagicBits + hi;
   const int n_bins = uni(F->n_bins);
   const bool noclamp = MODE == kModeLds && !SEARCH && uni(F->noclamp) != 0;
   // binary64: the correctly rounded root for every pair when t at or above
@@ -1409,64 +1101,32 @@ __device__ __forceinline__ void run_units(const PairKernelArgs &a, const WorkIte
   // (a generic pointer would give flat atomics, which also count as LDS
   // operations in lgkmcnt)
   using GlobalU64 = __attribute__((address_space(1))) unsigned long long;
-  GlobalU64 *const gout =
+  [[maybe_unused]] GlobalU64 *const gout =
       (GlobalU64 *)(F->out + static_cast<size_t>(w.hist) * static_cast<size_t>(n_bins));
 
-  // Counts one pair: binary64 at scaled distance v = t, binary32 from its bin
-  // bits v (bin_bits32). l: 0 for a pair that counts, the lane's discard slot
-  // for one that must not (the lower clamp); lb: the same bound in bin bits
-  // for the binary32 LDS clamp (guard word or discard slot), passed by the
-  // caller so that a diagonal unit selects it directly.
-  auto count_t = [&](auto clamp_c, auto v, uint32_t l, uint32_t lb) {
+  // Counts a binary64 pair at scaled distance t. l: 0 for a pair that counts,
+  // the lane's discard slot for one that must not (the lower clamp).
+  auto count64 = [&](auto clamp_c, double t, uint32_t l) {
     constexpr bool CLAMP = decltype(clamp_c)::value;
-    if constexpr (sizeof(T) == 4) {
-      const uint32_t b = v;
-      if constexpr (GLOBAL) {
-        const uint32_t k = max(b, kMagicBits) - kMagicBits;
-        if (l == 0u && k < static_cast<uint32_t>(n_bins))
-          __hip_atomic_fetch_add(gout + k, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      } else {
-        uint32_t m;  // bin + kMagicBits
-        if constexpr (!CLAMP) {
-          // fixed-point staging bounds every t below the stride; bin -1 is
-          // the guard word below the histogram, added to bin 0 on flush
-          m = b;
-        } else if constexpr (!SWEEP) {
-          m = med3_u32(b, lb, kMagicBits + hi);
-        } else {
-          // slot in the window; bins below it wrap to large values and are
-          // discarded with those above (window 0 has no bins below it: bin -1
-          // is its slot 0, the guard word)
-          const uint32_t hs = hi + s0;
-          m = med3_u32(b - sweep_base, l == 0u ? 0u : hs, hs);
-        }
-        __hip_atomic_fetch_add((LdsU32 *)(uintptr_t)(my_lds_m + (m << shift_bytes)), 1u,
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      }
+    if constexpr (GLOBAL) {
+      // a pair counts iff t < n_bins (in the working precision)
+      if (l == 0u && t < static_cast<double>(n_bins))
+        __hip_atomic_fetch_add(gout + static_cast<uint32_t>(t), 1ull, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
     } else {
-      const T t = v;
-      if constexpr (GLOBAL) {
-        // a pair counts iff t < n_bins (in the working precision)
-        if (l == 0u && t < static_cast<T>(n_bins))
-          __hip_atomic_fetch_add(gout + static_cast<uint32_t>(t), 1ull, __ATOMIC_RELAXED,
-                                 __HIP_MEMORY_SCOPE_AGENT);
+      uint32_t idx;
+      if constexpr (!CLAMP) {
+        // binary64 reads raw device coordinates: cap t so that even
+        // non-finite or absurd input stays inside the LDS histogram
+        idx = static_cast<uint32_t>(min_arith(t, cap64));
       } else {
-        uint32_t idx;
-        if constexpr (!CLAMP) {
-          // binary64 reads raw device coordinates: cap t so that even
-          // non-finite or absurd input stays inside the LDS histogram
-          idx = static_cast<uint32_t>(min_arith(t, cap64));
-        } else {
-          // floor(t), saturated; t >= 0 always
-          idx = static_cast<uint32_t>(min_arith(t, 4294967295.0));
-          if constexpr (SWEEP) idx -= static_cast<uint32_t>(b_lo);
-          // the slot clamped to [l, hi] (l is 0 or hi): one v_med3_u32
-          idx = med3_u32(idx, l, hi);
-        }
-        // byte offset with one shift (copies interleaved bin-major), so the
-        // address is a single v_lshl_add_u32
-        atomicAdd(reinterpret_cast<uint32_t *>(my_bytes + (idx << shift_bytes)), 1u);
+        // floor(t), saturated; t >= 0 always
+        idx = static_cast<uint32_t>(min_arith(t, 4294967295.0));
+        if constexpr (SWEEP) idx -= static_cast<uint32_t>(b_lo);
+        // the slot clamped to [l, hi] (l is 0 or hi): one v_med3_u32
+        idx = med3_u32(idx, l, hi);
       }
+      atomicAdd(my + idx, 1u);
     }
   };
 
@@ -1524,10 +1184,10 @@ __device__ __forceinline__ void run_units(const PairKernelArgs &a, const WorkIte
       q = search_oct<T>(e.x, e.y, e.z, q, code == 8 ? 8 * kOctCap : code * kOctCap, n, sh);
       n_images += static_cast<uint64_t>(cnt) * static_cast<uint64_t>(n);
       if constexpr (sizeof(T) == 4)
-        count_t(Yes{}, bin_bits32(__builtin_amdgcn_sqrtf(q)), v ? 0u : hi,
-                v ? kMagicBits - 1u : hib);
+        count32.template add<true>(
+            bin_bits32(__builtin_amdgcn_sqrtf(q), v ? kBinOffset : kNoBin));
       else
-        count_t(Yes{}, t_guarded64(q, g.s, big_bins), v ? 0u : hi, 0u);
+        count64(Yes{}, t_guarded64(q, g.s, big_bins), v ? 0u : hi);
       n_searched += cnt;  // wave-uniform; added to the frame's count once per item
       head += cnt;
       if (head >= cap) head -= cap;
@@ -1539,9 +1199,10 @@ __device__ __forceinline__ void run_units(const PairKernelArgs &a, const WorkIte
   // the i-particles of the current slice
   int wbase = -1;
   T xi[R], yi[R], zi[R];
-  // clamp bounds of each particle: the discard slot for a lane past the end
-  // of the item (lo), the same in bin bits or the guard word (lob)
-  uint32_t lo[R], lob[R];
+  // a lane past the end of the item: its lower clamp is its discard slot (lo,
+  // binary64), its bin offset is beyond every bin (off, binary32)
+  [[maybe_unused]] uint32_t lo[R];
+  [[maybe_unused]] float off[R];
   // -(b:a) of each i-particle for the packed periodic binary32 difference;
   // -(c' : c) of i-particles 2k and 2k+1: one 64-bit addition to j's (c : c)
   // gives both c differences, the second lowered by one unit when the first
@@ -1556,7 +1217,7 @@ __device__ __forceinline__ void run_units(const PairKernelArgs &a, const WorkIte
       const V p = X[ok ? i : w.i0];
       xi[r] = p.x; yi[r] = p.y; zi[r] = p.z;
       lo[r] = ok ? 0u : hi;
-      lob[r] = ok ? kMagicBits - 1u : hib;
+      off[r] = ok ? kBinOffset : kNoBin;
       if constexpr (sizeof(T) == 4)
         nab[r] = 0ull - ((static_cast<uint64_t>(__float_as_uint(yi[r])) << 32) |
                          __float_as_uint(xi[r]));
@@ -1603,17 +1264,18 @@ __device__ __forceinline__ void run_units(const PairKernelArgs &a, const WorkIte
       for (int r = 0; r < R; ++r) {
         uint32_t l = lo[r];
         if constexpr (DIAG) l = j > wbase + r * 64 + lane ? l : hi;
-        count_t(clamp_c, t[r], l, 0u);
+        count64(clamp_c, t[r], l);
       }
       return;
     } else {
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        uint32_t l = lo[r], lb = lob[r];
+        [[maybe_unused]] uint32_t l = lo[r];
+        [[maybe_unused]] float o = off[r];
         if constexpr (DIAG) {
           const bool up = j > wbase + r * 64 + lane;
           l = up ? l : hi;
-          lb = up ? lb : hib;
+          o = up ? o : kNoBin;
         }
         if constexpr (SEARCH) {
           T dx, dy, dz;
@@ -1625,12 +1287,12 @@ __device__ __forceinline__ void run_units(const PairKernelArgs &a, const WorkIte
           const T q0 = fmaT(dz, dz, fmaT(dy, dy, dx * dx));
           // valid pairs at least half the shortest lattice vector long
           // are searched later; they must not count now
-          const bool need = l == 0u && q0 >= qskip;
+          const bool need = (sizeof(T) == 4 ? o == kBinOffset : l == 0u) && q0 >= qskip;
           if constexpr (sizeof(T) == 4)
-            count_t(Yes{}, bin_bits32(__builtin_amdgcn_sqrtf(q0)), need ? hi : l,
-                    need ? hib : lb);
+            count32.template add<true>(
+                bin_bits32(__builtin_amdgcn_sqrtf(q0), need ? kNoBin : o));
           else
-            count_t(Yes{}, t_guarded64(q0, g.s, big_bins), need ? hi : l, 0u);
+            count64(Yes{}, t_guarded64(q0, g.s, big_bins), need ? hi : l);
           const uint64_t m = __builtin_amdgcn_ballot_w64(need);
           if (m != 0) {
             const int below = __builtin_amdgcn_mbcnt_hi(
@@ -1659,10 +1321,11 @@ __device__ __forceinline__ void run_units(const PairKernelArgs &a, const WorkIte
           const uint64_t dcc = pj.cc + nzz[r / 2];
           const float fc = static_cast<float>(static_cast<int32_t>(
               static_cast<uint32_t>(r % 2 == 0 ? dcc : dcc >> 32)));
-          count_t(clamp_c, bits32_packed_c<BOX>(pj.ab, nab[r], fc, g), l, lb);
+          count32.template add<decltype(clamp_c)::value>(
+              bits32_packed_c<BOX>(pj.ab, nab[r], fc, g, o));
         } else {
-          count_t(clamp_c, bin_bits32(pair_t<T, BOX>(xi[r], yi[r], zi[r], pj.x, pj.y, pj.z, g)),
-                  l, lb);
+          count32.template add<decltype(clamp_c)::value>(
+              bin_bits32(pair_t<T, BOX>(xi[r], yi[r], zi[r], pj.x, pj.y, pj.z, g), o));
         }
       }
     }
@@ -1676,7 +1339,7 @@ __device__ __forceinline__ void run_units(const PairKernelArgs &a, const WorkIte
   auto stream = [&](auto diag_c, auto clamp_c, int jb, int je) {
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<V *>(X + jb), 0, (je - jb) * static_cast<int>(sizeof(V)), kBufferFlags);
-    int off = 0;
+    int at = 0;
     auto load_j = [&](int k) -> J {
       union {
         V4u w[sizeof(V) / 16];
@@ -1685,7 +1348,7 @@ __device__ __forceinline__ void run_units(const PairKernelArgs &a, const WorkIte
 #pragma unroll
       for (int h = 0; h < static_cast<int>(sizeof(V) / 16); ++h)
         e.w[h] = __builtin_amdgcn_raw_buffer_load_b128(
-            rsrc, k * static_cast<int>(sizeof(V)) + 16 * h, off, 0);
+            rsrc, k * static_cast<int>(sizeof(V)) + 16 * h, at, 0);
       return e.j;
     };
     J p[kJAhead];
@@ -1693,7 +1356,7 @@ __device__ __forceinline__ void run_units(const PairKernelArgs &a, const WorkIte
     for (int k = 0; k < kJAhead; ++k) p[k] = load_j(k);
     int j = jb;
     for (; j + kJAhead <= je; j += kJAhead) {
-      off += kJAhead * static_cast<int>(sizeof(V));
+      at += kJAhead * static_cast<int>(sizeof(V));
 #pragma unroll
       for (int k = 0; k < kJAhead; ++k) {
         pairs_of(diag_c, clamp_c, p[k], j + k);
@@ -1763,13 +1426,25 @@ constexpr int max_threads() {
   return BOX == kBoxTricSearch ? 256 : 1024;
 }
 
+// Waves per SIMD the registers have to allow: eight for the binary32 kernels
+// without image search and with four particles per lane, so that two
+// workgroups of 1,024 threads share a CU where their histograms fit. A loop of
+// the short path's instructions takes 41 cycles per pair of a wave with four
+// waves per SIMD and 37 with eight (the root alone 14); 1M clustered points:
+// 89.3 and 85.7 ms; 24 orthorhombic frames: 21.9 and 21.4 ms.
+template <typename T, int R, int BOX>
+constexpr int min_waves() {
+  return sizeof(T) == 4 && BOX != kBoxTricSearch && (R == 4 || BOX == kBoxTricSorted) ? 8 : 1;
+}
+
 template <typename T, int R, int BOX, int MODE>
-__global__ __launch_bounds__(max_threads<BOX>()) void pairs_kernel(PairKernelArgs a) {
+__global__ __launch_bounds__(max_threads<BOX>(), (min_waves<T, R, BOX>())) void pairs_kernel(PairKernelArgs a) {
   using V = typename V4<T>::type;
   extern __shared__ __align__(32) unsigned char smem[];
-  __shared__ unsigned long long s_sum;
-  __shared__ int s_item, s_unit;
-  V *tile = reinterpret_cast<V *>(smem);
+  // control words: in-range counts of a flush, next item, next unit
+  unsigned long long &s_sum = *reinterpret_cast<unsigned long long *>(smem);
+  int &s_item = *reinterpret_cast<int *>(smem + 8), &s_unit = *reinterpret_cast<int *>(smem + 12);
+  V *tile = reinterpret_cast<V *>(smem + kControlBytes);
   // the histogram follows a guard of kGuardBytes: one word per copy for
   // binary32 bin -1 (t < 1/4), added to bin 0 on flush. (Sorted frames: the
   // two j-tiles of two entries per j and the tiles' group boxes come first.)
@@ -1777,19 +1452,16 @@ __global__ __launch_bounds__(max_threads<BOX>()) void pairs_kernel(PairKernelArg
   constexpr bool SORTED = BOX == kBoxTricSorted && sizeof(T) == 8;
   const size_t tiles_bytes =
       SORTED ? 2 * static_cast<size_t>(a.tj) * EPJ * sizeof(V) + kSortedBoxBytes : 0;
-  uint32_t *hist = reinterpret_cast<uint32_t *>(smem + tiles_bytes + kGuardBytes);
+  uint32_t *hist = reinterpret_cast<uint32_t *>(smem + tiles_bytes + kSlot0);
   const int tid = threadIdx.x;
-  // lane-interleaved sub-histogram copies: lanes of one instruction that
-  // hit the same bin use different words (and banks) when copies > 1
-  uint32_t *my = hist + (tid & 63) % a.copies;
   // image-search queues after the histogram, 32-byte aligned
-  const size_t q_off = (kGuardBytes + static_cast<size_t>(a.copies) * a.stride * 4 + 31) / 32 * 32;
+  const size_t q_off = (kSlot0 + static_cast<size_t>(a.stride) * 4 + 31) / 32 * 32;
   V *queue = reinterpret_cast<V *>(smem + q_off);
   V *shifts = queue + (blockDim.x / 64) * queue_cap(R);
 
   constexpr bool GLOBAL = MODE == kModeGlobal;
   if constexpr (!GLOBAL)
-    for (int k = tid - a.copies; k < a.copies * a.stride; k += blockDim.x) hist[k] = 0u;
+    for (int k = tid - 1; k < a.stride; k += blockDim.x) hist[k] = 0u;
 
   if (tid == 0) s_sum = 0;
   int cur_frame = -1, cur_hist = -1, cur_sweep = -1;
@@ -1822,20 +1494,20 @@ __global__ __launch_bounds__(max_threads<BOX>()) void pairs_kernel(PairKernelArg
     const FrameParams *F = a.frames + w.frame;
     if constexpr (SORTED) {
       if (w.flags & kItemDiag) {
-        run_tiles<T, R, BOX, MODE, true, true>(a, w, F, tile, my, queue, shifts);
+        run_tiles<T, R, BOX, MODE, true, true>(a, w, F, tile, hist, queue, shifts);
       } else {
         bool clamp = true;
         if constexpr (MODE == kModeLds) clamp = !((w.flags & kItemFull) && uni(F->noclamp));
         if (clamp)
-          run_tiles<T, R, BOX, MODE, false, true>(a, w, F, tile, my, queue, shifts);
+          run_tiles<T, R, BOX, MODE, false, true>(a, w, F, tile, hist, queue, shifts);
         else if constexpr (MODE == kModeLds)
-          run_tiles<T, R, BOX, kModeLds, false, false>(a, w, F, tile, my, queue, shifts);
+          run_tiles<T, R, BOX, kModeLds, false, false>(a, w, F, tile, hist, queue, shifts);
       }
       if (tid == 0) s_item = static_cast<int>(gridDim.x) + atomicAdd(a.counter, 1);
     } else if constexpr (BOX == kBoxTricSorted) {
-      run_sorted<MODE>(a, w, F, my, &s_unit, &s_item);
+      run_sorted<MODE>(a, w, F, &s_unit, &s_item);
     } else {
-      run_units<T, R, BOX, MODE>(a, w, F, my, queue, shifts, &s_unit, &s_item);
+      run_units<T, R, BOX, MODE>(a, w, F, hist, queue, shifts, &s_unit, &s_item);
     }
     // every wave has counted the item, and the next one is known
     __syncthreads();

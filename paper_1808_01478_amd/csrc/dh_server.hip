@@ -494,7 +494,6 @@ bool issue_launch(dh_server *s) {
   a.items = R.d_items;
   a.counter = reinterpret_cast<int32_t *>(R.d_items + kMaxItemsPerLaunch);
   a.n_items = static_cast<int32_t>(list.size());
-  a.copies = top.plan.cfg.copies;
   a.stride = stride;
   a.tj = top.plan.cfg.tj;
   if (e == hipSuccess)

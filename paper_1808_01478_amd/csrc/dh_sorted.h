@@ -40,7 +40,7 @@ using Int = std::integral_constant<int, N>;
 struct GroupPair {
   int kind;        // kFast, kFix + axis, kSlow, or kSkip
   bool diag;       // the same group: pairs j > i only
-  bool in_window;  // every t below the end of the window (no clamp needed)
+  bool in_window;  // every t below the LDS stride (no clamp needed)
   float sx, sy, sz;  // lattice shift B n of the lower-end wraps
 };
 constexpr int kSkip = 0, kFast = 1, kFix = 2, kSlow = 5;  // kFix + axis: 2, 3, 4
@@ -110,12 +110,13 @@ __device__ __forceinline__ GroupPair classify(const GroupBox &I, const GroupBox 
 
 // Distance bounds of a bin window in length units, widened by far more than
 // the rounding of any pair's distance: a pair outside [lo, hi] cannot count,
-// one inside `in` needs no clamp (bins up to kDump / 2 past the window are
-// slots that are never flushed).
+// one inside `in` needs no clamp (its t is below the LDS stride; slots past
+// the window are never flushed).
 struct WindowBounds {
   float lo, hi, in;
 };
-__device__ __forceinline__ WindowBounds window_bounds(const FrameParams *F, int b_lo, int win) {
+__device__ __forceinline__ WindowBounds window_bounds(const FrameParams *F, int b_lo, int win,
+                                                      int stride) {
   float size = 0.f;
 #pragma unroll
   for (int k = 0; k < 6; ++k) size += fabsf(uni(F->cell32[k]));
@@ -123,7 +124,7 @@ __device__ __forceinline__ WindowBounds window_bounds(const FrameParams *F, int 
   WindowBounds b;
   b.lo = b_lo > 0 ? fmaxf(static_cast<float>(b_lo) / s * (1.f - 0x1p-12f) - eps, 0.f) : 0.f;
   b.hi = static_cast<float>(b_lo + win) / s * (1.f + 0x1p-12f) + eps;
-  b.in = fmaxf((static_cast<float>(win) + 0.5f * kDump) / s * (1.f - 0x1p-12f) - eps, 0.f);
+  b.in = fmaxf(static_cast<float>(stride - 2) / s * (1.f - 0x1p-12f) - eps, 0.f);
   return b;
 }
 
@@ -134,10 +135,7 @@ __device__ __forceinline__ WindowBounds window_bounds(const FrameParams *F, int 
 // batch and server path gives the same counts.
 template <int MODE>
 __device__ __forceinline__ void run_sorted(const PairKernelArgs &a, const WorkItem &w,
-                                           const FrameParams *F, uint32_t *__restrict__ my,
-                                           int *s_unit, int *s_item) {
-  constexpr bool SWEEP = MODE == kModeSweep;
-  constexpr bool GLOBAL = MODE == kModeGlobal;
+                                           const FrameParams *F, int *s_unit, int *s_item) {
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
   const char *const staged = uni(static_cast<const char *>(F->coords));
   const int64_t n_pad = uni(static_cast<int>(F->n_pad));
@@ -151,43 +149,11 @@ __device__ __forceinline__ void run_sorted(const PairKernelArgs &a, const WorkIt
     cell[k] = uni(F->cell32[k]);
     h[k] = uni(F->hinv32[k]);
   }
-  const float s32 = uni(F->s32);
-  const int win = uni(F->win), n_bins = uni(F->n_bins);
-  const int b_lo = w.sweep * win;
-  const WindowBounds wb = window_bounds(F, b_lo, win);
+  const float s32 = uni(F->s32) * kBinScale;
+  const int win = uni(F->win);
+  const WindowBounds wb = window_bounds(F, w.sweep * win, win, a.stride);
   const bool noclamp = MODE == kModeLds && uni(F->noclamp) != 0;
-  const uint32_t shift_bytes = a.copies == 4 ? 4u : (a.copies == 2 ? 3u : 2u);
-  using LdsU32 = __attribute__((address_space(3))) uint32_t;
-  const uint32_t my_lds = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((LdsU32 *)my));
-  const uint32_t s0 = w.sweep == 0 ? 1u : 0u;
-  uint32_t my_lds_m = SWEEP ? my_lds - (s0 << shift_bytes) : my_lds - (kMagicBits << shift_bytes);
-  asm volatile("" : "+v"(my_lds_m));
-  const uint32_t sweep_base = kMagicBits + static_cast<uint32_t>(b_lo) - s0;
-  const uint32_t hi = static_cast<uint32_t>(win + lane);  // discard slot of this lane
-  using GlobalU64 = __attribute__((address_space(1))) unsigned long long;
-  GlobalU64 *const gout =
-      (GlobalU64 *)(F->out + static_cast<size_t>(w.hist) * static_cast<size_t>(n_bins));
-  // counts a pair from its bin bits; ok = false (DIAG) for j <= i
-  auto count = [&](auto clamp_c, auto diag_c, uint32_t b, bool ok) {
-    constexpr bool CLAMP = decltype(clamp_c)::value, DIAG = decltype(diag_c)::value;
-    if constexpr (GLOBAL) {
-      const uint32_t k = max(b, kMagicBits) - kMagicBits;
-      if ((!DIAG || ok) && k < static_cast<uint32_t>(n_bins))
-        __hip_atomic_fetch_add(gout + k, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-      uint32_t m;
-      if constexpr (SWEEP) {
-        const uint32_t hs = hi + s0;
-        m = med3_u32(b - sweep_base, DIAG && !ok ? hs : 0u, hs);
-      } else if constexpr (CLAMP) {
-        m = med3_u32(b, DIAG && !ok ? kMagicBits + hi : kMagicBits - 1u, kMagicBits + hi);
-      } else {
-        m = b;
-      }
-      __hip_atomic_fetch_add((LdsU32 *)(uintptr_t)(my_lds_m + (m << shift_bytes)), 1u,
-                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
-  };
+  const Count32<MODE> count(F, w, lane);
   using Yes = std::true_type;
   using No = std::false_type;
 
@@ -269,8 +235,8 @@ __device__ __forceinline__ void run_sorted(const PairKernelArgs &a, const WorkIt
         const uint64_t dcc = cc + nzz;
         const float fc = static_cast<float>(
             static_cast<int32_t>(static_cast<uint32_t>(odd ? dcc >> 32 : dcc)));
-        count(Yes{}, Yes{}, bits32_packed_c<kBoxTric>(ab, nab, fc, g32),
-              ok && (!DIAG || j > i));
+        count.template add<true>(bits32_packed_c<kBoxTric>(
+            ab, nab, fc, g32, ok && (!DIAG || j > i) ? kBinOffset : kNoBin));
       });
     } else {
       // A lane past the end of the item holds an i-point at infinity: its q is
@@ -314,9 +280,9 @@ __device__ __forceinline__ void run_sorted(const PairKernelArgs &a, const WorkIt
           }
           const float dx = c.x - x, dy = c.y - y, dz = c.z - z;
           const float q = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-          count(clamp_c, diag_c,
-                __float_as_uint(fmaf(__builtin_amdgcn_sqrtf(q), s32, kMagic32)),
-                !DIAG || j > i0);
+          const float o = DIAG && j <= i0 ? kNoBin : kBinOffset;
+          count.template add<decltype(clamp_c)::value>(
+              __float_as_uint(fmaf(__builtin_amdgcn_sqrtf(q), s32, o)));
         }
       });
     }
