@@ -450,9 +450,6 @@ BaseConfig base_config(size_t lds_per_block, int precision, const Knobs &k, int 
   // entry of pad: the look-ahead read of j may touch the entry just past the
   // second tile
   b.tile_bytes = kControlBytes + 32;
-  if (kind == kBoxTricSorted && !padded_frame(precision, kind))
-    b.tile_bytes += (2 * static_cast<size_t>(c.tj) + 1) * staged_point_bytes(precision, kind) +
-                   kSortedBoxBytes;
   // the search kernels keep their queues after the histogram; counting them
   // with the tiles leaves the histogram budget below them
   if (kind == kBoxTricSearch) b.tile_bytes += search_queue_bytes(precision, c.threads, c.r);
@@ -585,7 +582,7 @@ void plan_frame(int32_t frame, const int64_t *off, int32_t k, bool padded, const
 // idling for up to one full item; lists of fewer than four items per
 // workgroup are already cut fine. The grouping by (histogram, window) is
 // kept.
-void refine_tail(std::vector<WorkItem> &items, int grid, int step, bool split_diag) {
+void refine_tail(std::vector<WorkItem> &items, int grid, int step) {
   const size_t n = items.size();
   const size_t tail = static_cast<size_t>(std::max(grid, 0));
   if (tail == 0 || n < 4 * tail) return;
@@ -595,7 +592,7 @@ void refine_tail(std::vector<WorkItem> &items, int grid, int step, bool split_di
     const WorkItem &w = items[q];
     const int32_t len = w.j1 - w.j0;
     const int32_t piece = std::max<int32_t>(step, (len / 4 + step - 1) / step * step);
-    if ((!split_diag && (w.flags & kItemDiag)) || len <= piece) {
+    if (len <= piece) {
       out.push_back(w);
       continue;
     }
@@ -781,12 +778,11 @@ int run_frame(dh_ctx *ctx, hipStream_t st, const FrameJob &job, const Knobs &k, 
         (kMinBoundedPairs / L.cfg.iblock + L.cfg.tj - 1) / L.cfg.tj * L.cfg.tj;
     L.cfg.jchunk = std::max<int32_t>(
         L.cfg.jchunk, static_cast<int32_t>(std::min<int64_t>(min_jc, 64 * L.cfg.tj)));
-    if (fp.box != kBoxTricSorted || padded_frame(job.precision, fp.box))
-      L.cfg.dchunk = L.cfg.jchunk;
+    L.cfg.dchunk = L.cfg.jchunk;
   }
   std::vector<WorkItem> items;
   std::vector<uint64_t> pairs;
-  plan_frame(0, job.offsets, job.n_species, padded_frame(job.precision, job.kind), L, items,
+  plan_frame(0, job.offsets, job.n_species, padded_frame(job.kind), L, items,
              pairs);
   std::vector<size_t> cuts(1, 0);
   if (limit > 0 && work > limit) {
@@ -808,8 +804,7 @@ int run_frame(dh_ctx *ctx, hipStream_t st, const FrameJob &job, const Knobs &k, 
     for (size_t c = 0; c + 1 < cuts.size(); ++c) {
       seg.assign(items.begin() + static_cast<std::ptrdiff_t>(cuts[c]),
                  items.begin() + static_cast<std::ptrdiff_t>(cuts[c + 1]));
-      refine_tail(seg, L.grid, tail_step(job.precision, fp.box, L.cfg.tj),
-                  fp.box != kBoxTricSorted || padded_frame(job.precision, fp.box));
+      refine_tail(seg, L.grid, tail_step(fp.box));
       all.insert(all.end(), seg.begin(), seg.end());
       at.push_back(all.size());
     }
@@ -1330,8 +1325,10 @@ int histo_job(dh_ctx *ctx, hipStream_t stream, const double *d_coords, const int
   job.d_out = d_out;
   job.d_oor = accumulate ? nullptr : d_out_of_range;
   job.accumulate = accumulate;
-  job.kind = staged_kind(frame_consts(box_type, box, r_max, n_bins, job.fp), precision,
-                         job.fp.L, n);
+  const int geometric = frame_consts(box_type, box, r_max, n_bins, job.fp);
+  job.kind = staged_kind(geometric, precision, job.fp.L, job.fp.s, n_bins, n);
+  // (the sorted binary64 kernel goes back to the input for pairs at a bin edge)
+  job.fp.in = job.kind == kBoxTricSorted && precision == DH_FP64 ? d_coords : nullptr;
   job.fp.box = job.kind;
   job.fp.n_pad = static_cast<int32_t>(padded_start(offsets, n_species));
   for (int s = 0; s < n_species; ++s) {
@@ -1514,9 +1511,8 @@ int dh_batch_create(dh_ctx *ctx, const dh_frame_desc *frames, int32_t n_frames, 
     const int64_t n = d.offsets[d.n_species];
     if (!d.d_out || (n > 0 && !d.d_coords)) return fail(ctx, DH_EINVAL, "frame %d: null pointer", f);
     FrameInfo &fi = info[f];
-    const int kind =
-        staged_kind(frame_consts(d.box_type, d.box, d.r_max, d.n_bins, fi.fp), precision,
-                    fi.fp.L, n);
+    const int geometric = frame_consts(d.box_type, d.box, d.r_max, d.n_bins, fi.fp);
+    const int kind = staged_kind(geometric, precision, fi.fp.L, fi.fp.s, d.n_bins, n);
     fi.fp.box = kind;
     fi.fp.n_pad = static_cast<int32_t>(padded_start(d.offsets, d.n_species));
     fi.offsets.assign(d.offsets, d.offsets + d.n_species + 1);
@@ -1610,12 +1606,11 @@ int dh_batch_create(dh_ctx *ctx, const dh_frame_desc *frames, int32_t n_frames, 
       L.n_sweeps = info[f].fp.n_sweeps;
       pairs_base[f] = pairs.size();
       plan_frame(f, info[f].offsets.data(), frames[f].n_species,
-                 padded_frame(precision, info[f].fp.box), L, items, pairs);
+                 padded_frame(info[f].fp.box), L, items, pairs);
     }
     std::vector<WorkItem> own(items.begin() + static_cast<std::ptrdiff_t>(g.item_begin),
                               items.end());
-    refine_tail(own, g.grid, tail_step(precision, g.kind, g.cfg.tj),
-                g.kind != kBoxTricSorted || padded_frame(precision, g.kind));
+    refine_tail(own, g.grid, tail_step(g.kind));
     items.resize(g.item_begin);
     items.insert(items.end(), own.begin(), own.end());
     g.item_count = items.size() - g.item_begin;

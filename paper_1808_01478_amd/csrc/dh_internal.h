@@ -30,10 +30,14 @@ constexpr int64_t kSortMinPoints = int64_t{1} << 16;
 // frames in both precisions; orthorhombic ones in binary64, where the sorted
 // kernel with a diagonal cell matrix gives the orthorhombic sequence's
 // counts bit for bit) and the binary32 special case of equal orthorhombic
-// edges.
-inline int staged_kind(int kind, int precision, const double L[3], int64_t n_points) {
+// edges. The sorted binary64 kernel takes bins from a binary32 root of
+// numbers scaled by s 2^-22: fewer than 2^20 bins, and a scale whose square
+// is a normal number.
+inline int staged_kind(int kind, int precision, const double L[3], double s, int32_t n_bins,
+                       int64_t n_points) {
+  const bool fits = precision == 0 || (n_bins < (1 << 20) - 2 && s > 0x1p-400 && s < 0x1p400);
   // (padded indices fit in 32 bits)
-  if (n_points >= kSortMinPoints && n_points <= 0x7FFFFFFF - 64 * kMaxSpeciesStage &&
+  if (n_points >= kSortMinPoints && n_points <= 0x7FFFFFFF - 64 * kMaxSpeciesStage && fits &&
       (kind == kBoxTric || (kind == kBoxOrtho && precision != 0)))
     return kBoxTricSorted;
   if (precision != 0) return kind;
@@ -44,15 +48,15 @@ inline int staged_kind(int kind, int precision, const double L[3], int64_t n_poi
 // i-span of a work unit of a sorted frame (see dh_sorted.h)
 constexpr int32_t kUnitPoints = 512;
 
-// Binary32 sorted frames are staged with every species at a multiple of 64
-// points ("padded" indices, used by their work items too), so that index / 64
-// is a point's group: the Cartesian positions (float4), the fixed-point words
-// (three each) and the groups' boxes, which together fit in the 32 bytes per
-// point of staged_point_bytes (29 per padded point plus one box; frames have
-// at least kSortMinPoints points and at most kMaxSpeciesStage species).
-inline bool padded_frame(int precision, int kind) {
-  return kind == kBoxTricSorted && precision == 0;
-}
+// Sorted frames are staged with every species at a multiple of 64 points
+// ("padded" indices, used by their work items too), so that index / 64 is a
+// point's group: binary32 the Cartesian positions (float4) and the fixed-point
+// words (three each), binary64 the scaled positions (three doubles) and the
+// input indices (one word), then the groups' boxes. Together they fit in the
+// 32 bytes per point of staged_point_bytes (29 per padded point plus one box;
+// frames have at least kSortMinPoints points and at most kMaxSpeciesStage
+// species).
+inline bool padded_frame(int kind) { return kind == kBoxTricSorted; }
 __host__ __device__ inline int64_t padded_start(const int64_t *off, int32_t s) {
   int64_t p = 0;
   for (int32_t u = 0; u < s; ++u) p += (off[u + 1] - off[u] + 63) / 64 * 64;
@@ -63,7 +67,8 @@ __host__ __device__ inline int64_t padded_start(const int64_t *off, int32_t s) {
 struct GroupBox {
   uint32_t ulo[3], uhi[3];
   float clo[3], chi[3];
-  uint32_t unused[4];
+  float mag;  // binary64: largest |x| + |y| + |z| of the input (inf: not all finite)
+  uint32_t unused[3];
 };
 static_assert(sizeof(GroupBox) == 64, "one box per 64 points at one byte a point");
 
@@ -130,7 +135,7 @@ struct FrameParams {
   uint64_t *oor;       // caller's out-of-range counts [H] or null (device)
   const uint64_t *pairs;  // pairs per histogram [H] (device)
   int64_t n_points;
-  int32_t n_pad;   // sorted binary32 frames: points with every species padded
+  int32_t n_pad;   // sorted frames: points with every species padded
   int32_t n_hist;
   int32_t oor_by_flush;  // 1: oor starts at pairs and every flush subtracts its counts
   int32_t n_bins;
@@ -175,12 +180,6 @@ struct FrameParams {
   uint8_t oct_n;
 };
 
-// LDS of a spatially sorted frame's pair kernel besides its two j-tiles:
-// the bounding boxes of the tiles' groups of 64 points (two tiles, at most
-// four groups each, eight words per box: 32-bit fixed-point fractions in
-// binary32, binary64 fractions in binary64)
-constexpr size_t kSortedBoxBytes = 2 * 4 * 8 * sizeof(double);
-
 // One unit of work: particles [i0, i1) of the frame against [j0, j1), for
 // histogram `hist`, bin window `sweep`; flags: kItemDiag, kItemFull.
 struct WorkItem {
@@ -224,24 +223,20 @@ struct KernelConfig {
 // here (20,000 points in a cube, 1,000 bins: binary32 123 us with 8 items of
 // 32k pairs a workgroup, 86 us with two of 122k; binary64 234 and 202 us).
 //
-// Sorted binary32 frames are cut alike, in units of kUnitPoints, four times as
+// Sorted frames are cut alike, in units of kUnitPoints, four times as
 // fine: items beyond the cut-off cost next to nothing, so the others make the
 // end of the launch (1M clustered points: 89.9 ms, now 86.7 ms).
-//
-// Sorted binary64 frames: one slice per wave, whole j-tiles, the block on the
-// diagonal in one item.
 constexpr int64_t kMinItemPairs = int64_t{1} << 15;
 constexpr int32_t kMinChunk = 32;
 // granularity of the j-pieces the tail of a work list is cut into
-inline int32_t tail_step(int32_t precision, int32_t kind, int32_t tj) {
-  return kind != kBoxTricSorted ? kMinChunk : precision ? tj : kUnitPoints;
+inline int32_t tail_step(int32_t kind) {
+  return kind == kBoxTricSorted ? kUnitPoints : kMinChunk;
 }
 inline void set_items(KernelConfig &c, int32_t precision, int32_t kind, int grid, uint64_t work,
                       int items_per_wg) {
   const uint64_t g = static_cast<uint64_t>(grid > 0 ? grid : 1);
-  const int64_t full = static_cast<int64_t>(c.threads) * c.r;
-  int64_t bi = full, jc;
-  if (padded_frame(precision, kind)) {
+  int64_t bi = static_cast<int64_t>(c.threads) * c.r, jc;
+  if (padded_frame(kind)) {
     const int64_t target = static_cast<int64_t>(work / (g * 4 * items_per_wg));
     bi = 16 * kUnitPoints;
     while (bi > kUnitPoints && target / bi < bi) bi /= 2;
@@ -249,12 +244,6 @@ inline void set_items(KernelConfig &c, int32_t precision, int32_t kind, int grid
     jc = jc < kUnitPoints ? kUnitPoints : jc;
     jc = jc > 32 * kUnitPoints ? 32 * kUnitPoints : jc;
     c.dchunk = static_cast<int32_t>(jc);
-  } else if (kind == kBoxTricSorted) {
-    jc = static_cast<int64_t>(work / (g * items_per_wg * full + 1));
-    jc = (jc + c.tj - 1) / c.tj * c.tj;
-    jc = jc < c.tj ? c.tj : jc;
-    jc = jc > 64 * c.tj ? 64 * c.tj : jc;
-    c.dchunk = static_cast<int32_t>(bi);
   } else {
     const int64_t per_wg = static_cast<int64_t>(work / g), small = int64_t{1}
                                                                    << (precision ? 16 : 17);
@@ -379,9 +368,8 @@ template <> PairFn pick_pairs<double, kModeGlobal>(int r, int box);
 // host-side launchers (dh_kernels.hip)
 // Staging of a kBoxTricSorted frame: the points of every species in Morton
 // order of their wrapped fractional coordinates (keys: a workspace of
-// sort_keys_count(n) words); binary32: positions, words and group boxes at
-// padded indices (see padded_frame), binary64: the input coordinates as one
-// double4 per point.
+// sort_keys_count(n) words); staged arrays and group boxes at
+// padded indices (see padded_frame).
 hipError_t launch_stage_sorted(int precision, const double *in, void *out, int64_t n,
                                const int64_t *offsets, int32_t n_species, const FrameParams &fp,
                                uint64_t *keys, hipStream_t st);

@@ -218,20 +218,68 @@ __global__ void stage_sorted_kernel(const double *__restrict__ in,
     b.clo[ax] = wave_min(ok ? c[ax] : __builtin_inff());
     b.chi[ax] = wave_max(ok ? c[ax] : -__builtin_inff());
   }
+  b.mag = 0.f;
   for (uint32_t &v : b.unused) v = 0u;
   if (lane == 0) reinterpret_cast<GroupBox *>(out + 28 * static_cast<int64_t>(p.n_pad))[group] = b;
 }
 
-// binary64: the input point of the sorted position q, unchanged.
+// binary64 staging of a sorted frame, one group of 64 points per wave: the
+// position of the wrapped point relative to the cell centre in units of 2^22
+// bins, the point's input index, and the group's boxes.
 __global__ void stage_sorted64_kernel(const double *__restrict__ in,
-                                      const uint64_t *__restrict__ keys, int64_t n,
-                                      double4 *__restrict__ out) {
-  const int64_t step = static_cast<int64_t>(gridDim.x) * blockDim.x;
-  for (int64_t q = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; q < n;
-       q += step) {
-    const int64_t i = static_cast<int64_t>(keys[q] & 0x7FFFFFFFull);
-    out[q] = make_double4(in[3 * i], in[3 * i + 1], in[3 * i + 2], 0.0);
+                                      const uint64_t *__restrict__ keys, SpeciesOffsets off,
+                                      int32_t k, FrameParams p, char *__restrict__ out) {
+  const int lane = threadIdx.x & 63;
+  const int64_t group = blockIdx.x * static_cast<int64_t>(blockDim.x / 64) + threadIdx.x / 64;
+  if (64 * group >= p.n_pad) return;
+  int64_t g0 = 0;
+  int s = 0;
+  for (; s + 1 < k; ++s) {
+    const int64_t ng = (off.v[s + 1] - off.v[s] + 63) / 64;
+    if (group < g0 + ng) break;
+    g0 += ng;
   }
+  const int64_t q = off.v[s] + 64 * (group - g0) + lane;
+  const bool ok = q < off.v[s + 1];
+  uint32_t u[3] = {0u, 0u, 0u};
+  double c[3] = {0.0, 0.0, 0.0};
+  double mag = 0.0;
+  uint32_t from = 0;
+  if (ok) {
+    from = static_cast<uint32_t>(keys[q] & 0x7FFFFFFFull);
+    const double x = in[3 * static_cast<int64_t>(from)], y = in[3 * static_cast<int64_t>(from) + 1],
+                 z = in[3 * static_cast<int64_t>(from) + 2];
+    const double fa = fma(z, p.h13, fma(y, p.h12, x * p.h11));
+    const double fb = fma(z, p.h23, y * p.h22);
+    const double fc = z * p.h33;
+    u[0] = fix32(fa);
+    u[1] = fix32(fb);
+    u[2] = fix32(fc);
+    const double na = floor(fa) + 0.5, nb = floor(fb) + 0.5, nc = floor(fc) + 0.5;
+    c[0] = fma(-p.cx, nc, fma(-p.bx, nb, fma(-p.ax, na, x)));
+    c[1] = fma(-p.cy, nc, fma(-p.by, nb, y));
+    c[2] = fma(-p.cz, nc, z);
+    mag = fabs(x) + fabs(y) + fabs(z);
+    if (!(mag < 1e300)) mag = __builtin_inf();
+  }
+  const double scale = p.s * 0x1p-22;
+  const int64_t at = 64 * group + lane, n_pad = p.n_pad;
+  double *const pos = reinterpret_cast<double *>(out) + 3 * at;
+  reinterpret_cast<uint32_t *>(out + 24 * n_pad)[at] = from;
+  GroupBox b;
+#pragma unroll
+  for (int ax = 0; ax < 3; ++ax) {
+    pos[ax] = c[ax] * scale;
+    const float f = static_cast<float>(c[ax]);
+    b.ulo[ax] = wave_min(ok ? u[ax] : 0xFFFFFFFFu);
+    b.uhi[ax] = wave_max(ok ? u[ax] : 0u);
+    b.clo[ax] = wave_min(ok ? f : __builtin_inff());
+    b.chi[ax] = wave_max(ok ? f : -__builtin_inff());
+  }
+  // (rounded up)
+  b.mag = wave_max(static_cast<float>(mag)) * 1.000001f;
+  for (uint32_t &v : b.unused) v = 0u;
+  if (lane == 0) reinterpret_cast<GroupBox *>(out + 28 * n_pad)[group] = b;
 }
 
 // Batched staging: blockIdx.y selects the frame.
@@ -379,12 +427,13 @@ hipError_t launch_stage_sorted(int precision, const double *in, void *out, int64
       bitonic_global_kernel<<<grid_for(npad / 2, threads), threads, 0, st>>>(keys, npad, j, kk);
     bitonic_local_kernel<<<blocks, 1024, 0, st>>>(keys, kk, 0);
   }
+  const int wgs = static_cast<int>((fp.n_pad / 64 + 3) / 4);
   if (precision == 1)
-    stage_sorted64_kernel<<<grid_for(n, threads), threads, 0, st>>>(in, keys, n,
-                                                                    static_cast<double4 *>(out));
+    stage_sorted64_kernel<<<wgs, threads, 0, st>>>(in, keys, off, n_species, fp,
+                                                   static_cast<char *>(out));
   else
-    stage_sorted_kernel<<<static_cast<int>((fp.n_pad / 64 + 3) / 4), threads, 0, st>>>(
-        in, keys, off, n_species, fp, static_cast<char *>(out));
+    stage_sorted_kernel<<<wgs, threads, 0, st>>>(in, keys, off, n_species, fp,
+                                                 static_cast<char *>(out));
   return hipGetLastError();
 }
 

@@ -164,8 +164,8 @@ extern "C" int dh_histo_noalloc(dh_stream stream, const double *d_coords,
   hipStream_t st = static_cast<hipStream_t>(stream);
 
   FrameParams fp;
-  const int kind =
-      staged_kind(frame_constants(box_type, box, r_max, n_bins, fp), precision, fp.L, n);
+  const int geometric = frame_constants(box_type, box, r_max, n_bins, fp);
+  const int kind = staged_kind(geometric, precision, fp.L, fp.s, n_bins, n);
   fp.box = kind;
   fp.n_pad = static_cast<int32_t>(padded_start(offsets, n_species));
   const size_t point_bytes = staged_point_bytes(precision, kind);
@@ -205,6 +205,7 @@ extern "C" int dh_histo_noalloc(dh_stream stream, const double *d_coords,
   int32_t *counters = reinterpret_cast<int32_t *>(base + off_counters);
   fp.coords = base + off_staged;
   fp.out = d_out;
+  fp.in = kind == kBoxTricSorted && precision == DH_FP64 ? d_coords : nullptr;
   fp.win = L.win;
   fp.n_sweeps = L.n_sweeps;
   fp.noclamp = L.noclamp ? 1 : 0;
@@ -220,7 +221,7 @@ extern "C" int dh_histo_noalloc(dh_stream stream, const double *d_coords,
   pa.k = n_species;
   pa.n_sweeps = L.n_sweeps;
   pa.n_counters = n_counters;
-  pa.padded = padded_frame(precision, kind);
+  pa.padded = padded_frame(kind);
   pa.bi = bi;
   pa.jc = jc;
   pa.dc = dc;

@@ -40,13 +40,10 @@ struct V4<double> { using type = double4; };
 
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// s_waitcnt immediates (gfx9 encoding: vmcnt bits [3:0] and [15:14], expcnt
-// [6:4], lgkmcnt [11:8]); a field at its maximum does not wait.
-constexpr int kWaitVm0 = 0x0F70;    // vmcnt(0)
-constexpr int kWaitLgkm0 = 0xC07F;  // lgkmcnt(0)
 // last word of a raw buffer resource (32-bit elements, no swizzle)
 constexpr int kBufferFlags = 0x00020000;
 using V4u = unsigned int __attribute__((ext_vector_type(4)));
+using V2u = unsigned int __attribute__((ext_vector_type(2)));
 // j-particles in flight ahead of the arithmetic, and the fewest j of a unit
 constexpr int kJAhead = 4;
 constexpr int kMinUnitJ = 8;
@@ -353,28 +350,7 @@ __device__ __forceinline__ double min_arith(double a, double b) {
   return r;
 }
 
-// Minimum and maximum over the 64 lanes of a wave, as a wave-uniform value.
-__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = min(v, static_cast<uint32_t>(__shfl_xor(v, o)));
-  return static_cast<uint32_t>(uni(static_cast<int>(v)));
-}
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = max(v, static_cast<uint32_t>(__shfl_xor(v, o)));
-  return static_cast<uint32_t>(uni(static_cast<int>(v)));
-}
 
-__device__ __forceinline__ double wave_min_f64(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o));
-  return uni(v);
-}
-__device__ __forceinline__ double wave_max_f64(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
-  return uni(v);
-}
 
 // Triclinic reduced vector (t units) from packed fractional words.
 __device__ __forceinline__ void tric_vec32(uint64_t ab_j, uint64_t neg_ab_i, float zi, float zj,
@@ -668,373 +644,6 @@ __device__ __forceinline__ void flush_hist(uint32_t *hist, const PairKernelArgs 
   if (oor && threadIdx.x == 0 && *s_sum != 0) {
     atomicAdd(reinterpret_cast<unsigned long long *>(F->oor + hist_idx), 0ull - *s_sum);
     *s_sum = 0;
-  }
-}
-
-// Lattice shift along one axis shared by every pair of two groups of a
-// binary64 sorted frame. The fractional difference s of a pair (the first
-// step of Eq. 5, with its rounding) lies in [jlo - ihi, jhi - ilo] (the
-// groups' boxes of B^-1 x) widened by the margin m, which bounds the
-// rounding of s, of the boxes and of this test. When both ends of the
-// widened interval round to the same n, every s lies strictly inside
-// (n - 1/2, n + 1/2), so rint(s) = n for every pair, ties included. False
-// when the ends differ or a group is empty (an empty box has lo = +inf,
-// hi = -inf) or holds a non-finite value.
-__device__ __forceinline__ bool group_shift64(double ilo, double ihi, double jlo, double jhi,
-                                              double m, double &n) {
-  const double a = floor(((jlo - ihi) - m) + 0.5);
-  const double b = floor(((jhi - ilo) + m) + 0.5);
-  n = a;
-  return a == b;
-}
-
-// One j-tile of a spatially sorted binary64 frame for one wave. For every
-// group of 64 j-points and every slice r of the wave's i-points, each axis
-// whose Eq. 5 shift n is shared by all their pairs (group_shift64) and whose
-// terms B n are exact (|n| <= 1) skips that axis's fractional
-// coordinate and rounding: each fused step of Eq. 5 with that n, d - B_k n
-// rounded once, equals the plain sum d + P_k with the exact term
-// P_k = -B_k n. The other axes take Eq. 5's own steps. A pass over the
-// group's j serves all R slices with one kind of reduction (the axes that
-// need the rounding for any slice take it for all of them: for a shared
-// axis it yields the same n), so every reduced vector, q and t is
-// bit-identical to the canonical sequence. Sums along an axis whose shared
-// shift is zero for every slice are skipped (they would change only the sign
-// of a zero component).
-//
-// Box slot 6 of a group holds the largest |x| + |y| + |z| of its points,
-// which bounds the magnitudes, and with them the rounding, that the margin
-// of group_shift64 must cover: with u = 2^-53 and h the largest entry of
-// B^-1, every rounding error of the fractional difference, of the boxes and
-// of the test is below 12 u h (A_i + A_j), well inside 2^-48 h (A_i + A_j).
-template <int R, bool DIAG, typename CountT>
-__device__ __forceinline__ void sorted_tile64(
-    const double4 *__restrict__ tb, const double *__restrict__ boxes, int jt, int js,
-    int jcount, int wbase, int lane, const Geo64 &g, bool big_bins, const double (&xi)[R],
-    const double (&yi)[R], const double (&zi)[R], double ib_lo, double ib_hi, double ib_mag,
-    uint32_t ib_empty, const uint32_t (&lo)[R], uint32_t hi, CountT &count_t) {
-  const double hmax = fmax(fmax(fabs(g.h11), fabs(g.h12)),
-                           fmax(fmax(fabs(g.h13), fabs(g.h22)), fmax(fabs(g.h23), fabs(g.h33))));
-  // lane 3r + k tests axis k of slice r (lanes 3R and up repeat axis 0)
-  const int bk = lane < 3 * R ? lane % 3 : 0;
-  const uint32_t keep = ~ib_empty;
-  for (int g0 = js & ~63; g0 < jcount; g0 += 64) {
-    const int j_begin = max(js, g0), j_end = min(jcount, g0 + 64);
-    const double *gb = boxes + (g0 >> 6) * 8;
-    // this lane's axis: is the shift shared by all pairs of the two groups,
-    // and is its term -B_k n exact (|n| <= 1)? Four ballots give, per slice
-    // and axis, the rounded axes and the shared shifts +1 and -1 (an empty
-    // slice counts nothing: shift 0).
-    const double m = fma(hmax * (ib_mag + gb[6]), 0x1p-48, 0x1p-40);
-    double n;
-    const bool shared = group_shift64(ib_lo, ib_hi, gb[bk], gb[3 + bk], m, n);
-    const bool use = shared && fabs(n) <= 1.0;
-    const uint32_t m_amb = static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(!use)) & keep;
-    const uint32_t m_pos =
-        static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(use && n == 1.0)) & keep;
-    const uint32_t m_neg =
-        static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(use && n == -1.0)) & keep;
-    // amb: bit k when axis k (a, b, c) needs the rounding for some slice;
-    // nz: bit k when some slice has a shared non-zero shift along axis k
-    uint32_t amb = 0, nz = 0;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      amb |= (m_amb >> (3 * r)) & 7u;
-      nz |= ((m_pos | m_neg) >> (3 * r)) & 7u;
-    }
-    nz &= ~amb;
-    // exact term -B n of slice r along axis k for cell entry b, in the order
-    // of the canonical steps (zero where the slice's shift is 0 or the axis
-    // takes the rounding); selected from the ballots, so each loop below
-    // keeps only the terms it adds
-    auto P = [&](int r, int k, double b) {
-      const uint32_t bit = 1u << (3 * r + k);
-      return (m_pos & bit) ? -b : ((m_neg & bit) ? b : 0.0);
-    };
-
-    // The reduced vector, q and short root t of the pairs of all slices with
-    // one j, reduced as AMB says (each lane keeps in `gap` how close its t
-    // come to an integer, see t_fast64).
-    // AMB: the axes that take the rounding; NZ: the axes whose shared shift
-    // is non-zero for some slice (the others add nothing: their terms are 0).
-    auto reduce = [&](auto amb_c, auto nz_c, const double4 &pj, double *q, double *t,
-                      uint32_t &gap) {
-      constexpr uint32_t AMB = decltype(amb_c)::value;
-      constexpr uint32_t NZ = decltype(nz_c)::value;
-      static_assert((AMB & NZ) == 0, "an axis is either rounded or shared");
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        double dx = pj.x - xi[r], dy = pj.y - yi[r], dz = pj.z - zi[r];
-        // Eq. 5's n of the axes that need it, from the unreduced d
-        double na = 0.0, nb = 0.0, nc = 0.0;
-        if constexpr (AMB & 1u) na = rint(fma(dz, g.h13, fma(dy, g.h12, dx * g.h11)));
-        if constexpr (AMB & 2u) nb = rint(fma(dz, g.h23, dy * g.h22));
-        if constexpr (AMB & 4u) nc = rint(dz * g.h33);
-        if constexpr (AMB & 4u) dz = fma(-g.cz, nc, dz);
-        else if constexpr (NZ & 4u) dz = dz + P(r, 2, g.cz);
-        if constexpr (AMB & 2u) dy = fma(-g.by, nb, dy);
-        else if constexpr (NZ & 2u) dy = dy + P(r, 1, g.by);
-        if constexpr (AMB & 4u) dy = fma(-g.cy, nc, dy);
-        else if constexpr (NZ & 4u) dy = dy + P(r, 2, g.cy);
-        if constexpr (AMB & 1u) dx = fma(-g.ax, na, dx);
-        else if constexpr (NZ & 1u) dx = dx + P(r, 0, g.ax);
-        if constexpr (AMB & 2u) dx = fma(-g.bx, nb, dx);
-        else if constexpr (NZ & 2u) dx = dx + P(r, 1, g.bx);
-        if constexpr (AMB & 4u) dx = fma(-g.cx, nc, dx);
-        else if constexpr (NZ & 4u) dx = dx + P(r, 2, g.cx);
-        q[r] = fma(dz, dz, fma(dy, dy, dx * dx));
-        t[r] = t_fast64(q[r], g.s, gap);
-      }
-    };
-    // The counts of NJ consecutive j from j0: the correctly rounded root for
-    // all of them when any lane needs it, then one atomic per pair.
-    auto finish = [&](auto nj_c, const double *q, double *t, uint32_t gap, int j0) {
-      constexpr int NJ = decltype(nj_c)::value;
-      if (__builtin_expect(any_near(gap), 0))
-#pragma unroll
-        for (int k = 0; k < NJ * R; ++k) t[k] = sqrt_cr(q[k]) * g.s;
-#pragma unroll
-      for (int k = 0; k < NJ * R; ++k) {
-        const int r = k % R;
-        uint32_t l = lo[r];
-        if constexpr (DIAG) l = jt + j0 + k / R > wbase + r * 64 + lane ? l : hi;
-        count_t(t[k], l, 0u);
-      }
-    };
-    // One pass over the group's j, two j per step with one ballot. The next
-    // two j are read before the current ones' atomics (see sorted_tile); at
-    // the end of the group the look-ahead reads touch at most the two entries
-    // after it (the next group, the other tile or the box area), never used.
-    auto run_j = [&](auto amb_c, auto nz_c) {
-      using Two = std::integral_constant<int, 2>;
-      using One = std::integral_constant<int, 1>;
-      int vzero;
-      asm volatile("v_mov_b32 %0, 0" : "=v"(vzero));
-      const double4 *cp = tb + j_begin + vzero;
-      double4 pa = cp[0], pb = cp[1];
-      int j = j_begin;
-      for (; j + 1 < j_end; j += 2, cp += 2) {
-        double q[2 * R], t[2 * R];
-        uint32_t gap = gap_init(big_bins);
-        reduce(amb_c, nz_c, pa, q, t, gap);
-        reduce(amb_c, nz_c, pb, q + R, t + R, gap);
-        pa = cp[2];
-        pb = cp[3];
-        finish(Two{}, q, t, gap, j);
-      }
-      if (j < j_end) {
-        double q[R], t[R];
-        uint32_t gap = gap_init(big_bins);
-        reduce(amb_c, nz_c, pa, q, t, gap);
-        finish(One{}, q, t, gap, j);
-      }
-    };
-    using M0 = std::integral_constant<uint32_t, 0>;
-    using M1 = std::integral_constant<uint32_t, 1>;
-    using M2 = std::integral_constant<uint32_t, 2>;
-    using M3 = std::integral_constant<uint32_t, 3>;
-    using M4 = std::integral_constant<uint32_t, 4>;
-    using M5 = std::integral_constant<uint32_t, 5>;
-    using M6 = std::integral_constant<uint32_t, 6>;
-    using M7 = std::integral_constant<uint32_t, 7>;
-    if constexpr (DIAG) {
-      // items on the diagonal of a histogram (few pairs): Eq. 5 throughout
-      run_j(M7{}, M0{});
-    } else {
-      // the frequent kinds get their own loop (shared shifts along one axis
-      // at most, or one rounded axis with zero shifts along the others);
-      // the rest round their ambiguous axes and add the terms of all others
-      switch (amb * 8u + nz) {
-        case 0: run_j(M0{}, M0{}); break;
-        case 1: run_j(M0{}, M1{}); break;
-        case 2: run_j(M0{}, M2{}); break;
-        case 4: run_j(M0{}, M4{}); break;
-        case 8: run_j(M1{}, M0{}); break;
-        case 16: run_j(M2{}, M0{}); break;
-        case 32: run_j(M4{}, M0{}); break;
-        default:
-          switch (amb) {
-            case 0: run_j(M0{}, M7{}); break;
-            case 1: run_j(M1{}, M6{}); break;
-            case 2: run_j(M2{}, M5{}); break;
-            case 3: run_j(M3{}, M4{}); break;
-            case 4: run_j(M4{}, M3{}); break;
-            case 5: run_j(M5{}, M2{}); break;
-            case 6: run_j(M6{}, M1{}); break;
-            default: run_j(M7{}, M0{}); break;
-          }
-      }
-    }
-  }
-}
-
-// CLAMP = false: the host proved that every t of this frame is below the LDS
-// stride and the block has no invalid lanes, so the bin index needs no clamp
-// (out-of-range pairs land in slots [n_bins, stride) that are never flushed).
-//
-// BOX = kBoxTricSearch: the 27-image search only runs for pairs whose reduced
-// vector is not provably the nearest image (q0 >= qskip: at least half the
-// shortest lattice vector long). Those pairs are queued per wave in LDS and
-// searched 64 at a time by the whole wave, so the search never runs for a
-// wave with only a few lanes needing it; the others are counted directly.
-template <typename T, int R, int BOX, int MODE, bool DIAG, bool CLAMP>
-__device__ __forceinline__ void run_tiles(const PairKernelArgs &a, const WorkItem &w,
-                                         const FrameParams *F,
-                                         typename V4<T>::type *__restrict__ tile,
-                                         uint32_t *__restrict__ my,
-                                         typename V4<T>::type *__restrict__ queue,
-                                         typename V4<T>::type *__restrict__ sh) {
-  using V = typename V4<T>::type;
-  using G = typename Geo<T>::type;
-  constexpr bool SWEEP = MODE == kModeSweep;
-  constexpr bool GLOBAL = MODE == kModeGlobal;
-  constexpr bool SEARCH = BOX == kBoxTricSearch;
-  // spatially sorted frames: two float4 per point (fixed-point words, then
-  // the Cartesian position relative to the cell centre)
-  constexpr bool SORTED = BOX == kBoxTricSorted;
-  constexpr int EPJ = SORTED && sizeof(T) == 4 ? 2 : 1;
-  const V *__restrict__ X = static_cast<const V *>(F->coords);
-  const G g = Geo<T>::load(F);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int tj = a.tj;
-  const int win = uni(F->win);
-  const int b_lo = w.sweep * win;
-  // largest slot index of binary64 unclamped items
-  const double cap64 = static_cast<double>(a.stride - 1);
-
-  // i-particles: wave w holds [wbase, wbase + 64R), lane l the R values
-  // wbase + r*64 + l
-  const int wbase = w.i0 + wave * 64 * R;
-  const bool wave_active = wbase < w.i1;
-  T xi[R], yi[R], zi[R];
-  const uint32_t hi = static_cast<uint32_t>(win + lane);  // discard slot of this lane
-  uint32_t lo[R];
-  // sorted frames: Cartesian i-positions, and the fixed-point bounding box of
-  // each 64-particle slice r of the wave (its valid lanes), one axis per
-  // lane: lane 3r + k holds the lower (ib_lo) and upper (ib_hi) bound along
-  // axis k; ib_empty has bits 3r, 3r + 1, 3r + 2 set for a slice without
-  // valid lanes
-  [[maybe_unused]] float cxi[R], cyi[R], czi[R];
-  [[maybe_unused]] uint32_t ib_lo = 0, ib_hi = 0, ib_empty = 0;
-  // binary64 sorted frames: boxes of the fractional coordinates B^-1 x, one
-  // axis per lane (lane 3r + k: axis k of slice r), the largest
-  // |x| + |y| + |z| of slice r in lanes 3r to 3r + 2, and ib64_empty with
-  // bits 3r to 3r + 2 set for a slice without valid lanes
-  [[maybe_unused]] double ib64_lo = 0.0, ib64_hi = 0.0, ib64_mag = 0.0;
-  [[maybe_unused]] uint32_t ib64_empty = 0;
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int i = wbase + r * 64 + lane;
-    const bool ok = i < w.i1;
-    const V p = X[EPJ * (ok ? i : w.i0)];
-    xi[r] = p.x; yi[r] = p.y; zi[r] = p.z;
-    lo[r] = ok ? 0u : hi;
-    if constexpr (SORTED && sizeof(T) == 8) {
-      double sg[3];
-      frac64(p.x, p.y, p.z, g, sg);
-#pragma unroll
-      for (int ax = 0; ax < 3; ++ax) {
-        const double bl = wave_min_f64(ok ? sg[ax] : __builtin_inf());
-        const double bh = wave_max_f64(ok ? sg[ax] : -__builtin_inf());
-        if (lane == 3 * r + ax) {
-          ib64_lo = bl;
-          ib64_hi = bh;
-        }
-        if (ax == 0 && !(bl <= bh)) ib64_empty |= 7u << (3 * r);
-      }
-      const double mag = wave_max_f64(ok ? fabs(p.x) + fabs(p.y) + fabs(p.z) : 0.0);
-      if (lane >= 3 * r && lane < 3 * r + 3) ib64_mag = mag;
-    }
-  }
-  const int n_bins = uni(F->n_bins);
-  // binary64: the correctly rounded root for every pair when t at or above
-  // 2^20 can lie near a bin edge (this many bins) or the scale s is so large
-  // that a subnormal q could reach bin 1 (see t_fast64)
-  [[maybe_unused]] const bool big_bins =
-      n_bins >= (1 << 20) - 2 || !(uni(F->s) < 0x1p500);
-  // the output is global memory: say so, so the atomics are global_atomic_*
-  // (a generic pointer would give flat atomics, which also count as LDS
-  // operations in lgkmcnt)
-  using GlobalU64 = __attribute__((address_space(1))) unsigned long long;
-  GlobalU64 *const gout =
-      (GlobalU64 *)(F->out + static_cast<size_t>(w.hist) * static_cast<size_t>(n_bins));
-
-  // Counts one pair at scaled distance t. l: 0 for a pair that counts, the
-  // lane's discard slot for one that must not (the lower clamp).
-  auto count_t = [&](double t, uint32_t l, uint32_t) {
-    if constexpr (GLOBAL) {
-      if (l == 0u && t < static_cast<double>(n_bins))
-        __hip_atomic_fetch_add(gout + static_cast<uint32_t>(t), 1ull, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-      uint32_t idx;
-      if constexpr (!CLAMP) {
-        idx = static_cast<uint32_t>(min_arith(t, cap64));
-      } else {
-        idx = static_cast<uint32_t>(min_arith(t, 4294967295.0));
-        if constexpr (SWEEP) idx -= static_cast<uint32_t>(b_lo);
-        idx = med3_u32(idx, l, hi);
-      }
-      atomicAdd(my + idx, 1u);
-    }
-  };
-
-  // The i-particles are complete before the tile loop, so the only global
-  // load in flight inside it is the next tile's prefetch, which the j-loop
-  // never reads.
-  __builtin_amdgcn_s_waitcnt(kWaitVm0);
-
-  V pre = {};
-  [[maybe_unused]] V preC = {};
-  // sorted frames: bounding boxes of the tiles' groups of 64 j-points, after
-  // the two tiles (eight words per group)
-  [[maybe_unused]] uint32_t *const tboxes = reinterpret_cast<uint32_t *>(tile + 2 * tj * EPJ);
-  if (tid < tj && w.j0 + tid < w.j1) {
-    pre = X[EPJ * (w.j0 + tid)];
-    if constexpr (SORTED && sizeof(T) == 4) preC = X[EPJ * (w.j0 + tid) + 1];
-  }
-  int buf = 0;
-  for (int jt = w.j0; jt < w.j1; jt += tj, buf ^= 1) {
-    if (tid < tj) {
-      tile[(buf * tj + tid) * EPJ] = pre;
-      if constexpr (SORTED && sizeof(T) == 8) {
-        // the box of this wave's 64 j in fractional coordinates
-        const bool ok = jt + tid < w.j1;
-        double sg[3];
-        frac64(pre.x, pre.y, pre.z, g, sg);
-        double b6[7];
-#pragma unroll
-        for (int ax = 0; ax < 3; ++ax) {
-          b6[ax] = wave_min_f64(ok ? sg[ax] : __builtin_inf());
-          b6[3 + ax] = wave_max_f64(ok ? sg[ax] : -__builtin_inf());
-        }
-        b6[6] = wave_max_f64(ok ? fabs(pre.x) + fabs(pre.y) + fabs(pre.z) : 0.0);
-        if (lane < 7) {
-          double v = b6[0];
-#pragma unroll
-          for (int q = 1; q < 7; ++q) v = lane == q ? b6[q] : v;
-          reinterpret_cast<double *>(tboxes)[(buf * 4 + (tid >> 6)) * 8 + lane] = v;
-        }
-      }
-    }
-    __syncthreads();
-    {
-      const int jn = jt + tj + tid;
-      if (tid < tj && jn < w.j1) {
-        pre = X[EPJ * jn];
-        if constexpr (SORTED && sizeof(T) == 4) preC = X[EPJ * jn + 1];
-      }
-    }
-    const int jcount = min(tj, w.j1 - jt);
-    int js = 0;
-    if constexpr (DIAG) js = max(0, min(jcount, wbase + 1 - jt));
-    if constexpr (SORTED && sizeof(T) == 8) {
-      if (wave_active && js < jcount)
-        sorted_tile64<R, DIAG>(tile + buf * tj, reinterpret_cast<const double *>(tboxes) + buf * 32,
-                               jt, js, jcount, wbase, lane, g, big_bins, xi, yi, zi, ib64_lo,
-                               ib64_hi, ib64_mag, ib64_empty, lo,
-                               hi, count_t);
-    }
   }
 }
 
@@ -1444,15 +1053,9 @@ __global__ __launch_bounds__(max_threads<BOX>(), (min_waves<T, R, BOX>())) void 
   // control words: in-range counts of a flush, next item, next unit
   unsigned long long &s_sum = *reinterpret_cast<unsigned long long *>(smem);
   int &s_item = *reinterpret_cast<int *>(smem + 8), &s_unit = *reinterpret_cast<int *>(smem + 12);
-  V *tile = reinterpret_cast<V *>(smem + kControlBytes);
   // the histogram follows a guard of kGuardBytes: one word per copy for
-  // binary32 bin -1 (t < 1/4), added to bin 0 on flush. (Sorted frames: the
-  // two j-tiles of two entries per j and the tiles' group boxes come first.)
-  constexpr int EPJ = BOX == kBoxTricSorted && sizeof(T) == 4 ? 2 : 1;
-  constexpr bool SORTED = BOX == kBoxTricSorted && sizeof(T) == 8;
-  const size_t tiles_bytes =
-      SORTED ? 2 * static_cast<size_t>(a.tj) * EPJ * sizeof(V) + kSortedBoxBytes : 0;
-  uint32_t *hist = reinterpret_cast<uint32_t *>(smem + tiles_bytes + kSlot0);
+  // binary32 bin -1 (t < 1/4), added to bin 0 on flush
+  uint32_t *hist = reinterpret_cast<uint32_t *>(smem + kSlot0);
   const int tid = threadIdx.x;
   // image-search queues after the histogram, 32-byte aligned
   const size_t q_off = (kSlot0 + static_cast<size_t>(a.stride) * 4 + 31) / 32 * 32;
@@ -1492,18 +1095,8 @@ __global__ __launch_bounds__(max_threads<BOX>(), (min_waves<T, R, BOX>())) void 
     // the histogram is clear, the unit counter set
     __syncthreads();
     const FrameParams *F = a.frames + w.frame;
-    if constexpr (SORTED) {
-      if (w.flags & kItemDiag) {
-        run_tiles<T, R, BOX, MODE, true, true>(a, w, F, tile, hist, queue, shifts);
-      } else {
-        bool clamp = true;
-        if constexpr (MODE == kModeLds) clamp = !((w.flags & kItemFull) && uni(F->noclamp));
-        if (clamp)
-          run_tiles<T, R, BOX, MODE, false, true>(a, w, F, tile, hist, queue, shifts);
-        else if constexpr (MODE == kModeLds)
-          run_tiles<T, R, BOX, kModeLds, false, false>(a, w, F, tile, hist, queue, shifts);
-      }
-      if (tid == 0) s_item = static_cast<int>(gridDim.x) + atomicAdd(a.counter, 1);
+    if constexpr (BOX == kBoxTricSorted && sizeof(T) == 8) {
+      run_sorted64<MODE>(a, w, F, &s_unit, &s_item);
     } else if constexpr (BOX == kBoxTricSorted) {
       run_sorted<MODE>(a, w, F, &s_unit, &s_item);
     } else {

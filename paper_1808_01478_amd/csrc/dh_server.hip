@@ -247,7 +247,7 @@ uint64_t item_pairs(const WorkItem &w) {
 
 // Splits the last `grid` items of a launch into pieces of about a quarter of
 // their j-range (in multiples of `step`), so workgroups finish close together.
-void refine_tail(std::vector<WorkItem> &items, int grid, int step, bool split_diag) {
+void refine_tail(std::vector<WorkItem> &items, int grid, int step) {
   const size_t n = items.size();
   const size_t tail = static_cast<size_t>(std::max(grid, 0));
   if (tail == 0 || n < 4 * tail) return;
@@ -256,7 +256,7 @@ void refine_tail(std::vector<WorkItem> &items, int grid, int step, bool split_di
   for (const WorkItem &w : last) {
     const int32_t len = w.j1 - w.j0;
     const int32_t piece = std::max<int32_t>(step, (len / 4 + step - 1) / step * step);
-    if ((!split_diag && (w.flags & dh::kItemDiag)) || len <= piece) {
+    if (len <= piece) {
       items.push_back(w);
       continue;
     }
@@ -279,9 +279,9 @@ int start_job(dh_server *s, int slot_idx) {
   const size_t pts = static_cast<size_t>(std::max<int64_t>(1, j.n));
   const size_t in_b = pts * 3 * sizeof(double);
   FrameParams fp;
-  j.kind = dh::staged_kind(
-      dh::frame_constants(j.box_type, j.has_box ? j.box : nullptr, j.r_max, j.n_bins, fp),
-      j.precision, fp.L, j.n);
+  const int geometric =
+      dh::frame_constants(j.box_type, j.has_box ? j.box : nullptr, j.r_max, j.n_bins, fp);
+  j.kind = dh::staged_kind(geometric, j.precision, fp.L, fp.s, j.n_bins, j.n);
   fp.box = j.kind;
   fp.n_pad = static_cast<int32_t>(dh::padded_start(j.offsets.data(), k));
   const size_t staged_b = pts * dh::staged_point_bytes(j.precision, j.kind);
@@ -313,6 +313,7 @@ int start_job(dh_server *s, int slot_idx) {
   j.plan = dh::serve_launch(s->n_cu, s->lds_per_block, j.precision, fp, total, threads);
   fp.coords = sl.d_staged;
   fp.out = sl.d_out;
+  fp.in = sl.d_in;
   fp.win = j.plan.win;
   fp.n_sweeps = j.plan.n_sweeps;
   fp.noclamp = j.plan.noclamp ? 1 : 0;
@@ -331,7 +332,7 @@ int start_job(dh_server *s, int slot_idx) {
   j.items.clear();
   for (int32_t h = 0; h < j.n_hist; ++h) {
     const dh::HistRows r = dh::hist_rows(j.offsets.data(), k, h,
-                                         dh::padded_frame(j.precision, j.kind));
+                                         dh::padded_frame(j.kind));
     const int64_t nr = dh::hist_row_count(r, bi);
     for (int32_t sw = 0; sw < j.plan.n_sweeps; ++sw)
       for (int64_t row = 0; row < nr; ++row) {
@@ -478,8 +479,7 @@ bool issue_launch(dh_server *s) {
     if (j.next_item == j.items.size()) finished.push_back(q);
   }
   grid = std::max(1, std::min<int>(grid, static_cast<int>(list.size())));
-  refine_tail(list, grid, dh::tail_step(top.precision, top.kind, top.plan.cfg.tj),
-              top.kind != dh::kBoxTricSorted || dh::padded_frame(top.precision, top.kind));
+  refine_tail(list, grid, dh::tail_step(top.kind));
   Region &R = s->regions[reg];
   std::memcpy(R.h_items, list.data(), list.size() * sizeof(WorkItem));
   int32_t *h_counter = reinterpret_cast<int32_t *>(R.h_items + kMaxItemsPerLaunch);

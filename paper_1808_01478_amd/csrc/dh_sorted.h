@@ -31,6 +31,12 @@ static_assert(kUnitPoints == 64 * kUnitSlices, "i-span of a unit");
 __device__ __forceinline__ float lane_value(float v, int lane) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane(static_cast<int>(b & 0xffffffffll), lane);
+  const int hi = __builtin_amdgcn_readlane(static_cast<int>(b >> 32), lane);
+  return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned int>(lo));
+}
 
 template <int N>
 using Int = std::integral_constant<int, N>;
@@ -41,9 +47,13 @@ struct GroupPair {
   int kind;        // kFast, kFix + axis, kSlow, or kSkip
   bool diag;       // the same group: pairs j > i only
   bool in_window;  // every t below the LDS stride (no clamp needed)
-  float sx, sy, sz;  // lattice shift B n of the lower-end wraps
+  float sx, sy, sz;  // binary32: lattice shift B n of the lower-end wraps
+  int n[3];          // binary64: the shared wraps
 };
 constexpr int kSkip = 0, kFast = 1, kFix = 2, kSlow = 5;  // kFix + axis: 2, 3, 4
+// binary64 only: groups whose coordinates are too large for the bounds (or
+// not finite)
+constexpr int kExact = 6;
 
 // Along an axis the fixed-point differences of the pairs lie in
 // [jlo - ihi, jhi - ilo], and the wrap of u_j - u_i, floor((u_j - u_i + 2^31)
@@ -55,6 +65,13 @@ constexpr int kSkip = 0, kFast = 1, kFix = 2, kSlow = 5;  // kFix + axis: 2, 3, 
 // along K exceeds 1/2. Otherwise `slow`: the fixed-point words wrap per pair.
 // The distance bounds take the Cartesian boxes under every wrap the pairs can
 // have (a box spanning more than two wraps gives no bound).
+//
+// binary64 (F64): the intervals are widened by kWrapMargin, far more than the
+// rounding of any fractional coordinate; `fix` and `slow` pairs round their
+// one ambiguous axis, or all three, whatever its span, so the shift leaves
+// out the ambiguous axes.
+constexpr int64_t kWrapMargin = 1024;  // 2^-22 of a cell vector
+template <bool F64>
 __device__ __forceinline__ GroupPair classify(const GroupBox &I, const GroupBox &J,
                                               const float (&cell)[6], float r_lo, float r_hi,
                                               float r_in) {
@@ -64,15 +81,22 @@ __device__ __forceinline__ GroupPair classify(const GroupBox &I, const GroupBox 
   bool wide = false;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    nl[k] = static_cast<int>(J.ulo[k] - I.uhi[k] >= 0x80000000u) -
-            static_cast<int>(J.ulo[k] < I.uhi[k]);
-    nh[k] = static_cast<int>(J.uhi[k] - I.ulo[k] >= 0x80000000u) -
-            static_cast<int>(J.uhi[k] < I.ulo[k]);
+    if constexpr (F64) {
+      const int64_t lo = static_cast<int64_t>(J.ulo[k]) - static_cast<int64_t>(I.uhi[k]);
+      const int64_t hi = static_cast<int64_t>(J.uhi[k]) - static_cast<int64_t>(I.ulo[k]);
+      nl[k] = static_cast<int>((lo - kWrapMargin + 0x80000000ll) >> 32);
+      nh[k] = static_cast<int>((hi + kWrapMargin + 0x80000000ll) >> 32);
+    } else {
+      nl[k] = static_cast<int>(J.ulo[k] - I.uhi[k] >= 0x80000000u) -
+              static_cast<int>(J.ulo[k] < I.uhi[k]);
+      nh[k] = static_cast<int>(J.uhi[k] - I.ulo[k] >= 0x80000000u) -
+              static_cast<int>(J.uhi[k] < I.ulo[k]);
+    }
     amb |= nl[k] != nh[k] ? 1u << k : 0u;
     wide = wide || nh[k] - nl[k] > 1;
   }
   p.kind = amb == 0u ? kFast
-                     : ((amb & (amb - 1u)) == 0u && !wide ? kFix + (amb == 1u ? 0 : amb == 2u ? 1 : 2)
+                     : ((amb & (amb - 1u)) == 0u && (F64 || !wide) ? kFix + (amb == 1u ? 0 : amb == 2u ? 1 : 2)
                                                           : kSlow);
   auto shift = [&](int na, int nb, int nc, float &x, float &y, float &z) {
     const float fa = static_cast<float>(na), fb = static_cast<float>(nb),
@@ -104,7 +128,12 @@ __device__ __forceinline__ GroupPair classify(const GroupBox &I, const GroupBox 
   if (out && !wide) p.kind = kSkip;
   p.in_window = !wide && hi2 < r_in * r_in;
   p.diag = false;
-  shift(nl[0], nl[1], nl[2], p.sx, p.sy, p.sz);
+  if constexpr (F64) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) p.n[k] = nl[k] == nh[k] ? nl[k] : 0;
+  } else {
+    shift(nl[0], nl[1], nl[2], p.sx, p.sy, p.sz);
+  }
   return p;
 }
 
@@ -320,7 +349,7 @@ __device__ __forceinline__ void run_sorted(const PairKernelArgs &a, const WorkIt
       const int gi = (ib >> 6) + r, gj = (jb >> 6) + gr;
       const bool valid = ib + 64 * r < w.i1 && gr < gpu && jb + 64 * gr < w.j1 &&
                          !((w.flags & kItemDiag) && gj < gi);
-      gp = classify(boxes[valid ? gi : ib >> 6], boxes[valid ? gj : jb >> 6], cell, wb.lo, wb.hi,
+      gp = classify<false>(boxes[valid ? gi : ib >> 6], boxes[valid ? gj : jb >> 6], cell, wb.lo, wb.hi,
                     wb.in);
       gp.diag = (w.flags & kItemDiag) && gj == gi;
       gp.in_window = (gp.in_window || noclamp) && ib + 64 * r + 64 <= w.i1;
@@ -355,6 +384,329 @@ __device__ __forceinline__ void run_sorted(const PairKernelArgs &a, const WorkIt
           case kFix: pass(Int<kFix>{}, Int<1>{}, Yes{}, Yes{}, r, g); break;
           case kFix + 1: pass(Int<kFix + 1>{}, Int<1>{}, Yes{}, Yes{}, r, g); break;
           case kFix + 2: pass(Int<kFix + 2>{}, Int<1>{}, Yes{}, Yes{}, r, g); break;
+          default: pass(Int<kSlow>{}, Int<1>{}, Yes{}, Yes{}, r, g); break;
+        }
+      }
+    }
+    int nu = 0;
+    if (lane == 0) nu = atomicAdd(s_unit, 1);
+    u = uni(nu);
+    if (u == n_unit && lane == 0)
+      *s_item = static_cast<int>(gridDim.x) + atomicAdd(a.counter, 1);
+  }
+}
+
+// Counts pairs of a sorted binary64 frame by the canonical sequence on their
+// input points: the first m slices in rs (four bits each) of the unit at ib
+// against the j of [j0, j1) in `left` (bit b: j0 + 2b and the next). Not
+// inlined: it runs for one group of pairs in some 10^5.
+template <int MODE>
+__device__ __attribute__((noinline)) void exact_pairs(const FrameParams *F, int hist, int sweep,
+                                                      int ib, int i1, int j0, int j1,
+                                                      uint32_t rs, int m, uint32_t left,
+                                                      bool diag) {
+  const int lane = threadIdx.x & 63;
+  const int64_t n_pad = F->n_pad;
+  const uint32_t *const index =
+      reinterpret_cast<const uint32_t *>(static_cast<const char *>(F->coords) + 24 * n_pad);
+  const double *const in = F->in;
+  const Geo64 g = load_geo64(F);
+  WorkItem w;
+  w.hist = hist;
+  w.sweep = sweep;
+  const Count32<MODE> count(F, w, lane);
+  for (; left != 0u; left &= left - 1u)
+    for (int h = 0; h < 2; ++h) {
+      const int j = j0 + 2 * __builtin_ctz(left) + h;
+      if (j >= j1) continue;
+      const int64_t q = 3 * static_cast<int64_t>(index[j]);
+      const double xj = in[q], yj = in[q + 1], zj = in[q + 2];
+      for (int k = 0; k < m; ++k) {
+        const int i = ib + 64 * static_cast<int>((rs >> (4 * k)) & 15u) + lane;
+        const bool ok = i < i1 && (!diag || j > i);
+        const int64_t p = 3 * static_cast<int64_t>(index[ok ? i : ib]);
+        const double t = t64<kBoxTric>(in[p], in[p + 1], in[p + 2], xj, yj, zj, g);
+        // (a NaN t takes the other operand: out of range)
+        const uint32_t b = kBinBits + static_cast<uint32_t>(min_arith(t, 0x1p21));
+        count.template add<true>(ok ? b : kBinBits + (1u << 21));
+      }
+    }
+}
+
+// One work item of a spatially sorted binary64 frame. binary64 counts follow
+// the canonical sequence bit for bit, but a pair's bin needs that sequence
+// only when its distance lies next to a bin edge. The pairs here work on
+// positions of the wrapped points relative to the cell centre, scaled to
+// units in which a bin is 2^-22 wide, so with one shared shift per pair of
+// groups a pair takes three differences and q, in binary64. The root is a
+// binary32 guess, made exact by a binary64 comparison: with u = q in units of
+// a bin and m the integer nearest to the binary32 root of u (within 2/3 of the
+// root for t < 2^20, larger t being out of range), floor(sqrt(u)) is m when
+// u - m^2 >= 0 and m - 1 otherwise, and the sign of that one fused residual is
+// certain unless |u - m^2| is within `thr`, the bound of every rounding
+// between the inputs and u and between the inputs and the canonical t. The
+// smallest |residual| of eight pairs goes through one ballot; when it is not
+// above thr the wave takes the canonical sequence on the input points for all
+// of them (about one group of eight in 10^5 on the 1M-point frame).
+//
+// Bound by vector-unit issue: 15 instructions per pair on the short path (17
+// with the clamp) against 22 over the frame with a binary64 root per pair
+// (v_rsq_f64 alone holds a SIMD for 16 cycles, v_sqrt_f32 for 8). The
+// 1,000,000-point clustered triclinic frame (20,000 bins) took 371 ms with
+// every pair computed and that root, and takes 178 ms; 100,000 points in a
+// cube (cut-off half the edge, so little is skipped) 4.34 and 3.49 ms.
+template <int MODE>
+__device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const WorkItem &w,
+                                             const FrameParams *F, int *s_unit, int *s_item) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
+  const char *const staged = uni(static_cast<const char *>(F->coords));
+  const int64_t n_pad = uni(static_cast<int>(F->n_pad));
+  const double *const P = reinterpret_cast<const double *>(staged);
+  const GroupBox *const boxes = reinterpret_cast<const GroupBox *>(staged + 28 * n_pad);
+  float cell[6];
+#pragma unroll
+  for (int k = 0; k < 6; ++k) cell[k] = uni(F->cell32[k]);
+  // cell rows in scaled units, entries of B^-1 per scaled unit
+  const double s = uni(F->s) * 0x1p-22, is = 1.0 / s;
+  const double ax = uni(F->ax) * s, bx = uni(F->bx) * s, by = uni(F->by) * s;
+  const double cx = uni(F->cx) * s, cy = uni(F->cy) * s, cz = uni(F->cz) * s;
+  const double h11 = uni(F->h11) * is, h12 = uni(F->h12) * is, h13 = uni(F->h13) * is;
+  const double h22 = uni(F->h22) * is, h23 = uni(F->h23) * is, h33 = uni(F->h33) * is;
+  const int win = uni(F->win);
+  const WindowBounds wb = window_bounds(F, w.sweep * win, win, a.stride);
+  const bool noclamp = MODE == kModeLds && uni(F->noclamp) != 0;
+  const Count32<MODE> count(F, w, lane);
+  using Yes = std::true_type;
+  using No = std::false_type;
+
+  int ib = 0, jb = 0;
+  GroupPair gp;
+  double shx = 0.0, shy = 0.0, shz = 0.0;  // the lane's shift B n
+  float near_hi = 0.f;  // thr's upper word, as a float (see below)
+
+  auto frac = [&](auto axis_c, double x, double y, double z) {
+    constexpr int K = decltype(axis_c)::value;
+    if constexpr (K == 0)
+      return fma(z, h13, fma(y, h12, x * h11));
+    else if constexpr (K == 1)
+      return fma(z, h23, y * h22);
+    else
+      return z * h33;
+  };
+  // One group against M slices (four bits each in rs) of one kind.
+  auto pass = [&](auto kind_c, auto m_c, auto clamp_c, auto diag_c, uint32_t rs, int g) {
+    constexpr int KIND = decltype(kind_c)::value, M = decltype(m_c)::value;
+    constexpr bool DIAG = decltype(diag_c)::value;
+    const int j0 = jb + 64 * g, j1 = min(j0 + 64, w.j1);
+    auto slice = [&](int k) { return ib + 64 * static_cast<int>((rs >> (4 * k)) & 15u) + lane; };
+    // j pairs (bit b: j0 + 2b and the next) left to the canonical sequence
+    uint32_t left = 0;
+    if constexpr (KIND == kExact) {
+      left = ~0u;
+    } else {
+      // (a lane past the end of the item holds a point at infinity: q = +inf,
+      // beyond every bin)
+      double sx[M], sy[M], sz[M];
+      [[maybe_unused]] double fi[3][M];
+      constexpr int K = KIND >= kFix && KIND < kSlow ? KIND - kFix : 0;
+#pragma unroll
+      for (int k = 0; k < M; ++k) {
+        const int i = slice(k);
+        const bool ok = i < w.i1;
+        const double *const p = P + 3 * static_cast<int64_t>(ok ? i : ib);
+        const int src = g * kUnitSlices + static_cast<int>((rs >> (4 * k)) & 15u);
+        sx[k] = p[0] + lane_value(shx, src);
+        sy[k] = p[1] + lane_value(shy, src);
+        sz[k] = p[2] + lane_value(shz, src);
+        if constexpr (KIND == kSlow) {
+          fi[0][k] = frac(Int<0>{}, sx[k], sy[k], sz[k]);
+          fi[1][k] = frac(Int<1>{}, sx[k], sy[k], sz[k]);
+          fi[2][k] = frac(Int<2>{}, sx[k], sy[k], sz[k]);
+        } else if constexpr (KIND >= kFix) {
+          fi[0][k] = frac(Int<K>{}, sx[k], sy[k], sz[k]);
+        }
+        sx[k] = ok ? sx[k] : __builtin_inf();
+      }
+      struct J {
+        double x, y, z;
+      };
+      const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<double *>(P + 3 * static_cast<int64_t>(j0)), 0, (j1 - j0) * 24,
+          kBufferFlags);
+      int at = 0;
+      auto load = [&](int k) {
+        union {
+          struct {
+            V4u a;
+            V2u b;
+          } w;
+          J j;
+        } e;
+        e.w.a = __builtin_amdgcn_raw_buffer_load_b128(rsrc, 24 * k, at, 0);
+        e.w.b = __builtin_amdgcn_raw_buffer_load_b64(rsrc, 24 * k + 16, at, 0);
+        return e.j;
+      };
+      // bin bits and the smallest |residual| of the pairs of one j
+      auto bits_of = [&](const J &p, uint32_t *b, float &gap) {
+        [[maybe_unused]] double fj[3];
+        if constexpr (KIND == kSlow) {
+          fj[0] = frac(Int<0>{}, p.x, p.y, p.z);
+          fj[1] = frac(Int<1>{}, p.x, p.y, p.z);
+          fj[2] = frac(Int<2>{}, p.x, p.y, p.z);
+        } else if constexpr (KIND >= kFix) {
+          fj[0] = frac(Int<K>{}, p.x, p.y, p.z);
+        }
+#pragma unroll
+        for (int k = 0; k < M; ++k) {
+          double dx = p.x - sx[k], dy = p.y - sy[k], dz = p.z - sz[k];
+          if constexpr (KIND == kSlow) {
+            const double na = rint(fj[0] - fi[0][k]), nb = rint(fj[1] - fi[1][k]),
+                         nc = rint(fj[2] - fi[2][k]);
+            dz = fma(-cz, nc, dz);
+            dy = fma(-cy, nc, fma(-by, nb, dy));
+            dx = fma(-cx, nc, fma(-bx, nb, fma(-ax, na, dx)));
+          } else if constexpr (KIND >= kFix) {
+            const double n = rint(fj[0] - fi[0][k]);
+            if constexpr (K == 2) dz = fma(-cz, n, dz);
+            if constexpr (K >= 1) dy = fma(K == 1 ? -by : -cy, n, dy);
+            dx = fma(K == 0 ? -ax : K == 1 ? -bx : -cx, n, dx);
+          }
+          const double u = fma(dz, dz, fma(dy, dy, dx * dx));
+          const float f = __builtin_amdgcn_sqrtf(static_cast<float>(u)) + 2.f;
+          const double m = static_cast<double>(f - 2.f);
+          const double r = fma(-m, m, u);
+          const int rh = static_cast<int>(__double_as_longlong(r) >> 32);
+          gap = fminf(gap, fabsf(__int_as_float(rh)));
+          b[k] = __float_as_uint(f) + static_cast<uint32_t>(rh >> 31);
+        }
+      };
+      auto tally = [&](const uint32_t *b, int j) {
+#pragma unroll
+        for (int k = 0; k < M; ++k)
+          count.template add<decltype(clamp_c)::value>(
+              DIAG && j <= slice(k) ? kBinBits + (1u << 21) : b[k]);
+      };
+      J pa = load(0), pb = load(1);
+      int j = j0;
+      for (; j + 1 < j1; j += 2) {
+        at += 48;
+        uint32_t b[2 * M];
+        float gap = __builtin_inff();
+        bits_of(pa, b, gap);
+        pa = load(0);
+        bits_of(pb, b + M, gap);
+        pb = load(1);
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(gap <= near_hi) != 0, 0)) {
+          left |= 1u << ((j - j0) >> 1);
+          continue;
+        }
+        tally(b, j);
+        tally(b + M, j + 1);
+      }
+      if (j < j1) {
+        uint32_t b[M];
+        float gap = __builtin_inff();
+        bits_of(pa, b, gap);
+        if (__builtin_amdgcn_ballot_w64(gap <= near_hi) != 0)
+          left |= 1u << ((j - j0) >> 1);
+        else
+          tally(b, j);
+      }
+    }
+    if (__builtin_expect(left != 0u, 0))
+      exact_pairs<MODE>(F, w.hist, w.sweep, ib, w.i1, j0, j1, rs, M, left, DIAG);
+  };
+  // the slices in `m` (bit r) against group g, in passes of as many as fit
+  auto passes = [&](auto kind_c, auto clamp_c, uint32_t m, int g) {
+    auto take = [&](int n) {
+      uint32_t rs = 0;
+      for (int k = 0; k < n; ++k) {
+        rs |= static_cast<uint32_t>(__builtin_ctz(m)) << (4 * k);
+        m &= m - 1u;
+      }
+      return rs;
+    };
+    while (__builtin_popcount(m) >= 4) pass(kind_c, Int<4>{}, clamp_c, No{}, take(4), g);
+    if (__builtin_popcount(m) >= 2) pass(kind_c, Int<2>{}, clamp_c, No{}, take(2), g);
+    if (m != 0u) pass(kind_c, Int<1>{}, clamp_c, No{}, take(1), g);
+  };
+
+  const int n_ib = (w.i1 - w.i0 + kUnitPoints - 1) / kUnitPoints;
+  const int n_wave = static_cast<int>(blockDim.x) / 64;
+  int gpu = kUnitGroups;
+  while (gpu > 1 && n_ib * ((w.j1 - w.j0 + 64 * gpu - 1) / (64 * gpu)) < 4 * n_wave) gpu >>= 1;
+  const int n_unit = n_ib * ((w.j1 - w.j0 + 64 * gpu - 1) / (64 * gpu));
+  if (wave == n_unit && lane == 0)
+    *s_item = static_cast<int>(gridDim.x) + atomicAdd(a.counter, 1);
+  for (int u = wave; u < n_unit;) {
+    ib = w.i0 + (u % n_ib) * kUnitPoints;
+    jb = w.j0 + (u / n_ib) * 64 * gpu;
+    {
+      const int r = lane % kUnitSlices, gr = lane / kUnitSlices;
+      const int gi = (ib >> 6) + r, gj = (jb >> 6) + gr;
+      const bool valid = ib + 64 * r < w.i1 && gr < gpu && jb + 64 * gr < w.j1 &&
+                         !((w.flags & kItemDiag) && gj < gi);
+      const GroupBox &bi = boxes[valid ? gi : ib >> 6], &bj = boxes[valid ? gj : jb >> 6];
+      gp = classify<true>(bi, bj, cell, wb.lo, wb.hi, wb.in);
+      shx = (gp.n[0] * ax + gp.n[1] * bx) + gp.n[2] * cx;
+      shy = gp.n[1] * by + gp.n[2] * cy;
+      shz = gp.n[2] * cz;
+      // Rounding between the inputs and a coordinate difference, here and in
+      // the canonical sequence: each of the dozen steps rounds something no
+      // larger than the two points' |x| + |y| + |z| plus the cell, so 2^-48 of
+      // that covers them; in t: times s. A residual is then off by at most
+      // 2 t dt + 2^-48 t^2, t <= n_bins + 2 (beyond that the pair is out of
+      // range either way).
+      const double size = static_cast<double>(fabsf(cell[0]) + fabsf(cell[1]) + fabsf(cell[2]) +
+                                              fabsf(cell[3]) + fabsf(cell[4]) + fabsf(cell[5]));
+      const double mag = static_cast<double>(bi.mag) + static_cast<double>(bj.mag) + size;
+      const double dt = 0x1p-48 * mag * s, top = static_cast<double>(count.n_bins + 2u) * 0x1p-22;
+      const double hm = fmax(fmax(fabs(h11), fabs(h12)), fmax(fmax(fabs(h13), fabs(h22)),
+                                                              fmax(fabs(h23), fabs(h33)))) * s;
+      // (of this form so that a group that is not finite is exact)
+      const bool bounded = dt < 0x1p-25 && hm * mag < 0x1p20;
+      if (!bounded) {
+        gp.kind = kExact;
+        gp.in_window = false;
+      }
+      gp.diag = (w.flags & kItemDiag) && gj == gi;
+      gp.in_window = (gp.in_window || (noclamp && bounded)) && ib + 64 * r + 64 <= w.i1;
+      if (!valid) gp.kind = kSkip;
+      // the unit's largest threshold, as the upper word of a binary64 number
+      // read as a float (monotone for non-negative numbers), rounded up
+      double thr = gp.kind == kSkip || gp.kind == kExact ? 0.0 : 2.0 * top * dt + 0x1p-48 * top * top;
+      for (int o = 32; o > 0; o >>= 1) thr = fmax(thr, __shfl_xor(thr, o));
+      near_hi = uni(__int_as_float(static_cast<int>(__double_as_longlong(thr) >> 32) + 1));
+    }
+    const uint64_t m_fast = __builtin_amdgcn_ballot_w64(gp.kind == kFast && !gp.diag);
+    const uint64_t m_in = __builtin_amdgcn_ballot_w64(gp.in_window);
+    const uint64_t m_fix0 = __builtin_amdgcn_ballot_w64(gp.kind == kFix && !gp.diag);
+    const uint64_t m_fix1 = __builtin_amdgcn_ballot_w64(gp.kind == kFix + 1 && !gp.diag);
+    const uint64_t m_fix2 = __builtin_amdgcn_ballot_w64(gp.kind == kFix + 2 && !gp.diag);
+    const uint64_t m_slow = __builtin_amdgcn_ballot_w64(gp.kind == kSlow && !gp.diag);
+    const uint64_t m_exact = __builtin_amdgcn_ballot_w64(gp.kind == kExact && !gp.diag);
+    const uint64_t m_diag = __builtin_amdgcn_ballot_w64(gp.kind != kSkip && gp.diag);
+    for (int g = 0; g < gpu; ++g) {
+      auto bits = [&](uint64_t m) {
+        return static_cast<uint32_t>(m >> (g * kUnitSlices)) & ((1u << kUnitSlices) - 1u);
+      };
+      const uint32_t fast = bits(m_fast);
+      if (MODE == kModeLds && (fast & ~bits(m_in)) == 0u)
+        passes(Int<kFast>{}, No{}, fast, g);
+      else
+        passes(Int<kFast>{}, Yes{}, fast, g);
+      passes(Int<kFix>{}, Yes{}, bits(m_fix0), g);
+      passes(Int<kFix + 1>{}, Yes{}, bits(m_fix1), g);
+      passes(Int<kFix + 2>{}, Yes{}, bits(m_fix2), g);
+      passes(Int<kSlow>{}, Yes{}, bits(m_slow), g);
+      for (uint32_t m = bits(m_exact); m != 0u; m &= m - 1u)
+        pass(Int<kExact>{}, Int<1>{}, Yes{}, No{}, static_cast<uint32_t>(__builtin_ctz(m)), g);
+      if (const uint32_t m = bits(m_diag)) {
+        // at most one slice of the unit is the group itself
+        const uint32_t r = static_cast<uint32_t>(__builtin_ctz(m));
+        switch (__builtin_amdgcn_readlane(gp.kind, g * kUnitSlices + static_cast<int>(r))) {
+          case kFast: pass(Int<kFast>{}, Int<1>{}, Yes{}, Yes{}, r, g); break;
+          case kExact: pass(Int<kExact>{}, Int<1>{}, Yes{}, Yes{}, r, g); break;
           default: pass(Int<kSlow>{}, Int<1>{}, Yes{}, Yes{}, r, g); break;
         }
       }
