@@ -327,7 +327,8 @@ int frame_consts(int32_t box_type, const double *box, double r_max, int32_t n_bi
     }
     fp.qskip64 = 0.25 * lambda2 * (1.0 - 1e-6);
     fp.qskip32 = static_cast<float>(0.25 * lambda2 * fp.s * fp.s * (1.0 - 4e-6));
-    octant_images(fp);
+    // (about 4 us of host time, so only where the search runs)
+    if (kind == kBoxTricSearch) octant_images(fp);
   }
   fp.box = kind;
   return kind;
@@ -741,8 +742,9 @@ struct FrameJob {
 };
 
 // Stages a frame's coordinates into the context's scratch (spatially sorted
-// frames: the sort keys in the context's key buffer).
-int stage_job(dh_ctx *ctx, hipStream_t st, const FrameJob &job, const FrameParams &fp) {
+// frames: the sort keys in the context's key buffer) and clears the output.
+int stage_job(dh_ctx *ctx, hipStream_t st, const FrameJob &job, const FrameParams &fp,
+              const ZeroArgs &z) {
   const int64_t n = job.offsets[job.n_species];
   if (job.kind == kBoxTricSorted) {
     int rc = ensure_device(ctx, &ctx->d_keys, &ctx->keys_cap,
@@ -750,9 +752,10 @@ int stage_job(dh_ctx *ctx, hipStream_t st, const FrameJob &job, const FrameParam
     if (rc) return rc;
     DH_HIP(ctx, launch_stage_sorted(job.precision, job.d_coords, ctx->d_staged, n, job.offsets, job.n_species,
                                     fp, static_cast<uint64_t *>(ctx->d_keys), st));
+    DH_HIP(ctx, launch_zero(z, st));
     return DH_OK;
   }
-  DH_HIP(ctx, launch_stage(job.precision, job.kind, job.d_coords, ctx->d_staged, n, fp, st));
+  DH_HIP(ctx, launch_stage(job.precision, job.kind, job.d_coords, ctx->d_staged, n, fp, z, st));
   return DH_OK;
 }
 
@@ -844,15 +847,22 @@ int run_frame(dh_ctx *ctx, hipStream_t st, const FrameJob &job, const Knobs &k, 
   int rc = upload_blob(ctx, st, lay, frames, items, pairs, !job.accumulate);
   if (rc) return rc;
   char *db = static_cast<char *>(ctx->d_blob);
-  if (stage) {
-    const int rc_stage = stage_job(ctx, st, job, fp);
-    if (rc_stage) return rc_stage;
+  ZeroArgs z;
+  if (!job.accumulate) {
+    z.out = job.d_out;
+    z.n_words = static_cast<int64_t>(n_hist) * fp.n_bins;
+    z.counters = reinterpret_cast<int32_t *>(db + lay.counter);
+    z.n_counters = static_cast<int32_t>(n_counters);
+    z.n_hist = n_hist;
+    z.oor = fp.oor;
+    z.pairs = reinterpret_cast<const uint64_t *>(db + lay.pairs);
   }
-  if (!job.accumulate)
-    DH_HIP(ctx, launch_zero(job.d_out, static_cast<int64_t>(n_hist) * fp.n_bins,
-                            reinterpret_cast<int32_t *>(db + lay.counter),
-                            static_cast<int32_t>(n_counters), fp.oor,
-                            reinterpret_cast<const uint64_t *>(db + lay.pairs), n_hist, st));
+  if (stage) {
+    const int rc_stage = stage_job(ctx, st, job, fp, z);
+    if (rc_stage) return rc_stage;
+  } else {
+    DH_HIP(ctx, launch_zero(z, st));
+  }
   const int grid = std::max(1, std::min<int>(L.grid, static_cast<int>(items.size())));
   if (ctx->hold) {
     ctx->held.clear();
@@ -993,7 +1003,7 @@ int tune_frame(dh_ctx *ctx, hipStream_t st, const FrameJob &job, const std::stri
   fp.coords = ctx->d_staged;
   (void)n;
   {
-    const int rc_stage = stage_job(ctx, st, job, fp);
+    const int rc_stage = stage_job(ctx, st, job, fp, ZeroArgs{});
     if (rc_stage) return rc_stage;
   }
   hipEvent_t e0, e1;
@@ -1138,8 +1148,10 @@ int frame_constants(int32_t box_type, const double *box, double r_max, int32_t n
 }
 
 int zero_u64(uint64_t *p, int64_t n, hipStream_t st) {
-  return launch_zero(p, n, nullptr, 0, nullptr, nullptr, 0, st) == hipSuccess ? DH_OK
-                                                                           : DH_EDEVICE;
+  ZeroArgs z;
+  z.out = p;
+  z.n_words = n;
+  return launch_zero(z, st) == hipSuccess ? DH_OK : DH_EDEVICE;
 }
 
 size_t ctx_device_bytes(const dh_ctx *ctx) {
@@ -1248,6 +1260,7 @@ int dh_search_images(const double *box, int32_t *lists, int32_t *counts, int32_t
     for (int k = 0; k < kShifts - 1; ++k)
       lists[o * (kShifts - 1) + k] = k < len[o] ? list[o][k] : kZeroShift;
   }
+  octant_images(fp);
   *full_mask = fp.oct_full;
   return DH_OK;
 }
@@ -1478,7 +1491,7 @@ int dh_pair_t_async(dh_ctx *ctx, dh_stream stream, const double *d_coords, int64
   const BlobLayout lay = blob_layout(1, 0, 0);
   rc = upload_blob(ctx, st, lay, std::vector<FrameParams>(1, fp), {}, {});
   if (rc) return rc;
-  DH_HIP(ctx, launch_stage(precision, kind, d_coords, ctx->d_staged, n, fp, st));
+  DH_HIP(ctx, launch_stage(precision, kind, d_coords, ctx->d_staged, n, fp, ZeroArgs{}, st));
   DH_HIP(ctx, launch_pair_t(precision, kind, static_cast<const FrameParams *>(ctx->d_blob), d_pi,
                             d_pj, n_pairs, static_cast<int32_t>(n), d_t, st));
   return DH_OK;

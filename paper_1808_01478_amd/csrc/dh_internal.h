@@ -373,12 +373,22 @@ template <> PairFn pick_pairs<double, kModeGlobal>(int r, int box);
 hipError_t launch_stage_sorted(int precision, const double *in, void *out, int64_t n,
                                const int64_t *offsets, int32_t n_species, const FrameParams &fp,
                                uint64_t *keys, hipStream_t st);
+// Clearing of a call's output: out[n_words] and counters[n_counters] become 0
+// and, with oor, oor[h] = pairs[h] for h < n_hist (the flushes then subtract
+// the in-range counts).
+struct ZeroArgs {
+  uint64_t *out = nullptr;
+  int64_t n_words = 0;
+  int32_t *counters = nullptr;
+  int32_t n_counters = 0;
+  int32_t n_hist = 0;
+  uint64_t *oor = nullptr;
+  const uint64_t *pairs = nullptr;
+};
+// staging of an unsorted frame and the clearing in one launch
 hipError_t launch_stage(int precision, int box_kind, const double *in, void *out, int64_t n,
-                        const FrameParams &fp, hipStream_t st);
-// zeroes out[n_words] and counters[n_counters]; with oor, sets oor[h] =
-// pairs[h] for h < n_hist (the flushes then subtract the in-range counts)
-hipError_t launch_zero(uint64_t *out, int64_t n_words, int32_t *counters, int32_t n_counters,
-                       uint64_t *oor, const uint64_t *pairs, int32_t n_hist, hipStream_t st);
+                        const FrameParams &fp, const ZeroArgs &z, hipStream_t st);
+hipError_t launch_zero(const ZeroArgs &z, hipStream_t st);
 hipError_t launch_pairs(int precision, int box_kind, int mode, const KernelConfig &cfg,
                         const PairKernelArgs &args, int grid, size_t lds_bytes, hipStream_t st);
 hipError_t launch_oor(const uint64_t *hist, int32_t n_hist, int32_t n_bins, const uint64_t *pairs,

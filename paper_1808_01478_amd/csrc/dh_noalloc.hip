@@ -232,15 +232,20 @@ extern "C" int dh_histo_noalloc(dh_stream stream, const double *d_coords,
   pa.items = reinterpret_cast<WorkItem *>(base + off_items);
   noalloc_plan_kernel<<<1, kPlanThreads, 0, st>>>(fp, pa);
   hipError_t e = hipGetLastError();
-  if (e == hipSuccess)
-    e = kind == kBoxTricSorted
-            ? launch_stage_sorted(precision, d_coords, base + off_staged, n, offsets, n_species, fp,
-                                  reinterpret_cast<uint64_t *>(base + off_keys), st)
-            : launch_stage(precision, kind, d_coords, base + off_staged, n, fp, st);
-  // the counters were cleared by the planner: none passed here
-  if (e == hipSuccess)
-    e = launch_zero(d_out, static_cast<int64_t>(n_hist) * n_bins, nullptr, 0, fp.oor, pa.pairs,
-                    n_hist, st);
+  // the counters were cleared by the planner
+  ZeroArgs z;
+  z.out = d_out;
+  z.n_words = static_cast<int64_t>(n_hist) * n_bins;
+  z.n_hist = n_hist;
+  z.oor = fp.oor;
+  z.pairs = pa.pairs;
+  if (e == hipSuccess && kind == kBoxTricSorted) {
+    e = launch_stage_sorted(precision, d_coords, base + off_staged, n, offsets, n_species, fp,
+                            reinterpret_cast<uint64_t *>(base + off_keys), st);
+    if (e == hipSuccess) e = launch_zero(z, st);
+  } else if (e == hipSuccess) {
+    e = launch_stage(precision, kind, d_coords, base + off_staged, n, fp, z, st);
+  }
   if (e == hipSuccess && n_items > 0) {
     PairKernelArgs a;
     a.frames = pa.fp_dst;

@@ -361,14 +361,21 @@ int start_job(dh_server *s, int slot_idx) {
       hipMemcpyAsync(sl.d_pairs, sl.h_pairs, h_b, hipMemcpyHostToDevice, s->setup) !=
           hipSuccess)
     return DH_EDEVICE;
-  const hipError_t staged =
-      j.kind == dh::kBoxTricSorted
-          ? dh::launch_stage_sorted(j.precision, sl.d_in, sl.d_staged, j.n, j.offsets.data(), k, fp,
-                                    static_cast<uint64_t *>(sl.d_keys), s->setup)
-          : dh::launch_stage(j.precision, j.kind, sl.d_in, sl.d_staged, j.n, fp, s->setup);
+  dh::ZeroArgs z;
+  z.out = sl.d_out;
+  z.n_words = static_cast<int64_t>(j.n_hist) * j.n_bins;
+  z.n_hist = j.n_hist;
+  z.oor = fp.oor;
+  z.pairs = sl.d_pairs;
+  hipError_t staged;
+  if (j.kind == dh::kBoxTricSorted) {
+    staged = dh::launch_stage_sorted(j.precision, sl.d_in, sl.d_staged, j.n, j.offsets.data(), k,
+                                     fp, static_cast<uint64_t *>(sl.d_keys), s->setup);
+    if (staged == hipSuccess) staged = dh::launch_zero(z, s->setup);
+  } else {
+    staged = dh::launch_stage(j.precision, j.kind, sl.d_in, sl.d_staged, j.n, fp, z, s->setup);
+  }
   if (staged != hipSuccess ||
-      dh::launch_zero(sl.d_out, static_cast<int64_t>(j.n_hist) * j.n_bins, nullptr, 0, fp.oor,
-                      sl.d_pairs, j.n_hist, s->setup) != hipSuccess ||
       hipEventRecord(sl.setup, s->setup) != hipSuccess)
     return DH_EDEVICE;
   return DH_OK;
