@@ -528,7 +528,9 @@ Launch choose_launch(int n_cu, size_t lds_per_block, int precision, const FrameP
   // minimum image and of the distance.
   L.noclamp = false;
   const double tb = t_bound(fp);
-  if (b.noclamp && L.n_sweeps == 1 && tb > 0) {
+  // (unsorted binary64 frames always clamp)
+  if (b.noclamp && L.n_sweeps == 1 && tb > 0 &&
+      (precision == DH_FP32 || fp.box == kBoxTricSorted)) {
     const int64_t slots = static_cast<int64_t>(tb * (1.0 + 1e-4)) + 2;
     if (slots <= b.win_max + kDump) {
       L.noclamp = true;
@@ -1545,7 +1547,8 @@ int dh_batch_create(dh_ctx *ctx, const dh_frame_desc *frames, int32_t n_frames, 
       fi.fp.n_sweeps = 1;
     }
     const double tb = t_bound(fi.fp);
-    if (fbase.noclamp && fi.mode == kModeLds && tb > 0) {
+    if (fbase.noclamp && fi.mode == kModeLds && tb > 0 &&
+        (precision == DH_FP32 || kind == kBoxTricSorted)) {
       fi.slots = static_cast<int64_t>(tb * (1.0 + 1e-4)) + 2;
       fi.noclamp_ok = fi.slots <= fbase.win_max + kDump;
     }

@@ -144,60 +144,54 @@ __device__ __forceinline__ double sqrt_cr(double q) {
   return q == 0.0 ? q : (q > 0.0 ? q : __builtin_nan(""));
 }
 
-// The scaled distance t = sqrt(q) * s from a short root: v_rsq_f64 (relative
-// error at most 2^-23, the precision the ISA states for it) and one
-// Goldschmidt step, with s folded into the step's last fma (g s (1 + e)
-// instead of (g (1 + e)) s: one dependent step less), give t within about
-// 1.5 * 2^-46 relative plus three roundings, so it lies within 2^13 ulps of
-// the canonical t (correctly rounded root times s).
-// It decides the bin whenever it is farther than 2^16 ulps from every
-// integer. For t < 2^20 the integers are multiples of 2^32 ulps of t, so t
-// is that far from every integer when the low 32 bits of its encoding are
-// at least 2^16 away from a multiple of 2^32, i.e. when lo + 2^16 (mod 2^32)
-// is at least 2^17, lo being those bits (a conservative test). The caller
-// keeps the smallest lo + 2^16 of its pairs per lane in `gap` (a minimum the
-// compiler forms three at a time) and takes the correctly rounded root for
-// all of them when any lane's gap is below 2^17 (one ballot). Every t at or above 2^20 is
-// out of range, as is the canonical t, when n_bins < 2^20 - 2; with more
-// bins the callers take the correctly rounded root for every pair. The
-// bound holds for every normal q (all intermediates stay normal). q = 0
-// gives t = 0 * inf = NaN, whose encoding ends in 32 zero bits, so the test
-// flags it; so it does for a subnormal q if v_rsq_f64 flushed it (q * inf,
-// then inf - inf). Otherwise, for subnormal q the canonical t is below
-// 2^-511 s, under 2^-11 when s < 2^500 (the callers take the correctly
-// rounded root for every pair beyond that), and the short root, within a
-// few ulps of it, falls in bin 0 as well. A NaN t (q = +inf or NaN) counts
-// out of range like the canonical one.
-__device__ __forceinline__ double t_fast64(double q, double s, uint32_t &gap) {
-  const double y = __builtin_amdgcn_rsq(q);
-  const double g = q * y;
-  const double h = 0.5 * y;
-  const double e = fma(-h, g, 0.5);
-  const double gs = g * s;
-  const double t = fma(gs, e, gs);
-  gap = min(gap, static_cast<uint32_t>(__double_as_longlong(t)) + 0x10000u);
-  return t;
-}
+// The bin bits (see kBinBits) of a binary64 pair from a binary32 root made
+// exact by a binary64 residual. u is t^2 in units in which a bin is 2^-22
+// wide, f = 2 + the binary32 root of u rounded to whole bins: m = f - 2 lies
+// within 2/3 of a bin of the root for t < 2^20 (conversion and root are within
+// 2^-22.5 relative), so floor(t) is m when u - m^2 >= 0 and one less
+// otherwise. m^2 is exact and the residual one fma, so its sign is certain
+// unless it is within the rounding of u and of the canonical t; the caller
+// keeps the smallest |residual| of several pairs in `gap` (its upper word
+// read as a float, monotone) and takes the canonical root for all of them when
+// that is not above its threshold in some lane. Larger, infinite or NaN t
+// give bits beyond every bin (2^20 - 2 bins at most). q = 0 has the residual
+// 0. 12 instructions and one transcendental of 8 cycles, where a binary64
+// root (v_rsq_f64 holds the SIMD for 16 cycles, then a Goldschmidt step) and
+// its conversion took 13.
+__device__ __forceinline__ uint32_t root_bits64(double u, float &gap);
 
-// Initial gap of a group of pairs: 0 (the correctly rounded root for every
-// pair) when the histogram has 2^20 - 2 bins or more or s is huge (big_bins,
-// see run_item), else no pair yet.
-__device__ __forceinline__ uint32_t gap_init(bool big_bins) { return big_bins ? 0u : ~0u; }
-
-// Whether any lane of the wave has a pair whose short t may lie near an
-// integer (a uniform answer).
-__device__ __forceinline__ bool any_near(uint32_t gap) {
-  return __builtin_amdgcn_ballot_w64(gap < 0x20000u) != 0;
+// How a binary64 frame decides its bins: u = q scale, residuals up to `near`
+// (in u) go to the canonical root. The scale's rounding, the product's and the
+// canonical t's stay below 2^-49 of u together, and u <= (n_bins + 2)^2 2^-44
+// where it matters. Frames with 2^20 - 2 bins or more, or whose scale is no
+// normal number, take the canonical root for every pair (near = +inf).
+// (60,000 points, 4,096 bins: without a box 1,165 us with the binary64 root,
+// 948 us with this; in a cube 1,519 and 1,330 us, triclinic 1,842 and 1,649.)
+struct Bins64 {
+  double scale, s;
+  float near;
+};
+__device__ __forceinline__ Bins64 bins64(const FrameParams *F) {
+  Bins64 b;
+  const int n_bins = uni(F->n_bins);
+  b.s = uni(F->s);
+  b.scale = (b.s * 0x1p-22) * (b.s * 0x1p-22);
+  const double top = static_cast<double>(n_bins + 2) * 0x1p-22;
+  const double thr = top * top * 0x1p-47;
+  const bool fits = n_bins < (1 << 20) - 2 && b.s > 0x1p-400 && b.s < 0x1p400;
+  b.near = uni(fits ? __int_as_float(static_cast<int>(__double_as_longlong(thr) >> 32) + 1)
+                    : __builtin_inff());
+  return b;
 }
-
-// t with the canonical arithmetic for one pair: the short root, or, when any
-// lane of the wave needs it, the correctly rounded one (a uniform branch).
-__device__ __forceinline__ double t_guarded64(double q, double s, bool big_bins) {
-  uint32_t gap = gap_init(big_bins);
-  const double t = t_fast64(q, s, gap);
-  if (__builtin_expect(any_near(gap), 0)) return sqrt_cr(q) * s;
-  return t;
+// whether a lane of the wave has a residual too small to decide (a uniform
+// answer; a NaN distance leaves gap alone: it counts nowhere)
+__device__ __forceinline__ bool any_near(float gap, const Bins64 &b) {
+  return __builtin_amdgcn_ballot_w64(!(gap > b.near)) != 0;
 }
+// the bits of a canonical t: floor(t), saturated beyond every bin (2^24 at
+// most; a NaN t takes the other operand)
+constexpr uint32_t kNoBits = (1u << 30) + (1u << 25);
+__device__ __forceinline__ uint32_t canonical_bits(double q, double s);
 
 // d = x_j - x_i reduced by the minimum-image rule of the box kind.
 template <int BOX>
@@ -350,6 +344,18 @@ __device__ __forceinline__ double min_arith(double a, double b) {
   return r;
 }
 
+__device__ __forceinline__ uint32_t root_bits64(double u, float &gap) {
+  const float f = __builtin_amdgcn_sqrtf(static_cast<float>(u)) + 2.f;
+  const double m = static_cast<double>(f - 2.f);
+  const double r = fma(-m, m, u);
+  const int rh = static_cast<int>(__double_as_longlong(r) >> 32);
+  gap = fminf(gap, fabsf(__int_as_float(rh)));
+  return __float_as_uint(f) + static_cast<uint32_t>(rh >> 31);
+}
+__device__ __forceinline__ uint32_t canonical_bits(double q, double s) {
+  return kBinBits + static_cast<uint32_t>(min_arith(sqrt_cr(q) * s, 0x1p25));
+}
+
 
 
 // Triclinic reduced vector (t units) from packed fractional words.
@@ -469,14 +475,14 @@ __device__ __forceinline__ uint32_t bits32_packed_c(uint64_t ab_j, uint64_t neg_
   }
 }
 
-// Counts binary32 pairs from their bin bits (see bin_bits32). The clamp is an
+// Counts pairs from their bin bits (see bin_bits32, root_bits64). The clamp is an
 // upper one only: bin -1 is the guard word below the histogram, added to bin 0
 // on flush, and a lane whose pair must not count passes bits beyond every bin
 // (kNoBin). Two-operand instructions throughout: v_min_u32, v_lshlrev_b32 and
 // v_sub_u32 take about 2.7 cycles of a SIMD, the three-operand v_med3_u32 and
 // v_lshl_add_u32 about 4.5.
 template <int MODE>
-struct Count32 {
+struct Count {
   using LdsU32 = __attribute__((address_space(3))) uint32_t;
   using GlobalU64 = __attribute__((address_space(1))) unsigned long long;
   uint32_t top;     // the lane's discard slot (LDS: in bin bits; windows: as a slot)
@@ -484,7 +490,7 @@ struct Count32 {
   uint32_t n_bins;
   GlobalU64 *out;
 
-  __device__ __forceinline__ Count32(const FrameParams *F, const WorkItem &w, int lane) {
+  __device__ __forceinline__ Count(const FrameParams *F, const WorkItem &w, int lane) {
     const uint32_t win = static_cast<uint32_t>(uni(F->win));
     const uint32_t b_lo = static_cast<uint32_t>(w.sweep) * win;
     n_bins = static_cast<uint32_t>(uni(F->n_bins));
@@ -624,7 +630,7 @@ __device__ __forceinline__ void flush_hist(uint32_t *hist, const PairKernelArgs 
     uint64_t v = hist[b];
     hist[b] = 0u;
     if (b == 0) {
-      // the guard word: binary32 bin -1 (see Count32)
+      // the guard word: binary32 bin -1 (see Count)
       if (sweep == 0) v += hist[-1];
       hist[-1] = 0u;
     }
@@ -687,56 +693,21 @@ __device__ __forceinline__ void run_units(const PairKernelArgs &a, const WorkIte
                                           int *s_item) {
   using V = typename V4<T>::type;
   using G = typename Geo<T>::type;
-  constexpr bool SWEEP = MODE == kModeSweep;
-  constexpr bool GLOBAL = MODE == kModeGlobal;
   constexpr bool SEARCH = BOX == kBoxTricSearch;
   const V *__restrict__ X = uni(static_cast<const V *>(F->coords));
   const G g = Geo<T>::load(F);
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
-  const int win = uni(F->win);
-  const int b_lo = w.sweep * win;
-  [[maybe_unused]] const Count32<MODE> count32(F, w, lane);
-  // largest slot index of binary64 unclamped units
-  const double cap64 = static_cast<double>(a.stride - 1);
-  const uint32_t hi = static_cast<uint32_t>(win + lane);  // discard slot of this lane
-  const int n_bins = uni(F->n_bins);
-  const bool noclamp = MODE == kModeLds && !SEARCH && uni(F->noclamp) != 0;
-  // binary64: the correctly rounded root for every pair when t at or above
-  // 2^20 can lie near a bin edge (this many bins) or the scale s is so large
-  // that a subnormal q could reach bin 1 (see t_fast64)
-  [[maybe_unused]] const bool big_bins =
-      n_bins >= (1 << 20) - 2 || !(uni(F->s) < 0x1p500);
-  // the output is global memory: say so, so the atomics are global_atomic_*
-  // (a generic pointer would give flat atomics, which also count as LDS
-  // operations in lgkmcnt)
-  using GlobalU64 = __attribute__((address_space(1))) unsigned long long;
-  [[maybe_unused]] GlobalU64 *const gout =
-      (GlobalU64 *)(F->out + static_cast<size_t>(w.hist) * static_cast<size_t>(n_bins));
+  const Count<MODE> count(F, w, lane);
+  // binary32 frames whose every t is below the LDS stride need no clamp;
+  // binary64 reads raw device coordinates and keeps it for non-finite ones
+  const bool noclamp = MODE == kModeLds && !SEARCH && sizeof(T) == 4 && uni(F->noclamp) != 0;
+  [[maybe_unused]] const Bins64 bins = sizeof(T) == 8 ? bins64(F) : Bins64{};
 
-  // Counts a binary64 pair at scaled distance t. l: 0 for a pair that counts,
-  // the lane's discard slot for one that must not (the lower clamp).
-  auto count64 = [&](auto clamp_c, double t, uint32_t l) {
-    constexpr bool CLAMP = decltype(clamp_c)::value;
-    if constexpr (GLOBAL) {
-      // a pair counts iff t < n_bins (in the working precision)
-      if (l == 0u && t < static_cast<double>(n_bins))
-        __hip_atomic_fetch_add(gout + static_cast<uint32_t>(t), 1ull, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-      uint32_t idx;
-      if constexpr (!CLAMP) {
-        // binary64 reads raw device coordinates: cap t so that even
-        // non-finite or absurd input stays inside the LDS histogram
-        idx = static_cast<uint32_t>(min_arith(t, cap64));
-      } else {
-        // floor(t), saturated; t >= 0 always
-        idx = static_cast<uint32_t>(min_arith(t, 4294967295.0));
-        if constexpr (SWEEP) idx -= static_cast<uint32_t>(b_lo);
-        // the slot clamped to [l, hi] (l is 0 or hi): one v_med3_u32
-        idx = med3_u32(idx, l, hi);
-      }
-      atomicAdd(my + idx, 1u);
-    }
+  // bin bits of one binary64 pair (its own ballot)
+  [[maybe_unused]] auto bits_of = [&](double q) {
+    float gap = __builtin_inff();
+    const uint32_t b = root_bits64(q * bins.scale, gap);
+    return __builtin_expect(any_near(gap, bins), 0) ? canonical_bits(q, bins.s) : b;
   };
 
   // image-search ring of this wave: qn entries from head (wave-uniform)
@@ -793,10 +764,13 @@ __device__ __forceinline__ void run_units(const PairKernelArgs &a, const WorkIte
       q = search_oct<T>(e.x, e.y, e.z, q, code == 8 ? 8 * kOctCap : code * kOctCap, n, sh);
       n_images += static_cast<uint64_t>(cnt) * static_cast<uint64_t>(n);
       if constexpr (sizeof(T) == 4)
-        count32.template add<true>(
+        count.template add<true>(
             bin_bits32(__builtin_amdgcn_sqrtf(q), v ? kBinOffset : kNoBin));
       else
-        count64(Yes{}, t_guarded64(q, g.s, big_bins), v ? 0u : hi);
+      {
+        const uint32_t b = bits_of(q);
+        count.template add<true>(v ? b : kNoBits);
+      }
       n_searched += cnt;  // wave-uniform; added to the frame's count once per item
       head += cnt;
       if (head >= cap) head -= cap;
@@ -808,9 +782,9 @@ __device__ __forceinline__ void run_units(const PairKernelArgs &a, const WorkIte
   // the i-particles of the current slice
   int wbase = -1;
   T xi[R], yi[R], zi[R];
-  // a lane past the end of the item: its lower clamp is its discard slot (lo,
-  // binary64), its bin offset is beyond every bin (off, binary32)
-  [[maybe_unused]] uint32_t lo[R];
+  // a lane past the end of the item: its bin offset is beyond every bin
+  // (binary32); in binary64 its particle is at infinity, where every distance
+  // is infinite or NaN
   [[maybe_unused]] float off[R];
   // -(b:a) of each i-particle for the packed periodic binary32 difference;
   // -(c' : c) of i-particles 2k and 2k+1: one 64-bit addition to j's (c : c)
@@ -824,8 +798,8 @@ __device__ __forceinline__ void run_units(const PairKernelArgs &a, const WorkIte
       const int i = wbase + r * 64 + lane;
       const bool ok = i < w.i1;
       const V p = X[ok ? i : w.i0];
-      xi[r] = p.x; yi[r] = p.y; zi[r] = p.z;
-      lo[r] = ok ? 0u : hi;
+      xi[r] = sizeof(T) == 8 && !ok ? static_cast<T>(__builtin_inf()) : p.x;
+      yi[r] = p.y; zi[r] = p.z;
       off[r] = ok ? kBinOffset : kNoBin;
       if constexpr (sizeof(T) == 4)
         nab[r] = 0ull - ((static_cast<uint64_t>(__float_as_uint(yi[r])) << 32) |
@@ -856,36 +830,27 @@ __device__ __forceinline__ void run_units(const PairKernelArgs &a, const WorkIte
   auto pairs_of = [&](auto diag_c, auto clamp_c, const J &pj, int j) {
     constexpr bool DIAG = decltype(diag_c)::value;
     if constexpr (sizeof(T) == 8 && !SEARCH) {
-      // binary64: the short root for all R pairs, one ballot, and the
-      // correctly rounded root for all of them when any lane of the wave
-      // has a t near an integer (see t_fast64)
-      double q[R], t[R];
-      uint32_t gap = gap_init(big_bins);
+      // binary64: one ballot for all R pairs (see root_bits64)
+      double q[R];
+      uint32_t b[R];
+      float gap = __builtin_inff();
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         q[r] = q64<BOX>(xi[r], yi[r], zi[r], pj.x, pj.y, pj.z, g);
-        t[r] = t_fast64(q[r], g.s, gap);
+        b[r] = root_bits64(q[r] * bins.scale, gap);
       }
-      if (__builtin_expect(any_near(gap), 0))
+      if (__builtin_expect(any_near(gap, bins), 0))
 #pragma unroll
-        for (int r = 0; r < R; ++r) t[r] = sqrt_cr(q[r]) * g.s;
+        for (int r = 0; r < R; ++r) b[r] = canonical_bits(q[r], bins.s);
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        uint32_t l = lo[r];
-        if constexpr (DIAG) l = j > wbase + r * 64 + lane ? l : hi;
-        count64(clamp_c, t[r], l);
-      }
+      for (int r = 0; r < R; ++r)
+        count.template add<true>(DIAG && j <= wbase + r * 64 + lane ? kNoBits : b[r]);
       return;
     } else {
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        [[maybe_unused]] uint32_t l = lo[r];
         [[maybe_unused]] float o = off[r];
-        if constexpr (DIAG) {
-          const bool up = j > wbase + r * 64 + lane;
-          l = up ? l : hi;
-          o = up ? o : kNoBin;
-        }
+        if constexpr (DIAG) o = j > wbase + r * 64 + lane ? o : kNoBin;
         if constexpr (SEARCH) {
           T dx, dy, dz;
           if constexpr (kPacked)
@@ -896,12 +861,14 @@ __device__ __forceinline__ void run_units(const PairKernelArgs &a, const WorkIte
           const T q0 = fmaT(dz, dz, fmaT(dy, dy, dx * dx));
           // valid pairs at least half the shortest lattice vector long
           // are searched later; they must not count now
-          const bool need = (sizeof(T) == 4 ? o == kBinOffset : l == 0u) && q0 >= qskip;
-          if constexpr (sizeof(T) == 4)
-            count32.template add<true>(
+          const bool need = o == kBinOffset && q0 >= qskip;
+          if constexpr (sizeof(T) == 4) {
+            count.template add<true>(
                 bin_bits32(__builtin_amdgcn_sqrtf(q0), need ? kNoBin : o));
-          else
-            count64(Yes{}, t_guarded64(q0, g.s, big_bins), need ? hi : l);
+          } else {
+            const uint32_t b = bits_of(q0);
+            count.template add<true>(need || o != kBinOffset ? kNoBits : b);
+          }
           const uint64_t m = __builtin_amdgcn_ballot_w64(need);
           if (m != 0) {
             const int below = __builtin_amdgcn_mbcnt_hi(
@@ -930,10 +897,10 @@ __device__ __forceinline__ void run_units(const PairKernelArgs &a, const WorkIte
           const uint64_t dcc = pj.cc + nzz[r / 2];
           const float fc = static_cast<float>(static_cast<int32_t>(
               static_cast<uint32_t>(r % 2 == 0 ? dcc : dcc >> 32)));
-          count32.template add<decltype(clamp_c)::value>(
+          count.template add<decltype(clamp_c)::value>(
               bits32_packed_c<BOX>(pj.ab, nab[r], fc, g, o));
         } else {
-          count32.template add<decltype(clamp_c)::value>(
+          count.template add<decltype(clamp_c)::value>(
               bin_bits32(pair_t<T, BOX>(xi[r], yi[r], zi[r], pj.x, pj.y, pj.z, g), o));
         }
       }

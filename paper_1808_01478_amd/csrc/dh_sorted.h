@@ -182,7 +182,7 @@ __device__ __forceinline__ void run_sorted(const PairKernelArgs &a, const WorkIt
   const int win = uni(F->win);
   const WindowBounds wb = window_bounds(F, w.sweep * win, win, a.stride);
   const bool noclamp = MODE == kModeLds && uni(F->noclamp) != 0;
-  const Count32<MODE> count(F, w, lane);
+  const Count<MODE> count(F, w, lane);
   using Yes = std::true_type;
   using No = std::false_type;
 
@@ -414,7 +414,7 @@ __device__ __attribute__((noinline)) void exact_pairs(const FrameParams *F, int 
   WorkItem w;
   w.hist = hist;
   w.sweep = sweep;
-  const Count32<MODE> count(F, w, lane);
+  const Count<MODE> count(F, w, lane);
   for (; left != 0u; left &= left - 1u)
     for (int h = 0; h < 2; ++h) {
       const int j = j0 + 2 * __builtin_ctz(left) + h;
@@ -427,8 +427,8 @@ __device__ __attribute__((noinline)) void exact_pairs(const FrameParams *F, int 
         const int64_t p = 3 * static_cast<int64_t>(index[ok ? i : ib]);
         const double t = t64<kBoxTric>(in[p], in[p + 1], in[p + 2], xj, yj, zj, g);
         // (a NaN t takes the other operand: out of range)
-        const uint32_t b = kBinBits + static_cast<uint32_t>(min_arith(t, 0x1p21));
-        count.template add<true>(ok ? b : kBinBits + (1u << 21));
+        const uint32_t b = kBinBits + static_cast<uint32_t>(min_arith(t, 0x1p25));
+        count.template add<true>(ok ? b : kNoBits);
       }
     }
 }
@@ -438,16 +438,12 @@ __device__ __attribute__((noinline)) void exact_pairs(const FrameParams *F, int 
 // only when its distance lies next to a bin edge. The pairs here work on
 // positions of the wrapped points relative to the cell centre, scaled to
 // units in which a bin is 2^-22 wide, so with one shared shift per pair of
-// groups a pair takes three differences and q, in binary64. The root is a
-// binary32 guess, made exact by a binary64 comparison: with u = q in units of
-// a bin and m the integer nearest to the binary32 root of u (within 2/3 of the
-// root for t < 2^20, larger t being out of range), floor(sqrt(u)) is m when
-// u - m^2 >= 0 and m - 1 otherwise, and the sign of that one fused residual is
-// certain unless |u - m^2| is within `thr`, the bound of every rounding
-// between the inputs and u and between the inputs and the canonical t. The
-// smallest |residual| of eight pairs goes through one ballot; when it is not
-// above thr the wave takes the canonical sequence on the input points for all
-// of them (about one group of eight in 10^5 on the 1M-point frame).
+// groups a pair takes three differences and u = t^2 in binary64, and its bin
+// from root_bits64. Here the threshold of the residuals bounds every rounding
+// between the inputs and u and between the inputs and the canonical t; one
+// ballot serves the pairs of two j, and when it fires the wave leaves them to
+// the canonical sequence on the input points (about one such group in 10^5 on
+// the 1M-point frame).
 //
 // Bound by vector-unit issue: 15 instructions per pair on the short path (17
 // with the clamp) against 22 over the frame with a binary64 root per pair
@@ -475,7 +471,7 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
   const int win = uni(F->win);
   const WindowBounds wb = window_bounds(F, w.sweep * win, win, a.stride);
   const bool noclamp = MODE == kModeLds && uni(F->noclamp) != 0;
-  const Count32<MODE> count(F, w, lane);
+  const Count<MODE> count(F, w, lane);
   using Yes = std::true_type;
   using No = std::false_type;
 
@@ -572,19 +568,14 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
             dx = fma(K == 0 ? -ax : K == 1 ? -bx : -cx, n, dx);
           }
           const double u = fma(dz, dz, fma(dy, dy, dx * dx));
-          const float f = __builtin_amdgcn_sqrtf(static_cast<float>(u)) + 2.f;
-          const double m = static_cast<double>(f - 2.f);
-          const double r = fma(-m, m, u);
-          const int rh = static_cast<int>(__double_as_longlong(r) >> 32);
-          gap = fminf(gap, fabsf(__int_as_float(rh)));
-          b[k] = __float_as_uint(f) + static_cast<uint32_t>(rh >> 31);
+          b[k] = root_bits64(u, gap);
         }
       };
       auto tally = [&](const uint32_t *b, int j) {
 #pragma unroll
         for (int k = 0; k < M; ++k)
           count.template add<decltype(clamp_c)::value>(
-              DIAG && j <= slice(k) ? kBinBits + (1u << 21) : b[k]);
+              DIAG && j <= slice(k) ? kNoBits : b[k]);
       };
       J pa = load(0), pb = load(1);
       int j = j0;

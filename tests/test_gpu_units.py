@@ -48,3 +48,21 @@ def test_unit_edges(ctx, kind, shape):
         bad += oor_bound_violations(oor, ref.out_of_range, ref.edges)
         assert not bad, (sizes, bad[:3])
     ctx.set_config(None)
+
+
+@pytest.mark.parametrize("n_bins", [1, 37, 4096, (1 << 20) - 3, (1 << 20) - 2, (1 << 20) + 5])
+@pytest.mark.parametrize("box_type", [workloads.BOX_NONE, workloads.BOX_ORTHO])
+def test_binary64_bin_edges(ctx, box_type, n_bins):
+    """binary64 bins at their edges: points of a lattice (coincident ones
+    among them) whose distances hit whole bins exactly, and bin counts on both
+    sides of the limit of the binary32 root."""
+    rng = np.random.Generator(np.random.PCG64(n_bins))
+    x = rng.integers(0, 32, size=(1500, 3)) / 4.0
+    box = workloads.ortho_box(8, 8, 8) if box_type == workloads.BOX_ORTHO else None
+    offs = np.array([0, 900, 1500], np.int64)
+    for r_max in (n_bins / 8.0 if n_bins < 100 else 8.0, 6.7):
+        fr = workloads.Frame(np.ascontiguousarray(x), offs, box_type, box, r_max, n_bins, "lattice")
+        print(f"\n[case] bin edges box={box_type} bins={n_bins} r_max={r_max}", flush=True)
+        ref = oracle.frame_histogram(fr)
+        h, oor = run_gpu(ctx, fr, 1)
+        assert np.array_equal(h, ref.hist) and np.array_equal(oor, ref.out_of_range)
