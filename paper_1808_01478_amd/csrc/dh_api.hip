@@ -748,7 +748,7 @@ struct FrameJob {
 int stage_job(dh_ctx *ctx, hipStream_t st, const FrameJob &job, const FrameParams &fp,
               const ZeroArgs &z) {
   const int64_t n = job.offsets[job.n_species];
-  if (job.kind == kBoxTricSorted) {
+  if (padded_frame(job.kind)) {
     int rc = ensure_device(ctx, &ctx->d_keys, &ctx->keys_cap,
                            static_cast<size_t>(sort_keys_count(n)) * sizeof(uint64_t));
     if (rc) return rc;
@@ -838,7 +838,7 @@ int run_frame(dh_ctx *ctx, hipStream_t st, const FrameJob &job, const Knobs &k, 
     int rc0 = ensure_device(ctx, &ctx->d_blob, &ctx->blob_cap, lay.total);
     if (rc0) return rc0;
   }
-  fp.searched = job.kind == kBoxTricSearch && !job.accumulate
+  fp.searched = (job.kind == kBoxTricSearch || job.kind == kBoxSearchSorted) && !job.accumulate
                     ? reinterpret_cast<unsigned long long *>(
                           static_cast<char *>(ctx->d_blob) + lay.counter +
                           n_work_counters * sizeof(int32_t))
@@ -1341,9 +1341,10 @@ int histo_job(dh_ctx *ctx, hipStream_t stream, const double *d_coords, const int
   job.d_oor = accumulate ? nullptr : d_out_of_range;
   job.accumulate = accumulate;
   const int geometric = frame_consts(box_type, box, r_max, n_bins, job.fp);
-  job.kind = staged_kind(geometric, precision, job.fp.L, job.fp.s, n_bins, n);
+  // (a budgeted context keeps the search it has room for)
+  job.kind = staged_kind(geometric, precision, job.fp, n, ctx->budget == 0);
   // (the sorted binary64 kernel goes back to the input for pairs at a bin edge)
-  job.fp.in = job.kind == kBoxTricSorted && precision == DH_FP64 ? d_coords : nullptr;
+  job.fp.in = padded_frame(job.kind) && precision == DH_FP64 ? d_coords : nullptr;
   job.fp.box = job.kind;
   job.fp.n_pad = static_cast<int32_t>(padded_start(offsets, n_species));
   for (int s = 0; s < n_species; ++s) {
@@ -1527,7 +1528,7 @@ int dh_batch_create(dh_ctx *ctx, const dh_frame_desc *frames, int32_t n_frames, 
     if (!d.d_out || (n > 0 && !d.d_coords)) return fail(ctx, DH_EINVAL, "frame %d: null pointer", f);
     FrameInfo &fi = info[f];
     const int geometric = frame_consts(d.box_type, d.box, d.r_max, d.n_bins, fi.fp);
-    const int kind = staged_kind(geometric, precision, fi.fp.L, fi.fp.s, d.n_bins, n);
+    const int kind = staged_kind(geometric, precision, fi.fp, n, ctx->budget == 0);
     fi.fp.box = kind;
     fi.fp.n_pad = static_cast<int32_t>(padded_start(d.offsets, d.n_species));
     fi.offsets.assign(d.offsets, d.offsets + d.n_species + 1);
@@ -1656,7 +1657,7 @@ int dh_batch_create(dh_ctx *ctx, const dh_frame_desc *frames, int32_t n_frames, 
   const size_t blob_bytes = b->off_counters + align_up(b->groups.size() * sizeof(int32_t), 256);
   int64_t max_sorted = 0;
   for (int32_t f = 0; f < n_frames; ++f)
-    if (info[f].fp.box == kBoxTricSorted) max_sorted = std::max(max_sorted, info[f].fp.n_points);
+    if (padded_frame(info[f].fp.box)) max_sorted = std::max(max_sorted, info[f].fp.n_points);
   const size_t keys_bytes =
       max_sorted > 0 ? static_cast<size_t>(sort_keys_count(max_sorted)) * 8 : 0;
   // the batch's buffers count against the context's budget while it lives
@@ -1686,7 +1687,7 @@ int dh_batch_create(dh_ctx *ctx, const dh_frame_desc *frames, int32_t n_frames, 
     fp.coords = static_cast<char *>(b->d_staged) + staged_off[f];
     fp.pairs = reinterpret_cast<const uint64_t *>(db + off_pairs) + pairs_base[f];
     std::memcpy(host.data() + b->off_frames + f * sizeof(FrameParams), &fp, sizeof fp);
-    if (fp.box == kBoxTricSorted)
+    if (padded_frame(fp.box))
       b->sorted.push_back({f, frames[f].d_coords, const_cast<void *>(fp.coords),
                            info[f].offsets, fp});
   }

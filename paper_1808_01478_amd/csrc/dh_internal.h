@@ -16,6 +16,8 @@ enum BoxKind : int32_t {
   // Eq. 5 reduction only, points spatially sorted within each species at
   // staging (frames of at least kSortMinPoints; see staged_kind)
   kBoxTricSorted = 5,
+  // the same with the neighbouring images (binary64; see staged_kind)
+  kBoxSearchSorted = 6,
 };
 
 // Largest species count of a frame (the staging kernels take the offsets by
@@ -24,26 +26,6 @@ constexpr int kMaxSpeciesStage = 64;
 // frames with at least this many points may be staged in spatial order
 // (kBoxTricSorted, see staged_kind)
 constexpr int64_t kSortMinPoints = int64_t{1} << 16;
-
-// The minimum-image kind the kernels use for a frame: the geometric kind of
-// frame_constants, with large frames staged in spatial order (triclinic
-// frames in both precisions; orthorhombic ones in binary64, where the sorted
-// kernel with a diagonal cell matrix gives the orthorhombic sequence's
-// counts bit for bit) and the binary32 special case of equal orthorhombic
-// edges. The sorted binary64 kernel takes bins from a binary32 root of
-// numbers scaled by s 2^-22: fewer than 2^20 bins, and a scale whose square
-// is a normal number.
-inline int staged_kind(int kind, int precision, const double L[3], double s, int32_t n_bins,
-                       int64_t n_points) {
-  const bool fits = precision == 0 || (n_bins < (1 << 20) - 2 && s > 0x1p-400 && s < 0x1p400);
-  // (padded indices fit in 32 bits)
-  if (n_points >= kSortMinPoints && n_points <= 0x7FFFFFFF - 64 * kMaxSpeciesStage && fits &&
-      (kind == kBoxTric || (kind == kBoxOrtho && precision != 0)))
-    return kBoxTricSorted;
-  if (precision != 0) return kind;
-  if (kind == kBoxOrtho && L[0] == L[1] && L[1] == L[2]) return kBoxCube;
-  return kind;
-}
 
 // i-span of a work unit of a sorted frame (see dh_sorted.h)
 constexpr int32_t kUnitPoints = 512;
@@ -56,7 +38,9 @@ constexpr int32_t kUnitPoints = 512;
 // 32 bytes per point of staged_point_bytes (29 per padded point plus one box;
 // frames have at least kSortMinPoints points and at most kMaxSpeciesStage
 // species).
-inline bool padded_frame(int kind) { return kind == kBoxTricSorted; }
+inline bool padded_frame(int kind) {
+  return kind == kBoxTricSorted || kind == kBoxSearchSorted;
+}
 __host__ __device__ inline int64_t padded_start(const int64_t *off, int32_t s) {
   int64_t p = 0;
   for (int32_t u = 0; u < s; ++u) p += (off[u + 1] - off[u] + 63) / 64 * 64;
@@ -75,7 +59,7 @@ static_assert(sizeof(GroupBox) == 64, "one box per 64 points at one byte a point
 // Bytes per staged point (binary64 double4; binary32 float4, two of them
 // for spatially sorted frames) and the sort workspace of a frame.
 inline size_t staged_point_bytes(int precision, int kind) {
-  return precision != 0 ? 32 : (kind == kBoxTricSorted ? 32 : 16);
+  return precision != 0 || padded_frame(kind) ? 32 : 16;
 }
 inline int64_t sort_keys_count(int64_t n) {
   int64_t p = 2048;
@@ -180,6 +164,49 @@ struct FrameParams {
   uint8_t oct_n;
 };
 
+// The minimum-image kind the kernels use for a frame: the geometric kind of
+// frame_constants (fp), with large frames staged in spatial order (triclinic
+// frames in both precisions; orthorhombic ones in binary64, where the sorted
+// kernel with a diagonal cell matrix gives the orthorhombic sequence's
+// counts bit for bit; frames with image search in binary64, see below) and the
+// binary32 special case of equal orthorhombic edges.
+//
+// The sorted binary64 kernel takes bins from a binary32 root of numbers scaled
+// by s 2^-22: fewer than 2^20 bins, and a scale whose square is a normal
+// number. With image search it takes a pair's nearest image, which is the
+// canonical minimum over 27 images when no image outside them can be nearer:
+// such an image differs by two or more cell vectors along some axis from the
+// reduced vector, so it is at least 1.5 times the smallest cell width long,
+// and the reduced vector is no longer than the longest half diagonal.
+// (may_search: the caller can hold the sort workspace such a frame needs.)
+inline int staged_kind(int kind, int precision, const FrameParams &fp, int64_t n_points,
+                       bool may_search = true) {
+  const bool fits =
+      precision == 0 || (fp.n_bins < (1 << 20) - 2 && fp.s > 0x1p-400 && fp.s < 0x1p400);
+  // (padded indices fit in 32 bits)
+  const bool large =
+      n_points >= kSortMinPoints && n_points <= 0x7FFFFFFF - 64 * kMaxSpeciesStage && fits;
+  if (large && (kind == kBoxTric || (kind == kBoxOrtho && precision != 0))) return kBoxTricSorted;
+  if (large && kind == kBoxTricSearch && precision != 0 && may_search) {
+    double diagonal2 = 0.0;
+    for (int q = 0; q < 8; ++q) {
+      const double a = q & 1 ? 0.5 : -0.5, b = q & 2 ? 0.5 : -0.5, c = q & 4 ? 0.5 : -0.5;
+      const double x = a * fp.ax + b * fp.bx + c * fp.cx, y = b * fp.by + c * fp.cy,
+                   z = c * fp.cz;
+      const double d2 = x * x + y * y + z * z;
+      diagonal2 = d2 > diagonal2 ? d2 : diagonal2;
+    }
+    // 1 / width^2 along each axis: the squared rows of B^-1
+    const double ra = fp.h11 * fp.h11 + fp.h12 * fp.h12 + fp.h13 * fp.h13;
+    const double rb = fp.h22 * fp.h22 + fp.h23 * fp.h23, rc = fp.h33 * fp.h33;
+    const double r = ra > rb ? (ra > rc ? ra : rc) : (rb > rc ? rb : rc);
+    if (diagonal2 * r < 2.25 * (1.0 - 1e-6)) return kBoxSearchSorted;
+  }
+  if (precision != 0) return kind;
+  if (kind == kBoxOrtho && fp.L[0] == fp.L[1] && fp.L[1] == fp.L[2]) return kBoxCube;
+  return kind;
+}
+
 // One unit of work: particles [i0, i1) of the frame against [j0, j1), for
 // histogram `hist`, bin window `sweep`; flags: kItemDiag, kItemFull.
 struct WorkItem {
@@ -230,7 +257,7 @@ constexpr int64_t kMinItemPairs = int64_t{1} << 15;
 constexpr int32_t kMinChunk = 32;
 // granularity of the j-pieces the tail of a work list is cut into
 inline int32_t tail_step(int32_t kind) {
-  return kind == kBoxTricSorted ? kUnitPoints : kMinChunk;
+  return padded_frame(kind) ? kUnitPoints : kMinChunk;
 }
 inline void set_items(KernelConfig &c, int32_t precision, int32_t kind, int grid, uint64_t work,
                       int items_per_wg) {
@@ -366,7 +393,7 @@ template <> PairFn pick_pairs<double, kModeSweep>(int r, int box);
 template <> PairFn pick_pairs<double, kModeGlobal>(int r, int box);
 
 // host-side launchers (dh_kernels.hip)
-// Staging of a kBoxTricSorted frame: the points of every species in Morton
+// Staging of a sorted frame: the points of every species in Morton
 // order of their wrapped fractional coordinates (keys: a workspace of
 // sort_keys_count(n) words); staged arrays and group boxes at
 // padded indices (see padded_frame).

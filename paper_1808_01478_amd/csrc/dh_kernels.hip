@@ -303,7 +303,7 @@ template <int PREC>
 __global__ void stage_batch_kernel(const FrameParams *__restrict__ frames) {
   const FrameParams &p = frames[blockIdx.y];
   // spatially sorted frames are staged by their own sort
-  if (p.box == kBoxTricSorted) return;
+  if (p.box == kBoxTricSorted || p.box == kBoxSearchSorted) return;
   const int64_t n = p.n_points;
   const double *__restrict__ in = p.in;
   const int64_t step = static_cast<int64_t>(gridDim.x) * blockDim.x;
@@ -451,7 +451,7 @@ hipError_t launch_stage_sorted(int precision, const double *in, void *out, int64
 
 hipError_t launch_stage(int precision, int box_kind, const double *in, void *out, int64_t n,
                         const FrameParams &fp, const ZeroArgs &z, hipStream_t st) {
-  if (box_kind == kBoxTricSorted) return hipErrorInvalidValue;  // launch_stage_sorted
+  if (padded_frame(box_kind)) return hipErrorInvalidValue;  // launch_stage_sorted
   const int threads = 256;
   const int grid = grid_for(std::max(n, zero_span(z)), threads);
   if (precision == 1) {

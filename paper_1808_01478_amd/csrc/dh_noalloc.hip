@@ -165,12 +165,18 @@ extern "C" int dh_histo_noalloc(dh_stream stream, const double *d_coords,
 
   FrameParams fp;
   const int geometric = frame_constants(box_type, box, r_max, n_bins, fp);
-  const int kind = staged_kind(geometric, precision, fp.L, fp.s, n_bins, n);
+  // frames with image search are sorted where the sort keys fit beside the
+  // staged points with room for the work list
+  const bool may_search = static_cast<size_t>(n) * 32 + static_cast<size_t>(sort_keys_count(n)) *
+                                                            sizeof(uint64_t) +
+                              (size_t{4} << 20) <=
+                          kScratchBytes;
+  const int kind = staged_kind(geometric, precision, fp, n, may_search);
   fp.box = kind;
   fp.n_pad = static_cast<int32_t>(padded_start(offsets, n_species));
   const size_t point_bytes = staged_point_bytes(precision, kind);
   const size_t keys_bytes =
-      kind == kBoxTricSorted ? static_cast<size_t>(sort_keys_count(n)) * sizeof(uint64_t) : 0;
+      padded_frame(kind) ? static_cast<size_t>(sort_keys_count(n)) * sizeof(uint64_t) : 0;
   const int32_t n_hist = n_species * (n_species + 1) / 2;
   uint64_t total = 0;
   for (int32_t h = 0; h < n_hist; ++h) total += hist_rows(offsets, n_species, h).pairs;
@@ -205,14 +211,14 @@ extern "C" int dh_histo_noalloc(dh_stream stream, const double *d_coords,
   int32_t *counters = reinterpret_cast<int32_t *>(base + off_counters);
   fp.coords = base + off_staged;
   fp.out = d_out;
-  fp.in = kind == kBoxTricSorted && precision == DH_FP64 ? d_coords : nullptr;
+  fp.in = padded_frame(kind) && precision == DH_FP64 ? d_coords : nullptr;
   fp.win = L.win;
   fp.n_sweeps = L.n_sweeps;
   fp.noclamp = L.noclamp ? 1 : 0;
   const bool oor_flush = d_out_of_range != nullptr && L.mode != kModeGlobal;
   fp.oor = oor_flush ? d_out_of_range : nullptr;
   fp.oor_by_flush = oor_flush ? 1 : 0;
-  fp.searched = kind == kBoxTricSearch ? reinterpret_cast<unsigned long long *>(counters + 2)
+  fp.searched = kind == kBoxTricSearch || kind == kBoxSearchSorted ? reinterpret_cast<unsigned long long *>(counters + 2)
                                        : nullptr;
 
   PlanArgs pa;
@@ -239,7 +245,7 @@ extern "C" int dh_histo_noalloc(dh_stream stream, const double *d_coords,
   z.n_hist = n_hist;
   z.oor = fp.oor;
   z.pairs = pa.pairs;
-  if (e == hipSuccess && kind == kBoxTricSorted) {
+  if (e == hipSuccess && padded_frame(kind)) {
     e = launch_stage_sorted(precision, d_coords, base + off_staged, n, offsets, n_species, fp,
                             reinterpret_cast<uint64_t *>(base + off_keys), st);
     if (e == hipSuccess) e = launch_zero(z, st);

@@ -1062,8 +1062,8 @@ __global__ __launch_bounds__(max_threads<BOX>(), (min_waves<T, R, BOX>())) void 
     // the histogram is clear, the unit counter set
     __syncthreads();
     const FrameParams *F = a.frames + w.frame;
-    if constexpr (BOX == kBoxTricSorted && sizeof(T) == 8) {
-      run_sorted64<MODE>(a, w, F, &s_unit, &s_item);
+    if constexpr (sizeof(T) == 8 && (BOX == kBoxTricSorted || BOX == kBoxSearchSorted)) {
+      run_sorted64<MODE, BOX == kBoxSearchSorted>(a, w, F, &s_unit, &s_item);
     } else if constexpr (BOX == kBoxTricSorted) {
       run_sorted<MODE>(a, w, F, &s_unit, &s_item);
     } else {
@@ -1087,6 +1087,9 @@ PairFn pick_box(int box) {
       if constexpr (sizeof(T) == 4) return pairs_kernel<T, R, kBoxCube, SW>;
       return pairs_kernel<T, R, kBoxOrtho, SW>;
     case kBoxTricSorted: return pairs_kernel<T, R, kBoxTricSorted, SW>;
+    case kBoxSearchSorted:  // binary64 only
+      if constexpr (sizeof(T) == 8) return pairs_kernel<T, R, kBoxSearchSorted, SW>;
+      return nullptr;
     default: return pairs_kernel<T, R, kBoxTricSearch, SW>;
   }
 }

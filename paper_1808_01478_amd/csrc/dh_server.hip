@@ -281,7 +281,7 @@ int start_job(dh_server *s, int slot_idx) {
   FrameParams fp;
   const int geometric =
       dh::frame_constants(j.box_type, j.has_box ? j.box : nullptr, j.r_max, j.n_bins, fp);
-  j.kind = dh::staged_kind(geometric, j.precision, fp.L, fp.s, j.n_bins, j.n);
+  j.kind = dh::staged_kind(geometric, j.precision, fp, j.n);
   fp.box = j.kind;
   fp.n_pad = static_cast<int32_t>(dh::padded_start(j.offsets.data(), k));
   const size_t staged_b = pts * dh::staged_point_bytes(j.precision, j.kind);
@@ -296,7 +296,7 @@ int start_job(dh_server *s, int slot_idx) {
   if (!rc) rc = grow_pinned(reinterpret_cast<void **>(&sl.h_out), &sl.h_out_cap, out_b);
   if (!rc) rc = grow_pinned(reinterpret_cast<void **>(&sl.h_oor), &sl.h_oor_cap, h_b);
   if (!rc) rc = grow_pinned(reinterpret_cast<void **>(&sl.h_pairs), &sl.h_pairs_cap, h_b);
-  if (!rc && j.kind == dh::kBoxTricSorted)
+  if (!rc && dh::padded_frame(j.kind))
     rc = grow_device(&sl.d_keys, &sl.keys_cap,
                      static_cast<size_t>(dh::sort_keys_count(j.n)) * sizeof(uint64_t));
   if (rc) return rc;
@@ -368,7 +368,7 @@ int start_job(dh_server *s, int slot_idx) {
   z.oor = fp.oor;
   z.pairs = sl.d_pairs;
   hipError_t staged;
-  if (j.kind == dh::kBoxTricSorted) {
+  if (dh::padded_frame(j.kind)) {
     staged = dh::launch_stage_sorted(j.precision, sl.d_in, sl.d_staged, j.n, j.offsets.data(), k,
                                      fp, static_cast<uint64_t *>(sl.d_keys), s->setup);
     if (staged == hipSuccess) staged = dh::launch_zero(z, s->setup);

@@ -143,6 +143,7 @@ __device__ __forceinline__ GroupPair classify(const GroupBox &I, const GroupBox 
 // the window are never flushed).
 struct WindowBounds {
   float lo, hi, in;
+  float slack;  // the absolute part of the widening
 };
 __device__ __forceinline__ WindowBounds window_bounds(const FrameParams *F, int b_lo, int win,
                                                       int stride) {
@@ -151,6 +152,7 @@ __device__ __forceinline__ WindowBounds window_bounds(const FrameParams *F, int 
   for (int k = 0; k < 6; ++k) size += fabsf(uni(F->cell32[k]));
   const float eps = size * 0x1p-16f, s = uni(F->s32);
   WindowBounds b;
+  b.slack = eps;
   b.lo = b_lo > 0 ? fmaxf(static_cast<float>(b_lo) / s * (1.f - 0x1p-12f) - eps, 0.f) : 0.f;
   b.hi = static_cast<float>(b_lo + win) / s * (1.f + 0x1p-12f) + eps;
   b.in = fmaxf(static_cast<float>(stride - 2) / s * (1.f - 0x1p-12f) - eps, 0.f);
@@ -400,7 +402,7 @@ __device__ __forceinline__ void run_sorted(const PairKernelArgs &a, const WorkIt
 // input points: the first m slices in rs (four bits each) of the unit at ib
 // against the j of [j0, j1) in `left` (bit b: j0 + 2b and the next). Not
 // inlined: it runs for one group of pairs in some 10^5.
-template <int MODE>
+template <int MODE, int BOX>
 __device__ __attribute__((noinline)) void exact_pairs(const FrameParams *F, int hist, int sweep,
                                                       int ib, int i1, int j0, int j1,
                                                       uint32_t rs, int m, uint32_t left,
@@ -425,12 +427,78 @@ __device__ __attribute__((noinline)) void exact_pairs(const FrameParams *F, int 
         const int i = ib + 64 * static_cast<int>((rs >> (4 * k)) & 15u) + lane;
         const bool ok = i < i1 && (!diag || j > i);
         const int64_t p = 3 * static_cast<int64_t>(index[ok ? i : ib]);
-        const double t = t64<kBoxTric>(in[p], in[p + 1], in[p + 2], xj, yj, zj, g);
+        const double t = t64<BOX>(in[p], in[p + 1], in[p + 2], xj, yj, zj, g);
         // (a NaN t takes the other operand: out of range)
         const uint32_t b = kBinBits + static_cast<uint32_t>(min_arith(t, 0x1p25));
         count.template add<true>(ok ? b : kNoBits);
       }
     }
+}
+
+// The images of a pair of groups of a frame with image search (binary64): the
+// lattice shifts N under which some pair of the two groups can be nearest and
+// within the window, as an ordered list of at most kListed, from the distance
+// bounds of the groups' boxes under every N that a pair can need (its Eq. 5
+// wrap and one more step either way). A shift whose lower bound exceeds the
+// smallest upper bound is never the nearest; one beyond the window's end can
+// be the nearest only of pairs that are out of range, whose other images are
+// farther still. Frames come here only when no image outside the 27 of the
+// canonical search is ever nearest (see staged_kind), so the canonical minimum
+// over a pair's 27 images is the minimum over this list.
+constexpr int kListed = 8;
+struct Images {
+  uint64_t list;  // eight bits each: (a + 2) + 5 (b + 2) + 25 (c + 2)
+  int n;          // entries; kListed + 1: more than fit
+  float far2;     // square of an upper bound of every pair's distance
+};
+__device__ __forceinline__ Images group_images(const GroupBox &I, const GroupBox &J,
+                                               const float (&cell)[6], float r_hi, float slack) {
+  int n_lo[3], n_hi[3];
+  float dc[3], hw[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const int64_t lo = static_cast<int64_t>(J.ulo[k]) - static_cast<int64_t>(I.uhi[k]);
+    const int64_t hi = static_cast<int64_t>(J.uhi[k]) - static_cast<int64_t>(I.ulo[k]);
+    n_lo[k] = static_cast<int>((lo - kWrapMargin + 0x80000000ll) >> 32) - 1;
+    n_hi[k] = static_cast<int>((hi + kWrapMargin + 0x80000000ll) >> 32) + 1;
+    // centre and half width of the interval of j - i
+    dc[k] = 0.5f * ((J.clo[k] + J.chi[k]) - (I.clo[k] + I.chi[k]));
+    hw[k] = 0.5f * ((J.chi[k] - J.clo[k]) + (I.chi[k] - I.clo[k]));
+  }
+  // squares of the least and largest distance of a pair under each shift
+  auto scan = [&](auto &&visit) {
+    for (int c = -2; c <= 2; ++c) {
+      const float fc = static_cast<float>(c), tz = fabsf(dc[2] - fc * cell[5]);
+      const float gz = fmaxf(tz - hw[2], 0.f), fz = tz + hw[2];
+      for (int b = -2; b <= 2; ++b) {
+        const float fb = static_cast<float>(b), ty = fabsf(dc[1] - (fb * cell[2] + fc * cell[4]));
+        const float gy = fmaxf(ty - hw[1], 0.f), fy = ty + hw[1];
+        const float g2 = gz * gz + gy * gy, f2 = fz * fz + fy * fy;
+        const bool in = c >= n_lo[2] && c <= n_hi[2] && b >= n_lo[1] && b <= n_hi[1];
+        for (int a = -2; a <= 2; ++a) {
+          const float tx = fabsf(dc[0] - (static_cast<float>(a) * cell[0] + fb * cell[1] +
+                                          fc * cell[3]));
+          const float gx = fmaxf(tx - hw[0], 0.f), fx = tx + hw[0];
+          visit(in && a >= n_lo[0] && a <= n_hi[0], g2 + gx * gx, f2 + fx * fx,
+                (a + 2) + 5 * (b + 2) + 25 * (c + 2));
+        }
+      }
+    }
+  };
+  Images m;
+  m.far2 = __builtin_inff();
+  scan([&](bool in, float, float f2, int) { m.far2 = in ? fminf(m.far2, f2) : m.far2; });
+  // widened by far more than the rounding of the bounds and of any distance
+  const float lim = fminf(__builtin_sqrtf(m.far2) * (1.f + 0x1p-12f) + slack, r_hi);
+  m.list = 0;
+  m.n = 0;
+  scan([&](bool in, float g2, float, int id) {
+    if (in && g2 <= lim * lim) {
+      if (m.n < kListed) m.list |= static_cast<uint64_t>(id) << (8 * m.n);
+      m.n = m.n <= kListed ? m.n + 1 : m.n;
+    }
+  });
+  return m;
 }
 
 // One work item of a spatially sorted binary64 frame. binary64 counts follow
@@ -451,7 +519,7 @@ __device__ __attribute__((noinline)) void exact_pairs(const FrameParams *F, int 
 // 1,000,000-point clustered triclinic frame (20,000 bins) took 371 ms with
 // every pair computed and that root, and takes 178 ms; 100,000 points in a
 // cube (cut-off half the edge, so little is skipped) 4.34 and 3.49 ms.
-template <int MODE>
+template <int MODE, bool SEARCH>
 __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const WorkItem &w,
                                              const FrameParams *F, int *s_unit, int *s_item) {
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
@@ -470,7 +538,7 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
   const double h22 = uni(F->h22) * is, h23 = uni(F->h23) * is, h33 = uni(F->h33) * is;
   const int win = uni(F->win);
   const WindowBounds wb = window_bounds(F, w.sweep * win, win, a.stride);
-  const bool noclamp = MODE == kModeLds && uni(F->noclamp) != 0;
+  const bool noclamp = MODE == kModeLds && !SEARCH && uni(F->noclamp) != 0;
   const Count<MODE> count(F, w, lane);
   using Yes = std::true_type;
   using No = std::false_type;
@@ -479,6 +547,9 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
   GroupPair gp;
   double shx = 0.0, shy = 0.0, shz = 0.0;  // the lane's shift B n
   float near_hi = 0.f;  // thr's upper word, as a float (see below)
+  [[maybe_unused]] Images img{};
+  // image search: pairs evaluated over more than one image, and those images
+  [[maybe_unused]] uint64_t n_searched = 0, n_images = 0;
 
   auto frac = [&](auto axis_c, double x, double y, double z) {
     constexpr int K = decltype(axis_c)::value;
@@ -490,8 +561,11 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
       return z * h33;
   };
   // One group against M slices (four bits each in rs) of one kind.
-  auto pass = [&](auto kind_c, auto m_c, auto clamp_c, auto diag_c, uint32_t rs, int g) {
+  // IMAGES: shifts tried per pair (1 without image search, whose shift is gp's).
+  auto pass = [&](auto kind_c, auto images_c, auto m_c, auto clamp_c, auto diag_c, uint32_t rs,
+                  int g) {
     constexpr int KIND = decltype(kind_c)::value, M = decltype(m_c)::value;
+    constexpr int IMAGES = decltype(images_c)::value;
     constexpr bool DIAG = decltype(diag_c)::value;
     const int j0 = jb + 64 * g, j1 = min(j0 + 64, w.j1);
     auto slice = [&](int k) { return ib + 64 * static_cast<int>((rs >> (4 * k)) & 15u) + lane; };
@@ -502,7 +576,7 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
     } else {
       // (a lane past the end of the item holds a point at infinity: q = +inf,
       // beyond every bin)
-      double sx[M], sy[M], sz[M];
+      double sx[M * IMAGES], sy[M * IMAGES], sz[M * IMAGES];
       [[maybe_unused]] double fi[3][M];
       constexpr int K = KIND >= kFix && KIND < kSlow ? KIND - kFix : 0;
 #pragma unroll
@@ -511,6 +585,24 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
         const bool ok = i < w.i1;
         const double *const p = P + 3 * static_cast<int64_t>(ok ? i : ib);
         const int src = g * kUnitSlices + static_cast<int>((rs >> (4 * k)) & 15u);
+        if constexpr (SEARCH) {
+          const uint32_t lo = static_cast<uint32_t>(
+              __builtin_amdgcn_readlane(static_cast<int>(img.list), src));
+          const uint32_t hi = static_cast<uint32_t>(
+              __builtin_amdgcn_readlane(static_cast<int>(img.list >> 32), src));
+          const int n = __builtin_amdgcn_readlane(img.n, src);
+#pragma unroll
+          for (int e = 0; e < IMAGES; ++e) {
+            // (a list shorter than IMAGES repeats its first entry)
+            const int at = e < n ? e : 0;
+            const int id = static_cast<int>((at < 4 ? lo >> (8 * at) : hi >> (8 * at - 32)) & 255u);
+            const double na = id % 5 - 2, nb = id / 5 % 5 - 2, nc = id / 25 - 2;
+            sx[k * IMAGES + e] = (ok ? p[0] : __builtin_inf()) + ((na * ax + nb * bx) + nc * cx);
+            sy[k * IMAGES + e] = p[1] + (nb * by + nc * cy);
+            sz[k * IMAGES + e] = p[2] + nc * cz;
+          }
+          continue;
+        }
         sx[k] = p[0] + lane_value(shx, src);
         sy[k] = p[1] + lane_value(shy, src);
         sz[k] = p[2] + lane_value(shz, src);
@@ -554,6 +646,18 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
         }
 #pragma unroll
         for (int k = 0; k < M; ++k) {
+          if constexpr (SEARCH) {
+            double u = 0.0;
+#pragma unroll
+            for (int e = 0; e < IMAGES; ++e) {
+              const double dx = p.x - sx[k * IMAGES + e], dy = p.y - sy[k * IMAGES + e],
+                           dz = p.z - sz[k * IMAGES + e];
+              const double v = fma(dz, dz, fma(dy, dy, dx * dx));
+              u = e == 0 ? v : min_arith(u, v);
+            }
+            b[k] = root_bits64(u, gap);
+            continue;
+          }
           double dx = p.x - sx[k], dy = p.y - sy[k], dz = p.z - sz[k];
           if constexpr (KIND == kSlow) {
             const double na = rint(fj[0] - fi[0][k]), nb = rint(fj[1] - fi[1][k]),
@@ -605,10 +709,20 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
       }
     }
     if (__builtin_expect(left != 0u, 0))
-      exact_pairs<MODE>(F, w.hist, w.sweep, ib, w.i1, j0, j1, rs, M, left, DIAG);
+      exact_pairs<MODE, SEARCH ? kBoxTricSearch : kBoxTric>(F, w.hist, w.sweep, ib, w.i1, j0, j1,
+                                                            rs, M, left, DIAG);
+    if constexpr (SEARCH && IMAGES != 1) {
+      const uint64_t n = static_cast<uint64_t>(j1 - j0);
+      uint64_t pairs = DIAG ? n * (n - 1) / 2 : 0;
+      for (int k = 0; k < M && !DIAG; ++k)
+        pairs += n * static_cast<uint64_t>(max(0, min(64, w.i1 - (slice(k) - lane))));
+      n_searched += pairs;
+      n_images += pairs * (KIND == kExact ? kShifts : IMAGES);
+    }
   };
   // the slices in `m` (bit r) against group g, in passes of as many as fit
-  auto passes = [&](auto kind_c, auto clamp_c, uint32_t m, int g) {
+  auto passes = [&](auto kind_c, auto images_c, auto clamp_c, uint32_t m, int g) {
+    constexpr int IMAGES = decltype(images_c)::value;
     auto take = [&](int n) {
       uint32_t rs = 0;
       for (int k = 0; k < n; ++k) {
@@ -617,15 +731,20 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
       }
       return rs;
     };
-    while (__builtin_popcount(m) >= 4) pass(kind_c, Int<4>{}, clamp_c, No{}, take(4), g);
-    if (__builtin_popcount(m) >= 2) pass(kind_c, Int<2>{}, clamp_c, No{}, take(2), g);
-    if (m != 0u) pass(kind_c, Int<1>{}, clamp_c, No{}, take(1), g);
+    if constexpr (IMAGES == 1)
+      while (__builtin_popcount(m) >= 4)
+        pass(kind_c, images_c, Int<4>{}, clamp_c, No{}, take(4), g);
+    if constexpr (IMAGES <= 2)
+      while (__builtin_popcount(m) >= 2)
+        pass(kind_c, images_c, Int<2>{}, clamp_c, No{}, take(2), g);
+    while (m != 0u) pass(kind_c, images_c, Int<1>{}, clamp_c, No{}, take(1), g);
   };
 
   const int n_ib = (w.i1 - w.i0 + kUnitPoints - 1) / kUnitPoints;
   const int n_wave = static_cast<int>(blockDim.x) / 64;
   int gpu = kUnitGroups;
-  while (gpu > 1 && n_ib * ((w.j1 - w.j0 + 64 * gpu - 1) / (64 * gpu)) < 4 * n_wave) gpu >>= 1;
+  while (gpu > 1 && n_ib * ((w.j1 - w.j0 + 64 * gpu - 1) / (64 * gpu)) < (SEARCH ? 2 : 4) * n_wave)
+    gpu >>= 1;
   const int n_unit = n_ib * ((w.j1 - w.j0 + 64 * gpu - 1) / (64 * gpu));
   if (wave == n_unit && lane == 0)
     *s_item = static_cast<int>(gridDim.x) + atomicAdd(a.counter, 1);
@@ -638,7 +757,20 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
       const bool valid = ib + 64 * r < w.i1 && gr < gpu && jb + 64 * gr < w.j1 &&
                          !((w.flags & kItemDiag) && gj < gi);
       const GroupBox &bi = boxes[valid ? gi : ib >> 6], &bj = boxes[valid ? gj : jb >> 6];
-      gp = classify<true>(bi, bj, cell, wb.lo, wb.hi, wb.in);
+      if constexpr (SEARCH) {
+        img = group_images(bi, bj, cell, wb.hi, wb.slack);
+        gp.kind = img.n == 0 || img.far2 < wb.lo * wb.lo ? kSkip
+                  : img.n == 1                           ? kFast
+                  : img.n == 2                           ? kFix
+                  : img.n <= 4                           ? kFix + 1
+                  : img.n <= kListed                     ? kFix + 2
+                                                         : kExact;
+        // (the nearest image's shift is in the list when it is within the window)
+        gp.in_window = img.far2 < fminf(wb.in * wb.in, wb.hi * wb.hi);
+        gp.n[0] = gp.n[1] = gp.n[2] = 0;
+      } else {
+        gp = classify<true>(bi, bj, cell, wb.lo, wb.hi, wb.in);
+      }
       shx = (gp.n[0] * ax + gp.n[1] * bx) + gp.n[2] * cx;
       shy = gp.n[1] * by + gp.n[2] * cy;
       shz = gp.n[2] * cz;
@@ -682,24 +814,36 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
         return static_cast<uint32_t>(m >> (g * kUnitSlices)) & ((1u << kUnitSlices) - 1u);
       };
       const uint32_t fast = bits(m_fast);
-      if (MODE == kModeLds && (fast & ~bits(m_in)) == 0u)
-        passes(Int<kFast>{}, No{}, fast, g);
+      const bool inside = MODE == kModeLds && (fast & ~bits(m_in)) == 0u;
+      if (inside)
+        passes(Int<kFast>{}, Int<1>{}, No{}, fast, g);
       else
-        passes(Int<kFast>{}, Yes{}, fast, g);
-      passes(Int<kFix>{}, Yes{}, bits(m_fix0), g);
-      passes(Int<kFix + 1>{}, Yes{}, bits(m_fix1), g);
-      passes(Int<kFix + 2>{}, Yes{}, bits(m_fix2), g);
-      passes(Int<kSlow>{}, Yes{}, bits(m_slow), g);
+        passes(Int<kFast>{}, Int<1>{}, Yes{}, fast, g);
+      if constexpr (SEARCH) {
+        passes(Int<kFast>{}, Int<2>{}, Yes{}, bits(m_fix0), g);
+        passes(Int<kFast>{}, Int<4>{}, Yes{}, bits(m_fix1), g);
+        passes(Int<kFast>{}, Int<kListed>{}, Yes{}, bits(m_fix2), g);
+      } else {
+        passes(Int<kFix>{}, Int<1>{}, Yes{}, bits(m_fix0), g);
+        passes(Int<kFix + 1>{}, Int<1>{}, Yes{}, bits(m_fix1), g);
+        passes(Int<kFix + 2>{}, Int<1>{}, Yes{}, bits(m_fix2), g);
+        passes(Int<kSlow>{}, Int<1>{}, Yes{}, bits(m_slow), g);
+      }
       for (uint32_t m = bits(m_exact); m != 0u; m &= m - 1u)
-        pass(Int<kExact>{}, Int<1>{}, Yes{}, No{}, static_cast<uint32_t>(__builtin_ctz(m)), g);
+        pass(Int<kExact>{}, Int<0>{}, Int<1>{}, Yes{}, No{},
+             static_cast<uint32_t>(__builtin_ctz(m)), g);
       if (const uint32_t m = bits(m_diag)) {
         // at most one slice of the unit is the group itself
         const uint32_t r = static_cast<uint32_t>(__builtin_ctz(m));
-        switch (__builtin_amdgcn_readlane(gp.kind, g * kUnitSlices + static_cast<int>(r))) {
-          case kFast: pass(Int<kFast>{}, Int<1>{}, Yes{}, Yes{}, r, g); break;
-          case kExact: pass(Int<kExact>{}, Int<1>{}, Yes{}, Yes{}, r, g); break;
-          default: pass(Int<kSlow>{}, Int<1>{}, Yes{}, Yes{}, r, g); break;
-        }
+        const int kind = __builtin_amdgcn_readlane(gp.kind, g * kUnitSlices + static_cast<int>(r));
+        if (kind == kFast)
+          pass(Int<kFast>{}, Int<1>{}, Int<1>{}, Yes{}, Yes{}, r, g);
+        else if (kind == kExact)
+          pass(Int<kExact>{}, Int<0>{}, Int<1>{}, Yes{}, Yes{}, r, g);
+        else if constexpr (SEARCH)
+          pass(Int<kFast>{}, Int<kListed>{}, Int<1>{}, Yes{}, Yes{}, r, g);
+        else
+          pass(Int<kSlow>{}, Int<1>{}, Int<1>{}, Yes{}, Yes{}, r, g);
       }
     }
     int nu = 0;
@@ -707,6 +851,12 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
     u = uni(nu);
     if (u == n_unit && lane == 0)
       *s_item = static_cast<int>(gridDim.x) + atomicAdd(a.counter, 1);
+  }
+  if constexpr (SEARCH) {
+    if (F->searched != nullptr && n_searched != 0 && lane == 0) {
+      atomicAdd(F->searched, static_cast<unsigned long long>(n_searched));
+      atomicAdd(F->searched + 1, static_cast<unsigned long long>(n_images));
+    }
   }
 }
 

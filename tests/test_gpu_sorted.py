@@ -61,6 +61,41 @@ def test_shorter_cutoff_is_a_prefix(ctx, k, box_type, clustered, precision):
     ctx.set_config(None)
 
 
+@pytest.mark.parametrize("clustered", [False, True])
+@pytest.mark.parametrize("k", range(len(SIZES)))
+def test_search_against_no_search(ctx, k, clustered):
+    """binary64 image search of sorted frames: below half the cell the same
+    scale needs no search, so the histograms must agree there; beyond it every
+    pair is in a bin or out of range; bin windows and global atomics give the
+    same counts, and a second species split only moves pairs between rows."""
+    full = frame(SIZES[k], workloads.BOX_TRICLINIC, clustered, 0.8, 4096)
+    print(f"\n[case] search {SIZES[k]} clustered={clustered}", flush=True)
+    ctx.set_config(None)
+    ref, ref_oor = run_gpu(ctx, full, 1)
+    assert np.array_equal(ref.sum(1) + ref_oor, np.array(full.hist_pairs(), np.uint64))
+    for div in (2, 8):
+        part = frame(SIZES[k], workloads.BOX_TRICLINIC, clustered, 0.8 / div, 4096 // div)
+        h, _ = run_gpu(ctx, part, 1)
+        assert np.array_equal(h, ref[:, :4096 // div]), div
+    one = workloads.Frame(full.coords, np.array([0, full.n], np.int64), full.box_type, full.box,
+                          full.r_max, full.n_bins, "one species")
+    h, _ = run_gpu(ctx, one, 1)
+    assert np.array_equal(h[0], ref.sum(0))
+    for knobs in ([4, 4, 128, 1, 0, 4, 1024, 0], [8, 1, 128, 0, 0, 16, 256, 1]):
+        ctx.set_config(knobs)
+        h, oor = run_gpu(ctx, full, 1)
+        assert np.array_equal(h, ref) and np.array_equal(oor, ref_oor), knobs
+    ctx.set_config(None)
+
+
+def test_search_oracle(ctx):
+    fr = frame([66_000, 300], workloads.BOX_TRICLINIC, True, 1.0, 500)
+    print(f"\n[case] search oracle {fr.name}", flush=True)
+    ref = oracle.frame_histogram(fr)
+    h, oor = run_gpu(ctx, fr, 1)
+    assert np.array_equal(h, ref.hist) and np.array_equal(oor, ref.out_of_range)
+
+
 @pytest.mark.parametrize("box_type", [workloads.BOX_ORTHO, workloads.BOX_TRICLINIC])
 def test_oracle(ctx, box_type):
     fr = frame(SIZES[1], box_type, True, 0.3, 700)
