@@ -62,7 +62,7 @@ inline size_t staged_point_bytes(int precision, int kind) {
   return precision != 0 || padded_frame(kind) ? 32 : 16;
 }
 inline int64_t sort_keys_count(int64_t n) {
-  int64_t p = 2048;
+  int64_t p = 8192;  // one block of the sort
   while (p < n) p <<= 1;
   return p;
 }

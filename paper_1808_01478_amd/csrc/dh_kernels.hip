@@ -125,52 +125,87 @@ __global__ void sort_keys_kernel(const double *__restrict__ in, int64_t n, int64
   }
 }
 
-constexpr int kBitonicBlock = 2048;  // keys sorted in LDS by one workgroup of 1024
+constexpr int kBitonicBlock = 8192;  // keys sorted in LDS by one workgroup of 1024
 
-__device__ __forceinline__ void bitonic_cas(uint64_t &a, uint64_t &b, bool ascending) {
+template <typename K>
+__device__ __forceinline__ void bitonic_cas(K &a, K &b, bool ascending) {
   if ((a > b) == ascending) {
-    const uint64_t t = a;
+    const K t = a;
     a = b;
     b = t;
   }
 }
 
+// Index of the lower element of compare-exchange t of a step j (a power of
+// two): t with a zero inserted at the bit of j.
+__device__ __forceinline__ int cas_index(int t, int j) {
+  return ((t & ~(j - 1)) << 1) | (t & (j - 1));
+}
+
+// The step j of stage kk on a block of keys in LDS (1,024 threads). The 128
+// elements of a wave's 64 exchanges are the same in every step below 128, so
+// only steps of 64 and more need a barrier; the others need the wave's own LDS
+// order, which the hardware keeps.
+__device__ __forceinline__ void bitonic_step(uint64_t *key, int j, int64_t kk, int64_t base) {
+  if (j >= 64)
+    __syncthreads();
+  else
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+  for (int t = threadIdx.x; t < kBitonicBlock / 2; t += 1024) {
+    const int at = cas_index(t, j);
+    bitonic_cas(key[at], key[at + j], ((base + at) & kk) == 0);
+  }
+}
+
+// (The whole sort of 100,000 points, 131,072 keys: 5 launches here at 22 us and
+// 6 over the whole array at 5 us. With blocks of 2,048 keys, divisions for the
+// index, a barrier per step and one step per global launch there were 7 and 21
+// launches.)
 // All stages k <= kBitonicBlock of each block (first == true), or the steps
 // j < kBitonicBlock of stage k (first == false), in LDS.
 __global__ __launch_bounds__(1024) void bitonic_local_kernel(uint64_t *__restrict__ keys,
                                                              int64_t k_stage, int first) {
   __shared__ uint64_t sk[kBitonicBlock];
-  const int t = threadIdx.x;
   const int64_t base = static_cast<int64_t>(blockIdx.x) * kBitonicBlock;
-  sk[t] = keys[base + t];
-  sk[t + 1024] = keys[base + t + 1024];
-  const int64_t k_lo = first ? 2 : k_stage, k_hi = first ? kBitonicBlock : k_stage;
-  for (int64_t kk = k_lo; kk <= k_hi; kk <<= 1) {
-    for (int j = kk / 2 < kBitonicBlock / 2 ? static_cast<int>(kk / 2) : kBitonicBlock / 2;
-         j > 0; j >>= 1) {
-      __syncthreads();
-      const int lo = 2 * j * (t / j) + (t % j);
-      const bool asc = ((base + lo) & kk) == 0;
-      bitonic_cas(sk[lo], sk[lo + j], asc);
-    }
-  }
+  for (int t = threadIdx.x; t < kBitonicBlock; t += 1024) sk[t] = keys[base + t];
   __syncthreads();
-  keys[base + t] = sk[t];
-  keys[base + t + 1024] = sk[t + 1024];
+  const int64_t k_lo = first ? 2 : k_stage, k_hi = first ? kBitonicBlock : k_stage;
+  for (int64_t kk = k_lo; kk <= k_hi; kk <<= 1)
+    for (int j = kk / 2 < kBitonicBlock / 2 ? static_cast<int>(kk / 2) : kBitonicBlock / 2;
+         j > 0; j >>= 1)
+      bitonic_step(sk, j, kk, base);
+  __syncthreads();
+  for (int t = threadIdx.x; t < kBitonicBlock; t += 1024) keys[base + t] = sk[t];
 }
 
-// One step j >= kBitonicBlock of stage k over the whole array.
+// The step j >= kBitonicBlock of stage k over the whole array, with TWO the
+// step j / 2 as well (half the passes over memory and half the launches).
+template <bool TWO>
 __global__ void bitonic_global_kernel(uint64_t *__restrict__ keys, int64_t npad, int64_t j,
                                       int64_t k_stage) {
-  const int64_t half = npad / 2;
   const int64_t step = static_cast<int64_t>(gridDim.x) * blockDim.x;
-  for (int64_t t = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; t < half;
-       t += step) {
-    const int64_t lo = 2 * j * (t / j) + (t % j);
-    uint64_t a = keys[lo], b = keys[lo + j];
-    bitonic_cas(a, b, (lo & k_stage) == 0);
-    keys[lo] = a;
-    keys[lo + j] = b;
+  const int64_t h = TWO ? j / 2 : j;
+  for (int64_t t = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
+       t < npad / (TWO ? 4 : 2); t += step) {
+    const int64_t at = ((t & ~(h - 1)) << (TWO ? 2 : 1)) | (t & (h - 1));
+    const bool asc = (at & k_stage) == 0;
+    if constexpr (TWO) {
+      uint64_t a = keys[at], b = keys[at + h], c = keys[at + j], e = keys[at + j + h];
+      bitonic_cas(a, c, asc);
+      bitonic_cas(b, e, asc);
+      bitonic_cas(a, b, asc);
+      bitonic_cas(c, e, asc);
+      keys[at] = a;
+      keys[at + h] = b;
+      keys[at + j] = c;
+      keys[at + j + h] = e;
+    } else {
+      uint64_t a = keys[at], b = keys[at + j];
+      bitonic_cas(a, b, asc);
+      keys[at] = a;
+      keys[at + j] = b;
+    }
   }
 }
 
@@ -237,6 +272,141 @@ __global__ void stage_sorted_kernel(const double *__restrict__ in,
   b.mag = 0.f;
   for (uint32_t &v : b.unused) v = 0u;
   if (lane == 0) reinterpret_cast<GroupBox *>(out + 28 * static_cast<int64_t>(p.n_pad))[group] = b;
+}
+
+// Morton order alone leaves loose groups: 64 consecutive points straddle the
+// curve's jumps (mean box 8.3 x 6.2 x 4.6 where 64 points fill a cube of 4.5),
+// and everything decided per pair of groups weakens with that. So each run of
+// kRefine points of the curve is halved six times, along the axis in which its
+// points spread most, down to the groups of 64 (mean box 4.7 x 4.7 x 4.5).
+// Binary64 against the Morton order alone: 1,000,000 clustered triclinic points
+// 176 and 160 ms, image search of 70,001 points 7.33 and 4.20 ms.
+//
+// One workgroup per run: 16-bit fractional coordinates in LDS, a 32-bit key
+// (coordinate : place in the run) per point, four consecutive keys per thread
+// in registers. A level sorts its segments by the bitonic network (308 steps
+// in all): steps of 1 and 2 stay in a thread, those up to 128 in a wave
+// (shuffles), only the 20 wider ones go through LDS with a barrier (100,000
+// points: 141 us a launch with all steps in LDS, 99 us so). Runs of 2,048 are
+// quicker to halve and worse (66 us; image search of 70,001 points 5.0 against
+// 4.2 ms).
+constexpr int kRefine = 4096;
+
+__global__ __launch_bounds__(1024) void refine_order_kernel(const double *__restrict__ in,
+                                                            uint64_t *__restrict__ keys,
+                                                            SpeciesOffsets off, int32_t k,
+                                                            FrameParams p) {
+  __shared__ uint16_t co[3][kRefine];
+  __shared__ uint4 key[kRefine / 4];
+  __shared__ uint32_t own[kRefine];
+  __shared__ uint32_t lo[kRefine / 128][3], hi[kRefine / 128][3];
+  const int tid = threadIdx.x, lane = tid & 63;
+  int64_t b0 = 0;
+  int s = 0;
+  for (; s + 1 < k; ++s) {
+    const int64_t nb = (off.v[s + 1] - off.v[s] + kRefine - 1) / kRefine;
+    if (blockIdx.x < b0 + nb) break;
+    b0 += nb;
+  }
+  const int64_t first = off.v[s] + (blockIdx.x - b0) * kRefine;
+  const int count = static_cast<int>(min(static_cast<int64_t>(kRefine), off.v[s + 1] - first));
+  for (int q = tid; q < count; q += 1024) {
+    own[q] = static_cast<uint32_t>(keys[first + q] & 0x7FFFFFFFull);
+    const int64_t i = 3 * static_cast<int64_t>(own[q]);
+    const double x = in[i], y = in[i + 1], z = in[i + 2];
+    co[0][q] = static_cast<uint16_t>(fix32(fma(z, p.h13, fma(y, p.h12, x * p.h11))) >> 16);
+    co[1][q] = static_cast<uint16_t>(fix32(fma(z, p.h23, y * p.h22)) >> 16);
+    co[2][q] = static_cast<uint16_t>(fix32(z * p.h33) >> 16);
+  }
+  // lengths of the cell vectors: the spread along an axis in length units
+  const float len[3] = {static_cast<float>(p.ax),
+                        sqrtf(static_cast<float>(p.bx * p.bx + p.by * p.by)),
+                        sqrtf(static_cast<float>(p.cx * p.cx + p.cy * p.cy + p.cz * p.cz))};
+  // the thread's four consecutive places: keys at 4 tid .. 4 tid + 3
+  uint32_t v[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) v[r] = static_cast<uint32_t>(4 * tid + r);
+  for (int m = kRefine; m > 64; m >>= 1) {
+    const int g = 4 * tid / m;
+    if (tid < kRefine / 128 * 3) {
+      lo[tid / 3][tid % 3] = 0xFFFFFFFFu;
+      hi[tid / 3][tid % 3] = 0u;
+    }
+    __syncthreads();
+    // (a wave holds 256 places, so at m = 128 two segments)
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax) {
+      uint32_t l = 0xFFFFFFFFu, h = 0u;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int e = static_cast<int>(v[r] & (kRefine - 1));
+        const bool ok = e < count;
+        l = min(l, ok ? static_cast<uint32_t>(co[ax][e]) : 0xFFFFFFFFu);
+        h = max(h, ok ? static_cast<uint32_t>(co[ax][e]) : 0u);
+      }
+#pragma unroll
+      for (int o = 16; o > 0; o >>= 1) {
+        l = min(l, static_cast<uint32_t>(__shfl_xor(l, o)));
+        h = max(h, static_cast<uint32_t>(__shfl_xor(h, o)));
+      }
+      if ((lane & 31) == 0) {
+        atomicMin(&lo[g][ax], l);
+        atomicMax(&hi[g][ax], h);
+      }
+    }
+    __syncthreads();
+    int ax = 0;
+    float widest = -1.f;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const float w = static_cast<float>(static_cast<int>(hi[g][a] - lo[g][a])) * len[a];
+      if (w > widest) {
+        widest = w;
+        ax = a;
+      }
+    }
+    __syncthreads();  // (lo and hi are cleared for the next level)
+    // places past the run's end go last
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const uint32_t e = v[r] & (kRefine - 1);
+      v[r] = ((static_cast<int>(e) < count ? static_cast<uint32_t>(co[ax][e]) : 0xFFFFFu) << 12) |
+             e;
+    }
+    for (int kk = 2; kk <= m; kk <<= 1)
+      for (int j = kk / 2; j > 0; j >>= 1) {
+        const bool asc = ((4 * tid) & (m - 1) & kk) == 0;
+        if (j == 1) {
+          // (stage 2 sorts the second two the other way)
+          bitonic_cas(v[0], v[1], asc);
+          bitonic_cas(v[2], v[3], kk == 2 ? false : asc);
+        } else if (j == 2) {
+          bitonic_cas(v[0], v[2], asc);
+          bitonic_cas(v[1], v[3], asc);
+        } else {
+          uint32_t o[4];
+          if (j <= 128) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) o[r] = __shfl_xor(v[r], j / 4);
+          } else {
+            __syncthreads();
+            key[tid] = make_uint4(v[0], v[1], v[2], v[3]);
+            __syncthreads();
+            const uint4 w = key[tid ^ (j / 4)];
+            o[0] = w.x;
+            o[1] = w.y;
+            o[2] = w.z;
+            o[3] = w.w;
+          }
+          const bool least = ((tid & (j / 4)) == 0) == asc;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) v[r] = least ? min(v[r], o[r]) : max(v[r], o[r]);
+        }
+      }
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    if (4 * tid + r < count) keys[first + 4 * tid + r] = own[v[r] & (kRefine - 1)];
 }
 
 // binary64 staging of a sorted frame, one group of 64 points per wave: the
@@ -430,21 +600,30 @@ hipError_t launch_stage_sorted(int precision, const double *in, void *out, int64
   SpeciesOffsets off;
   for (int s = 0; s <= kMaxSpeciesStage; ++s) off.v[s] = offsets[s < n_species ? s : n_species];
   const int threads = 256;
+  const int wgs = static_cast<int>((fp.n_pad / 64 + 3) / 4);
   sort_keys_kernel<<<grid_for(npad, threads), threads, 0, st>>>(in, n, npad, off, n_species, fp,
                                                                 keys);
   const int blocks = static_cast<int>(npad / kBitonicBlock);
   bitonic_local_kernel<<<blocks, 1024, 0, st>>>(keys, 0, 1);
   for (int64_t kk = 2 * kBitonicBlock; kk <= npad; kk <<= 1) {
-    for (int64_t j = kk / 2; j >= kBitonicBlock; j >>= 1)
-      bitonic_global_kernel<<<grid_for(npad / 2, threads), threads, 0, st>>>(keys, npad, j, kk);
+    int64_t j = kk / 2;
+    for (; j >= 2 * kBitonicBlock; j >>= 2)
+      bitonic_global_kernel<true><<<grid_for(npad / 4, threads), threads, 0, st>>>(keys, npad, j,
+                                                                                  kk);
+    if (j >= kBitonicBlock)
+      bitonic_global_kernel<false><<<grid_for(npad / 2, threads), threads, 0, st>>>(keys, npad, j,
+                                                                                   kk);
     bitonic_local_kernel<<<blocks, 1024, 0, st>>>(keys, kk, 0);
   }
-  const int wgs = static_cast<int>((fp.n_pad / 64 + 3) / 4);
-  if (precision == 1)
-    stage_sorted64_kernel<<<wgs, threads, 0, st>>>(in, keys, off, n_species, fp,
-                                                   static_cast<char *>(out));
-  else
+  if (precision == 0) {
     stage_sorted_kernel<<<wgs, threads, 0, st>>>(in, keys, off, n_species, fp,
+                                                 static_cast<char *>(out));
+    return hipGetLastError();
+  }
+  int64_t runs = 0;
+  for (int s = 0; s < n_species; ++s) runs += (off.v[s + 1] - off.v[s] + kRefine - 1) / kRefine;
+  refine_order_kernel<<<static_cast<int>(runs), 1024, 0, st>>>(in, keys, off, n_species, fp);
+  stage_sorted64_kernel<<<wgs, threads, 0, st>>>(in, keys, off, n_species, fp,
                                                  static_cast<char *>(out));
   return hipGetLastError();
 }
