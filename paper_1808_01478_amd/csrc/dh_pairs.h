@@ -327,14 +327,6 @@ __device__ __forceinline__ uint32_t bin_bits32(float t, float offset = kBinOffse
   return __float_as_uint(fmaf(t, kBinScale, offset));
 }
 
-// median of three unsigned values: x clamped to [lo, hi] when lo <= hi (the
-// compiler forms v_med3_u32 only for constant bounds)
-__device__ __forceinline__ uint32_t med3_u32(uint32_t x, uint32_t lo, uint32_t hi) {
-  uint32_t r;
-  asm("v_med3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(lo), "v"(hi));
-  return r;
-}
-
 // min(a, b) for an a that is an arithmetic result (never a signalling NaN):
 // one v_min_f64, without the canonicalisation fmin adds for arbitrary input.
 // A NaN a gives b, as fmin does.
