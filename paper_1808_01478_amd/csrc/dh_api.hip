@@ -257,6 +257,16 @@ void octant_images(FrameParams &fp) {
       fp.oct_shift[o][k] = static_cast<uint8_t>(k < n ? list[o][k] : kZeroShift);
   }
   fp.oct_n = static_cast<uint8_t>(longest);
+  // whether every listed image is one of the seven towards its vector: each
+  // component shifted by the opposite of the vector's sign, or not at all
+  fp.oct_seven = fp.oct_full == 0 ? 1 : 0;
+  for (int o = 0; o < 8; ++o)
+    for (int k = 0; k < len[o]; ++k) {
+      const int m = list[o][k];
+      const int n[3] = {m / 9 - 1, m / 3 % 3 - 1, m % 3 - 1};
+      for (int c = 0; c < 3; ++c)
+        if (n[c] != 0 && (n[c] > 0) != (((o >> c) & 1) != 0)) fp.oct_seven = 0;
+    }
 }
 
 // Canonical constants of a frame (binary64), plus their binary32 images.

@@ -158,10 +158,12 @@ struct FrameParams {
   // can be nearer than the vector itself, as indices into the shift tables
   // padded with the zero shift (kZeroShift); oct_full bit o when octant o
   // needs more than kOctCap images (it searches all 27); oct_n the longest
-  // of the other lists
+  // of the other lists; oct_seven 1 when every octant's list holds only
+  // images shifted against the vector's signs
   uint8_t oct_shift[8][kOctCap];
   uint8_t oct_full;
   uint8_t oct_n;
+  uint8_t oct_seven;
 };
 
 // The minimum-image kind the kernels use for a frame: the geometric kind of

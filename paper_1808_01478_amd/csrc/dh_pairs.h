@@ -549,6 +549,88 @@ __device__ __forceinline__ T search_oct(T dx, T dy, T dz, T q, int base, int n,
   return min_arith(qa, min_arith(qb, qc));
 }
 
+// Image shifts of the seven neighbours towards a reduced vector whose
+// third fractional component is not negative (c always shifted by -1), for
+// either sign of the first two (the table's values).
+template <typename T>
+struct Seven {
+  T xa;                // ( 1, 0, 0)
+  T xb, yb;            // ( 0, 1, 0)
+  T xs, xd;            // ( 1, 1, 0), (-1, 1, 0)
+  T xc, yc, zc;        // ( 0, 0,-1)
+  T xca[2];            // (-1, 0,-1), ( 1, 0,-1)
+  T xcb[2], ycb[2];    // ( 0,-1,-1), ( 0, 1,-1)
+  T xcab[2][2];        // [b][a]
+};
+template <typename T>
+__device__ __forceinline__ Seven<T> load_seven(const FrameParams *F) {
+  auto at = [&](int i, int j, int k, int c) {
+    const int m = 9 * (i + 1) + 3 * (j + 1) + (k + 1);
+    if constexpr (sizeof(T) == 4)
+      return uni(F->shift32[m][c]);
+    else
+      return uni(F->shift64[m][c]);
+  };
+  Seven<T> s;
+  s.xa = at(1, 0, 0, 0);
+  s.xb = at(0, 1, 0, 0); s.yb = at(0, 1, 0, 1);
+  s.xs = at(1, 1, 0, 0); s.xd = at(-1, 1, 0, 0);
+  s.xc = at(0, 0, -1, 0); s.yc = at(0, 0, -1, 1); s.zc = at(0, 0, -1, 2);
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    s.xca[p] = at(2 * p - 1, 0, -1, 0);
+    s.xcb[p] = at(0, 2 * p - 1, -1, 0);
+    s.ycb[p] = at(0, 2 * p - 1, -1, 1);
+#pragma unroll
+    for (int v = 0; v < 2; ++v) s.xcab[p][v] = at(2 * v - 1, 2 * p - 1, -1, 0);
+  }
+  return s;
+}
+
+// The minimum of search_oct where every octant's list is its seven images
+// towards the vector, without the table: the vector is turned into the half
+// space c >= 0 (an image and its opposite differ in sign alone, and so do the
+// table's entries), which leaves two signs to choose the shifts by; images
+// share their y and z. Every image's q is the one of the table's entry.
+// The table's rows, read per lane, were what bounded the search: seven 16-byte
+// LDS reads are 56 cycles of a CU per 64 vectors whatever rows the lanes take.
+// 200,000 points in a sheared triclinic cell, 48 % of the pairs searched:
+// 54.5 ms with the table, 30.5 ms with this, 27.9 ms with ring positions that
+// wrap by a mask and the octant from three shifts besides; now bound by
+// vector issue. Binary64, 60,000 and 20,000 points: 7.40 and 5.78 ms, 975 and
+// 842 us.
+__device__ __forceinline__ float flip_sign(float v, uint32_t sign) {
+  return __uint_as_float(__float_as_uint(v) ^ sign);
+}
+__device__ __forceinline__ double flip_sign(double v, uint32_t sign) {
+  return __longlong_as_double(__double_as_longlong(v) ^
+                              static_cast<long long>(static_cast<uint64_t>(sign) << 32));
+}
+template <typename T>
+__device__ __forceinline__ T search_seven(T dx, T dy, T dz, T q, int code, const Seven<T> &s) {
+  const uint32_t turn = (static_cast<uint32_t>(code) << 29) & 0x80000000u;
+  dx = flip_sign(dx, turn); dy = flip_sign(dy, turn); dz = flip_sign(dz, turn);
+  // the signs of the first two components after the turn: a set bit means
+  // negative, where the image nearer to the vector is the positive one
+  const uint32_t ta = static_cast<uint32_t>(code) ^ (static_cast<uint32_t>(code) >> 2);
+  const uint32_t tb = (static_cast<uint32_t>(code) >> 1) ^ (static_cast<uint32_t>(code) >> 2);
+  const bool a = (ta & 1u) != 0, b = (tb & 1u) != 0, same = ((ta ^ tb) & 1u) == 0;
+  const uint32_t sa = (~ta) << 31, sb = (~tb) << 31;
+  const T yb = dy + flip_sign(s.yb, sb), yc = dy + s.yc, zc = dz + s.zc;
+  const T ycb = dy + (b ? s.ycb[1] : s.ycb[0]);
+  auto len = [](T x, T y, T z) { return fmaT(z, z, fmaT(y, y, x * x)); };
+  const T q1 = len(dx + flip_sign(s.xa, sa), dy, dz);
+  const T q2 = len(dx + flip_sign(s.xb, sb), yb, dz);
+  const T q3 = len(dx + flip_sign(same ? s.xs : s.xd, sb), yb, dz);
+  const T q4 = len(dx + s.xc, yc, zc);
+  const T q5 = len(dx + (a ? s.xca[1] : s.xca[0]), yc, zc);
+  const T q6 = len(dx + (b ? s.xcb[1] : s.xcb[0]), ycb, zc);
+  const T u = a ? s.xcab[0][1] : s.xcab[0][0], v = a ? s.xcab[1][1] : s.xcab[1][0];
+  const T q7 = len(dx + (b ? v : u), ycb, zc);
+  q = min_arith(min_arith(q, q1), min_arith(q2, q3));
+  return min_arith(q, min_arith(min_arith(q4, q5), min_arith(q6, q7)));
+}
+
 // Octant of a reduced binary64 vector: bit k when fractional component k is
 // negative; 8 (the full list) when a component lies outside the octant boxes
 // of the host (|f| beyond 1/2 plus half their slack, or NaN).
@@ -569,9 +651,11 @@ __device__ __forceinline__ int octant64(double dx, double dy, double dz, const G
 // differences (exact, within [-1/2, 1/2) of a cell vector).
 __device__ __forceinline__ int octant32(uint64_t ab_j, uint64_t neg_ab_i, float zi, float zj) {
   const uint64_t dab = ab_j + neg_ab_i;
-  return (static_cast<int32_t>(static_cast<uint32_t>(dab)) < 0 ? 1 : 0) |
-         (static_cast<int32_t>(static_cast<uint32_t>(dab >> 32)) < 0 ? 2 : 0) |
-         (static_cast<int32_t>(__float_as_uint(zj) - __float_as_uint(zi)) < 0 ? 4 : 0);
+  // (each step shifts the next sign in from the right)
+  uint32_t code = (__float_as_uint(zj) - __float_as_uint(zi)) >> 31;
+  code = __builtin_amdgcn_alignbit(code, static_cast<uint32_t>(dab >> 32), 31);
+  code = __builtin_amdgcn_alignbit(code, static_cast<uint32_t>(dab), 31);
+  return static_cast<int>(code);
 }
 
 template <typename T>
@@ -704,6 +788,7 @@ __device__ __forceinline__ void run_units(const PairKernelArgs &a, const WorkIte
 
   // image-search ring of this wave: qn entries from head (wave-uniform)
   constexpr int cap = queue_cap(R);
+  static_assert((cap & (cap - 1)) == 0, "ring positions wrap by a mask");
   V *const wq = queue + wave * cap;
   int head = 0, qn = 0;
   [[maybe_unused]] uint64_t n_searched = 0;  // pairs this wave searched in this item
@@ -715,6 +800,12 @@ __device__ __forceinline__ void run_units(const PairKernelArgs &a, const WorkIte
     qskip = uni(F->qskip64);
   [[maybe_unused]] uint32_t oct_full = 0;
   [[maybe_unused]] int oct_n = 0;
+  [[maybe_unused]] bool oct_seven = false;
+  [[maybe_unused]] Seven<T> seven;
+  if constexpr (SEARCH) {
+    oct_seven = uni(static_cast<int>(F->oct_seven)) != 0;
+    seven = load_seven<T>(F);
+  }
   if constexpr (SEARCH) {
     oct_full = static_cast<uint32_t>(uni(static_cast<int>(F->oct_full)));
     oct_n = uni(static_cast<int>(F->oct_n));
@@ -739,9 +830,7 @@ __device__ __forceinline__ void run_units(const PairKernelArgs &a, const WorkIte
     if constexpr (SEARCH) {
       __builtin_amdgcn_wave_barrier();
       const bool v = lane < cnt;
-      int idx = head + (v ? lane : 0);
-      if (idx >= cap) idx -= cap;
-      const V e = wq[idx];
+      const V e = wq[(head + (v ? lane : 0)) & (cap - 1)];
       T q = fmaT(e.z, e.z, fmaT(e.y, e.y, e.x * e.x));
       // the vector's octant (8: outside the octant boxes), 8 as well when its
       // list is the full one; the wave runs the full list when any of its
@@ -751,10 +840,15 @@ __device__ __forceinline__ void run_units(const PairKernelArgs &a, const WorkIte
         code = __float_as_int(e.w);
       else
         code = octant64(e.x, e.y, e.z, g);
-      if ((oct_full >> code) & 1u) code = 8;
-      const int n = __builtin_amdgcn_ballot_w64(code == 8) != 0 ? kShifts : oct_n;
-      q = search_oct<T>(e.x, e.y, e.z, q, code == 8 ? 8 * kOctCap : code * kOctCap, n, sh);
-      n_images += static_cast<uint64_t>(cnt) * static_cast<uint64_t>(n);
+      if (oct_seven && (sizeof(T) == 4 || __builtin_amdgcn_ballot_w64(code == 8) == 0)) {
+        q = search_seven<T>(e.x, e.y, e.z, q, code, seven);
+        n_images += static_cast<uint64_t>(cnt) * 7u;
+      } else {
+        if ((oct_full >> code) & 1u) code = 8;
+        const int n = __builtin_amdgcn_ballot_w64(code == 8) != 0 ? kShifts : oct_n;
+        q = search_oct<T>(e.x, e.y, e.z, q, code == 8 ? 8 * kOctCap : code * kOctCap, n, sh);
+        n_images += static_cast<uint64_t>(cnt) * static_cast<uint64_t>(n);
+      }
       if constexpr (sizeof(T) == 4)
         count.template add<true>(
             bin_bits32(__builtin_amdgcn_sqrtf(q), v ? kBinOffset : kNoBin));
@@ -764,8 +858,7 @@ __device__ __forceinline__ void run_units(const PairKernelArgs &a, const WorkIte
         count.template add<true>(v ? b : kNoBits);
       }
       n_searched += cnt;  // wave-uniform; added to the frame's count once per item
-      head += cnt;
-      if (head >= cap) head -= cap;
+      head = (head + cnt) & (cap - 1);
       qn -= cnt;
       __builtin_amdgcn_wave_barrier();
     }
@@ -863,12 +956,12 @@ __device__ __forceinline__ void run_units(const PairKernelArgs &a, const WorkIte
           }
           const uint64_t m = __builtin_amdgcn_ballot_w64(need);
           if (m != 0) {
-            const int below = __builtin_amdgcn_mbcnt_hi(
+            const int end = static_cast<int>(__builtin_amdgcn_mbcnt_hi(
                 static_cast<uint32_t>(m >> 32),
-                __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u));
+                __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m),
+                                          static_cast<uint32_t>(head + qn))));
             if (need) {
-              int pos = head + qn + below;  // < 2 cap: head < cap, qn + below < cap
-              if (pos >= cap) pos -= cap;
+              const int pos = end & (cap - 1);
               // binary32: the octant from the exact signs of the
               // fixed-point differences, as the bits of w; binary64 takes
               // it in the drain from the vector itself

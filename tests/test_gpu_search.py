@@ -1,0 +1,64 @@
+"""The neighbour-image search without its table (every octant's
+images are the seven towards the vector) and with it (longer lists): random
+points, and points of a lattice of eighths of the cell, whose reduced vectors
+lie on the octants' faces. binary64 bit for bit against the oracle, which
+searches all 27 images of every pair, binary32 within the edge-pair bound."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from gpu_util import fp32_bound_violations, oor_bound_violations, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+CELLS = {"orthogonal": (np.diag([9.0, 10.0, 11.0]), True),
+         "skew": (np.array([[10.0, 0, 0], [3.0, 9.5, 0], [2.0, 2.4, 9.0]]), True),
+         "skew-back": (np.array([[10.0, 0, 0], [-3.0, 9.5, 0], [2.0, -2.4, 9.0]]), True),
+         "face-centred": (np.array([[8.0, 0, 0], [4.0, 6.9, 0], [4.0, 2.3, 6.5]]), False)}
+
+
+def seven(box):
+    """Whether every octant lists only images shifted against its signs."""
+    import paper_1808_01478_amd as dh
+    lists, _, full = dh.search_images(box)
+    if full:
+        return False
+    for o, images in enumerate(lists):
+        for m in images:
+            n = (m // 9 - 1, m // 3 % 3 - 1, m % 3 - 1)
+            if any(v != 0 and (v > 0) != bool(o >> c & 1) for c, v in enumerate(n)):
+                return False
+    return True
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import paper_1808_01478_amd as dh
+    c = dh.Context(0)
+    yield c
+    c.close()
+
+
+@pytest.mark.parametrize("points", ["random", "eighths"])
+@pytest.mark.parametrize("name", sorted(CELLS))
+def test_search_images(ctx, name, points):
+    box, plain = CELLS[name]
+    assert seven(box) == plain
+    rng = np.random.Generator(np.random.PCG64(5))
+    f = rng.uniform(-0.2, 1.2, size=(1300, 3))
+    if points == "eighths":
+        f = rng.integers(0, 8, size=f.shape) / 8.0
+    x = np.ascontiguousarray(workloads.rows_combine(f, box))
+    for r in (0.55, 0.97):
+        fr = workloads.Frame(x, np.array([0, 700, 1300], np.int64), workloads.BOX_TRICLINIC, box,
+                             r * workloads.min_width(box), 211, name)
+        print(f"\n[case] search {name} {points} r={r}", flush=True)
+        w = oracle.edge_window(fr.coords, fr.box, fr.r_max)
+        ref = oracle.frame_histogram(fr, edge_window=w)
+        h, oor = run_gpu(ctx, fr, 1)
+        assert np.array_equal(h, ref.hist) and np.array_equal(oor, ref.out_of_range)
+        h, oor = run_gpu(ctx, fr, 0)
+        bad = fp32_bound_violations(h, ref.hist, ref.edges)
+        bad += oor_bound_violations(oor, ref.out_of_range, ref.edges)
+        assert not bad, bad[:3]
