@@ -385,13 +385,18 @@ constexpr int64_t kMinBoundedPairs = int64_t{1} << 21;
 constexpr int kNumKnobs = 8;
 
 // Bin windows from which the global-atomic kernel replaces LDS windows when
-// no tuned shape says otherwise. Measured on MI355X (100k points, periodic
-// cube, half the pairs in range): a binary32 window pass costs about 1.75 ms
-// and a binary64 one about 5.5 ms, while uint64 global atomics run at about
-// 2.4e10 per second whatever the bin count, so global atomics pay off from
-// about 63 windows (binary32) and 20 windows (binary64).
+// no tuned shape says otherwise. Measured on MI355X (100,000 points, periodic
+// cube, half the pairs in range): a binary32 window pass takes 1.43 ms and a
+// binary64 one 9 ms (at 2^20 - 2 bins and more, with the canonical root), one
+// pass of uint64 atomics 105 ms whatever the bin count, even at 73 and 12
+// windows; with 20,000 points at 60 to 100 and 16 to 29. Sorted frames skip
+// the group pairs outside a window: 26 windows take 26 ms in binary64 (1,000,000
+// bins; atomics 106 ms) and 75 windows 50 ms in binary32 (atomics 91 ms), even
+// at 80 to 160 and 116 to 137. Their item list grows with the windows, so the
+// later switch is for callers without a limit on scratch.
 constexpr int32_t kWideDefault32 = 60;
 constexpr int32_t kWideDefault64 = 20;
+constexpr int32_t kWideSorted = 100;
 
 struct Knobs {
   int32_t r = 4;             // i-particles per lane: 4 or 8
@@ -424,13 +429,14 @@ struct Knobs {
   }
 };
 
-Knobs default_knobs(int precision) {
+Knobs default_knobs(int precision, bool sorted_windows = false) {
   Knobs k;
   if (precision == DH_FP64) {
     k.r = 4;
     k.tj = 128;
     k.wide = kWideDefault64;
   }
+  if (sorted_windows) k.wide = kWideSorted;
   return k;
 }
 
@@ -1368,7 +1374,7 @@ int histo_job(dh_ctx *ctx, hipStream_t stream, const double *d_coords, const int
                          staged_point_bytes(precision, job.kind));
   if (rc) return rc;
 
-  Knobs k = default_knobs(precision);
+  Knobs k = default_knobs(precision, padded_frame(job.kind) && ctx->budget == 0);
   const std::string key = tune_key(ctx, job);
   if (ctx->forced) {
     k = Knobs::unpack(ctx->forced_knobs);
@@ -1552,7 +1558,9 @@ int dh_batch_create(dh_ctx *ctx, const dh_frame_desc *frames, int32_t n_frames, 
       fi.fp.win = (d.n_bins + fi.fp.n_sweeps - 1) / fi.fp.n_sweeps;
       fi.mode = kModeSweep;
     }
-    if (bk.wide > 0 && fi.fp.n_sweeps >= bk.wide) {
+    const int32_t wide =
+        !ctx->forced && padded_frame(kind) && ctx->budget == 0 ? kWideSorted : bk.wide;
+    if (wide > 0 && fi.fp.n_sweeps >= wide) {
       fi.mode = kModeGlobal;
       fi.fp.win = d.n_bins;
       fi.fp.n_sweeps = 1;

@@ -78,7 +78,7 @@ __global__ void stage32_kernel(const double *__restrict__ in, float4 *__restrict
 // their wrapped fractional coordinates (9 bits per axis), ties by input
 // index, so that 64 consecutive points are close together in the cell. The
 // pair kernel then finds, for most pairs of such groups, one lattice shift
-// that is the Eq. 5 wrap of every pair of the two groups (see run_item).
+// that is the Eq. 5 wrap of every pair of the two groups (see run_sorted).
 // The order is a permutation within each species, so the histograms are
 // those of the input; the sort is a bitonic network on 64-bit keys
 // (species : Morton code : input index), which makes the order unique.

@@ -3,18 +3,20 @@
 //
 // The pair kernel is persistent: a grid of a few workgroups per CU drains a
 // work list of (frame, histogram, bin window, i-block, j-range) items through
-// an atomic counter. Per item, every lane keeps R i-particles in registers;
-// the workgroup streams the j-range through a double-buffered LDS tile with
-// coalesced loads, and every wave reads each j as a uniform (broadcast) LDS
-// load. Each pair's bin is counted with one ds_add_u32 into a u32 LDS
-// sub-histogram (Sec. 2.4: groups of processing units share a private
-// histogram; Sec. 3.2.3: partial histograms in on-chip memory). Lanes whose
-// pair must not count (out of range, j <= i on a diagonal block, ragged
-// i-block tail) are steered by a clamp to a per-lane discard slot past the
-// bin window instead of a branch, so the atomic is issued without divergence
-// and discarded pairs never collide on one address. When the histogram,
-// window or frame changes, or before any u32 slot could wrap, the workgroup
-// sums its copies and adds them to the uint64 output with global atomics
+// an atomic counter. Its waves draw units of an item (64 R i-particles, R a
+// lane in registers, against a piece of the j-range) from an LDS counter, so
+// no barrier stands between units and a small frame's few items still keep
+// every wave busy; j-particles arrive by buffer loads with a uniform offset,
+// four ahead of the arithmetic. The wave that finds no unit left draws the
+// workgroup's next item. Each pair's bin is counted with one ds_add_u32 into
+// the workgroup's u32 LDS histogram (Sec. 2.4: groups of processing units
+// share a private histogram; Sec. 3.2.3: partial histograms in on-chip
+// memory). Lanes whose pair must not count (out of range, j <= i on a diagonal
+// block, ragged i-block tail) are steered by a clamp to a per-lane discard
+// slot past the bin window instead of a branch, so the atomic is issued
+// without divergence and discarded pairs never collide on one address. When
+// the histogram, window or frame changes, or before any u32 slot could wrap,
+// the workgroup adds the counts to the uint64 output with global atomics
 // (Sec. 3.1: u32 private histograms flushed into a u64 global one).
 //
 // Histograms too wide for LDS either run as bin windows (one LDS window per

@@ -108,3 +108,19 @@ def test_oracle(ctx, box_type):
     bad = fp32_bound_violations(h, ref.hist, ref.edges)
     bad += oor_bound_violations(oor, ref.out_of_range, ref.edges)
     assert not bad, bad[:3]
+
+
+@pytest.mark.parametrize("precision,n_bins", [(1, 800_000), (1, (1 << 20) - 3), (0, 2_600_000)])
+def test_wide_windows_against_atomics(ctx, precision, n_bins):
+    """Wide histograms of sorted frames run as bin windows, whose skipped group
+    pairs must not lose a count: equal to one pass of global atomics."""
+    fr = frame(SIZES[1], workloads.BOX_TRICLINIC, True, 0.3, n_bins)
+    print(f"\n[case] wide {fr.name} precision={precision} bins={n_bins}", flush=True)
+    ctx.set_config(None)
+    h, oor = run_gpu(ctx, fr, precision)
+    assert ctx.last_config()["mode"] == 1
+    ctx.set_config([4, 1, 128 if precision else 256, 1, 0, 4, 0, 1])
+    g, oor_g = run_gpu(ctx, fr, precision)
+    assert ctx.last_config()["mode"] == 2
+    ctx.set_config(None)
+    assert np.array_equal(h, g) and np.array_equal(oor, oor_g)
