@@ -199,7 +199,8 @@ int dh_histo_async(dh_ctx *ctx, dh_stream stream, const double *d_coords,
  * in binary64: about 1.4 million binary64 or 2.9 million binary32 points;
  * frames of at least 65,536 points staged in spatial order, triclinic ones
  * and binary64 orthorhombic ones, take 32 bytes per point and sort keys:
- * about 1.0 million points).
+ * about 1.0 million points; a binary64 frame with image search is staged so
+ * only where that fits).
  * A frame that does not fit gets DH_EINVAL before anything is enqueued.
  * Calls share that array: calls that overlap on one device (several streams
  * or host threads) race and must be serialised by the caller. Failures
@@ -488,8 +489,9 @@ int dh_traj_histo_hybrid(dh_ctx *ctx, dh_traj *t, const int64_t *species_offsets
                          int32_t flags, int64_t *intervals_done, int64_t *cpu_frames);
 
 /* ---------------------------------------------------------------------------
- * Launch tuning. The launch shape of a frame (i-particles per lane, LDS
- * sub-histogram copies, j-tile length, unclamped interior blocks, workgroups
+ * Launch tuning. The launch shape of a frame (i-particles per lane, the LDS
+ * reserved in histogram copies, longest j-range of a wave's unit, unclamped
+ * interior blocks, workgroups
  * per CU, work items per workgroup, workgroup size, and for histograms wider
  * than LDS the choice between LDS bin windows and uint64 global atomics)
  * changes speed only: every shape gives the same counts (the paper picks its
@@ -515,9 +517,9 @@ int dh_ctx_set_tuning(dh_ctx *ctx, int32_t mode, const char *cache_path);
  * on it (NULL restores tuning):
  * knobs[8] = {r (4|8), copies (1|2|4), tj (128|256), noclamp (0|1),
  * occ_cap (0..16, 0 = as many as fit), items_per_wg (1..64),
- * threads (256|512|1024, or 0 = the smallest workgroup that gives every SIMD
- * four waves within the LDS limit on workgroups per CU; the 27-image search
- * always runs 256),
+ * threads (256|512|1024, or 0 = the size that puts most waves on a CU within
+ * the LDS limit on workgroups per CU, the smallest of equals, 512 at least
+ * from 2^22 pairs; the unsorted image search always runs 256),
  * wide (0..65536: count with uint64 global atomics instead of LDS
  * sub-histograms when the histogram would need at least this many LDS bin
  * windows; 0 = never, 1 = always)}.
@@ -559,7 +561,9 @@ int dh_ctx_profile_read(dh_ctx *ctx, double *kernel_ms, int64_t *launches);
  * neighbouring boxes) in the last single-frame histogram on ctx
  * (dh_histo_async or dh_histo through ctx): the pairs whose Eq. 5 reduced
  * vector is at least half the shortest lattice vector long, counted by the
- * pair kernel. 0 when that call ran no search (r_max below half the smallest
+ * pair kernel; in binary64 frames staged in spatial order (65,536 points and
+ * more) the pairs evaluated over more than one image, which their two groups
+ * of 64 points leave open. 0 when that call ran no search (r_max below half the smallest
  * width, or no triclinic cell) or the frame was added into an accumulating
  * sum. The caller must have waited for that call's stream; this reads the
  * device counter with a blocking copy. DH_EINVAL for a null argument.
@@ -569,8 +573,9 @@ int dh_ctx_searched_pairs(dh_ctx *ctx, uint64_t *searched);
 /*
  * Images evaluated for those pairs in the same call (Sec. 2.3's neighbouring
  * images; the kernel evaluates for each searched vector only the images of
- * its octant list, or all 27, and a wave runs to its longest list, so this
- * is the arithmetic actually spent on the search). 0 as for
+ * its octant list, or all 27, and a wave runs to its longest list, in spatial
+ * order the images its pair of groups can have, rounded up to 2, 4 or 8, so
+ * this is the arithmetic actually spent on the search). 0 as for
  * dh_ctx_searched_pairs; same waiting rule and errors.
  */
 int dh_ctx_searched_images(dh_ctx *ctx, uint64_t *images);
