@@ -518,8 +518,9 @@ int dh_ctx_set_tuning(dh_ctx *ctx, int32_t mode, const char *cache_path);
  * knobs[8] = {r (4|8), copies (1|2|4), tj (128|256), noclamp (0|1),
  * occ_cap (0..16, 0 = as many as fit), items_per_wg (1..64),
  * threads (256|512|1024, or 0 = the size that puts most waves on a CU within
- * the LDS limit on workgroups per CU, the smallest of equals, 512 at least
- * from 2^22 pairs; the unsorted image search always runs 256),
+ * the LDS limit on workgroups per CU; of equals the smallest, but 512 at least
+ * from 2^17 pairs and the largest for histograms over 32 KiB of unsorted
+ * binary64 frames; the unsorted image search always runs 256),
  * wide (0..65536: count with uint64 global atomics instead of LDS
  * sub-histograms when the histogram would need at least this many LDS bin
  * windows; 0 = never, 1 = always)}.

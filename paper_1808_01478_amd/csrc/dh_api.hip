@@ -481,22 +481,36 @@ BaseConfig base_config(size_t lds_per_block, int precision, const Knobs &k, int 
 }
 
 // Workgroup size "auto": the LDS histogram caps the workgroups per CU, so
-// take the size that puts most waves on a CU, the smallest of equals. Frames
-// of kSmallWork pairs and more start at 512 threads: every workgroup adds its
-// own histogram into the output, and half as many of them save more than the
-// finer grain gives (60,000 points in a cube, 1,000 bins, binary32: 482 us
-// against 497 us with 256 threads; 20,000 points: 86 and 94 us).
-constexpr uint64_t kSmallWork = uint64_t{1} << 22;
+// take the size that puts most waves on a CU. Every workgroup adds its own
+// histogram into the output, so fewer, larger ones save flushes and finer ones
+// end more evenly. Of equals:
+// * 512 at least from kSmallWork pairs on. 256 loses everywhere below 40,000
+//   points (1,000 points, 4,000 bins, no box: 15.3 and 11.8 us in binary32,
+//   29.1 and 23.5 in binary64) and gains at most 3 % above; under kSmallWork
+//   the automatic size stays the documented smallest (400 points: 15.0 and
+//   11.9 us).
+// * 1,024 for unsorted binary64 frames whose histogram takes more than 32 KiB,
+//   where flushes count: 10,000, 20,000 and 64,000 points in a cube, 16,000 bins,
+//   binary64: 114, 243 and 1,511 us with 512 threads, 93, 208 and 1,502 us with
+//   1,024. With 4,000 bins it is worth -6 to +15 %; binary32 takes 1,024
+//   for its waves where the histogram leaves no room for four workgroups of
+//   512, and gains nothing elsewhere (24 frames in one batch, 4,096 bins: 22.0
+//   ms with 512, 22.2 with 1,024).
+constexpr uint64_t kSmallWork = uint64_t{1} << 17;
+constexpr size_t kWideFlush = 32 * 1024;
+
 void resolve_threads(int precision, int kind, int mode, const Knobs &k, size_t lds,
                      uint64_t work, KernelConfig &cfg) {
   if (k.threads != 0 || kind == kBoxTricSearch) return;
+  const bool largest =
+      precision != 0 && mode != kModeGlobal && lds > kWideFlush && !padded_frame(kind);
   int best = 0;
   for (int th : {256, 512, 1024}) {
     if (th == 256 && work >= kSmallWork) continue;
     KernelConfig c = cfg;
     c.threads = th;
     const int waves = pairs_occupancy(precision, kind, mode, c, lds) * (th / 64);
-    if (waves > best) {
+    if (waves > best || (largest && waves == best)) {
       best = waves;
       cfg.threads = th;
     }
