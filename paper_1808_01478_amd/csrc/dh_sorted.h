@@ -637,7 +637,7 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
         return e.j;
       };
       // bin bits and the smallest |residual| of the pairs of one j
-      auto bits_of = [&](const J &p, uint32_t *b, float &gap) {
+      auto bits_of = [&](const J &p, int j, uint32_t *b, float &gap) {
         [[maybe_unused]] double fj[3];
         if constexpr (KIND == kSlow) {
           fj[0] = frac(Int<0>{}, p.x, p.y, p.z);
@@ -657,6 +657,7 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
               const double v = fma(dz, dz, fma(dy, dy, dx * dx));
               u = e == 0 ? v : min_arith(u, v);
             }
+            if constexpr (DIAG) u = j <= slice(k) ? kFarU : u;
             b[k] = root_bits64(u, gap);
             continue;
           }
@@ -673,7 +674,8 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
             if constexpr (K >= 1) dy = fma(K == 1 ? -by : -cy, n, dy);
             dx = fma(K == 0 ? -ax : K == 1 ? -bx : -cx, n, dx);
           }
-          const double u = fma(dz, dz, fma(dy, dy, dx * dx));
+          double u = fma(dz, dz, fma(dy, dy, dx * dx));
+          if constexpr (DIAG) u = j <= slice(k) ? kFarU : u;
           b[k] = root_bits64(u, gap);
         }
       };
@@ -689,9 +691,9 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
         at += 48;
         uint32_t b[2 * M];
         float gap = __builtin_inff();
-        bits_of(pa, b, gap);
+        bits_of(pa, j, b, gap);
         pa = load(0);
-        bits_of(pb, b + M, gap);
+        bits_of(pb, j + 1, b + M, gap);
         pb = load(1);
         if (__builtin_expect(__builtin_amdgcn_ballot_w64(gap <= near_hi) != 0, 0)) {
           left |= 1u << ((j - j0) >> 1);
@@ -703,7 +705,7 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
       if (j < j1) {
         uint32_t b[M];
         float gap = __builtin_inff();
-        bits_of(pa, b, gap);
+        bits_of(pa, j, b, gap);
         if (__builtin_amdgcn_ballot_w64(gap <= near_hi) != 0)
           left |= 1u << ((j - j0) >> 1);
         else
