@@ -484,14 +484,14 @@ BaseConfig base_config(size_t lds_per_block, int precision, const Knobs &k, int 
 // take the size that puts most waves on a CU. Every workgroup adds its own
 // histogram into the output, so fewer, larger ones save flushes and finer ones
 // end more evenly. Of equals:
-// * 512 at least from kSmallWork pairs on. 256 loses everywhere below 40,000
-//   points (1,000 points, 4,000 bins, no box: 15.3 and 11.8 us in binary32,
-//   29.1 and 23.5 in binary64) and gains at most 3 % above; under kSmallWork
-//   the automatic size stays the documented smallest (400 points: 15.0 and
-//   11.9 us).
+// * 512 at least from kSmallWork pairs on. 256 loses on small frames
+//   (1,000 points, 4,000 bins, no box: 15.3 and 11.8 us in binary32, 17.5 and
+//   15.8 in binary64) and gains at most 6 % from 10,000 points on; under
+//   kSmallWork the automatic size stays the documented smallest (400 points:
+//   15.0 and 11.9 us).
 // * 1,024 for unsorted binary64 frames whose histogram takes more than 32 KiB,
 //   where flushes count: 10,000, 20,000 and 64,000 points in a cube, 16,000 bins,
-//   binary64: 114, 243 and 1,511 us with 512 threads, 93, 208 and 1,502 us with
+//   binary64: 112, 240 and 1,497 us with 512 threads, 85, 203 and 1,486 us with
 //   1,024. With 4,000 bins it is worth -6 to +15 %; binary32 takes 1,024
 //   for its waves where the histogram leaves no room for four workgroups of
 //   512, and gains nothing elsewhere (24 frames in one batch, 4,096 bins: 22.0
