@@ -188,7 +188,7 @@ __device__ __forceinline__ Bins64 bins64(const FrameParams *F) {
 // u in the middle of a bin (2^19), for pairs that do not count: a particle
 // against itself has the residual 0, which sent every j of a diagonal unit to
 // the canonical root (1,000 points in a cube: 24.6 us, 15.5 with this; 10,000:
-// 85 and 63 us; sorted with image search, 70,001 points: 3.95 and 3.77 ms).
+// 85 and 63 us; sorted, 100,000 points: 2,890 and 2,860 us).
 // (Not in the unsorted image search, whose ballots are per pair: no change.)
 constexpr double kFarU = 0x1.00002p-6;
 // whether a lane of the wave has a residual too small to decide (a uniform
