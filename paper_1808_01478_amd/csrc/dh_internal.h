@@ -3,6 +3,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <cmath>
 #include <cstdint>
 
 namespace dh {
@@ -55,6 +56,22 @@ struct GroupBox {
   uint32_t unused[3];
 };
 static_assert(sizeof(GroupBox) == 64, "one box per 64 points at one byte a point");
+
+// The cell n a fractional coordinate f lies in and its place in that cell as
+// 32-bit fixed point, floor(2^32 (f - n)). Both come from one decision: for f
+// just below an integer f - floor(f) rounds to 1, and the point is then at the
+// lower face of the next cell in both. (With n = floor(f) and the place wrapped
+// to 0 a group's box named one image of such a point and its position the
+// next, a whole cell vector away.)
+__host__ __device__ inline double wrap_cell(double f, uint32_t &place) {
+  double n = floor(f), w = f - n;
+  if (w >= 1.0) {
+    n += 1.0;
+    w = 0.0;
+  }
+  place = static_cast<uint32_t>(static_cast<uint64_t>(w * 4294967296.0));
+  return n;
+}
 
 // Bytes per staged point (binary64 double4; binary32 float4, two of them
 // for spatially sorted frames) and the sort workspace of a frame.

@@ -438,10 +438,8 @@ __global__ void stage_sorted64_kernel(const double *__restrict__ in,
     const double fa = fma(z, p.h13, fma(y, p.h12, x * p.h11));
     const double fb = fma(z, p.h23, y * p.h22);
     const double fc = z * p.h33;
-    u[0] = fix32(fa);
-    u[1] = fix32(fb);
-    u[2] = fix32(fc);
-    const double na = floor(fa) + 0.5, nb = floor(fb) + 0.5, nc = floor(fc) + 0.5;
+    const double na = wrap_cell(fa, u[0]) + 0.5, nb = wrap_cell(fb, u[1]) + 0.5,
+                 nc = wrap_cell(fc, u[2]) + 0.5;
     c[0] = fma(-p.cx, nc, fma(-p.bx, nb, fma(-p.ax, na, x)));
     c[1] = fma(-p.cy, nc, fma(-p.by, nb, y));
     c[2] = fma(-p.cz, nc, z);
