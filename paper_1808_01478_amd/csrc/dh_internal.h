@@ -190,6 +190,12 @@ struct FrameParams {
 // counts bit for bit; frames with image search in binary64, see below) and the
 // binary32 special case of equal orthorhombic edges.
 //
+// Sorted kernels decide whole groups of pairs from squares of lengths in
+// binary32, widened by 2^-16 of the cell's entries (their sum): frames whose
+// squares of the cell or of that widening come near the ends of binary32 stay
+// unsorted. (Cube of edge 6e-22: subnormal squares rounded by up to 1/2 of
+// themselves, and group pairs with a pair within the cut-off were left out.)
+//
 // The sorted binary64 kernel takes bins from a binary32 root of numbers scaled
 // by s 2^-22: fewer than 2^20 bins, and a scale whose square is a normal
 // number. With image search it takes a pair's nearest image, which is the
@@ -202,9 +208,13 @@ inline int staged_kind(int kind, int precision, const FrameParams &fp, int64_t n
                        bool may_search = true) {
   const bool fits =
       precision == 0 || (fp.n_bins < (1 << 20) - 2 && fp.s > 0x1p-400 && fp.s < 0x1p400);
+  double size = 0.0;
+  for (double v : {fp.ax, fp.bx, fp.by, fp.cx, fp.cy, fp.cz}) size += fabs(v);
+  const bool ranged = size > 0x1p-40 && size < 0x1p60;
   // (padded indices fit in 32 bits)
   const bool large =
-      n_points >= kSortMinPoints && n_points <= 0x7FFFFFFF - 64 * kMaxSpeciesStage && fits;
+      n_points >= kSortMinPoints && n_points <= 0x7FFFFFFF - 64 * kMaxSpeciesStage && fits &&
+      ranged;
   if (large && (kind == kBoxTric || (kind == kBoxOrtho && precision != 0))) return kBoxTricSorted;
   if (large && kind == kBoxTricSearch && precision != 0 && may_search) {
     double diagonal2 = 0.0;

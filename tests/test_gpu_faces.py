@@ -64,3 +64,19 @@ def test_points_on_cell_faces(ctx, kind):
     bad = fp32_bound_violations(h, ref.hist, ref.edges)
     bad += oor_bound_violations(oor, ref.out_of_range, ref.edges)
     assert not bad, bad[:3]
+
+
+@pytest.mark.parametrize("kind", list(KINDS))
+def test_scale_of_the_cell_does_not_change_binary64_counts(ctx, kind):
+    """Lengths times a power of two leave every step of the canonical sequence
+    exact, so the counts: from cells whose squares underflow in binary32 to
+    cells whose squares overflow there."""
+    fr = face_frame(kind)
+    ref, ref_oor = run_gpu(ctx, fr, 1)
+    for k in (-300, -71, -45, -38, 55, 62, 300):
+        print(f"\n[case] {fr.name} scale 2^{k}", flush=True)
+        s = 2.0 ** k
+        part = workloads.Frame(fr.coords * s, fr.offsets, fr.box_type, fr.box * s, fr.r_max * s,
+                               fr.n_bins, fr.name)
+        h, oor = run_gpu(ctx, part, 1)
+        assert np.array_equal(h, ref) and np.array_equal(oor, ref_oor), k

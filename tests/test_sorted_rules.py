@@ -1,6 +1,7 @@
 """Host rules of spatially sorted frames, compiled for the CPU from the
 library's own header: where a point lies (the cell and the place in it name one
-image, also for points on a cell face)."""
+image, also for points on a cell face), and which frames are sorted (none
+whose squared lengths leave the binary32 range)."""
 import ctypes
 import math
 import os
@@ -10,11 +11,21 @@ from fractions import Fraction
 import numpy as np
 import pytest
 
+import workloads
 from paper_1808_01478_amd import build
+
+SKEW = np.array([[10.0, 0, 0], [3.0, 9.5, 0], [-2.0, 3.5, 9.0]])
+TRIC, SEARCH, SORTED, SEARCH_SORTED = 2, 3, 5, 6  # BoxKind
 
 SOURCE = """
 #include "dh_internal.h"
 extern "C" double wrap_cell(double f, unsigned int *place) { return dh::wrap_cell(f, *place); }
+extern "C" int staged_kind(int box_type, const double *box, double r_max, int n_bins,
+                           int precision, long n) {
+  dh::FrameParams fp;
+  const int kind = dh::frame_constants(box_type, box, r_max, n_bins, fp);
+  return dh::staged_kind(kind, precision, fp, n);
+}
 """
 
 
@@ -25,10 +36,13 @@ def lib(tmp_path_factory):
     rocm = os.path.dirname(os.path.dirname(os.path.realpath(build.hipcc())))
     subprocess.run([build.hipcc(), *build.CPU_FLAGS, "-shared", "-D__HIP_PLATFORM_AMD__",
                     f"-I{rocm}/include", f"-I{build.INCLUDE}", f"-I{build.CSRC}",
-                    str(d / "rules.cpp"), "-o", str(d / "rules.so")], check=True)
+                    str(d / "rules.cpp"), "-x", "none", build.LIB, f"-Wl,-rpath,{build.PKG}",
+                    "-o", str(d / "rules.so")], check=True)
     so = ctypes.CDLL(str(d / "rules.so"))
     so.wrap_cell.argtypes = [ctypes.c_double, ctypes.POINTER(ctypes.c_uint)]
     so.wrap_cell.restype = ctypes.c_double
+    so.staged_kind.argtypes = [ctypes.c_int, ctypes.c_void_p, ctypes.c_double, ctypes.c_int,
+                               ctypes.c_int, ctypes.c_long]
     return so
 
 
@@ -59,3 +73,27 @@ def test_cell_and_place_name_one_image(lib):
         # (2^-32) and the rounding of the difference (2^-53)
         gap = Fraction(f) - Fraction(n) - Fraction(place.value, 1 << 32)
         assert -Fraction(1, 1 << 53) <= gap < Fraction(1, 1 << 32), (f, n, place.value)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("box_type", [workloads.BOX_ORTHO, workloads.BOX_TRICLINIC])
+def test_frames_of_extreme_scale_stay_unsorted(lib, box_type, precision):
+    """Sorted frames compare squares of binary32 lengths down to 2^-16 of the
+    cell: those have to be normal numbers."""
+    rows = np.diag(np.diag(SKEW)) if box_type == workloads.BOX_ORTHO else SKEW
+    for r, plain, in_order in ((0.45, TRIC, SORTED), (0.8, SEARCH, SEARCH_SORTED)):
+        searched = box_type == workloads.BOX_TRICLINIC and r > 0.5
+        if box_type == workloads.BOX_ORTHO:
+            plain, in_order = 1, SORTED
+        sorts = precision == 1 or (box_type == workloads.BOX_TRICLINIC and not searched)
+        for k in range(-150, 151, 2):
+            box = np.ascontiguousarray(rows * 2.0 ** k)
+            r_max = r * workloads.min_width(rows) * 2.0 ** k
+            kind = lib.staged_kind(box_type, box.ctypes.data, r_max, 1000, precision, 1 << 16)
+            size = np.abs(box).sum()
+            squares = np.array([size * 2.0 ** -16, 8.0 * size]) ** 2
+            normal = squares[0] > 2.0 ** -126 and squares[1] < 2.0 ** 126
+            assert kind in (plain, in_order)
+            assert kind == plain or normal, (k, kind)
+            if sorts and 2.0 ** -30 < size < 2.0 ** 40:
+                assert kind == in_order, (k, kind)
