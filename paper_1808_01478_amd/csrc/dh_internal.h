@@ -57,6 +57,10 @@ struct GroupBox {
 };
 static_assert(sizeof(GroupBox) == 64, "one box per 64 points at one byte a point");
 
+// First of the three fixed-point words of padded point i (binary32): beyond 32
+// bits from 715,827,883 points on, and frames may have almost 2^31.
+__host__ __device__ inline int64_t first_word(int32_t i) { return 3 * static_cast<int64_t>(i); }
+
 // The cell n a fractional coordinate f lies in and its place in that cell as
 // 32-bit fixed point, floor(2^32 (f - n)). Both come from one decision: for f
 // just below an integer f - floor(f) rounds to 1, and the point is then at the
@@ -211,9 +215,9 @@ inline int staged_kind(int kind, int precision, const FrameParams &fp, int64_t n
   double size = 0.0;
   for (double v : {fp.ax, fp.bx, fp.by, fp.cx, fp.cy, fp.cz}) size += fabs(v);
   const bool ranged = size > 0x1p-40 && size < 0x1p60;
-  // (padded indices fit in 32 bits)
+  // (padded indices fit in 32 bits, those of a unit past the last point too)
   const bool large =
-      n_points >= kSortMinPoints && n_points <= 0x7FFFFFFF - 64 * kMaxSpeciesStage && fits &&
+      n_points >= kSortMinPoints && n_points <= 0x7FFFFFFF - 128 * kMaxSpeciesStage && fits &&
       ranged;
   if (large && (kind == kBoxTric || (kind == kBoxOrtho && precision != 0))) return kBoxTricSorted;
   if (large && kind == kBoxTricSearch && precision != 0 && may_search) {

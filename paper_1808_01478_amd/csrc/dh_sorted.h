@@ -209,7 +209,7 @@ __device__ __forceinline__ void run_sorted(const PairKernelArgs &a, const WorkIt
     constexpr int AHEAD = decltype(ahead_c)::value;
     constexpr int STRIDE = decltype(words_c)::value ? 12 : 16;
     const int j1 = min(j0 + 64, w.j1);
-    const void *first = decltype(words_c)::value ? static_cast<const void *>(W + 3 * j0)
+    const void *first = decltype(words_c)::value ? static_cast<const void *>(W + first_word(j0))
                                                  : static_cast<const void *>(C + j0);
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<void *>(first), 0, (j1 - j0) * STRIDE + (16 - STRIDE), kBufferFlags);
@@ -253,10 +253,10 @@ __device__ __forceinline__ void run_sorted(const PairKernelArgs &a, const WorkIt
       const int i = ib + 64 * r + lane;
       const bool ok = i < w.i1;
       const int ic = ok ? i : ib;
-      const uint32_t za = W[3 * ic + 2];
-      const uint32_t zb = r & 1 ? W[3 * (ok ? i - 64 : ib) + 2] : 0u;
-      const uint64_t nab =
-          0ull - ((static_cast<uint64_t>(W[3 * ic + 1]) << 32) | W[3 * ic]);
+      const uint32_t *const wi = W + first_word(ic);
+      const uint32_t za = wi[2];
+      const uint32_t zb = r & 1 ? W[first_word(ok ? i - 64 : ib) + 2] : 0u;
+      const uint64_t nab = 0ull - ((static_cast<uint64_t>(wi[1]) << 32) | wi[0]);
       const uint64_t nzz = r & 1 ? 0ull - ((static_cast<uint64_t>(za) << 32) | zb)
                                  : 0ull - static_cast<uint64_t>(za);
       const bool odd = (r & 1) != 0;

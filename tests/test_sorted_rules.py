@@ -20,6 +20,7 @@ TRIC, SEARCH, SORTED, SEARCH_SORTED = 2, 3, 5, 6  # BoxKind
 SOURCE = """
 #include "dh_internal.h"
 extern "C" double wrap_cell(double f, unsigned int *place) { return dh::wrap_cell(f, *place); }
+extern "C" long first_word(int i) { return dh::first_word(i); }
 extern "C" int staged_kind(int box_type, const double *box, double r_max, int n_bins,
                            int precision, long n) {
   dh::FrameParams fp;
@@ -41,6 +42,7 @@ def lib(tmp_path_factory):
     so = ctypes.CDLL(str(d / "rules.so"))
     so.wrap_cell.argtypes = [ctypes.c_double, ctypes.POINTER(ctypes.c_uint)]
     so.wrap_cell.restype = ctypes.c_double
+    so.first_word.restype = ctypes.c_long
     so.staged_kind.argtypes = [ctypes.c_int, ctypes.c_void_p, ctypes.c_double, ctypes.c_int,
                                ctypes.c_int, ctypes.c_long]
     return so
@@ -97,3 +99,14 @@ def test_frames_of_extreme_scale_stay_unsorted(lib, box_type, precision):
             assert kind == plain or normal, (k, kind)
             if sorts and 2.0 ** -30 < size < 2.0 ** 40:
                 assert kind == in_order, (k, kind)
+
+
+def test_word_index_of_the_last_points(lib):
+    """Frames may have almost 2^31 points, three words each."""
+    for i in (0, 1, 715_827_882, 715_827_883, 1 << 30, 0x7FFFFFFF):
+        assert lib.first_word(i) == 3 * i
+    box = np.ascontiguousarray(SKEW)
+    for n in (1 << 30, 0x7FFFFFFF - 9000, 0x7FFFFFFF - 8191, 0x7FFFFFFF):
+        kind = lib.staged_kind(workloads.BOX_TRICLINIC, box.ctypes.data, 1.0, 1000, 0, n)
+        # a unit starts at most at the last of 64 padded species
+        assert kind == TRIC or n + 63 * 64 + 512 <= 0x7FFFFFFF, n
