@@ -400,43 +400,6 @@ __device__ __forceinline__ void run_sorted(const PairKernelArgs &a, const WorkIt
   }
 }
 
-// Counts pairs of a sorted binary64 frame by the canonical sequence on their
-// input points: the first m slices in rs (four bits each) of the unit at ib
-// against the j of [j0, j1) in `left` (bit b: j0 + 2b and the next). Not
-// inlined: it runs for one group of pairs in some 10^5.
-template <int MODE, int BOX>
-__device__ __attribute__((noinline)) void exact_pairs(const FrameParams *F, int hist, int sweep,
-                                                      int ib, int i1, int j0, int j1,
-                                                      uint32_t rs, int m, uint32_t left,
-                                                      bool diag) {
-  const int lane = threadIdx.x & 63;
-  const int64_t n_pad = F->n_pad;
-  const uint32_t *const index =
-      reinterpret_cast<const uint32_t *>(static_cast<const char *>(F->coords) + 24 * n_pad);
-  const double *const in = F->in;
-  const Geo64 g = load_geo64(F);
-  WorkItem w;
-  w.hist = hist;
-  w.sweep = sweep;
-  const Count<MODE> count(F, w, lane);
-  for (; left != 0u; left &= left - 1u)
-    for (int h = 0; h < 2; ++h) {
-      const int j = j0 + 2 * __builtin_ctz(left) + h;
-      if (j >= j1) continue;
-      const int64_t q = 3 * static_cast<int64_t>(index[j]);
-      const double xj = in[q], yj = in[q + 1], zj = in[q + 2];
-      for (int k = 0; k < m; ++k) {
-        const int i = ib + 64 * static_cast<int>((rs >> (4 * k)) & 15u) + lane;
-        const bool ok = i < i1 && (!diag || j > i);
-        const int64_t p = 3 * static_cast<int64_t>(index[ok ? i : ib]);
-        const double t = t64<BOX>(in[p], in[p + 1], in[p + 2], xj, yj, zj, g);
-        // (a NaN t takes the other operand: out of range)
-        const uint32_t b = kBinBits + static_cast<uint32_t>(min_arith(t, 0x1p25));
-        count.template add<true>(ok ? b : kNoBits);
-      }
-    }
-}
-
 // The images of a pair of groups of a frame with image search (binary64): the
 // lattice shifts N under which some pair of the two groups can be nearest and
 // within the window, as an ordered list of at most kListed, from the distance
@@ -503,6 +466,156 @@ __device__ __forceinline__ Images group_images(const GroupBox &I, const GroupBox
   return m;
 }
 
+// Pairs of a sorted binary64 frame next to a bin edge. A pass leaves its pairs
+// of two j here as soon as one of them is too close to an edge (see
+// run_sorted64): each pair's bin is taken again from the staged positions, the
+// pairs near an edge of the window are gathered in lanes, from whatever i and
+// j, and 64 at a time go through the canonical sequence on their input points.
+// With random points about one pass in 10^5 leaves anything; where distances
+// repeat at whole bins (a crystal, the bin a fraction of its spacing) all of
+// them leave everything, some per cent of it near an edge. The canonical
+// sequence for every pair left took, for 103,823 points of a cubic lattice
+// (spacing 3.61, cut-off 70, bins of 0.01), @BEFORE@ ms, this @AFTER@ ms.
+//
+// The first m slices in rs (four bits each) of the unit at ib against the j of
+// [j0, j1) in `left` (bit b: j0 + 2b and the next). SEARCH: the images of slice
+// r and the group are those of lane src + r; without, its shift.
+constexpr int kSettleDiag = 1, kSettleExact = 2, kSettleFast = 4;
+template <int MODE, bool SEARCH>
+__device__ __attribute__((noinline)) void settle_pairs(const FrameParams *frame, WorkItem w, int ib_,
+                                                       int j0_, int j1_, uint32_t rs_, int m_,
+                                                       uint32_t left_, int flags_, int src_,
+                                                       float near_, double shx, double shy,
+                                                       double shz, Images img) {
+  const FrameParams *const F = uni(frame);
+  const int ib = uni(ib_), i1 = uni(w.i1), j0 = uni(j0_), j1 = uni(j1_), m = uni(m_);
+  const int flags = uni(flags_), src = uni(src_);
+  const uint32_t rs = static_cast<uint32_t>(uni(static_cast<int>(rs_)));
+  const float near_hi = uni(near_);
+  w.hist = uni(w.hist);
+  w.sweep = uni(w.sweep);
+  const int lane = threadIdx.x & 63;
+  const int64_t n_pad = F->n_pad;
+  const double *const P = static_cast<const double *>(F->coords);
+  const uint32_t *const index =
+      reinterpret_cast<const uint32_t *>(static_cast<const char *>(F->coords) + 24 * n_pad);
+  const double *const in = F->in;
+  const Geo64 g = load_geo64(F);
+  // (as in run_sorted64)
+  const double s = g.s * 0x1p-22, is = 1.0 / s;
+  const double ax = g.ax * s, bx = g.bx * s, by = g.by * s;
+  const double cx = g.cx * s, cy = g.cy * s, cz = g.cz * s;
+  const Count<MODE> count(F, w, lane);
+  const int b_lo = w.sweep * uni(F->win), b_hi = b_lo + uni(F->win);
+
+  // pairs waiting for the canonical sequence: lane q < qn holds one, as the
+  // offsets of its i from ib and its j from j0
+  int qn = 0, held = 0;
+  auto drain = [&](int cnt) {
+    const bool v = lane < cnt;
+    const int64_t p = 3 * static_cast<int64_t>(index[v ? ib + (held & 511) : ib]);
+    const int64_t q = 3 * static_cast<int64_t>(index[v ? j0 + (held >> 9) : j0]);
+    const double t = t64<SEARCH ? kBoxTricSearch : kBoxTric>(in[p], in[p + 1], in[p + 2], in[q],
+                                                             in[q + 1], in[q + 2], g);
+    // (a NaN t takes the other operand: out of range)
+    const uint32_t b = kBinBits + static_cast<uint32_t>(min_arith(t, 0x1p25));
+    count.template add<true>(v ? b : kNoBits);
+  };
+  auto push = [&](bool take, int i, int j) {
+    const uint64_t mask = __builtin_amdgcn_ballot_w64(take);
+    if (mask == 0) return;
+    const int cnt = __builtin_popcountll(mask);
+    const int below = static_cast<int>(__builtin_amdgcn_mbcnt_hi(
+        static_cast<uint32_t>(mask >> 32),
+        __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0u)));
+    // the lanes taken to qn, qn + 1, ... (round the wave), the others after them
+    const int to = qn + (take ? below : cnt + lane - below);
+    const int got = __builtin_amdgcn_ds_permute((to & 63) << 2, (i - ib) | (j - j0) << 9);
+    held = lane >= qn ? got : held;
+    qn += cnt;
+    if (qn >= 64) {
+      drain(64);
+      held = got;
+      qn -= 64;
+    }
+  };
+
+  // lane l holds the group's point l
+  const bool jv = j0 + lane < j1;
+  const double *const pj = P + 3 * static_cast<int64_t>(jv ? j0 + lane : j0);
+  const double jx = pj[0], jy = pj[1], jz = pj[2];
+  auto frac = [&](double x, double y, double z, double (&f)[3]) {
+    f[0] = fma(z, g.h13 * is, fma(y, g.h12 * is, x * (g.h11 * is)));
+    f[1] = fma(z, g.h23 * is, y * (g.h22 * is));
+    f[2] = z * (g.h33 * is);
+  };
+  for (int k = 0; k < m; ++k) {
+    const int r = static_cast<int>((rs >> (4 * k)) & 15u), at = src + r;
+    const int i = ib + 64 * r + lane;
+    const double *const pi = P + 3 * static_cast<int64_t>(i < i1 ? i : ib);
+    double x = pi[0], y = pi[1], z = pi[2];
+    [[maybe_unused]] uint64_t list = 0;
+    [[maybe_unused]] int n_img = 0;
+    [[maybe_unused]] double fi[3];
+    if constexpr (SEARCH) {
+      list = static_cast<uint64_t>(static_cast<uint32_t>(
+                 __builtin_amdgcn_readlane(static_cast<int>(img.list), at))) |
+             static_cast<uint64_t>(static_cast<uint32_t>(
+                 __builtin_amdgcn_readlane(static_cast<int>(img.list >> 32), at)))
+                 << 32;
+      n_img = __builtin_amdgcn_readlane(img.n, at);
+    } else {
+      x += lane_value(shx, at);
+      y += lane_value(shy, at);
+      z += lane_value(shz, at);
+      frac(x, y, z, fi);
+    }
+    for (uint32_t left = static_cast<uint32_t>(uni(static_cast<int>(left_))); left != 0u;
+         left &= left - 1u)
+      for (int h = 0; h < 2; ++h) {
+        const int o = 2 * __builtin_ctz(left) + h, j = j0 + o;
+        if (j >= j1) continue;
+        const bool counts = i < i1 && (!(flags & kSettleDiag) || j > i);
+        if (flags & kSettleExact) {
+          push(counts, i, j);
+          continue;
+        }
+        double dx = lane_value(jx, o) - x, dy = lane_value(jy, o) - y, dz = lane_value(jz, o) - z;
+        double u = 0.0;
+        if constexpr (SEARCH) {
+          for (int e = 0; e < n_img; ++e) {
+            const int id = static_cast<int>((list >> (8 * e)) & 255u);
+            const double na = id % 5 - 2, nb = id / 5 % 5 - 2, nc = id / 25 - 2;
+            const double vx = dx - ((na * ax + nb * bx) + nc * cx), vy = dy - (nb * by + nc * cy),
+                         vz = dz - nc * cz;
+            const double v = fma(vz, vz, fma(vy, vy, vx * vx));
+            u = e == 0 ? v : min_arith(u, v);
+          }
+        } else {
+          if (!(flags & kSettleFast)) {
+            double fj[3];
+            frac(lane_value(jx, o), lane_value(jy, o), lane_value(jz, o), fj);
+            const double na = rint(fj[0] - fi[0]), nb = rint(fj[1] - fi[1]),
+                         nc = rint(fj[2] - fi[2]);
+            dz = fma(-cz, nc, dz);
+            dy = fma(-cy, nc, fma(-by, nb, dy));
+            dx = fma(-cx, nc, fma(-bx, nb, fma(-ax, na, dx)));
+          }
+          u = fma(dz, dz, fma(dy, dy, dx * dx));
+        }
+        float gap = __builtin_inff();
+        const uint32_t b = root_bits64(u, gap);
+        // the pair's bin is b or a neighbour: settled when it is not near an
+        // edge, or when none of the three is in the window
+        const int bin = static_cast<int>(b - kBinBits);
+        const bool open = counts && gap <= near_hi && bin >= b_lo - 1 && bin <= b_hi;
+        count.template add<true>(counts && !open ? b : kNoBits);
+        push(open, i, j);
+      }
+  }
+  if (qn > 0) drain(qn);
+}
+
 // One work item of a spatially sorted binary64 frame. binary64 counts follow
 // the canonical sequence bit for bit, but a pair's bin needs that sequence
 // only when its distance lies next to a bin edge. The pairs here work on
@@ -512,8 +625,7 @@ __device__ __forceinline__ Images group_images(const GroupBox &I, const GroupBox
 // from root_bits64. Here the threshold of the residuals bounds every rounding
 // between the inputs and u and between the inputs and the canonical t; one
 // ballot serves the pairs of two j, and when it fires the wave leaves them to
-// the canonical sequence on the input points (about one such group in 10^5 on
-// the 1M-point frame).
+// settle_pairs (about one such group in 10^5 on the 1M-point frame).
 //
 // Bound by vector-unit issue: 15 instructions per pair on the short path (17
 // with the clamp) against 22 over the frame with a binary64 root per pair
@@ -686,8 +798,8 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
               DIAG && j <= slice(k) ? kNoBits : b[k]);
       };
       J pa = load(0), pb = load(1);
-      int j = j0;
-      for (; j + 1 < j1; j += 2) {
+      int j = j0, je = j1;
+      for (; j + 1 < je; j += 2) {
         at += 48;
         uint32_t b[2 * M];
         float gap = __builtin_inff();
@@ -697,12 +809,17 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
         pb = load(1);
         if (__builtin_expect(__builtin_amdgcn_ballot_w64(gap <= near_hi) != 0, 0)) {
           left |= 1u << ((j - j0) >> 1);
+          // (all of the first eight j: distances repeat at bin edges here)
+          if (left == 15u) {
+            left = ~0u;
+            je = j0;
+          }
           continue;
         }
         tally(b, j);
         tally(b + M, j + 1);
       }
-      if (j < j1) {
+      if (j < je) {
         uint32_t b[M];
         float gap = __builtin_inff();
         bits_of(pa, j, b, gap);
@@ -713,8 +830,10 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
       }
     }
     if (__builtin_expect(left != 0u, 0))
-      exact_pairs<MODE, SEARCH ? kBoxTricSearch : kBoxTric>(F, w.hist, w.sweep, ib, w.i1, j0, j1,
-                                                            rs, M, left, DIAG);
+      settle_pairs<MODE, SEARCH>(F, w, ib, j0, j1, rs, M, left,
+                                 (DIAG ? kSettleDiag : 0) | (KIND == kExact ? kSettleExact : 0) |
+                                     (KIND == kFast ? kSettleFast : 0),
+                                 g * kUnitSlices, near_hi, shx, shy, shz, img);
     if constexpr (SEARCH && IMAGES != 1) {
       const uint64_t n = static_cast<uint64_t>(j1 - j0);
       uint64_t pairs = DIAG ? n * (n - 1) / 2 : 0;
