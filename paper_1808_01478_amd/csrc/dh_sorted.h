@@ -473,9 +473,10 @@ __device__ __forceinline__ Images group_images(const GroupBox &I, const GroupBox
 // j, and 64 at a time go through the canonical sequence on their input points.
 // With random points about one pass in 10^5 leaves anything; where distances
 // repeat at whole bins (a crystal, the bin a fraction of its spacing) all of
-// them leave everything, some per cent of it near an edge. The canonical
-// sequence for every pair left took, for 103,823 points of a cubic lattice
-// (spacing 3.61, cut-off 70, bins of 0.01), @BEFORE@ ms, this @AFTER@ ms.
+// them leave everything, some per cent of it near an edge. 103,823 points of a
+// cubic lattice (spacing 3.61, cut-off 70, 7,000 bins): 11.9 ms with the
+// canonical sequence for every pair left, 10.3 ms unsorted with a binary64
+// root per pair, 6.7 ms with this; random points of the same frame 2.7 ms.
 //
 // The first m slices in rs (four bits each) of the unit at ib against the j of
 // [j0, j1) in `left` (bit b: j0 + 2b and the next). SEARCH: the images of slice
