@@ -562,9 +562,7 @@ int dh_ctx_profile_read(dh_ctx *ctx, double *kernel_ms, int64_t *launches);
  * neighbouring boxes) in the last single-frame histogram on ctx
  * (dh_histo_async or dh_histo through ctx): the pairs whose Eq. 5 reduced
  * vector is at least half the shortest lattice vector long, counted by the
- * pair kernel; in binary64 frames staged in spatial order (65,536 points and
- * more) the pairs evaluated over more than one image, which their two groups
- * of 64 points leave open. 0 when that call ran no search (r_max below half the smallest
+ * pair kernel. 0 when that call ran no search (r_max below half the smallest
  * width, or no triclinic cell) or the frame was added into an accumulating
  * sum. The caller must have waited for that call's stream; this reads the
  * device counter with a blocking copy. DH_EINVAL for a null argument.
@@ -572,11 +570,14 @@ int dh_ctx_profile_read(dh_ctx *ctx, double *kernel_ms, int64_t *launches);
 int dh_ctx_searched_pairs(dh_ctx *ctx, uint64_t *searched);
 
 /*
- * Images evaluated for those pairs in the same call (Sec. 2.3's neighbouring
+ * Images evaluated for the search in the same call (Sec. 2.3's neighbouring
  * images; the kernel evaluates for each searched vector only the images of
- * its octant list, or all 27, and a wave runs to its longest list, in spatial
- * order the images its pair of groups can have, rounded up to 2, 4 or 8, so
- * this is the arithmetic actually spent on the search). 0 as for
+ * its octant list, or all 27, and a wave runs to its longest list, so this
+ * is the arithmetic actually spent on the search. Binary64 frames staged in
+ * spatial order, 65,536 points and more, search whole pairs of groups of 64
+ * points instead, over the images some pair of the two can have, rounded up
+ * to 2, 4 or 8; groups that can have only one need no search, so their pairs
+ * add none). 0 as for
  * dh_ctx_searched_pairs; same waiting rule and errors.
  */
 int dh_ctx_searched_images(dh_ctx *ctx, uint64_t *images);

@@ -218,8 +218,9 @@ extern "C" int dh_histo_noalloc(dh_stream stream, const double *d_coords,
   const bool oor_flush = d_out_of_range != nullptr && L.mode != kModeGlobal;
   fp.oor = oor_flush ? d_out_of_range : nullptr;
   fp.oor_by_flush = oor_flush ? 1 : 0;
-  fp.searched = kind == kBoxTricSearch || kind == kBoxSearchSorted ? reinterpret_cast<unsigned long long *>(counters + 2)
-                                       : nullptr;
+  // (no caller can read the counts: not where they cost a pass of their own)
+  fp.searched =
+      kind == kBoxTricSearch ? reinterpret_cast<unsigned long long *>(counters + 2) : nullptr;
 
   PlanArgs pa;
   for (int s = 0; s <= n_species; ++s) pa.off[s] = offsets[s];

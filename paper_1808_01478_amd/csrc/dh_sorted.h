@@ -617,6 +617,172 @@ __device__ __attribute__((noinline)) void settle_pairs(const FrameParams *frame,
   if (qn > 0) drain(qn);
 }
 
+// Rounding between the inputs and a coordinate difference of a pair of two
+// groups (binary64), here and in the canonical sequence: each of the dozen steps
+// rounds something no larger than the two points' |x| + |y| + |z| plus the cell,
+// so 2^-48 of that covers them; dt is that times s, in scaled units. Whether the
+// groups' coordinates are small enough for it to decide anything (false for a
+// group that is not finite); hm is the largest entry of B^-1.
+__device__ __forceinline__ bool rounding_bound(const GroupBox &I, const GroupBox &J,
+                                               const float (&cell)[6], double s, double hm,
+                                               double &dt) {
+  const double size = static_cast<double>(fabsf(cell[0]) + fabsf(cell[1]) + fabsf(cell[2]) +
+                                          fabsf(cell[3]) + fabsf(cell[4]) + fabsf(cell[5]));
+  const double mag = static_cast<double>(I.mag) + static_cast<double>(J.mag) + size;
+  dt = 0x1p-48 * mag * s;
+  return dt < 0x1p-25 && hm * mag < 0x1p20;
+}
+
+// The pairs of a unit of a sorted frame with image search that the search is
+// defined for: Eq. 5 vector of the canonical sequence at least half the
+// shortest lattice vector long (q >= qskip64), whatever the images evaluated.
+// Pairs of groups whose boxes lie on one side of that sphere count without a
+// look at their pairs. The others are looked at in binary32, wrapped as 32-bit
+// fixed-point fractions (see dh_pairs.h), and where its rounding could decide,
+// of the length or of a wrap, by the canonical sequence on the input.
+// The frame of 70,001 points takes 5.1 ms with the count and 4.0 without (7.1
+// with it in binary64, a slice at a time; 10.6 before such frames were sorted).
+__device__ __attribute__((noinline)) uint64_t searched_pairs(const FrameParams *frame, WorkItem w,
+                                                             int ib_, int jb_, int gpu_) {
+  const FrameParams *const F = uni(frame);
+  const int ib = uni(ib_), jb = uni(jb_), gpu = uni(gpu_), i1 = uni(w.i1), j1 = uni(w.j1);
+  const bool diag_item = (uni(w.flags) & kItemDiag) != 0;
+  const int lane = threadIdx.x & 63;
+  const int64_t n_pad = F->n_pad;
+  const char *const staged = static_cast<const char *>(F->coords);
+  const double *const P = reinterpret_cast<const double *>(staged);
+  const uint32_t *const index = reinterpret_cast<const uint32_t *>(staged + 24 * n_pad);
+  const GroupBox *const boxes = reinterpret_cast<const GroupBox *>(staged + 28 * n_pad);
+  const double *const in = F->in;
+  float cell[6], size = 0.f;
+#pragma unroll
+  for (int k = 0; k < 6; ++k) {
+    cell[k] = uni(F->cell32[k]);
+    size += fabsf(cell[k]);
+  }
+  const Geo64 geo = load_geo64(F);
+  const Geo32 g32 = load_geo32(F);
+  const double qskip = uni(F->qskip64);
+  const float radius = static_cast<float>(sqrt_cr(qskip)), slack = size * 0x1p-16f;
+
+  const int r = lane % kUnitSlices, gr = lane / kUnitSlices;
+  const int gi = (ib >> 6) + r, gj = (jb >> 6) + gr;
+  const bool valid =
+      ib + 64 * r < i1 && gr < gpu && jb + 64 * gr < j1 && !(diag_item && gj < gi);
+  const bool diag = diag_item && gj == gi;
+  const GroupBox &bi = boxes[valid ? gi : ib >> 6], &bj = boxes[valid ? gj : jb >> 6];
+  // (widened as the distance bounds of a window)
+  const GroupPair gp = classify<true>(bi, bj, cell, 0.f, radius * (1.f + 0x1p-12f) + slack,
+                                      fmaxf(radius * (1.f - 0x1p-12f) - slack, 0.f));
+  double dt;
+  const double hm = fmax(fmax(fabs(geo.h11), fabs(geo.h12)),
+                         fmax(fmax(fabs(geo.h13), fabs(geo.h22)),
+                              fmax(fabs(geo.h23), fabs(geo.h33))));
+  const bool bounded = rounding_bound(bi, bj, cell, geo.s * 0x1p-22, hm, dt);
+  const bool longer = bounded && gp.kind == kSkip, shorter = bounded && gp.in_window && !longer;
+  const int n_i = min(64, i1 - (ib + 64 * r)), n_j = min(64, j1 - (jb + 64 * gr));
+  int sum = !valid || shorter ? 0 : diag ? n_j * (n_j - 1) / 2 : n_i * n_j;
+  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+  int below = 0;  // pairs under qskip among those looked at
+  const bool look = valid && !longer && !shorter;
+  const uint64_t m_look = __builtin_amdgcn_ballot_w64(look);
+  const uint64_t m_exact = __builtin_amdgcn_ballot_w64(look && !bounded);
+  const uint64_t m_wrap = __builtin_amdgcn_ballot_w64(look && gp.kind != kFast);
+
+  // Squares in units of 2^-64 of a_x squared. A component of the binary32
+  // vector is off by less than 2^-21 of the sum of the cell's entries.
+  const float unit = 0x1p32f / cell[0], off = size * 0x1p-20f;
+  const float r_lo = fmaxf(radius - off, 0.f) * unit, r_hi = (radius + off) * unit;
+  const float q_lo = r_lo * r_lo, q_hi = r_hi * r_hi;
+  // fixed-point fractions of a staged point
+  const double to = 1.0 / (geo.s * 0x1p-22) * 0x1p32;
+  const double h11 = geo.h11 * to, h12 = geo.h12 * to, h13 = geo.h13 * to;
+  const double h22 = geo.h22 * to, h23 = geo.h23 * to, h33 = geo.h33 * to;
+  auto fixed = [&](int at, int (&u)[3]) {
+    const double *const p = P + 3 * static_cast<int64_t>(at);
+    const double x = p[0], y = p[1], z = p[2];
+    auto whole = [](double v) {
+      return static_cast<int>(fmin(fmax(v, -0x1p31), 0x1p31 - 1.0));
+    };
+    u[0] = whole(fma(z, h13, fma(y, h12, x * h11)));
+    u[1] = whole(fma(z, h23, y * h22));
+    u[2] = whole(z * h33);
+  };
+  for (int g = 0; g < gpu; ++g) {
+    const int ja = jb + 64 * g, n = min(64, j1 - ja);
+    auto bits = [&](uint64_t m) {
+      return static_cast<uint32_t>(m >> (g * kUnitSlices)) & ((1u << kUnitSlices) - 1u);
+    };
+    if (bits(m_look) == 0u) continue;
+    // the canonical sequence: pairs of slice q with j under qskip
+    auto canonical = [&](int q, int j) {
+      const int i = ib + 64 * q + lane;
+      const bool ok = i < i1 && (!diag_item || (i >> 6) != (ja >> 6) || j > i);
+      const int64_t a = 3 * static_cast<int64_t>(index[i < i1 ? i : ib]);
+      const int64_t b = 3 * static_cast<int64_t>(index[j]);
+      const double q0 =
+          q64<kBoxTric>(in[a], in[a + 1], in[a + 2], in[b], in[b + 1], in[b + 2], geo);
+      return __builtin_popcountll(__builtin_amdgcn_ballot_w64(ok && !(q0 >= qskip)));
+    };
+    for (uint32_t m = bits(m_exact); m != 0u; m &= m - 1u)
+      for (int j = 0; j < n; ++j) below += canonical(__builtin_ctz(m), ja + j);
+    int uj[3];
+    fixed(ja + (lane < n ? lane : 0), uj);
+    auto slices = [&](auto m_c, uint32_t rs, bool wrap) {
+      constexpr int M = decltype(m_c)::value;
+      int ui[M][3];
+      int after[M];  // the lane's pairs are those with j from here on
+#pragma unroll
+      for (int k = 0; k < M; ++k) {
+        const int i = ib + 64 * static_cast<int>((rs >> (4 * k)) & 15u) + lane;
+        fixed(i < i1 ? i : ib, ui[k]);
+        after[k] = i >= i1 ? 64 : diag_item && (i >> 6) == (ja >> 6) ? lane + 1 : 0;
+      }
+      for (int j = 0; j < n; ++j) {
+        const int ua = __builtin_amdgcn_readlane(uj[0], j), ub = __builtin_amdgcn_readlane(uj[1], j),
+                  uc = __builtin_amdgcn_readlane(uj[2], j);
+#pragma unroll
+        for (int k = 0; k < M; ++k) {
+          auto diff = [](int a, int b) {
+            return static_cast<float>(
+                static_cast<int>(static_cast<uint32_t>(a) - static_cast<uint32_t>(b)));
+          };
+          const float fa = diff(ua, ui[k][0]), fb = diff(ub, ui[k][1]), fc = diff(uc, ui[k][2]);
+          const float dx = fmaf(g32.ncx, fc, fmaf(g32.nbx, fb, fa)),
+                      dy = fmaf(g32.ncy, fc, g32.nby * fb), dz = g32.ncz * fc;
+          float q = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+          q = j >= after[k] ? q : __builtin_inff();
+          const uint64_t in_lo = __builtin_amdgcn_ballot_w64(q < q_lo);
+          uint64_t open = __builtin_amdgcn_ballot_w64(q < q_hi) ^ in_lo;
+          if (wrap)
+            open |= __builtin_amdgcn_ballot_w64(fmaxf(fabsf(fa), fmaxf(fabsf(fb), fabsf(fc))) >
+                                                0x1p31f * (1.f - 0x1p-21f));
+          if (__builtin_expect(open != 0, 0))
+            below += canonical(static_cast<int>((rs >> (4 * k)) & 15u), ja + j);
+          else
+            below += __builtin_popcountll(in_lo);
+        }
+      }
+    };
+    // those with an ambiguous wrap apart from the others
+    for (int wrap = 0; wrap < 2; ++wrap) {
+      uint32_t m = bits(m_look & ~m_exact) & (wrap ? bits(m_wrap) : ~bits(m_wrap));
+      auto take = [&](int n_s) {
+        uint32_t rs = 0;
+        for (int k = 0; k < n_s; ++k) {
+          rs |= static_cast<uint32_t>(__builtin_ctz(m)) << (4 * k);
+          m &= m - 1u;
+        }
+        return rs;
+      };
+      while (__builtin_popcount(m) >= 4) slices(Int<4>{}, take(4), wrap != 0);
+      if (__builtin_popcount(m) >= 2) slices(Int<2>{}, take(2), wrap != 0);
+      if (m != 0u) slices(Int<1>{}, take(1), wrap != 0);
+    }
+  }
+  return static_cast<uint64_t>(uni(sum) - uni(below));
+}
+
 // One work item of a spatially sorted binary64 frame. binary64 counts follow
 // the canonical sequence bit for bit, but a pair's bin needs that sequence
 // only when its distance lies next to a bin edge. The pairs here work on
@@ -663,8 +829,10 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
   double shx = 0.0, shy = 0.0, shz = 0.0;  // the lane's shift B n
   float near_hi = 0.f;  // thr's upper word, as a float (see below)
   [[maybe_unused]] Images img{};
-  // image search: pairs evaluated over more than one image, and those images
+  // image search: pairs it is defined for (see searched_pairs; once for all
+  // bin windows, each of which searches them), and the images evaluated
   [[maybe_unused]] uint64_t n_searched = 0, n_images = 0;
+  [[maybe_unused]] const bool tell = SEARCH && F->searched != nullptr && w.sweep == 0;
 
   auto frac = [&](auto axis_c, double x, double y, double z) {
     constexpr int K = decltype(axis_c)::value;
@@ -840,7 +1008,6 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
       uint64_t pairs = DIAG ? n * (n - 1) / 2 : 0;
       for (int k = 0; k < M && !DIAG; ++k)
         pairs += n * static_cast<uint64_t>(max(0, min(64, w.i1 - (slice(k) - lane))));
-      n_searched += pairs;
       n_images += pairs * (KIND == kExact ? kShifts : IMAGES);
     }
   };
@@ -882,6 +1049,7 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
                          !((w.flags & kItemDiag) && gj < gi);
       const GroupBox &bi = boxes[valid ? gi : ib >> 6], &bj = boxes[valid ? gj : jb >> 6];
       if constexpr (SEARCH) {
+        if (tell) n_searched += searched_pairs(F, w, ib, jb, gpu);
         img = group_images(bi, bj, cell, wb.hi, wb.slack);
         gp.kind = img.n == 0 || img.far2 < wb.lo * wb.lo ? kSkip
                   : img.n == 1                           ? kFast
@@ -898,20 +1066,13 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
       shx = (gp.n[0] * ax + gp.n[1] * bx) + gp.n[2] * cx;
       shy = gp.n[1] * by + gp.n[2] * cy;
       shz = gp.n[2] * cz;
-      // Rounding between the inputs and a coordinate difference, here and in
-      // the canonical sequence: each of the dozen steps rounds something no
-      // larger than the two points' |x| + |y| + |z| plus the cell, so 2^-48 of
-      // that covers them; in t: times s. A residual is then off by at most
-      // 2 t dt + 2^-48 t^2, t <= n_bins + 2 (beyond that the pair is out of
-      // range either way).
-      const double size = static_cast<double>(fabsf(cell[0]) + fabsf(cell[1]) + fabsf(cell[2]) +
-                                              fabsf(cell[3]) + fabsf(cell[4]) + fabsf(cell[5]));
-      const double mag = static_cast<double>(bi.mag) + static_cast<double>(bj.mag) + size;
-      const double dt = 0x1p-48 * mag * s, top = static_cast<double>(count.n_bins + 2u) * 0x1p-22;
+      // A residual is off by at most 2 t dt + 2^-48 t^2, t <= n_bins + 2
+      // (beyond that the pair is out of range either way).
+      double dt;
+      const double top = static_cast<double>(count.n_bins + 2u) * 0x1p-22;
       const double hm = fmax(fmax(fabs(h11), fabs(h12)), fmax(fmax(fabs(h13), fabs(h22)),
                                                               fmax(fabs(h23), fabs(h33)))) * s;
-      // (of this form so that a group that is not finite is exact)
-      const bool bounded = dt < 0x1p-25 && hm * mag < 0x1p20;
+      const bool bounded = rounding_bound(bi, bj, cell, s, hm, dt);
       if (!bounded) {
         gp.kind = kExact;
         gp.in_window = false;
@@ -977,8 +1138,9 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
       *s_item = static_cast<int>(gridDim.x) + atomicAdd(a.counter, 1);
   }
   if constexpr (SEARCH) {
-    if (F->searched != nullptr && n_searched != 0 && lane == 0) {
-      atomicAdd(F->searched, static_cast<unsigned long long>(n_searched));
+    if (F->searched != nullptr && lane == 0 && (n_searched | n_images) != 0) {
+      atomicAdd(F->searched,
+                static_cast<unsigned long long>(n_searched * static_cast<uint64_t>(F->n_sweeps)));
       atomicAdd(F->searched + 1, static_cast<unsigned long long>(n_images));
     }
   }

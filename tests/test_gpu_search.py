@@ -62,3 +62,34 @@ def test_search_images(ctx, name, points):
         bad = fp32_bound_violations(h, ref.hist, ref.edges)
         bad += oor_bound_violations(oor, ref.out_of_range, ref.edges)
         assert not bad, bad[:3]
+
+
+@pytest.mark.parametrize("points", ["random", "eighths", "outliers"])
+@pytest.mark.parametrize("name", sorted(CELLS))
+def test_searched_pairs_do_not_depend_on_the_staging(ctx, name, points):
+    """The pairs the search is defined for, of a frame staged in spatial order
+    and of the same frame in a context with a memory budget, which is not; the
+    counts as well. Outliers: coordinates that are not finite or too large for
+    any bound, whose groups take the canonical sequence throughout."""
+    import paper_1808_01478_amd as dh
+    box, _ = CELLS[name]
+    n = 66_003
+    rng = np.random.Generator(np.random.PCG64(n))
+    f = rng.uniform(-0.2, 1.2, size=(n, 3))
+    if points == "eighths":
+        f = rng.integers(0, 40, size=f.shape) / 40.0
+    x = np.ascontiguousarray(workloads.rows_combine(f, box))
+    if points == "outliers":
+        x[rng.integers(0, n, 40), rng.integers(0, 3, 40)] = rng.choice(
+            [np.nan, np.inf, -np.inf, 1e18, -3e12, 1e308], 40)
+    fr = workloads.Frame(x, np.array([0, 50_001, n], np.int64), workloads.BOX_TRICLINIC, box,
+                         0.7 * workloads.min_width(box), 300, name)
+    print(f"\n[case] searched pairs {name} {points}", flush=True)
+    h, oor = run_gpu(ctx, fr, 1)
+    searched, images = ctx.searched_pairs(), ctx.searched_images()
+    with dh.Context(0, hbm_budget_bytes=1 << 30) as plain:
+        g, oor_g = run_gpu(plain, fr, 1)
+        want = plain.searched_pairs()
+    assert np.array_equal(h, g) and np.array_equal(oor, oor_g)
+    assert 0 < want < fr.total_pairs() and searched == want, (searched, want)
+    assert images > 0
