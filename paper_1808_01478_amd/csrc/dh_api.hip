@@ -817,23 +817,26 @@ int run_frame(dh_ctx *ctx, hipStream_t st, const FrameJob &job, const Knobs &k, 
   }
   std::vector<WorkItem> items;
   std::vector<uint64_t> pairs;
-  plan_frame(0, job.offsets, job.n_species, padded_frame(job.kind), L, items,
-             pairs);
-  std::vector<size_t> cuts(1, 0);
-  if (limit > 0 && work > limit) {
-    uint64_t acc = 0;
-    for (size_t q = 0; q < items.size(); ++q) {
-      acc += static_cast<uint64_t>(items[q].i1 - items[q].i0) *
-             static_cast<uint64_t>(items[q].j1 - items[q].j0);
-      if (acc >= limit && q + 1 < items.size()) {
-        cuts.push_back(q + 1);
-        acc = 0;
+  std::vector<size_t> cuts;
+  auto plan = [&](bool tails) {
+    items.clear();
+    pairs.clear();
+    plan_frame(0, job.offsets, job.n_species, padded_frame(job.kind), L, items, pairs);
+    cuts.assign(1, 0);
+    if (limit > 0 && work > limit) {
+      uint64_t acc = 0;
+      for (size_t q = 0; q < items.size(); ++q) {
+        acc += static_cast<uint64_t>(items[q].i1 - items[q].i0) *
+               static_cast<uint64_t>(items[q].j1 - items[q].j0);
+        if (acc >= limit && q + 1 < items.size()) {
+          cuts.push_back(q + 1);
+          acc = 0;
+        }
       }
     }
-  }
-  cuts.push_back(items.size());
-  // every launch drains its own list: refine the tail of each
-  {
+    cuts.push_back(items.size());
+    if (!tails) return;
+    // every launch drains its own list: refine the tail of each
     std::vector<WorkItem> all, seg;
     std::vector<size_t> at(1, 0);
     for (size_t c = 0; c + 1 < cuts.size(); ++c) {
@@ -845,6 +848,23 @@ int run_frame(dh_ctx *ctx, hipStream_t st, const FrameJob &job, const Knobs &k, 
     }
     items.swap(all);
     cuts.swap(at);
+  };
+  // counters: one work counter per launch, then (8-byte aligned) the counts
+  // of image-searched pairs and of the images evaluated for them; the upload
+  // or the zero kernel clears them all
+  auto work_counters = [&] { return cuts.size() / 2 * 2; };
+  auto layout = [&] { return blob_layout(1, items.size(), pairs.size(), work_counters() + 4); };
+  plan(true);
+  if (ctx->budget) {
+    // items are a matter of speed: as coarse as the budget asks for
+    const size_t keys =
+        padded_frame(job.kind) ? static_cast<size_t>(sort_keys_count(n)) * sizeof(uint64_t) : 0;
+    const size_t others = ctx_device_bytes(ctx) - ctx->blob_cap + ctx->batch_bytes +
+                          (keys > ctx->keys_cap ? keys - ctx->keys_cap : 0);
+    // (a launch of bounded size keeps at least four)
+    while (others + layout().total > ctx->budget &&
+           (limit == 0 || 4ull * L.cfg.iblock * L.cfg.jchunk <= limit) && coarsen_items(L.cfg))
+      plan(false);
   }
   const size_t n_launches = cuts.size() - 1;
   fp.coords = ctx->d_staged;
@@ -854,12 +874,8 @@ int run_frame(dh_ctx *ctx, hipStream_t st, const FrameJob &job, const Knobs &k, 
   const bool oor_flush = job.d_oor && L.mode != kModeGlobal;
   fp.oor = oor_flush ? job.d_oor : nullptr;
   fp.oor_by_flush = oor_flush ? 1 : 0;
-  // counters: one work counter per launch, then (8-byte aligned) the counts
-  // of image-searched pairs and of the images evaluated for them; the upload
-  // or the zero kernel clears them all
-  const size_t n_work_counters = (n_launches + 1) / 2 * 2;
-  const size_t n_counters = n_work_counters + 4;
-  const BlobLayout lay = blob_layout(1, items.size(), pairs.size(), n_counters);
+  const size_t n_work_counters = work_counters(), n_counters = n_work_counters + 4;
+  const BlobLayout lay = layout();
   // the counter's device address goes into the frame constants, so the blob
   // is allocated before they are uploaded (a new allocation is never taken
   // for an unchanged plan)
@@ -1608,9 +1624,6 @@ int dh_batch_create(dh_ctx *ctx, const dh_frame_desc *frames, int32_t n_frames, 
   for (int32_t f = 0; f < n_frames; ++f)
     classes[{info[f].fp.box, info[f].mode}].push_back(f);
 
-  std::vector<WorkItem> items;
-  std::vector<uint64_t> pairs;
-  std::vector<size_t> pairs_base(n_frames, 0);
   for (auto &kv : classes) {
     std::vector<int32_t> &fs = kv.second;
     dh_batch::Group g;
@@ -1648,25 +1661,38 @@ int dh_batch_create(dh_ctx *ctx, const dh_frame_desc *frames, int32_t n_frames, 
     // large frames first: the tail of the work list is made of small items
     std::stable_sort(fs.begin(), fs.end(),
                      [&](int32_t x, int32_t y) { return info[x].pairs > info[y].pairs; });
-    g.item_begin = items.size();
-    Launch L;
-    L.cfg = g.cfg;
-    for (int32_t f : fs) {
-      L.n_sweeps = info[f].fp.n_sweeps;
-      pairs_base[f] = pairs.size();
-      plan_frame(f, info[f].offsets.data(), frames[f].n_species,
-                 padded_frame(info[f].fp.box), L, items, pairs);
-    }
-    std::vector<WorkItem> own(items.begin() + static_cast<std::ptrdiff_t>(g.item_begin),
-                              items.end());
-    refine_tail(own, g.grid, tail_step(g.kind));
-    items.resize(g.item_begin);
-    items.insert(items.end(), own.begin(), own.end());
-    g.item_count = items.size() - g.item_begin;
     b->groups.push_back(g);
     b->total_pairs += static_cast<double>(work);
   }
-  b->n_items = static_cast<int64_t>(items.size());
+  std::vector<WorkItem> items;
+  std::vector<uint64_t> pairs;
+  std::vector<size_t> pairs_base(n_frames, 0);
+  auto plan = [&](bool tails) {
+    items.clear();
+    pairs.clear();
+    auto g = b->groups.begin();
+    for (auto &kv : classes) {
+      g->item_begin = items.size();
+      Launch L;
+      L.cfg = g->cfg;
+      for (int32_t f : kv.second) {
+        L.n_sweeps = info[f].fp.n_sweeps;
+        pairs_base[f] = pairs.size();
+        plan_frame(f, info[f].offsets.data(), frames[f].n_species,
+                   padded_frame(info[f].fp.box), L, items, pairs);
+      }
+      if (tails) {
+        std::vector<WorkItem> own(items.begin() + static_cast<std::ptrdiff_t>(g->item_begin),
+                                  items.end());
+        refine_tail(own, g->grid, tail_step(g->kind));
+        items.resize(g->item_begin);
+        items.insert(items.end(), own.begin(), own.end());
+      }
+      g->item_count = items.size() - g->item_begin;
+      ++g;
+    }
+  };
+  plan(true);
 
   // staged coordinates
   std::vector<size_t> staged_off(n_frames);
@@ -1681,19 +1707,37 @@ int dh_batch_create(dh_ctx *ctx, const dh_frame_desc *frames, int32_t n_frames, 
     b->max_hist = std::max(b->max_hist, info[f].fp.n_hist);
     b->any_oor = b->any_oor || frames[f].d_out_of_range != nullptr;
   }
-  // blob: frames | items | pairs | counters
-  b->off_frames = 0;
-  b->off_items = align_up(n_frames * sizeof(FrameParams), 256);
-  const size_t off_pairs = align_up(b->off_items + items.size() * sizeof(WorkItem), 256);
-  b->off_counters = align_up(off_pairs + pairs.size() * sizeof(uint64_t), 256);
-  const size_t blob_bytes = b->off_counters + align_up(b->groups.size() * sizeof(int32_t), 256);
   int64_t max_sorted = 0;
   for (int32_t f = 0; f < n_frames; ++f)
     if (padded_frame(info[f].fp.box)) max_sorted = std::max(max_sorted, info[f].fp.n_points);
   const size_t keys_bytes =
       max_sorted > 0 ? static_cast<size_t>(sort_keys_count(max_sorted)) * 8 : 0;
+  // blob: frames | items | pairs | counters
+  b->off_frames = 0;
+  b->off_items = align_up(n_frames * sizeof(FrameParams), 256);
+  size_t off_pairs = 0, blob_bytes = 0;
+  auto layout = [&] {
+    off_pairs = align_up(b->off_items + items.size() * sizeof(WorkItem), 256);
+    b->off_counters = align_up(off_pairs + pairs.size() * sizeof(uint64_t), 256);
+    blob_bytes = b->off_counters + align_up(b->groups.size() * sizeof(int32_t), 256);
+    return staged_bytes + blob_bytes + keys_bytes;
+  };
   // the batch's buffers count against the context's budget while it lives
-  const size_t own = staged_bytes + blob_bytes + keys_bytes;
+  size_t own = layout();
+  if (ctx->budget) {
+    // items are a matter of speed: as coarse as the budget asks for
+    const size_t held = ctx_device_bytes(ctx) + ctx->batch_bytes;
+    auto coarsen = [&] {
+      bool any = false;
+      for (dh_batch::Group &g : b->groups) any = coarsen_items(g.cfg) || any;
+      return any;
+    };
+    while (held + own > ctx->budget && coarsen()) {
+      plan(false);
+      own = layout();
+    }
+  }
+  b->n_items = static_cast<int64_t>(items.size());
   if (ctx->budget) {
     const size_t held = ctx_device_bytes(ctx) + ctx->batch_bytes;
     if (held > ctx->budget || own > ctx->budget - held)

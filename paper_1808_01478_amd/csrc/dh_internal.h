@@ -320,6 +320,19 @@ inline void set_items(KernelConfig &c, int32_t precision, int32_t kind, int grid
   c.jchunk = static_cast<int32_t>(jc);
 }
 
+// The next coarser cut (about a quarter of the items), for contexts whose memory
+// budget has no room for the list; false at the coarsest, 8,192 i by 16,384 j an
+// item.
+inline bool coarsen_items(KernelConfig &c) {
+  constexpr int32_t kTopI = 16 * kUnitPoints, kTopJ = 32 * kUnitPoints;
+  if (c.iblock >= kTopI && c.jchunk >= kTopJ && c.dchunk >= kTopJ) return false;
+  auto twice = [](int32_t v, int32_t top) { return v < top / 2 ? 2 * v : v < top ? top : v; };
+  c.iblock = twice(c.iblock, kTopI);
+  c.jchunk = twice(c.jchunk, kTopJ);
+  c.dchunk = twice(c.dchunk, kTopJ);
+  return true;
+}
+
 // Species pair (s, t) of histogram h among k species, in the library order:
 // (0,0), (1,1), ..., (k-1,k-1), then (s,t) for s < t lexicographically.
 __host__ __device__ inline void hist_pair(int32_t k, int32_t h, int32_t &s, int32_t &t) {
