@@ -515,7 +515,8 @@ int dh_ctx_set_tuning(dh_ctx *ctx, int32_t mode, const char *cache_path);
 /*
  * Forces a launch shape for every later call on ctx and for batches created
  * on it (NULL restores tuning):
- * knobs[8] = {r (4|8), copies (1|2|4), tj (128|256), noclamp (0|1),
+ * knobs[8] = {r (4|8), copies (1|2|4: LDS for that many histograms, of which
+ * one is used; cached shapes reserve one), tj (128|256), noclamp (0|1),
  * occ_cap (0..16, 0 = as many as fit), items_per_wg (1..64),
  * threads (256|512|1024, or 0 = the size that puts most waves on a CU within
  * the LDS limit on workgroups per CU; of equals the smallest, but 512 at least

@@ -411,6 +411,9 @@ struct Knobs {
   // global-atomic kernel when the LDS plan needs at least this many bin
   // windows (0: never, 1: always)
   int32_t wide = kWideDefault32;
+  // from a tuning cache: its `copies` may be of kernels that counted into
+  // several, so no LDS is reserved for more than the one
+  bool cached = false;
   std::array<int32_t, kNumKnobs> pack() const {
     return {r, copies, tj, noclamp, occ_cap, items_per_wg, threads, wide};
   }
@@ -457,7 +460,7 @@ BaseConfig base_config(size_t lds_per_block, int precision, const Knobs &k, int 
   // resolved by resolve_threads once the LDS size is known
   c.threads = kind == kBoxTricSearch ? 256 : (k.threads ? k.threads : 256);
   c.r = k.r;
-  c.copies = k.copies;
+  c.copies = k.cached ? 1 : k.copies;
   c.tj = k.tj;
   c.wg_per_cu = k.occ_cap;
   c.iblock = c.threads * c.r;
@@ -1412,6 +1415,7 @@ int histo_job(dh_ctx *ctx, hipStream_t stream, const double *d_coords, const int
     auto it = ctx->tune_cache.find(key);
     if (it != ctx->tune_cache.end()) {
       k = Knobs::unpack(it->second);
+      k.cached = true;
     } else if (ctx->tune_mode == DH_TUNE_ON && job.total > 0 && !accumulate && !stepped) {
       // (tuning overwrites the output, so accumulating calls never tune;
       // nor do stepped jobs, whose launches someone else paces)
