@@ -97,7 +97,6 @@ enum HistMode : int32_t {
 
 // WorkItem::flags
 constexpr int32_t kItemDiag = 1;  // the j-range lies in the i-block: count j > i only
-constexpr int32_t kItemFull = 2;  // every lane holds a valid i-particle
 
 constexpr int kShifts = 27;
 // index of the zero shift (i = j = k = 0) in the shift tables
@@ -170,10 +169,6 @@ struct FrameParams {
   float cell32[6];
   float hinv32[6];
   float s32;
-  // spatially sorted binary32 frames: the lattice shift B n for the wraps
-  // n_k = +1 (bit k of q), -1 (bit 3 + k) or 0, in binary32 as
-  // (n_a a_x + n_b b_x) + n_c c_x, n_b b_y + n_c c_y, n_c c_z (w unused)
-  alignas(16) float gshift32[64][4];
   // image search: for each octant of a reduced vector's fractional
   // coordinates (bit k set when component k is negative) the images that
   // can be nearer than the vector itself, as indices into the shift tables
@@ -241,7 +236,7 @@ inline int staged_kind(int kind, int precision, const FrameParams &fp, int64_t n
 }
 
 // One unit of work: particles [i0, i1) of the frame against [j0, j1), for
-// histogram `hist`, bin window `sweep`; flags: kItemDiag, kItemFull.
+// histogram `hist`, bin window `sweep`; flags: kItemDiag.
 struct WorkItem {
   int32_t frame, hist, sweep, flags;
   int32_t i0, i1, j0, j1;
@@ -407,11 +402,10 @@ __host__ __device__ inline int64_t emit_row(const HistRows &r, int32_t h, int32_
                                             WorkItem *dst) {
   const int64_t b0 = r.lane0 + row * bi;
   const int64_t b1 = b0 + bi < r.lane1 ? b0 + bi : r.lane1;
-  const int32_t full = b1 - b0 == bi ? kItemFull : 0;
   int64_t n = 0;
   auto put = [&](int64_t j0, int64_t j1, int32_t diag) {
     WorkItem w;
-    w.frame = 0; w.hist = h; w.sweep = sweep; w.flags = diag | full;
+    w.frame = 0; w.hist = h; w.sweep = sweep; w.flags = diag;
     w.i0 = static_cast<int32_t>(b0); w.i1 = static_cast<int32_t>(b1);
     w.j0 = static_cast<int32_t>(j0); w.j1 = static_cast<int32_t>(j1);
     dst[n++] = w;

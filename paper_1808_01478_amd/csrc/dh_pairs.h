@@ -1105,7 +1105,7 @@ constexpr int max_threads() {
 // 89.3 and 85.7 ms; 24 orthorhombic frames: 21.9 and 21.4 ms.
 template <typename T, int R, int BOX>
 constexpr int min_waves() {
-  return sizeof(T) == 4 && BOX != kBoxTricSearch && (R == 4 || BOX == kBoxTricSorted) ? 8 : 1;
+  return sizeof(T) == 4 && BOX != kBoxTricSearch && R == 4 ? 8 : 1;
 }
 
 template <typename T, int R, int BOX, int MODE>
@@ -1181,9 +1181,10 @@ PairFn pick_box(int box) {
     case kBoxCube:
       if constexpr (sizeof(T) == 4) return pairs_kernel<T, R, kBoxCube, SW>;
       return pairs_kernel<T, R, kBoxOrtho, SW>;
-    case kBoxTricSorted: return pairs_kernel<T, R, kBoxTricSorted, SW>;
+    // (units of a sorted frame are the same for every R)
+    case kBoxTricSorted: return pairs_kernel<T, 4, kBoxTricSorted, SW>;
     case kBoxSearchSorted:  // binary64 only
-      if constexpr (sizeof(T) == 8) return pairs_kernel<T, R, kBoxSearchSorted, SW>;
+      if constexpr (sizeof(T) == 8) return pairs_kernel<T, 4, kBoxSearchSorted, SW>;
       return nullptr;
     default: return pairs_kernel<T, R, kBoxTricSearch, SW>;
   }
