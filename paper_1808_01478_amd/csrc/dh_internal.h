@@ -195,6 +195,13 @@ struct FrameParams {
 // unsorted. (Cube of edge 6e-22: subnormal squares rounded by up to 1/2 of
 // themselves, and group pairs with a pair within the cut-off were left out.)
 //
+// Without image search a wrap that rounding decides otherwise than the canonical
+// sequence must not matter: such a pair is half a cell apart along some axis up
+// to 2^-25 of it (see rounding_bound), so it is out of range under either wrap
+// when the cut-off keeps 2^-22 from half the smallest width; binary64 frames that
+// come closer stay unsorted. (In an orthorhombic cell the two images are equally
+// far to within the bound of the rounding.)
+//
 // The sorted binary64 kernel takes bins from a binary32 root of numbers scaled
 // by s 2^-22: fewer than 2^20 bins, and a scale whose square is a normal
 // number. With image search it takes a pair's nearest image, which is the
@@ -214,7 +221,14 @@ inline int staged_kind(int kind, int precision, const FrameParams &fp, int64_t n
   const bool large =
       n_points >= kSortMinPoints && n_points <= 0x7FFFFFFF - 128 * kMaxSpeciesStage && fits &&
       ranged;
-  if (large && (kind == kBoxTric || (kind == kBoxOrtho && precision != 0))) return kBoxTricSorted;
+  // 1 / width^2 along each axis: the squared rows of B^-1
+  const double ra = fp.h11 * fp.h11 + fp.h12 * fp.h12 + fp.h13 * fp.h13;
+  const double rb = fp.h22 * fp.h22 + fp.h23 * fp.h23, rc = fp.h33 * fp.h33;
+  const double r = ra > rb ? (ra > rc ? ra : rc) : (rb > rc ? rb : rc);
+  const double cut = 2.0 * fp.n_bins / fp.s;  // twice the cut-off
+  const bool clear = precision == 0 || kind != kBoxTric || cut * cut * r < 1.0 - 0x1p-21;
+  if (large && clear && (kind == kBoxTric || (kind == kBoxOrtho && precision != 0)))
+    return kBoxTricSorted;
   if (large && kind == kBoxTricSearch && precision != 0 && may_search) {
     double diagonal2 = 0.0;
     for (int q = 0; q < 8; ++q) {
@@ -224,10 +238,6 @@ inline int staged_kind(int kind, int precision, const FrameParams &fp, int64_t n
       const double d2 = x * x + y * y + z * z;
       diagonal2 = d2 > diagonal2 ? d2 : diagonal2;
     }
-    // 1 / width^2 along each axis: the squared rows of B^-1
-    const double ra = fp.h11 * fp.h11 + fp.h12 * fp.h12 + fp.h13 * fp.h13;
-    const double rb = fp.h22 * fp.h22 + fp.h23 * fp.h23, rc = fp.h33 * fp.h33;
-    const double r = ra > rb ? (ra > rc ? ra : rc) : (rb > rc ? rb : rc);
     if (diagonal2 * r < 2.25 * (1.0 - 1e-6)) return kBoxSearchSorted;
   }
   if (precision != 0) return kind;

@@ -101,6 +101,19 @@ def test_frames_of_extreme_scale_stay_unsorted(lib, box_type, precision):
                 assert kind == in_order, (k, kind)
 
 
+def test_cutoff_next_to_half_the_width_stays_unsorted(lib):
+    """A binary64 pair half a cell apart may be wrapped either way by rounding;
+    sorted frames keep its length out of range by 2^-23 of the width."""
+    box = np.ascontiguousarray(SKEW)
+    half = 0.5 * workloads.min_width(SKEW)
+    for k in range(10, 31):
+        r_max = half * (1.0 - 2.0 ** -k)
+        kind = lib.staged_kind(workloads.BOX_TRICLINIC, box.ctypes.data, r_max, 1000, 1, 1 << 17)
+        assert kind == (SORTED if k < 22 else TRIC if k < 30 else SEARCH_SORTED) or k in (22, 29)
+        kind = lib.staged_kind(workloads.BOX_TRICLINIC, box.ctypes.data, r_max, 1000, 0, 1 << 17)
+        assert kind == (SORTED if k < 30 else SEARCH) or k == 29
+
+
 def test_word_index_of_the_last_points(lib):
     """Frames may have almost 2^31 points, three words each."""
     for i in (0, 1, 715_827_882, 715_827_883, 1 << 30, 0x7FFFFFFF):
