@@ -477,6 +477,9 @@ __device__ __forceinline__ Images group_images(const GroupBox &I, const GroupBox
 // cubic lattice (spacing 3.61, cut-off 70, 7,000 bins): 11.9 ms with the
 // canonical sequence for every pair left, 10.3 ms unsorted with a binary64
 // root per pair, 6.7 ms with this; random points of the same frame 2.7 ms.
+// Groups without a rounding bound (kExact) are taken from the input throughout,
+// as an unsorted frame's: 100,000 points of a cube, all too far out for a bound,
+// 7.3 ms (19.1 with the canonical sequence for each pair).
 //
 // The first m slices in rs (four bits each) of the unit at ib against the j of
 // [j0, j1) in `left` (bit b: j0 + 2b and the next). SEARCH: the images of slice
@@ -541,10 +544,15 @@ __device__ __attribute__((noinline)) void settle_pairs(const FrameParams *frame,
     }
   };
 
+  // the staged or, for groups without a rounding bound, the input points;
   // lane l holds the group's point l
-  const bool jv = j0 + lane < j1;
-  const double *const pj = P + 3 * static_cast<int64_t>(jv ? j0 + lane : j0);
+  const bool exact = (flags & kSettleExact) != 0;
+  auto point = [&](int at) {
+    return exact ? in + 3 * static_cast<int64_t>(index[at]) : P + 3 * static_cast<int64_t>(at);
+  };
+  const double *const pj = point(j0 + lane < j1 ? j0 + lane : j0);
   const double jx = pj[0], jy = pj[1], jz = pj[2];
+  const Bins64 bins = bins64(F);
   auto frac = [&](double x, double y, double z, double (&f)[3]) {
     f[0] = fma(z, g.h13 * is, fma(y, g.h12 * is, x * (g.h11 * is)));
     f[1] = fma(z, g.h23 * is, y * (g.h22 * is));
@@ -553,7 +561,7 @@ __device__ __attribute__((noinline)) void settle_pairs(const FrameParams *frame,
   for (int k = 0; k < m; ++k) {
     const int r = static_cast<int>((rs >> (4 * k)) & 15u), at = src + r;
     const int i = ib + 64 * r + lane;
-    const double *const pi = P + 3 * static_cast<int64_t>(i < i1 ? i : ib);
+    const double *const pi = point(i < i1 ? i : ib);
     double x = pi[0], y = pi[1], z = pi[2];
     [[maybe_unused]] uint64_t list = 0;
     [[maybe_unused]] int n_img = 0;
@@ -565,7 +573,7 @@ __device__ __attribute__((noinline)) void settle_pairs(const FrameParams *frame,
                  __builtin_amdgcn_readlane(static_cast<int>(img.list >> 32), at)))
                  << 32;
       n_img = __builtin_amdgcn_readlane(img.n, at);
-    } else {
+    } else if (!exact) {
       x += lane_value(shx, at);
       y += lane_value(shy, at);
       z += lane_value(shz, at);
@@ -577,8 +585,17 @@ __device__ __attribute__((noinline)) void settle_pairs(const FrameParams *frame,
         const int o = 2 * __builtin_ctz(left) + h, j = j0 + o;
         if (j >= j1) continue;
         const bool counts = i < i1 && (!(flags & kSettleDiag) || j > i);
-        if (flags & kSettleExact) {
-          push(counts, i, j);
+        if (exact) {
+          // as an unsorted frame's pair
+          double dx, dy, dz;
+          reduce64<kBoxTric>(x, y, z, lane_value(jx, o), lane_value(jy, o), lane_value(jz, o), g,
+                             dx, dy, dz);
+          double q = fma(dz, dz, fma(dy, dy, dx * dx));
+          if constexpr (SEARCH) q = search_q64(dx, dy, dz, q, g);
+          float gap = __builtin_inff();
+          uint32_t b = root_bits64(q * bins.scale, gap);
+          if (__builtin_expect(any_near(gap, bins), 0)) b = canonical_bits(q, bins.s);
+          count.template add<true>(counts ? b : kNoBits);
           continue;
         }
         double dx = lane_value(jx, o) - x, dy = lane_value(jy, o) - y, dz = lane_value(jz, o) - z;
@@ -607,9 +624,11 @@ __device__ __attribute__((noinline)) void settle_pairs(const FrameParams *frame,
         float gap = __builtin_inff();
         const uint32_t b = root_bits64(u, gap);
         // the pair's bin is b or a neighbour: settled when it is not near an
-        // edge, or when none of the three is in the window
+        // edge, when it is within half a bin of 0 (coincident points), or when
+        // none of the three is in the window
         const int bin = static_cast<int>(b - kBinBits);
-        const bool open = counts && gap <= near_hi && bin >= b_lo - 1 && bin <= b_hi;
+        const bool open =
+            counts && gap <= near_hi && u >= 0x1p-46 && bin >= b_lo - 1 && bin <= b_hi;
         count.template add<true>(counts && !open ? b : kNoBits);
         push(open, i, j);
       }
@@ -622,7 +641,11 @@ __device__ __attribute__((noinline)) void settle_pairs(const FrameParams *frame,
 // rounds something no larger than the two points' |x| + |y| + |z| plus the cell,
 // so 2^-48 of that covers them; dt is that times s, in scaled units. Whether the
 // groups' coordinates are small enough for it to decide anything (false for a
-// group that is not finite); hm is the largest entry of B^-1.
+// group that is not finite); hm is the largest entry of B^-1. Up to 2^24 cells
+// out, a pair's fractional differences here and in the canonical sequence (each
+// some eight roundings of 2^-53 of hm mag) agree to 2^-25, well within
+// kWrapMargin; where they round to different wraps the pair is out of range
+// under both (see staged_kind).
 __device__ __forceinline__ bool rounding_bound(const GroupBox &I, const GroupBox &J,
                                                const float (&cell)[6], double s, double hm,
                                                double &dt) {
@@ -630,7 +653,7 @@ __device__ __forceinline__ bool rounding_bound(const GroupBox &I, const GroupBox
                                           fabsf(cell[3]) + fabsf(cell[4]) + fabsf(cell[5]));
   const double mag = static_cast<double>(I.mag) + static_cast<double>(J.mag) + size;
   dt = 0x1p-48 * mag * s;
-  return dt < 0x1p-25 && hm * mag < 0x1p20;
+  return dt < 0x1p-25 && hm * mag < 0x1p24;
 }
 
 // The pairs of a unit of a sorted frame with image search that the search is

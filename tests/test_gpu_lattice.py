@@ -55,3 +55,25 @@ def test_distances_on_bin_edges(ctx, kind, k):
             h, oor = run_gpu(ctx, fr, 1)
             assert np.array_equal(h, ref.hist) and np.array_equal(oor, ref.out_of_range)
     ctx.set_config(None)
+
+
+@pytest.mark.parametrize("points", ["far", "coincident"])
+@pytest.mark.parametrize("kind", list(KINDS))
+def test_groups_without_a_bound_and_coincident_points(ctx, kind, points):
+    """A third of the points 2^26 to 2^40 cells away, where no rounding bound
+    decides anything and whole groups are taken from the input, or all at a few
+    places, where every distance of a pair is 0 or one of a few."""
+    box_type, rows, r_max = KINDS[kind]
+    n = 65_700
+    rng = np.random.Generator(np.random.PCG64(n))
+    f = rng.uniform(0.0, 1.0, size=(n, 3))
+    if points == "far":
+        f[rng.permutation(n)[:n // 3]] += 2.0 ** rng.integers(26, 41, size=(n // 3, 1))
+    else:
+        f = f[rng.integers(0, 5, n)]
+    fr = workloads.Frame(np.ascontiguousarray(workloads.rows_combine(f, rows)),
+                         np.array([0, 40_000, n], np.int64), box_type, rows, r_max, 700, points)
+    print(f"\n[case] {points} {kind}", flush=True)
+    ref = oracle.frame_histogram(fr)
+    h, oor = run_gpu(ctx, fr, 1)
+    assert np.array_equal(h, ref.hist) and np.array_equal(oor, ref.out_of_range)
