@@ -825,7 +825,8 @@ __device__ __attribute__((noinline)) uint64_t searched_pairs(const FrameParams *
 // cube (cut-off half the edge, so little is skipped) 4.34 and 3.49 ms.
 template <int MODE, bool SEARCH>
 __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const WorkItem &w,
-                                             const FrameParams *F, int *s_unit, int *s_item) {
+                                             const FrameParams *F, int *s_unit, int *s_item,
+                                             unsigned long long *s_search) {
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
   const char *const staged = uni(static_cast<const char *>(F->coords));
   const int64_t n_pad = uni(static_cast<int>(F->n_pad));
@@ -1161,11 +1162,7 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
       *s_item = static_cast<int>(gridDim.x) + atomicAdd(a.counter, 1);
   }
   if constexpr (SEARCH) {
-    if (F->searched != nullptr && lane == 0 && (n_searched | n_images) != 0) {
-      atomicAdd(F->searched,
-                static_cast<unsigned long long>(n_searched * static_cast<uint64_t>(F->n_sweeps)));
-      atomicAdd(F->searched + 1, static_cast<unsigned long long>(n_images));
-    }
+    add_searched(s_search, lane, n_searched * static_cast<uint64_t>(uni(F->n_sweeps)), n_images);
   }
 }
 

@@ -93,3 +93,22 @@ def test_searched_pairs_do_not_depend_on_the_staging(ctx, name, points):
     assert np.array_equal(h, g) and np.array_equal(oor, oor_g)
     assert 0 < want < fr.total_pairs() and searched == want, (searched, want)
     assert images > 0
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_searched_pairs_of_many_small_items(ctx, precision):
+    """The counts of searched pairs add up over waves, items and species: 32
+    species against the same points as one."""
+    box, _ = CELLS["skew"]
+    rng = np.random.Generator(np.random.PCG64(9))
+    x = np.ascontiguousarray(workloads.rows_combine(rng.uniform(0, 1, size=(1000, 3)), box))
+    got = []
+    for k in (32, 1):
+        offs = np.linspace(0, 1000, k + 1).astype(np.int64)
+        fr = workloads.Frame(x, offs, workloads.BOX_TRICLINIC, box, 0.8 * workloads.min_width(box),
+                             128, f"{k} species")
+        print(f"\n[case] searched pairs, {k} species", flush=True)
+        h, _ = run_gpu(ctx, fr, precision)
+        got.append((ctx.searched_pairs(), h.sum()))
+        assert 7 * got[-1][0] <= ctx.searched_images() <= 27 * got[-1][0]
+    assert got[0] == got[1] and got[0][0] > 0
