@@ -244,32 +244,37 @@ __device__ __forceinline__ void run_sorted(const PairKernelArgs &a, const WorkIt
     constexpr bool DIAG = decltype(diag_c)::value;
     const int j0 = jb + 64 * g;
     if constexpr (KIND == kSlow) {
-      static_assert(M == 1, "fixed-point passes take one slice");
-      // -(b:a) of the i-point and -(c':c), c' the c of the point 64 before an
-      // odd slice's (one 64-bit addition to j's (c:c) gives both c
-      // differences, an odd slice's lowered by one unit when the even one
-      // borrows, as in unsorted frames)
-      const int r = static_cast<int>(rs & 15u);
-      const int i = ib + 64 * r + lane;
-      const bool ok = i < w.i1;
-      const int ic = ok ? i : ib;
-      const uint32_t *const wi = W + first_word(ic);
-      const uint32_t za = wi[2];
-      const uint32_t zb = r & 1 ? W[first_word(ok ? i - 64 : ib) + 2] : 0u;
-      const uint64_t nab = 0ull - ((static_cast<uint64_t>(wi[1]) << 32) | wi[0]);
-      const uint64_t nzz = r & 1 ? 0ull - ((static_cast<uint64_t>(za) << 32) | zb)
-                                 : 0ull - static_cast<uint64_t>(za);
-      const bool odd = (r & 1) != 0;
+      // -(b:a) of the i-points and -(c:c'), c' the c of the point 64 before an
+      // odd slice's and 0 otherwise: the upper word of one 64-bit addition to
+      // j's (c:c) is the c difference, an odd slice's lowered by one unit when
+      // the even one borrows, as in unsorted frames
+      uint64_t nab[M], nzz[M];
+      float off[M];
+      [[maybe_unused]] int i0 = 0;
+#pragma unroll
+      for (int k = 0; k < M; ++k) {
+        const int r = static_cast<int>((rs >> (4 * k)) & 15u);
+        const int i = ib + 64 * r + lane;
+        const bool ok = i < w.i1;
+        const uint32_t *const wi = W + first_word(ok ? i : ib);
+        const uint32_t zb = r & 1 ? W[first_word(ok ? i - 64 : ib) + 2] : 0u;
+        nab[k] = 0ull - ((static_cast<uint64_t>(wi[1]) << 32) | wi[0]);
+        nzz[k] = 0ull - ((static_cast<uint64_t>(wi[2]) << 32) | zb);
+        off[k] = ok ? kBinOffset : kNoBin;
+        if constexpr (DIAG) i0 = i;
+      }
       run_j(Int<4>{}, Yes{}, j0, [&](const float4 &e, int j) {
         const uint64_t ab =
             (static_cast<uint64_t>(__float_as_uint(e.y)) << 32) | __float_as_uint(e.x);
         const uint64_t cc =
             (static_cast<uint64_t>(__float_as_uint(e.z)) << 32) | __float_as_uint(e.z);
-        const uint64_t dcc = cc + nzz;
-        const float fc = static_cast<float>(
-            static_cast<int32_t>(static_cast<uint32_t>(odd ? dcc >> 32 : dcc)));
-        count.template add<true>(bits32_packed_c<kBoxTric>(
-            ab, nab, fc, g32, ok && (!DIAG || j > i) ? kBinOffset : kNoBin));
+#pragma unroll
+        for (int k = 0; k < M; ++k) {
+          const float fc = static_cast<float>(
+              static_cast<int32_t>(static_cast<uint32_t>((cc + nzz[k]) >> 32)));
+          count.template add<true>(bits32_packed_c<kBoxTric>(
+              ab, nab[k], fc, g32, DIAG && j <= i0 ? kNoBin : off[k]));
+        }
       });
     } else {
       // A lane past the end of the item holds an i-point at infinity: its q is
@@ -378,8 +383,7 @@ __device__ __forceinline__ void run_sorted(const PairKernelArgs &a, const WorkIt
       passes(Int<kFix>{}, Yes{}, bits(m_fix0), g);
       passes(Int<kFix + 1>{}, Yes{}, bits(m_fix1), g);
       passes(Int<kFix + 2>{}, Yes{}, bits(m_fix2), g);
-      for (uint32_t m = bits(m_slow); m != 0u; m &= m - 1u)
-        pass(Int<kSlow>{}, Int<1>{}, Yes{}, No{}, static_cast<uint32_t>(__builtin_ctz(m)), g);
+      passes(Int<kSlow>{}, Yes{}, bits(m_slow), g);
       if (const uint32_t m = bits(m_diag)) {
         // at most one slice of the unit is the group itself
         const uint32_t r = static_cast<uint32_t>(__builtin_ctz(m));
