@@ -182,6 +182,12 @@ struct FrameParams {
   uint8_t oct_seven;
 };
 
+// Whether binary32 squares of lengths decide about groups of pairs in a cell whose
+// entries add up to `size`.
+__host__ __device__ inline bool bounds_decide(double size) {
+  return size > 0x1p-40 && size < 0x1p60;
+}
+
 // The minimum-image kind the kernels use for a frame: the geometric kind of
 // frame_constants (fp), with large frames staged in spatial order (triclinic
 // frames in both precisions; orthorhombic ones in binary64, where the sorted
@@ -190,10 +196,12 @@ struct FrameParams {
 // binary32 special case of equal orthorhombic edges.
 //
 // Sorted kernels decide whole groups of pairs from squares of lengths in
-// binary32, widened by 2^-16 of the cell's entries (their sum): frames whose
-// squares of the cell or of that widening come near the ends of binary32 stay
-// unsorted. (Cube of edge 6e-22: subnormal squares rounded by up to 1/2 of
-// themselves, and group pairs with a pair within the cut-off were left out.)
+// binary32, widened by 2^-16 of the cell's entries (their sum); where the squares
+// of the cell or of that widening come near the ends of binary32 they decide
+// nothing (cube of edge 6e-22: subnormal squares rounded by up to 1/2 of
+// themselves, and group pairs with a pair within the cut-off were left out).
+// Such binary64 frames stay unsorted; binary32 frames, whose counts depend on the
+// kernel in the last places, keep their order and compute every pair.
 //
 // Without image search a wrap that rounding decides otherwise than the canonical
 // sequence must not matter: such a pair is half a cell apart along some axis up
@@ -216,7 +224,7 @@ inline int staged_kind(int kind, int precision, const FrameParams &fp, int64_t n
       precision == 0 || (fp.n_bins < (1 << 20) - 2 && fp.s > 0x1p-400 && fp.s < 0x1p400);
   double size = 0.0;
   for (double v : {fp.ax, fp.bx, fp.by, fp.cx, fp.cy, fp.cz}) size += fabs(v);
-  const bool ranged = size > 0x1p-40 && size < 0x1p60;
+  const bool ranged = precision == 0 || bounds_decide(size);
   // (padded indices fit in 32 bits, those of a unit past the last point too)
   const bool large =
       n_points >= kSortMinPoints && n_points <= 0x7FFFFFFF - 128 * kMaxSpeciesStage && fits &&

@@ -158,6 +158,10 @@ __device__ __forceinline__ WindowBounds window_bounds(const FrameParams *F, int 
   b.lo = b_lo > 0 ? fmaxf(static_cast<float>(b_lo) / s * (1.f - 0x1p-12f) - eps, 0.f) : 0.f;
   b.hi = static_cast<float>(b_lo + win) / s * (1.f + 0x1p-12f) + eps;
   b.in = fmaxf(static_cast<float>(stride - 2) / s * (1.f - 0x1p-12f) - eps, 0.f);
+  if (!bounds_decide(size)) {
+    b.lo = b.in = 0.f;
+    b.hi = __builtin_inff();
+  }
   return b;
 }
 

@@ -80,3 +80,18 @@ def test_scale_of_the_cell_does_not_change_binary64_counts(ctx, kind):
                                fr.n_bins, fr.name)
         h, oor = run_gpu(ctx, part, 1)
         assert np.array_equal(h, ref) and np.array_equal(oor, ref_oor), k
+
+
+def test_binary32_counts_of_extreme_cells(ctx):
+    """binary32 lengths times a power of two: exact as well while the squares of
+    the pairs' own differences stay normal numbers, so the counts do not change
+    where the groups' bounds stop deciding."""
+    fr = face_frame("triclinic")
+    ref, ref_oor = run_gpu(ctx, fr, 0)
+    for k in (-50, -46, -44, 40, 56):
+        print(f"\n[case] {fr.name} binary32, scale 2^{k}", flush=True)
+        s = 2.0 ** k
+        part = workloads.Frame(fr.coords * s, fr.offsets, fr.box_type, fr.box * s, fr.r_max * s,
+                               fr.n_bins, fr.name)
+        h, oor = run_gpu(ctx, part, 0)
+        assert np.array_equal(h, ref) and np.array_equal(oor, ref_oor), k
