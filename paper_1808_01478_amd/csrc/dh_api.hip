@@ -1383,7 +1383,8 @@ int histo_job(dh_ctx *ctx, hipStream_t stream, const double *d_coords, const int
   job.accumulate = accumulate;
   const int geometric = frame_consts(box_type, box, r_max, n_bins, job.fp);
   // (a budgeted context keeps the search it has room for)
-  job.kind = staged_kind(geometric, precision, job.fp, n, ctx->budget == 0);
+  job.kind = staged_kind(geometric, precision, job.fp, n,
+                         ctx->budget == 0 && tight_species(offsets, n_species));
   // (the sorted binary64 kernel goes back to the input for pairs at a bin edge)
   job.fp.in = padded_frame(job.kind) && precision == DH_FP64 ? d_coords : nullptr;
   job.fp.box = job.kind;
@@ -1570,7 +1571,8 @@ int dh_batch_create(dh_ctx *ctx, const dh_frame_desc *frames, int32_t n_frames, 
     if (!d.d_out || (n > 0 && !d.d_coords)) return fail(ctx, DH_EINVAL, "frame %d: null pointer", f);
     FrameInfo &fi = info[f];
     const int geometric = frame_consts(d.box_type, d.box, d.r_max, d.n_bins, fi.fp);
-    const int kind = staged_kind(geometric, precision, fi.fp, n, ctx->budget == 0);
+    const int kind = staged_kind(geometric, precision, fi.fp, n,
+                                 ctx->budget == 0 && tight_species(d.offsets, d.n_species));
     fi.fp.box = kind;
     fi.fp.n_pad = static_cast<int32_t>(padded_start(d.offsets, d.n_species));
     fi.offsets.assign(d.offsets, d.offsets + d.n_species + 1);

@@ -167,7 +167,8 @@ extern "C" int dh_histo_noalloc(dh_stream stream, const double *d_coords,
   const int geometric = frame_constants(box_type, box, r_max, n_bins, fp);
   // frames with image search are sorted where the sort keys fit beside the
   // staged points with room for the work list
-  const bool may_search = static_cast<size_t>(n) * 32 + static_cast<size_t>(sort_keys_count(n)) *
+  const bool may_search = tight_species(offsets, n_species) &&
+                          static_cast<size_t>(n) * 32 + static_cast<size_t>(sort_keys_count(n)) *
                                                             sizeof(uint64_t) +
                               (size_t{4} << 20) <=
                           kScratchBytes;

@@ -281,7 +281,8 @@ int start_job(dh_server *s, int slot_idx) {
   FrameParams fp;
   const int geometric =
       dh::frame_constants(j.box_type, j.has_box ? j.box : nullptr, j.r_max, j.n_bins, fp);
-  j.kind = dh::staged_kind(geometric, j.precision, fp, j.n);
+  j.kind = dh::staged_kind(geometric, j.precision, fp, j.n,
+                           dh::tight_species(j.offsets.data(), k));
   fp.box = j.kind;
   fp.n_pad = static_cast<int32_t>(dh::padded_start(j.offsets.data(), k));
   const size_t staged_b = pts * dh::staged_point_bytes(j.precision, j.kind);

@@ -21,6 +21,9 @@ SOURCE = """
 #include "dh_internal.h"
 extern "C" double wrap_cell(double f, unsigned int *place) { return dh::wrap_cell(f, *place); }
 extern "C" long first_word(int i) { return dh::first_word(i); }
+extern "C" int tight_species(const long *off, int k) {
+  return dh::tight_species(off, k);
+}
 extern "C" int bounds_decide(double size) { return dh::bounds_decide(size); }
 extern "C" int staged_kind(int box_type, const double *box, double r_max, int n_bins,
                            int precision, long n) {
@@ -115,6 +118,17 @@ def test_cutoff_next_to_half_the_width_stays_unsorted(lib):
         assert kind == (SORTED if k < 22 else TRIC if k < 30 else SEARCH_SORTED) or k in (22, 29)
         kind = lib.staged_kind(workloads.BOX_TRICLINIC, box.ctypes.data, r_max, 1000, 0, 1 << 17)
         assert kind == (SORTED if k < 30 else SEARCH) or k == 29
+
+
+def test_image_search_of_small_species_stays_unsorted(lib):
+    """Groups of a small species span much of the cell: at most a sixteenth of
+    the points may be in species of fewer than 4,096."""
+    for sizes, tight in (([65_536], True), ([4096] * 16, True), ([4095] * 17, False),
+                         ([61_440, 4096], True), ([61_440, 2048, 2048], True),
+                         ([61_439, 2049, 2048], False), ([2062] * 32, False),
+                         ([61_440, 4095, 0, 1], True), ([30_000, 30_000] + [90] * 62, False)):
+        off = np.ascontiguousarray(np.concatenate([[0], np.cumsum(sizes)]), np.int64)
+        assert bool(lib.tight_species(off.ctypes.data_as(ctypes.c_void_p), len(sizes))) == tight
 
 
 def test_word_index_of_the_last_points(lib):
