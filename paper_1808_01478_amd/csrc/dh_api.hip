@@ -581,8 +581,10 @@ void plan_frame(int32_t frame, const int64_t *off, int32_t k, bool padded, const
                 std::vector<WorkItem> &items, std::vector<uint64_t> &pairs) {
   const int64_t bi = L.cfg.iblock, jc = L.cfg.jchunk, dc = L.cfg.dchunk;
   const int32_t n_hist = k * (k + 1) / 2;
+  int64_t start[kMaxSpeciesStage + 1];
+  padded_starts(off, k, start);
   for (int32_t h = 0; h < n_hist; ++h) {
-    const HistRows r = hist_rows(off, k, h, padded);
+    const HistRows r = hist_rows(off, k, h, padded ? start : nullptr);
     pairs.push_back(r.pairs);
     const size_t first = items.size();
     const int64_t nr = hist_row_count(r, bi);

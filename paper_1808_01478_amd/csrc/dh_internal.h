@@ -47,6 +47,9 @@ __host__ __device__ inline int64_t padded_start(const int64_t *off, int32_t s) {
   for (int32_t u = 0; u < s; ++u) p += (off[u + 1] - off[u] + 63) / 64 * 64;
   return p;
 }
+inline void padded_starts(const int64_t *off, int32_t k, int64_t (&start)[kMaxSpeciesStage + 1]) {
+  for (int32_t s = 0; s <= k; ++s) start[s] = padded_start(off, s);
+}
 // Bounding boxes of a group of 64 points of one species: fixed-point
 // fractional coordinates and Cartesian positions relative to the cell centre.
 struct GroupBox {
@@ -389,14 +392,15 @@ struct HistRows {
   uint64_t pairs;        // pairs of the histogram
 };
 
+// (start: where the species begin in a sorted frame's padded indices, see
+// padded_starts; else null)
 __host__ __device__ inline HistRows hist_rows(const int64_t *off, int32_t k, int32_t h,
-                                              bool padded = false) {
+                                              const int64_t *start = nullptr) {
   int32_t s, t;
   hist_pair(k, h, s, t);
   HistRows r;
   const int64_t ns = off[s + 1] - off[s], nt = off[t + 1] - off[t];
-  const int64_t ps = padded ? padded_start(off, s) : off[s];
-  const int64_t pt = padded ? padded_start(off, t) : off[t];
+  const int64_t ps = start ? start[s] : off[s], pt = start ? start[t] : off[t];
   r.intra = s == t;
   if (r.intra) {
     r.lane0 = r.str0 = ps;
@@ -413,8 +417,13 @@ __host__ __device__ inline HistRows hist_rows(const int64_t *off, int32_t k, int
   return r;
 }
 
+// (in 32 bits, where the sums of two particle indices and a chunk fit unsigned:
+// the device planner divides per histogram)
+__host__ __device__ inline int64_t chunks(int64_t n, int64_t size) {
+  return (static_cast<uint32_t>(n) + static_cast<uint32_t>(size) - 1u) / static_cast<uint32_t>(size);
+}
 __host__ __device__ inline int64_t hist_row_count(const HistRows &r, int64_t bi) {
-  return (r.lane1 - r.lane0 + bi - 1) / bi;
+  return chunks(r.lane1 - r.lane0, bi);
 }
 
 __host__ __device__ inline int64_t row_item_count(const HistRows &r, int64_t row, int64_t bi,
@@ -422,8 +431,8 @@ __host__ __device__ inline int64_t row_item_count(const HistRows &r, int64_t row
   const int64_t b0 = r.lane0 + row * bi;
   const int64_t b1 = b0 + bi < r.lane1 ? b0 + bi : r.lane1;
   if (r.intra)
-    return (b1 - b0 >= 2 ? (b1 - b0 + dc - 1) / dc : 0) + (r.lane1 - b1 + jc - 1) / jc;
-  return (r.str1 - r.str0 + jc - 1) / jc;
+    return (b1 - b0 >= 2 ? chunks(b1 - b0, dc) : 0) + chunks(r.lane1 - b1, jc);
+  return chunks(r.str1 - r.str0, jc);
 }
 
 // Writes the items of one row (for bin window `sweep`) from dst on; returns

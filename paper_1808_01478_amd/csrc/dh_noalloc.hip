@@ -100,18 +100,20 @@ struct PlanArgs {
 // One workgroup: frame constants, pairs per histogram, cleared counters, and
 // the work list grouped by (histogram, bin window) as the host plan groups it.
 __global__ __launch_bounds__(kPlanThreads) void noalloc_plan_kernel(FrameParams fp, PlanArgs a) {
-  __shared__ int64_t off[kMaxSpeciesNA + 1];
+  __shared__ int64_t off[kMaxSpeciesNA + 1], start[kMaxSpeciesNA + 1];
   __shared__ int64_t scan[kPlanThreads];
   const int tid = threadIdx.x;
   for (int s = tid; s <= a.k; s += blockDim.x) off[s] = a.off[s];
   if (tid == 0) *a.fp_dst = fp;
   for (int c = tid; c < a.n_counters; c += blockDim.x) a.counters[c] = 0;
   __syncthreads();
+  for (int s = tid; s <= a.k; s += blockDim.x) start[s] = a.padded ? padded_start(off, s) : off[s];
+  __syncthreads();
   const int32_t n_hist = a.k * (a.k + 1) / 2;
   for (int h = tid; h < n_hist; h += blockDim.x) a.pairs[h] = hist_rows(off, a.k, h).pairs;
   int64_t base = 0;
   for (int32_t h = 0; h < n_hist; ++h) {
-    const HistRows r = hist_rows(off, a.k, h, a.padded);
+    const HistRows r = hist_rows(off, a.k, h, start);
     const int64_t nr = hist_row_count(r, a.bi);
     for (int32_t sw = 0; sw < a.n_sweeps; ++sw) {
       for (int64_t r0 = 0; r0 < nr; r0 += blockDim.x) {

@@ -331,9 +331,11 @@ int start_job(dh_server *s, int slot_idx) {
                 kItemsPerWg);
   const int64_t bi = j.plan.cfg.iblock, jc = j.plan.cfg.jchunk, dc = j.plan.cfg.dchunk;
   j.items.clear();
+  int64_t start[dh::kMaxSpeciesStage + 1];
+  dh::padded_starts(j.offsets.data(), k, start);
   for (int32_t h = 0; h < j.n_hist; ++h) {
     const dh::HistRows r = dh::hist_rows(j.offsets.data(), k, h,
-                                         dh::padded_frame(j.kind));
+                                         dh::padded_frame(j.kind) ? start : nullptr);
     const int64_t nr = dh::hist_row_count(r, bi);
     for (int32_t sw = 0; sw < j.plan.n_sweeps; ++sw)
       for (int64_t row = 0; row < nr; ++row) {
