@@ -40,9 +40,9 @@
  *                 DH_FP32: a binary32 evaluation; a pair may change bin
  *                 only if its binary64 distance lies within a few binary32
  *                 ulps of the bin edge. The bin is taken from the bits of
- *                 t + (2^23 - 1/2) rounded to nearest, which is floor(t)
+ *                 t 2^-22 + (2 - 2^-23) rounded to nearest, which is floor(t)
  *                 except that an exactly integer odd t counts one bin
- *                 lower (a tie); in a cube r * s and the offset are one
+ *                 lower (a tie); with a cell r * s and the offset are one
  *                 fused operation. Every device path (LDS histograms, bin
  *                 windows, global atomics, batches) bins alike, so binary32
  *                 counts do not depend on the launch shape.

@@ -126,7 +126,7 @@ namespace {
 
 constexpr int32_t kMaxSpecies = 64;
 constexpr int32_t kMaxBins = 1 << 24;
-// binary32 bins come from t + (2^23 - 1/2), exact for t < 2^22
+// binary32 bins come from t 2^-22 + (2 - 2^-23), whose spacing is a bin for t < 2^22
 constexpr int32_t kMaxBins32 = 1 << 22;
 constexpr int64_t kMaxN = 2147483647LL;
 
@@ -392,12 +392,11 @@ constexpr int32_t kWideSorted = 100;
 struct Knobs {
   int32_t r = 4;             // i-particles per lane: 4 or 8
   int32_t copies = 1;        // LDS sized for 1, 2 or 4 histograms (one is counted into)
-  int32_t tj = 256;          // j-tile length: 128 or 256
+  int32_t tj = 256;          // longest j-piece of a unit: 128 or 256
   int32_t noclamp = 1;       // allow unclamped interior blocks
   int32_t occ_cap = 0;       // workgroups per CU at most (0: as many as fit)
   int32_t items_per_wg = 4;  // work items per workgroup (sets the item size)
-  // workgroup size: 256, 512 or 1024; 0 = the smallest that gives every
-  // SIMD at least four waves within the LDS limit on workgroups per CU
+  // workgroup size: 256, 512 or 1024; 0 = see resolve_threads
   int32_t threads = 0;
   // global-atomic kernel when the LDS plan needs at least this many bin
   // windows (0: never, 1: always)
@@ -437,7 +436,7 @@ Knobs default_knobs(int precision, bool sorted_windows = false) {
 // Base kernel configuration and LDS budget of a precision and knob set.
 struct BaseConfig {
   KernelConfig cfg;
-  size_t tile_bytes;
+  size_t fixed_bytes;  // LDS beside the histogram
   int64_t win_max;  // widest bin window that fits the LDS budget
   int occ_cap;
   int items_per_wg;
@@ -456,15 +455,11 @@ BaseConfig base_config(size_t lds_per_block, int precision, const Knobs &k, int 
   c.wg_per_cu = k.occ_cap;
   c.iblock = c.threads * c.r;
   c.jchunk = c.dchunk = c.tj;
-  // control words and the guard below the histogram; binary64 sorted frames
-  // keep two j-tiles, plus one
-  // entry of pad: the look-ahead read of j may touch the entry just past the
-  // second tile
-  b.tile_bytes = kControlBytes + 32;
-  // the search kernels keep their queues after the histogram; counting them
-  // with the tiles leaves the histogram budget below them
-  if (kind == kBoxTricSearch) b.tile_bytes += search_queue_bytes(precision, c.threads, c.r);
-  const size_t budget = std::min<size_t>(lds_per_block, 160 * 1024) - b.tile_bytes - 256;
+  // control words and the guard below the histogram, rounded up
+  b.fixed_bytes = kControlBytes + 32;
+  // the unsorted search keeps its queues after the histogram
+  if (kind == kBoxTricSearch) b.fixed_bytes += search_queue_bytes(precision, c.threads, c.r);
+  const size_t budget = std::min<size_t>(lds_per_block, 160 * 1024) - b.fixed_bytes - 256;
   // at most 38 passes of a 1,024-thread flush
   b.win_max = std::min<int64_t>(static_cast<int64_t>(budget / 4 / c.copies) - kDump, 38 * 1024);
   b.occ_cap = k.occ_cap;
@@ -534,12 +529,12 @@ Launch choose_launch(int n_cu, size_t lds_per_block, int precision, const FrameP
     L.win = (n_bins + L.n_sweeps - 1) / L.n_sweeps;
   }
   if (k.wide > 0 && L.n_sweeps >= k.wide) {
-    // one pass, uint64 atomics into the output; LDS holds the j-tiles only
+    // one pass, uint64 atomics into the output, no histogram in LDS
     L.mode = kModeGlobal;
     L.n_sweeps = 1;
     L.win = n_bins;
     L.stride = 0;
-    L.lds = b.tile_bytes;
+    L.lds = b.fixed_bytes;
     resolve_threads(precision, fp.box, L.mode, k, L.lds, total_pairs, L.cfg);
     L.grid = grid_for_config(n_cu, precision, fp.box, L.mode, b, L.lds, L.cfg);
     set_items(L.cfg, precision, fp.box, L.grid, total_pairs, b.items_per_wg);
@@ -561,7 +556,7 @@ Launch choose_launch(int n_cu, size_t lds_per_block, int precision, const FrameP
       L.stride = static_cast<int>(std::max<int64_t>(L.stride, slots));
     }
   }
-  L.lds = b.tile_bytes + static_cast<size_t>(L.cfg.copies) * L.stride * 4;
+  L.lds = b.fixed_bytes + static_cast<size_t>(L.cfg.copies) * L.stride * 4;
   resolve_threads(precision, fp.box, L.mode, k, L.lds, total_pairs, L.cfg);
   L.grid = grid_for_config(n_cu, precision, fp.box, L.mode, b, L.lds, L.cfg);
   set_items(L.cfg, precision, fp.box, L.grid, total_pairs * static_cast<uint64_t>(L.n_sweeps),
@@ -1203,39 +1198,6 @@ size_t ctx_device_bytes(const dh_ctx *ctx) {
   return ctx->staged_cap + ctx->blob_cap + ctx->in_cap + ctx->out_cap + ctx->keys_cap;
 }
 
-void ctx_release_scratch(dh_ctx *ctx) {
-  if (hipSetDevice(ctx->device) != hipSuccess) return;
-  void **bufs[5] = {&ctx->d_staged, &ctx->d_blob, reinterpret_cast<void **>(&ctx->d_in),
-                    reinterpret_cast<void **>(&ctx->d_out), &ctx->d_keys};
-  size_t *caps[5] = {&ctx->staged_cap, &ctx->blob_cap, &ctx->in_cap, &ctx->out_cap,
-                     &ctx->keys_cap};
-  for (int k = 0; k < 5; ++k) {
-    if (*bufs[k]) (void)hipFree(*bufs[k]);
-    *bufs[k] = nullptr;
-    *caps[k] = 0;
-  }
-  ctx->blob_last.clear();
-  (void)hipGetLastError();
-}
-
-size_t job_scratch_bytes(int64_t n_points, int32_t n_hist, int32_t n_bins, int32_t precision,
-                         int64_t launch_pairs) {
-  // staged coordinates plus the work blob (frame constants, pair counts and
-  // work items: a few MB, plus one item per kMinBoundedPairs pairs of every bin
-  // window when the frame runs as bounded launches, and the tail pieces of
-  // every launch, at most three more items per workgroup of a grid of at
-  // most 2,048; at least 9,000 bins fit one window, and beyond 64 windows
-  // the global-atomic mode needs one pass)
-  const uint64_t n = static_cast<uint64_t>(std::max<int64_t>(1, n_points));
-  const uint64_t windows = std::min<uint64_t>(64, (static_cast<uint64_t>(n_bins) + 8999) / 9000);
-  const uint64_t work = n * (n - 1) / 2 * windows;
-  const uint64_t launches =
-      launch_pairs > 0 ? work / static_cast<uint64_t>(launch_pairs) + 1 : 1;
-  return static_cast<size_t>(n) * coord_bytes(precision) + (4u << 20) +
-         static_cast<size_t>(n_hist) * 8 +
-         static_cast<size_t>(work / kMinBoundedPairs + launches * 3 * 2048) * sizeof(WorkItem);
-}
-
 }  // namespace dh
 
 // The launch sequence of a batch: stage, zero, one persistent pair kernel per
@@ -1578,7 +1540,7 @@ int dh_batch_create(dh_ctx *ctx, const dh_frame_desc *frames, int32_t n_frames, 
     fi.fp.box = kind;
     fi.fp.n_pad = static_cast<int32_t>(padded_start(d.offsets, d.n_species));
     fi.offsets.assign(d.offsets, d.offsets + d.n_species + 1);
-    // the bin window that fits beside this kind's j-tiles
+    // the bin window that fits this kind's LDS
     const BaseConfig fbase = base_config(ctx->lds_per_block, precision, bk, kind);
     if (d.n_bins <= fbase.win_max) {
       fi.fp.win = d.n_bins;
@@ -1650,7 +1612,7 @@ int dh_batch_create(dh_ctx *ctx, const dh_frame_desc *frames, int32_t n_frames, 
     }
     for (int32_t f : fs) info[f].fp.noclamp = (info[f].noclamp_ok && info[f].slots <= stride) ? 1 : 0;
     g.stride = static_cast<int>(stride);
-    g.lds = gbase.tile_bytes + static_cast<size_t>(g.cfg.copies) * g.stride * 4;
+    g.lds = gbase.fixed_bytes + static_cast<size_t>(g.cfg.copies) * g.stride * 4;
     resolve_threads(precision, g.kind, g.mode, bk, g.lds, work, g.cfg);
     g.grid = grid_for_config(ctx->n_cu, precision, g.kind, g.mode, gbase, g.lds, g.cfg);
     // four times as many items as a single frame gets: the list ends with the

@@ -281,8 +281,8 @@ struct PairKernelArgs {
   const WorkItem *items;
   int32_t *counter;  // dynamic work counter, zero before launch
   int32_t n_items;
-  int32_t stride;    // slots per copy (>= win + kDump of every frame); 0 in kModeGlobal
-  int32_t tj;        // j-tile length staged through LDS
+  int32_t stride;    // LDS slots (>= win + kDump of every frame); 0 in kModeGlobal
+  int32_t tj;        // longest j-piece of a unit (unsorted frames)
 };
 
 // Kernel configuration (chosen per launch by the tuner).
@@ -290,7 +290,7 @@ struct KernelConfig {
   int32_t threads;   // workgroup size: 256, 512 or 1024
   int32_t r;         // i-particles per lane (4 or 8)
   int32_t copies;    // histograms the LDS of a workgroup is sized for (1, 2, 4)
-  int32_t tj;        // j-tile length (sorted frames), longest j-piece of a unit
+  int32_t tj;        // longest j-piece of a unit (unsorted frames)
   int32_t iblock;    // i-range of one work item (multiple of 64 r)
   int32_t jchunk;    // j-range of one work item
   int32_t dchunk;    // j-range of one item on the diagonal of its i-block
@@ -520,12 +520,6 @@ struct dh_ctx;
 namespace dh {
 // device bytes held by a context's scratch (staged coordinates, work blob)
 size_t ctx_device_bytes(const dh_ctx *ctx);
-// frees a context's scratch (the context must be idle); it regrows on use
-void ctx_release_scratch(dh_ctx *ctx);
-// device footprint of a single-frame job besides the caller's buffers
-// (launch_pairs: the bounded launch size the job runs with, 0 = one launch)
-size_t job_scratch_bytes(int64_t n_points, int32_t n_hist, int32_t n_bins, int32_t precision,
-                         int64_t launch_pairs);
 // binary64 constants of a frame (s, inverse cell, shifts, box kind; returns
 // the kind: none, ortho, triclinic, triclinic with image search)
 int frame_constants(int32_t box_type, const double *box, double r_max, int32_t n_bins,

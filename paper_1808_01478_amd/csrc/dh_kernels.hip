@@ -71,14 +71,16 @@ __global__ void stage32_kernel(const double *__restrict__ in, float4 *__restrict
 }
 
 // --------------------------------------------------------------------------
-// Spatially sorted binary32 staging (triclinic cells without image search)
+// Spatially sorted staging
 // --------------------------------------------------------------------------
 //
 // The points of every species are put in the order of a Morton curve over
 // their wrapped fractional coordinates (9 bits per axis), ties by input
 // index, so that 64 consecutive points are close together in the cell. The
 // pair kernel then finds, for most pairs of such groups, one lattice shift
-// that is the Eq. 5 wrap of every pair of the two groups (see run_sorted).
+// that is the Eq. 5 wrap of every pair of the two groups (see run_sorted), or
+// that all their pairs are out of range. Binary64 frames are put into tighter
+// groups still (see refine_order_kernel).
 // The order is a permutation within each species, so the histograms are
 // those of the input; the sort is a bitonic network on 64-bit keys
 // (species : Morton code : input index), which makes the order unique.

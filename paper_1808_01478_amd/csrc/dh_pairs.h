@@ -768,9 +768,9 @@ namespace {
 // busy, and only the units that touch the diagonal of an intra-species
 // histogram pay for the mask. Bound by vector-unit issue in large frames
 // (100,000 points in a cube, binary32, 10,000 bins: 1,410 us with the j-tiles
-// in LDS and a barrier per tile, 1,300 us now), by latency in small ones,
+// in LDS and a barrier per tile, 1,285 us now), by latency in small ones,
 // whose block on the diagonal used to run as one serial item (5,000 points,
-// binary64: 634 us, now 34 us; 1,000 points, binary32: 113 and 22 us).
+// binary64: 634 us, now 23 us; 1,000 points, binary32: 113 and 16 us).
 //
 // Units whose lanes all hold a particle run without the clamp where the host
 // proved that every t of the frame is below the LDS stride (out-of-range

@@ -17,7 +17,7 @@
 // short path. With every pair computed, j-tiles in LDS and a barrier per tile
 // the frame took 147 ms in binary32; skipping them in independent units
 // took 90 ms, at eight waves per SIMD (half the registers) it takes 85 ms.
-// Binary64 (run_sorted64): 371 and 160 ms.
+// Binary64 (run_sorted64): 371 and 162 ms.
 #pragma once
 
 #include "dh_internal.h"
@@ -829,8 +829,9 @@ __device__ __attribute__((noinline)) uint64_t searched_pairs(const FrameParams *
 // with the clamp) against 22 over the frame with a binary64 root per pair
 // (v_rsq_f64 alone holds a SIMD for 16 cycles, v_sqrt_f32 for 8). The
 // 1,000,000-point clustered triclinic frame (20,000 bins) took 371 ms with
-// every pair computed and that root, and takes 178 ms; 100,000 points in a
-// cube (cut-off half the edge, so little is skipped) 4.34 and 3.49 ms.
+// every pair computed and that root, 178 ms in Morton order, and takes 162 ms;
+// 100,000 points in a cube (cut-off half the edge, so little is skipped) 4.34,
+// 3.49 and 2.87 ms.
 template <int MODE, bool SEARCH>
 __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const WorkItem &w,
                                              const FrameParams *F, int *s_unit, int *s_item,
