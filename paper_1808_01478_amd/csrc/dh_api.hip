@@ -386,7 +386,6 @@ constexpr int kNumKnobs = 8;
 // at 80 to 160 and 116 to 137. Their item list grows with the windows, so the
 // later switch is for callers without a limit on scratch.
 constexpr int32_t kWideDefault32 = 60;
-constexpr int32_t kWideDefault64 = 20;
 constexpr int32_t kWideSorted = 100;
 
 struct Knobs {

@@ -103,6 +103,10 @@ inline bool tight_species(const int64_t *off, int32_t k) {
   return 16 * loose <= off[k];
 }
 
+// Bin windows from which one pass of global atomics replaces them by default, in
+// binary64 (see kWideDefault32)
+constexpr int32_t kWideDefault64 = 20;
+
 // How a pair kernel accumulates its counts.
 enum HistMode : int32_t {
   kModeLds = 0,     // the whole histogram in LDS sub-histograms

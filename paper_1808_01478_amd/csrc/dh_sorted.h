@@ -862,8 +862,8 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
   double shx = 0.0, shy = 0.0, shz = 0.0;  // the lane's shift B n
   float near_hi = 0.f;  // thr's upper word, as a float (see below)
   [[maybe_unused]] Images img{};
-  // image search: pairs it is defined for (see searched_pairs; once for all
-  // bin windows, each of which searches them), and the images evaluated
+  // image search: pairs it is defined for (see searched_pairs; counted in the
+  // first bin window), and the images evaluated
   [[maybe_unused]] uint64_t n_searched = 0, n_images = 0;
   [[maybe_unused]] const bool tell = SEARCH && F->searched != nullptr && w.sweep == 0;
 
@@ -1171,7 +1171,12 @@ __device__ __forceinline__ void run_sorted64(const PairKernelArgs &a, const Work
       *s_item = static_cast<int>(gridDim.x) + atomicAdd(a.counter, 1);
   }
   if constexpr (SEARCH) {
-    add_searched(s_search, lane, n_searched * static_cast<uint64_t>(uni(F->n_sweeps)), n_images);
+    // (the unsorted search counts them in every bin window, and once where it
+    // takes one pass of atomics instead)
+    const int windows = uni(F->n_sweeps);
+    add_searched(s_search, lane,
+                 n_searched * static_cast<uint64_t>(windows < kWideDefault64 ? windows : 1),
+                 n_images);
   }
 }
 

@@ -112,3 +112,22 @@ def test_searched_pairs_of_many_small_items(ctx, precision):
         got.append((ctx.searched_pairs(), h.sum()))
         assert 7 * got[-1][0] <= ctx.searched_images() <= 27 * got[-1][0]
     assert got[0] == got[1] and got[0][0] > 0
+
+
+@pytest.mark.parametrize("n_bins", [60_000, 800_000])
+def test_searched_pairs_of_wide_histograms(ctx, n_bins):
+    """Wide histograms: bin windows in both stagings, or windows of the sorted
+    frame against one pass of atomics."""
+    import paper_1808_01478_amd as dh
+    box, _ = CELLS["skew"]
+    rng = np.random.Generator(np.random.PCG64(11))
+    x = np.ascontiguousarray(workloads.rows_combine(rng.uniform(0, 1, size=(66_000, 3)), box))
+    fr = workloads.Frame(x, np.array([0, 66_000], np.int64), workloads.BOX_TRICLINIC, box,
+                         0.7 * workloads.min_width(box), n_bins, "wide search")
+    print(f"\n[case] searched pairs, {n_bins} bins", flush=True)
+    h, oor = run_gpu(ctx, fr, 1)
+    searched = ctx.searched_pairs()
+    with dh.Context(0, hbm_budget_bytes=1 << 30) as plain:
+        g, oor_g = run_gpu(plain, fr, 1)
+        assert searched == plain.searched_pairs()
+    assert np.array_equal(h, g) and np.array_equal(oor, oor_g)
