@@ -668,11 +668,13 @@ __device__ __forceinline__ bool rounding_bound(const GroupBox &I, const GroupBox
 // defined for: Eq. 5 vector of the canonical sequence at least half the
 // shortest lattice vector long (q >= qskip64), whatever the images evaluated.
 // Pairs of groups whose boxes lie on one side of that sphere count without a
-// look at their pairs. The others are looked at in binary32, wrapped as 32-bit
-// fixed-point fractions (see dh_pairs.h), and where its rounding could decide,
-// of the length or of a wrap, by the canonical sequence on the input.
-// The frame of 70,001 points takes 5.1 ms with the count and 4.0 without (7.1
-// with it in binary64, a slice at a time; 10.6 before such frames were sorted).
+// look at their pairs. The others are looked at in binary32, groups with one
+// shared wrap by their shifted positions, the others wrapped as 32-bit fixed-point
+// fractions (see dh_pairs.h), and where its rounding could decide, of the length
+// or of a wrap, by the canonical sequence on the input.
+// The frame of 70,001 points takes 4.8 ms with the count and 4.1 without (7.1
+// with it in binary64, a slice at a time; 10.6 before such frames were sorted);
+// 200,000 points 24.3 and 19.1 ms.
 __device__ __attribute__((noinline)) uint64_t searched_pairs(const FrameParams *frame, WorkItem w,
                                                              int ib_, int jb_, int gpu_) {
   const FrameParams *const F = uni(frame);
@@ -720,24 +722,33 @@ __device__ __attribute__((noinline)) uint64_t searched_pairs(const FrameParams *
   const uint64_t m_exact = __builtin_amdgcn_ballot_w64(look && !bounded);
   const uint64_t m_wrap = __builtin_amdgcn_ballot_w64(look && gp.kind != kFast);
 
-  // Squares in units of 2^-64 of a_x squared. A component of the binary32
-  // vector is off by less than 2^-21 of the sum of the cell's entries.
-  const float unit = 0x1p32f / cell[0], off = size * 0x1p-20f;
-  const float r_lo = fmaxf(radius - off, 0.f) * unit, r_hi = (radius + off) * unit;
-  const float q_lo = r_lo * r_lo, q_hi = r_hi * r_hi;
-  // fixed-point fractions of a staged point
-  const double to = 1.0 / (geo.s * 0x1p-22) * 0x1p32;
+  // Groups with one shared wrap: binary32 positions with its shift, lengths in
+  // units of the cell; the others: fixed-point fractions, in units of 2^-32 of
+  // a_x. A component of either vector is off by less than 2^-21 of the sum of the
+  // cell's entries.
+  const float off = size * 0x1p-20f, unit = 0x1p32f / cell[0];
+  const float r_lo = fmaxf(radius - off, 0.f), r_hi = radius + off;
+  const double shx = gp.n[0] * geo.ax + gp.n[1] * geo.bx + gp.n[2] * geo.cx,
+               shy = gp.n[1] * geo.by + gp.n[2] * geo.cy, shz = gp.n[2] * geo.cz;
+  const double len = 1.0 / (geo.s * 0x1p-22), to = len * 0x1p32;
   const double h11 = geo.h11 * to, h12 = geo.h12 * to, h13 = geo.h13 * to;
   const double h22 = geo.h22 * to, h23 = geo.h23 * to, h33 = geo.h33 * to;
-  auto fixed = [&](int at, int (&u)[3]) {
+  // a staged point as three words: its fractions, or its position plus S
+  auto words = [&](auto wrap_c, int at, double Sx, double Sy, double Sz, int (&u)[3]) {
     const double *const p = P + 3 * static_cast<int64_t>(at);
     const double x = p[0], y = p[1], z = p[2];
-    auto whole = [](double v) {
-      return static_cast<int>(fmin(fmax(v, -0x1p31), 0x1p31 - 1.0));
-    };
-    u[0] = whole(fma(z, h13, fma(y, h12, x * h11)));
-    u[1] = whole(fma(z, h23, y * h22));
-    u[2] = whole(z * h33);
+    if constexpr (decltype(wrap_c)::value) {
+      auto whole = [](double v) {
+        return static_cast<int>(fmin(fmax(v, -0x1p31), 0x1p31 - 1.0));
+      };
+      u[0] = whole(fma(z, h13, fma(y, h12, x * h11)));
+      u[1] = whole(fma(z, h23, y * h22));
+      u[2] = whole(z * h33);
+    } else {
+      u[0] = __float_as_int(static_cast<float>(x * len + Sx));
+      u[1] = __float_as_int(static_cast<float>(y * len + Sy));
+      u[2] = __float_as_int(static_cast<float>(z * len + Sz));
+    }
   };
   for (int g = 0; g < gpu; ++g) {
     const int ja = jb + 64 * g, n = min(64, j1 - ja);
@@ -757,59 +768,87 @@ __device__ __attribute__((noinline)) uint64_t searched_pairs(const FrameParams *
     };
     for (uint32_t m = bits(m_exact); m != 0u; m &= m - 1u)
       for (int j = 0; j < n; ++j) below += canonical(__builtin_ctz(m), ja + j);
-    int uj[3];
-    fixed(ja + (lane < n ? lane : 0), uj);
-    auto slices = [&](auto m_c, uint32_t rs, bool wrap) {
+    // (mask_c: not all of the slices' and the group's pairs belong to the item)
+    auto slices = [&](auto wrap_c, auto m_c, auto mask_c, uint32_t rs, const int (&uj)[3]) {
       constexpr int M = decltype(m_c)::value;
+      constexpr bool WRAP = decltype(wrap_c)::value, MASK = decltype(mask_c)::value;
+      const float far = WRAP ? unit : 1.f;
+      const float q_lo = r_lo * far * (r_lo * far), q_hi = r_hi * far * (r_hi * far);
       int ui[M][3];
-      int after[M];  // the lane's pairs are those with j from here on
+      [[maybe_unused]] int after[M];  // the lane's pairs are those with j from here on
 #pragma unroll
       for (int k = 0; k < M; ++k) {
-        const int i = ib + 64 * static_cast<int>((rs >> (4 * k)) & 15u) + lane;
-        fixed(i < i1 ? i : ib, ui[k]);
+        const int r_k = static_cast<int>((rs >> (4 * k)) & 15u), at = g * kUnitSlices + r_k;
+        const int i = ib + 64 * r_k + lane;
+        words(wrap_c, i < i1 ? i : ib, lane_value(shx, at), lane_value(shy, at),
+              lane_value(shz, at), ui[k]);
         after[k] = i >= i1 ? 64 : diag_item && (i >> 6) == (ja >> 6) ? lane + 1 : 0;
       }
       for (int j = 0; j < n; ++j) {
         const int ua = __builtin_amdgcn_readlane(uj[0], j), ub = __builtin_amdgcn_readlane(uj[1], j),
                   uc = __builtin_amdgcn_readlane(uj[2], j);
+        int found = 0;
+        uint64_t open[M], any = 0;
 #pragma unroll
         for (int k = 0; k < M; ++k) {
-          auto diff = [](int a, int b) {
-            return static_cast<float>(
-                static_cast<int>(static_cast<uint32_t>(a) - static_cast<uint32_t>(b)));
-          };
-          const float fa = diff(ua, ui[k][0]), fb = diff(ub, ui[k][1]), fc = diff(uc, ui[k][2]);
-          const float dx = fmaf(g32.ncx, fc, fmaf(g32.nbx, fb, fa)),
-                      dy = fmaf(g32.ncy, fc, g32.nby * fb), dz = g32.ncz * fc;
+          float dx, dy, dz;
+          uint64_t tie = 0;
+          if constexpr (WRAP) {
+            auto diff = [](int a, int b) {
+              return static_cast<float>(
+                  static_cast<int>(static_cast<uint32_t>(a) - static_cast<uint32_t>(b)));
+            };
+            const float fa = diff(ua, ui[k][0]), fb = diff(ub, ui[k][1]), fc = diff(uc, ui[k][2]);
+            dx = fmaf(g32.ncx, fc, fmaf(g32.nbx, fb, fa));
+            dy = fmaf(g32.ncy, fc, g32.nby * fb);
+            dz = g32.ncz * fc;
+            tie = __builtin_amdgcn_ballot_w64(fmaxf(fabsf(fa), fmaxf(fabsf(fb), fabsf(fc))) >
+                                              0x1p31f * (1.f - 0x1p-21f));
+          } else {
+            dx = __int_as_float(ua) - __int_as_float(ui[k][0]);
+            dy = __int_as_float(ub) - __int_as_float(ui[k][1]);
+            dz = __int_as_float(uc) - __int_as_float(ui[k][2]);
+          }
           float q = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-          q = j >= after[k] ? q : __builtin_inff();
+          if constexpr (MASK) q = j >= after[k] ? q : __builtin_inff();
           const uint64_t in_lo = __builtin_amdgcn_ballot_w64(q < q_lo);
-          uint64_t open = __builtin_amdgcn_ballot_w64(q < q_hi) ^ in_lo;
-          if (wrap)
-            open |= __builtin_amdgcn_ballot_w64(fmaxf(fabsf(fa), fmaxf(fabsf(fb), fabsf(fc))) >
-                                                0x1p31f * (1.f - 0x1p-21f));
-          if (__builtin_expect(open != 0, 0))
-            below += canonical(static_cast<int>((rs >> (4 * k)) & 15u), ja + j);
-          else
-            below += __builtin_popcountll(in_lo);
+          open[k] = (__builtin_amdgcn_ballot_w64(q < q_hi) ^ in_lo) | tie;
+          any |= open[k];
+          found += open[k] == 0 ? __builtin_popcountll(in_lo) : 0;
         }
+        below += found;
+        if (__builtin_expect(any != 0, 0))
+          for (int k = 0; k < M; ++k)
+            if (open[k] != 0) below += canonical(static_cast<int>((rs >> (4 * k)) & 15u), ja + j);
       }
     };
-    // those with an ambiguous wrap apart from the others
-    for (int wrap = 0; wrap < 2; ++wrap) {
-      uint32_t m = bits(m_look & ~m_exact) & (wrap ? bits(m_wrap) : ~bits(m_wrap));
-      auto take = [&](int n_s) {
+    auto group = [&](auto wrap_c, uint32_t m) {
+      if (m == 0u) return;
+      int uj[3];  // lane l holds the group's point l
+      words(wrap_c, ja + (lane < n ? lane : 0), 0.0, 0.0, 0.0, uj);
+      using Yes = std::true_type;
+      using No = std::false_type;
+      // the group itself, and the slice at the end of the item, by themselves
+      const int own = (ja - ib) >> 6, last = (i1 - ib) >> 6;
+      uint32_t part = 0;
+      if (diag_item && own >= 0 && own < kUnitSlices) part |= 1u << own;
+      if (last < kUnitSlices && ((i1 - ib) & 63) != 0) part |= 1u << last;
+      for (uint32_t b = m & part; b != 0u; b &= b - 1u)
+        slices(wrap_c, Int<1>{}, Yes{}, static_cast<uint32_t>(__builtin_ctz(b)), uj);
+      m &= ~part;
+      while (__builtin_popcount(m) >= 4) {
         uint32_t rs = 0;
-        for (int k = 0; k < n_s; ++k) {
+        for (int k = 0; k < 4; ++k) {
           rs |= static_cast<uint32_t>(__builtin_ctz(m)) << (4 * k);
           m &= m - 1u;
         }
-        return rs;
-      };
-      while (__builtin_popcount(m) >= 4) slices(Int<4>{}, take(4), wrap != 0);
-      if (__builtin_popcount(m) >= 2) slices(Int<2>{}, take(2), wrap != 0);
-      if (m != 0u) slices(Int<1>{}, take(1), wrap != 0);
-    }
+        slices(wrap_c, Int<4>{}, No{}, rs, uj);
+      }
+      for (; m != 0u; m &= m - 1u)
+        slices(wrap_c, Int<1>{}, No{}, static_cast<uint32_t>(__builtin_ctz(m)), uj);
+    };
+    group(std::false_type{}, bits(m_look & ~m_exact & ~m_wrap));
+    group(std::true_type{}, bits(m_look & ~m_exact & m_wrap));
   }
   return static_cast<uint64_t>(uni(sum) - uni(below));
 }
