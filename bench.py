@@ -219,7 +219,8 @@ def bench_image_search(steps=3):
                     "searched pairs and the images it evaluated for them: only the images "
                     "of each vector's octant list, in binary64 those its pair of groups can "
                     "have); canonical_search_flops counts all 26 images of every searched "
-                    "pair instead"}
+                    "pair instead, far more than the binary64 kernel evaluates (its "
+                    "fraction exceeds 1)"}
     xt = torch.from_numpy(x).cuda()
     h = torch.empty((3, 4000), dtype=torch.int64, device="cuda")
     with dh.Context(0) as c:
