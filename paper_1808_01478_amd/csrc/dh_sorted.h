@@ -474,6 +474,37 @@ __device__ __forceinline__ Images group_images(const GroupBox &I, const GroupBox
   return m;
 }
 
+// Pairs gathered in the lanes of a wave, from whatever i and j, for arithmetic that
+// few of them need: lane q < n holds the word of one.
+struct LaneQueue {
+  int held = 0, n = 0;
+  // takes in the words of the lanes that say so; a full wave of them goes to drain
+  template <typename F>
+  __device__ __forceinline__ void push(bool take, int word, F &&drain) {
+    const uint64_t mask = __builtin_amdgcn_ballot_w64(take);
+    if (mask == 0) return;
+    const int lane = threadIdx.x & 63, cnt = __builtin_popcountll(mask);
+    const int below = static_cast<int>(__builtin_amdgcn_mbcnt_hi(
+        static_cast<uint32_t>(mask >> 32),
+        __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0u)));
+    // the lanes taken to n, n + 1, ... (round the wave), the others after them
+    const int to = n + (take ? below : cnt + lane - below);
+    const int got = __builtin_amdgcn_ds_permute((to & 63) << 2, word);
+    held = lane >= n ? got : held;
+    n += cnt;
+    if (n >= 64) {
+      drain(held, 64);
+      held = got;
+      n -= 64;
+    }
+  }
+  template <typename F>
+  __device__ __forceinline__ void finish(F &&drain) {
+    if (n > 0) drain(held, n);
+    n = 0;
+  }
+};
+
 // Pairs of a sorted binary64 frame next to a bin edge. A pass leaves its pairs
 // of two j here as soon as one of them is too close to an edge (see
 // run_sorted64): each pair's bin is taken again from the staged positions, the
@@ -520,36 +551,17 @@ __device__ __attribute__((noinline)) void settle_pairs(const FrameParams *frame,
   const Count<MODE> count(F, w, lane);
   const int b_lo = w.sweep * uni(F->win), b_hi = b_lo + uni(F->win);
 
-  // pairs waiting for the canonical sequence: lane q < qn holds one, as the
-  // offsets of its i from ib and its j from j0
-  int qn = 0, held = 0;
-  auto drain = [&](int cnt) {
+  // pairs for the canonical sequence, as the offsets of i from ib and j from j0
+  LaneQueue queue;
+  auto drain = [&](int word, int cnt) {
     const bool v = lane < cnt;
-    const int64_t p = 3 * static_cast<int64_t>(index[v ? ib + (held & 511) : ib]);
-    const int64_t q = 3 * static_cast<int64_t>(index[v ? j0 + (held >> 9) : j0]);
+    const int64_t p = 3 * static_cast<int64_t>(index[v ? ib + (word & 511) : ib]);
+    const int64_t q = 3 * static_cast<int64_t>(index[v ? j0 + (word >> 9) : j0]);
     const double t = t64<SEARCH ? kBoxTricSearch : kBoxTric>(in[p], in[p + 1], in[p + 2], in[q],
                                                              in[q + 1], in[q + 2], g);
     // (a NaN t takes the other operand: out of range)
     const uint32_t b = kBinBits + static_cast<uint32_t>(min_arith(t, 0x1p25));
     count.template add<true>(v ? b : kNoBits);
-  };
-  auto push = [&](bool take, int i, int j) {
-    const uint64_t mask = __builtin_amdgcn_ballot_w64(take);
-    if (mask == 0) return;
-    const int cnt = __builtin_popcountll(mask);
-    const int below = static_cast<int>(__builtin_amdgcn_mbcnt_hi(
-        static_cast<uint32_t>(mask >> 32),
-        __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0u)));
-    // the lanes taken to qn, qn + 1, ... (round the wave), the others after them
-    const int to = qn + (take ? below : cnt + lane - below);
-    const int got = __builtin_amdgcn_ds_permute((to & 63) << 2, (i - ib) | (j - j0) << 9);
-    held = lane >= qn ? got : held;
-    qn += cnt;
-    if (qn >= 64) {
-      drain(64);
-      held = got;
-      qn -= 64;
-    }
   };
 
   // the staged or, for groups without a rounding bound, the input points;
@@ -638,10 +650,10 @@ __device__ __attribute__((noinline)) void settle_pairs(const FrameParams *frame,
         const bool open =
             counts && gap <= near_hi && u >= 0x1p-46 && bin >= b_lo - 1 && bin <= b_hi;
         count.template add<true>(counts && !open ? b : kNoBits);
-        push(open, i, j);
+        queue.push(open, (i - ib) | (j - j0) << 9, drain);
       }
   }
-  if (qn > 0) drain(qn);
+  queue.finish(drain);
 }
 
 // Rounding between the inputs and a coordinate difference of a pair of two
@@ -672,9 +684,10 @@ __device__ __forceinline__ bool rounding_bound(const GroupBox &I, const GroupBox
 // shared wrap by their shifted positions, the others wrapped as 32-bit fixed-point
 // fractions (see dh_pairs.h), and where its rounding could decide, of the length
 // or of a wrap, by the canonical sequence on the input.
-// The frame of 70,001 points takes 4.8 ms with the count and 4.1 without (7.1
+// The frame of 70,001 points takes 4.6 ms with the count and 4.0 without (7.1
 // with it in binary64, a slice at a time; 10.6 before such frames were sorted);
-// 200,000 points 24.3 and 19.1 ms.
+// 74,088 points of a grid, whose wraps tie, 5.0 ms, 6.3 with the canonical
+// sequence for all pairs of a tie's slice.
 __device__ __attribute__((noinline)) uint64_t searched_pairs(const FrameParams *frame, WorkItem w,
                                                              int ib_, int jb_, int gpu_) {
   const FrameParams *const F = uni(frame);
@@ -750,24 +763,28 @@ __device__ __attribute__((noinline)) uint64_t searched_pairs(const FrameParams *
       u[2] = __float_as_int(static_cast<float>(z * len + Sz));
     }
   };
+  // pairs for the canonical sequence, as the offsets of i from ib and j from jb
+  LaneQueue queue;
+  auto drain = [&](int word, int cnt) {
+    const bool v = lane < cnt;
+    const int64_t a = 3 * static_cast<int64_t>(index[v ? ib + (word & 511) : ib]);
+    const int64_t b = 3 * static_cast<int64_t>(index[v ? jb + (word >> 9) : jb]);
+    const double q0 =
+        q64<kBoxTric>(in[a], in[a + 1], in[a + 2], in[b], in[b + 1], in[b + 2], geo);
+    below += __builtin_popcountll(__builtin_amdgcn_ballot_w64(v && !(q0 >= qskip)));
+  };
   for (int g = 0; g < gpu; ++g) {
     const int ja = jb + 64 * g, n = min(64, j1 - ja);
     auto bits = [&](uint64_t m) {
       return static_cast<uint32_t>(m >> (g * kUnitSlices)) & ((1u << kUnitSlices) - 1u);
     };
     if (bits(m_look) == 0u) continue;
-    // the canonical sequence: pairs of slice q with j under qskip
-    auto canonical = [&](int q, int j) {
-      const int i = ib + 64 * q + lane;
-      const bool ok = i < i1 && (!diag_item || (i >> 6) != (ja >> 6) || j > i);
-      const int64_t a = 3 * static_cast<int64_t>(index[i < i1 ? i : ib]);
-      const int64_t b = 3 * static_cast<int64_t>(index[j]);
-      const double q0 =
-          q64<kBoxTric>(in[a], in[a + 1], in[a + 2], in[b], in[b + 1], in[b + 2], geo);
-      return __builtin_popcountll(__builtin_amdgcn_ballot_w64(ok && !(q0 >= qskip)));
-    };
-    for (uint32_t m = bits(m_exact); m != 0u; m &= m - 1u)
-      for (int j = 0; j < n; ++j) below += canonical(__builtin_ctz(m), ja + j);
+    for (uint32_t m = bits(m_exact); m != 0u; m &= m - 1u) {
+      const int i = ib + 64 * __builtin_ctz(m) + lane;
+      for (int j = ja; j < ja + n; ++j)
+        queue.push(i < i1 && (!diag_item || (i >> 6) != (ja >> 6) || j > i),
+                   (i - ib) | (j - jb) << 9, drain);
+    }
     // (mask_c: not all of the slices' and the group's pairs belong to the item)
     auto slices = [&](auto wrap_c, auto m_c, auto mask_c, uint32_t rs, const int (&uj)[3]) {
       constexpr int M = decltype(m_c)::value;
@@ -792,7 +809,7 @@ __device__ __attribute__((noinline)) uint64_t searched_pairs(const FrameParams *
 #pragma unroll
         for (int k = 0; k < M; ++k) {
           float dx, dy, dz;
-          uint64_t tie = 0;
+          bool tie = false;
           if constexpr (WRAP) {
             auto diff = [](int a, int b) {
               return static_cast<float>(
@@ -802,8 +819,8 @@ __device__ __attribute__((noinline)) uint64_t searched_pairs(const FrameParams *
             dx = fmaf(g32.ncx, fc, fmaf(g32.nbx, fb, fa));
             dy = fmaf(g32.ncy, fc, g32.nby * fb);
             dz = g32.ncz * fc;
-            tie = __builtin_amdgcn_ballot_w64(fmaxf(fabsf(fa), fmaxf(fabsf(fb), fabsf(fc))) >
-                                              0x1p31f * (1.f - 0x1p-21f));
+            tie = fmaxf(fabsf(fa), fmaxf(fabsf(fb), fabsf(fc))) > 0x1p31f * (1.f - 0x1p-21f);
+            if constexpr (MASK) tie = tie && j >= after[k];
           } else {
             dx = __int_as_float(ua) - __int_as_float(ui[k][0]);
             dy = __int_as_float(ub) - __int_as_float(ui[k][1]);
@@ -812,14 +829,17 @@ __device__ __attribute__((noinline)) uint64_t searched_pairs(const FrameParams *
           float q = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
           if constexpr (MASK) q = j >= after[k] ? q : __builtin_inff();
           const uint64_t in_lo = __builtin_amdgcn_ballot_w64(q < q_lo);
-          open[k] = (__builtin_amdgcn_ballot_w64(q < q_hi) ^ in_lo) | tie;
+          open[k] = __builtin_amdgcn_ballot_w64(q < q_hi) ^ in_lo;
+          if constexpr (WRAP) open[k] |= __builtin_amdgcn_ballot_w64(tie);
           any |= open[k];
-          found += open[k] == 0 ? __builtin_popcountll(in_lo) : 0;
+          found += __builtin_popcountll(in_lo & ~open[k]);
         }
         below += found;
         if (__builtin_expect(any != 0, 0))
           for (int k = 0; k < M; ++k)
-            if (open[k] != 0) below += canonical(static_cast<int>((rs >> (4 * k)) & 15u), ja + j);
+            queue.push((open[k] >> lane & 1u) != 0,
+                       (64 * static_cast<int>((rs >> (4 * k)) & 15u) + lane) | (ja - jb + j) << 9,
+                       drain);
       }
     };
     auto group = [&](auto wrap_c, uint32_t m) {
@@ -850,6 +870,7 @@ __device__ __attribute__((noinline)) uint64_t searched_pairs(const FrameParams *
     group(std::false_type{}, bits(m_look & ~m_exact & ~m_wrap));
     group(std::true_type{}, bits(m_look & ~m_exact & m_wrap));
   }
+  queue.finish(drain);
   return static_cast<uint64_t>(uni(sum) - uni(below));
 }
 
