@@ -602,13 +602,12 @@ void plan_frame(int32_t frame, const int64_t *off, int32_t k, bool padded, const
 // Splits the last `grid` items of a work list (the ones workgroups take
 // when the rest is done) into pieces of about a quarter of their j-range, in
 // multiples of `step`, so that the workgroups finish close together instead of
-// idling for up to one full item; lists of fewer than four items per
-// workgroup are already cut fine. The grouping by (histogram, window) is
-// kept.
+// idling for up to one full item, where cut_tail says so. The grouping by
+// (histogram, window) is kept.
 void refine_tail(std::vector<WorkItem> &items, int grid, int step) {
   const size_t n = items.size();
   const size_t tail = static_cast<size_t>(std::max(grid, 0));
-  if (tail == 0 || n < 4 * tail) return;
+  if (!cut_tail(items.data(), n, tail)) return;
   std::vector<WorkItem> out(items.begin(), items.end() - static_cast<std::ptrdiff_t>(tail));
   out.reserve(n + 3 * tail);
   for (size_t q = n - tail; q < n; ++q) {

@@ -321,6 +321,19 @@ struct KernelConfig {
 // end of the launch (1M clustered points: 89.9 ms, now 86.7 ms).
 constexpr int64_t kMinItemPairs = int64_t{1} << 15;
 constexpr int32_t kMinChunk = 32;
+// Whether the last items of a list are cut into pieces (see refine_tail): lists of
+// fewer than four items per workgroup are cut fine already, and where a histogram
+// has fewer than four items every piece adds a flush of its own (20,000 points of
+// 64 species without a box, binary32, 4,160 items of 2,080 histograms: 199 us with
+// the last 1,024 in quarters, 143 us without).
+inline bool cut_tail(const WorkItem *items, size_t n, size_t grid) {
+  if (grid == 0 || n < 4 * grid) return false;
+  size_t runs = 0;
+  for (size_t q = 0; q < n; ++q)
+    runs += q == 0 || items[q].frame != items[q - 1].frame || items[q].hist != items[q - 1].hist ||
+            items[q].sweep != items[q - 1].sweep;
+  return n >= 4 * runs;
+}
 // granularity of the j-pieces the tail of a work list is cut into
 inline int32_t tail_step(int32_t kind) {
   return padded_frame(kind) ? kUnitPoints : kMinChunk;

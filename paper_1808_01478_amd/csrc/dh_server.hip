@@ -250,7 +250,7 @@ uint64_t item_pairs(const WorkItem &w) {
 void refine_tail(std::vector<WorkItem> &items, int grid, int step) {
   const size_t n = items.size();
   const size_t tail = static_cast<size_t>(std::max(grid, 0));
-  if (tail == 0 || n < 4 * tail) return;
+  if (!dh::cut_tail(items.data(), n, tail)) return;
   std::vector<WorkItem> last(items.end() - static_cast<std::ptrdiff_t>(tail), items.end());
   items.resize(n - tail);
   for (const WorkItem &w : last) {

@@ -1,4 +1,4 @@
-"""Host rules of spatially sorted frames, compiled for the CPU from the
+"""Host rules of spatially sorted frames and of work lists, compiled for the CPU from the
 library's own header: where a point lies (the cell and the place in it name one
 image, also for points on a cell face), and which frames are sorted (no binary64
 frame whose squared lengths leave the binary32 range)."""
@@ -19,8 +19,14 @@ TRIC, SEARCH, SORTED, SEARCH_SORTED = 2, 3, 5, 6  # BoxKind
 
 SOURCE = """
 #include "dh_internal.h"
+#include <vector>
 extern "C" double wrap_cell(double f, unsigned int *place) { return dh::wrap_cell(f, *place); }
 extern "C" long first_word(int i) { return dh::first_word(i); }
+extern "C" int cut_tail(const int *hist, long n, long grid) {
+  std::vector<dh::WorkItem> items(n);
+  for (long q = 0; q < n; ++q) items[q].hist = hist[q];
+  return dh::cut_tail(items.data(), n, grid);
+}
 extern "C" int tight_species(const long *off, int k) {
   return dh::tight_species(off, k);
 }
@@ -140,3 +146,14 @@ def test_word_index_of_the_last_points(lib):
         kind = lib.staged_kind(workloads.BOX_TRICLINIC, box.ctypes.data, 1.0, 1000, 0, n)
         # a unit starts at most at the last of 64 padded species
         assert kind == TRIC or n + 63 * 64 + 512 <= 0x7FFFFFFF, n
+
+
+def test_tail_of_short_lists_and_small_histograms_stays_whole(lib):
+    """Four items per workgroup and per histogram at least: fewer are cut fine, or
+    pay a flush for every piece."""
+    def cut(per_hist, n, grid):
+        hist = np.ascontiguousarray(np.arange(n) // per_hist, np.int32)
+        return bool(lib.cut_tail(hist.ctypes.data_as(ctypes.c_void_p), ctypes.c_long(n),
+                                 ctypes.c_long(grid)))
+    assert not cut(1 << 20, 0, 0) and not cut(1 << 20, 4000, 1024) and cut(1 << 20, 4096, 1024)
+    assert not cut(3, 4160, 1024) and cut(4, 4160, 1024) and not cut(2, 1 << 16, 512)
