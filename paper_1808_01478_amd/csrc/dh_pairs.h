@@ -1108,10 +1108,13 @@ constexpr int max_threads() {
 // workgroups of 1,024 threads share a CU where their histograms fit. A loop of
 // the short path's instructions takes 41 cycles per pair of a wave with four
 // waves per SIMD and 37 with eight (the root alone 14); 1M clustered points:
-// 89.3 and 85.7 ms; 24 orthorhombic frames: 21.9 and 21.4 ms.
+// 89.3 and 85.7 ms; 24 orthorhombic frames: 21.9 and 21.4 ms. Four for the
+// binary64 search, which lies at the 128 registers of four waves (eight frames of
+// 8,000 to 29,000 points in a batch: 4.92 ms at 126 registers, 5.17 at 129).
 template <typename T, int R, int BOX>
 constexpr int min_waves() {
-  return sizeof(T) == 4 && BOX != kBoxTricSearch && R == 4 ? 8 : 1;
+  if (BOX == kBoxTricSearch) return sizeof(T) == 8 && R == 4 ? 4 : 1;
+  return sizeof(T) == 4 && R == 4 ? 8 : 1;
 }
 
 template <typename T, int R, int BOX, int MODE>
